@@ -340,7 +340,7 @@ int nugpr_profile_read(nugpr_ctx* ctx, double* total_ms /*HOST*/, int32_t* launc
 double nugpr_profile_bytes(const nugpr_ctx* ctx, int32_t ncols);
 
 /* Name of the kernel instantiation behind that launch for vector blocks of `ncols` columns, as profilers print it
- * without the namespace (e.g. "k_strip_ring<1, 32, 4, true, 17>"), copied into buf (HOST, at most len bytes
+ * without the namespace (e.g. "k_strip<1, true, 1>"), copied into buf (HOST, at most len bytes
  * including the terminating zero).  Pure host logic; lets a caller match stored counter readings to the code
  * that is actually running. */
 int nugpr_profile_kernel_name(const nugpr_ctx* ctx, int32_t ncols, char* buf /*HOST*/, int32_t len);

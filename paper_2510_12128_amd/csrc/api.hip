@@ -178,7 +178,7 @@ void build_tables(const Layout& L, Tables& t) {
   // P = C S: strips over the n_c r rows of C, columns split into nsP slabs of cpp tiles.  C is symmetric:
   // with the strips grouped like the slabs, the strips of row group I on slab k and the strips of row group
   // k on slab I share their tiles (one set reads them transposed) and form one group of work; see
-  // k_strip_ring for the order in which they visit them.
+  // k_strip for the order in which they visit them.
   {
     const uint32_t ncr = (uint32_t)L.ncr, chunks = (uint32_t)L.ldc / TILE, cpp = (chunks + L.nsP - 1) / L.nsP;
     const uint32_t ngroups = (chunks + cpp - 1) / cpp;              // non-empty slabs = row groups
@@ -231,6 +231,7 @@ int upload_table(const std::vector<StripItem>& v, StripItem*& cursor, StripTable
   tab.dev = cursor;
   tab.count = (int)v.size();
   tab.sym = false;
+  tab.rowmajor = !v.empty() && v[0].blocked == 0;
   for (const StripItem& it : v) tab.sym = tab.sym || (it.blocked & 2u) != 0;
   if (!v.empty())
     NUGPR_HIP(hipMemcpyAsync(cursor, v.data(), v.size() * sizeof(StripItem), hipMemcpyHostToDevice, s));
@@ -483,7 +484,7 @@ int nugpr_destroy(nugpr_ctx* c) {
 
 int nugpr_build_blocks(nugpr_ctx* c, const double* theta, void* stream) {
   if (!c) { set_error("ctx is null"); return NUGPR_ERR_INVALID; }
-  return launch_build(c, theta, as_stream(stream), !kd_lower_suffices(c));
+  return launch_build(c, theta, as_stream(stream), false);
 }
 
 int nugpr_set_nystrom_basis(nugpr_ctx* c, const double* theta, double jitter, void* stream) {
@@ -630,7 +631,7 @@ static int set_operator(nugpr_ctx* c, const double* theta, bool allow_reuse, hip
   bool same = allow_reuse && c->built && (int)c->theta_built.size() == L.p &&
               !(c->params.flags & NUGPR_NO_SHORTCUTS);
   for (int k = 0; same && k < nl; ++k) same = (theta[k] == c->theta_built[k]);
-  if (!same) return launch_build(c, theta, s, !kd_lower_suffices(c));
+  if (!same) return launch_build(c, theta, s, false);
   for (int i = 0; i < L.p; ++i)
     if (!(theta[i] > 0.0) || !std::isfinite(theta[i])) { set_error("theta entries must be finite and > 0"); return NUGPR_ERR_INVALID; }
   const double a0 = c->theta_built[L.p - 2], s0 = c->theta_built[L.p - 1];
@@ -796,7 +797,7 @@ int nugpr_train_step(nugpr_ctx* c, double* log_theta, double* adam_m, double* ad
     const double tp = std::exp(log_theta[i] + h), tm = std::exp(log_theta[i] - h);
     const bool pair = pairs && i < p - 2;
     if (pair) {
-      rc = launch_build_pair(c, theta.data(), i, h, tp, tm, as_stream(stream), !kd_lower_suffices(c));
+      rc = launch_build_pair(c, theta.data(), i, h, tp, tm, as_stream(stream), false);
       if (rc) return rc;
     }
     theta[i] = tp;

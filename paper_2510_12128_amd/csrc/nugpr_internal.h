@@ -102,12 +102,12 @@ struct StripArgs {
   StripPort port[2];
   const StripItem* items;
   int32_t T;                 // columns of the vector blocks (row stride)
-  uint32_t magicT;           // floor(2^32 / T) + 1, for division by T
 };
 
 struct StripTable {
   StripItem* dev = nullptr;
   int count = 0;
+  bool rowmajor = false; // the items' matrix is stored row-major (all of them, or none)
   bool sym = false;      // some items are strips of symmetric blocks (StripItem::blocked bit 1)
 };
 
@@ -246,8 +246,8 @@ struct nugpr_ctx {
   // device state when it meets a NaN or Inf among the points or representatives (the kernel values of such a
   // point would otherwise quietly come out as zero)
   int32_t assembly_mark = 0;
-  // The assembly may leave out the strictly upper tiles of the K_ii (the product's usual launch reads the
-  // lower ones only, see k_strip_ring); whoever needs whole strips calls ensure_kd_upper first.
+  // The assembly leaves out the strictly upper tiles of the K_ii (the product reads the lower ones only, see
+  // k_strip); the export of a whole block calls ensure_kd_upper first.
   bool kd_upper_valid = false, spare_upper_valid = false;
   // the same for the coupling matrix, whose strips pair up when c_paired (set with the work tables)
   bool c_upper_valid = false, spare_c_upper_valid = false, c_paired = false;
@@ -288,14 +288,12 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L);
 // build_blocks.hip ----------------------------------------------------------
 int launch_setup(nugpr_ctx* c, const float* user_reps, const float* user_W, hipStream_t s);
 // need_upper = false: the strictly upper tiles of the K_ii are not written (kd_upper_valid records it)
-int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s, bool need_upper = true);
+int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s, bool need_upper = false);
 // The two assemblies of a central difference in lengthscale `param` (step h on its logarithm) in one pass:
 // ell e^{+h} into the blocks in force, ell e^{-h} into the spare ones; swap_pair puts the spare ones in force.
 int launch_build_pair(nugpr_ctx* c, const double* theta, int param, double h, double value_plus, double value_minus,
                       hipStream_t s, bool need_upper);
 int swap_pair(nugpr_ctx* c);
-// true when every product this context launches on its own vector blocks reads lower tiles only
-bool kd_lower_suffices(const nugpr_ctx* c);
 // fills the strictly upper tiles of the K_ii from the lower ones if the last assembly left them out
 int ensure_kd_upper(nugpr_ctx* c, hipStream_t s);
 int ensure_c_upper(nugpr_ctx* c, hipStream_t s);
