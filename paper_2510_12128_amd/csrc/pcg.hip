@@ -466,34 +466,46 @@ static int scaled_copy(void* out, const void* x, double a, int64_t count, hipStr
 // ST: type of the block that is read.  Dwide (may be null): every point belongs to exactly one representative,
 // so the gather visits every row of D once and can leave a copy of it in the solver's own type on the way
 // (the widening of a caller's fp32 block, which the strip kernels then read, costs no pass of its own).
+// A representative's points are dealt to `parts` threads per column (8 to 16 points each, see project_shape), whose
+// sums are added in a fixed order: the gathers are dependent pairs of loads (point index, then row), so one thread per
+// representative and column spent 125 us at 128 points each, and 1 ms and more with few representatives of large clusters.
 template <typename VT, typename ST>
-__global__ __launch_bounds__(256) void k_onehot_project(const ST* __restrict__ D, VT* __restrict__ Dwide,
-                                                        const int32_t* __restrict__ rep_ptr,
-                                                        const int32_t* __restrict__ rep_pts, VT* __restrict__ S,
-                                                        int ncr, int T) {
-  const int rpp = 256 / T;
+__global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ D, VT* __restrict__ Dwide,
+                                                         const int32_t* __restrict__ rep_ptr,
+                                                         const int32_t* __restrict__ rep_pts, VT* __restrict__ S,
+                                                         int ncr, int T, int parts) {
+  __shared__ double red[1024];
+  const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
-  if (myrow >= rpp) return;
-  for (int a = blockIdx.x * rpp + myrow; a < ncr; a += gridDim.x * rpp) {
-    double s = 0.0;
-    const int q1 = rep_ptr[a + 1];
-    // eight gathers in flight at a time; the additions stay in ascending point order
-    for (int q = rep_ptr[a]; q < q1; q += 8) {
+  const int reps = rpp / parts;                  // representatives of a workgroup
+  const int part = myrow % parts;
+  const int a = (int)blockIdx.x * reps + myrow / parts;
+  const bool live = myrow < reps * parts && a < ncr;
+  double s = 0.0;
+  if (live) {
+    const int q0 = rep_ptr[a], q1 = rep_ptr[a + 1];
+    // eight gathers in flight at a time
+    for (int q = q0 + part; q < q1; q += 8 * parts) {
       int idx[8];
       double v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) idx[j] = rep_pts[q + j < q1 ? q + j : q1 - 1];
+      for (int j = 0; j < 8; ++j) idx[j] = rep_pts[q + j * parts < q1 ? q + j * parts : q];
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = (double)D[(int64_t)idx[j] * T + col];
       if (Dwide) {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          if (q + j < q1) Dwide[(int64_t)idx[j] * T + col] = (VT)v[j];
+          if (q + j * parts < q1) Dwide[(int64_t)idx[j] * T + col] = (VT)v[j];
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) s += q + j < q1 ? v[j] : 0.0;
+      for (int j = 0; j < 8; ++j) s += q + j * parts < q1 ? v[j] : 0.0;
     }
+  }
+  red[tid] = s;
+  __syncthreads();
+  if (live && part == 0) {
+    for (int k = 1; k < parts; ++k) s += red[tid + k * T];
     S[(int64_t)a * T + col] = (VT)s;
   }
 }
@@ -554,10 +566,17 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
   const Layout& L = c->L;
   if (D32 && !(c->onehot && c->acc64)) { set_error("internal: fused widening needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot) {
-    const int grid = elementwise_grid(L.ncr, T);
-    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), dim3(grid), dim3(256), 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T);
-    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), dim3(grid), dim3(256), 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T);
-    else hipLaunchKernelGGL((k_onehot_project<float, float>), dim3(grid), dim3(256), 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T);
+    // threads per representative and column: as many as leave each about eight points (one round of gathers); large
+    // workgroups once that is more than an ordinary one holds
+    const int64_t want = (L.n + 8 * (int64_t)L.ncr - 1) / (8 * (int64_t)L.ncr);
+    const int block = want > 256 / T ? 1024 : 256, rpp = block / T;
+    int parts = 1;
+    while (2 * parts <= rpp && parts < want) parts *= 2;
+    const int reps = rpp / parts;
+    const dim3 grid((unsigned)((L.ncr + reps - 1) / reps)), blk((unsigned)block);
+    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), grid, blk, 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts);
+    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), grid, blk, 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts);
+    else hipLaunchKernelGGL((k_onehot_project<float, float>), grid, blk, 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T, parts);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }

@@ -10,6 +10,7 @@ SIZES = {
     "around-a-tile": [63, 65, 129],
     "tiny": [5, 3, 1],
     "many-tiles": [200, 257, 64, 90, 33, 640],
+    "few-representatives": [1700, 900],  # one for each: its points are shared out among up to 16 threads a column
     "wide-coupling": [150] * 11,         # 11 x 65 representatives: row groups of the coupling matrix of unequal size
 }
 
@@ -21,7 +22,7 @@ def test_products_and_applies_at_tile_edges(lib, name, dense, acc_fp32):
     import torch
     from paper_2510_12128_amd import binding as B
     sizes = SIZES[name]
-    rank = {"tiny": 1, "wide-coupling": 65}.get(name, 7)
+    rank = {"tiny": 1, "few-representatives": 1, "wide-coupling": 65}.get(name, 7)
     n, d, t = sum(sizes), 3, 32
     rng = np.random.default_rng(11)
     off = np.concatenate([[0], np.cumsum(sizes)])
