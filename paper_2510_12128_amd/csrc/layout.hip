@@ -130,7 +130,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_S0 = take(cur, (size_t)L.ncr * L.T * sizeof(double));
   L.o_Spart = take(cur, (size_t)L.nsS * L.ncr * L.T * sizeof(double));
   L.o_Ppart = take(cur, (size_t)L.nsP * L.ncr * L.T * sizeof(double));
-  L.o_dot = take(cur, (size_t)2 * L.n_dot_blocks * MAX_COLS * sizeof(double));
+  L.o_dot = take(cur, (size_t)4 * L.n_dot_blocks * MAX_COLS * sizeof(double));
   L.o_state = take(cur, sizeof(PcgState));
   L.o_alog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
   L.o_blog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));

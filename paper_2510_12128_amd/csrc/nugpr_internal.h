@@ -115,7 +115,7 @@ struct StripTable {
 // device-side PCG scalars (all double), one slot per column
 // ---------------------------------------------------------------------------
 struct PcgState {
-  double rho[MAX_COLS];
+  double rho[2][MAX_COLS];   // iteration j reads slot j % 2 and leaves the next value in the other one
   double rho0[MAX_COLS];     // <r_0, M^-1 r_0>: squared norm of the Lanczos start vector
   double bnorm2[MAX_COLS];
   double alpha[MAX_COLS];
@@ -229,6 +229,7 @@ struct nugpr_ctx {
   nugpr::HostFlags* h_flags = nullptr;   // pinned
   uint64_t flag_seq = 0, tail_seq = 0;   // last numbers handed to the device
   int expect_iters[2] = {1, 1};          // iterations the last solve of each system took (when to report early)
+  int recent_iters[2][3] = {{1, 1, 1}, {1, 1, 1}};   // and the last three (how many to issue without asking in between)
   double* h_buf = nullptr;               // pinned scratch for small device->host reads
   size_t h_buf_doubles = 0;
   float diag_residual = 0.f;             // (alpha + sigma^2) - float(alpha + sigma^2) of the stored blocks

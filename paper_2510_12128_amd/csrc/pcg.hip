@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_pcg_begin(PcgState* __restrict__ st, co
   if (tid == 0) {
     const bool act = bb > 0.0 && rz == rz;
     st->bnorm2[c] = bb;
-    st->rho[c] = rz;
+    st->rho[0][c] = rz;
     st->rho0[c] = rz;
     st->alpha[c] = 0.0;
     st->beta[c] = 0.0;
@@ -105,7 +105,7 @@ __global__ void k_pcg_begin_known(PcgState* __restrict__ st, int which, int T) {
   const double bb = st->known_bb[which][c], rz = st->known_rz[which][c];
   const bool act = bb > 0.0 && rz == rz;
   st->bnorm2[c] = bb;
-  st->rho[c] = rz;
+  st->rho[0][c] = rz;
   st->rho0[c] = rz;
   st->alpha[c] = 0.0;
   st->beta[c] = 0.0;
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void k_pcg_alpha(PcgState* __restrict__ st, co
   if (tid == 0) {
     double a = 0.0;
     if (st->active[c]) {
-      if (dq > 0.0) a = st->rho[c] / dq;
+      if (dq > 0.0) a = st->rho[iter & 1][c] / dq;
       else { st->indef[c] = 1; st->active[c] = 0; }      // <d, K'd> <= 0 (or NaN)
     }
     st->alpha[c] = a;
@@ -197,13 +197,31 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
         st->active[c] = 0;
         st->indef[c] = 1;
       } else {
-        bta = rz / st->rho[c];
-        st->rho[c] = rz;
+        bta = rz / st->rho[iter & 1][c];
+        st->rho[(iter + 1) & 1][c] = rz;
       }
     }
     st->beta[c] = bta;
     blog[(int64_t)iter * MAX_COLS + c] = bta;
   }
+}
+
+// Problems of up to FUSE_BLOCKS partial sums per column (32768 points): the kernels that apply alpha and beta sum them
+// up themselves, every workgroup in the same fixed order (17 KB of L2 reads a workgroup at 128 x 17), and the first
+// one keeps the records.  That saves a launch of 3 - 5 us each; with 1024 partial sums every workgroup would read 139 KB.
+constexpr int FUSE_BLOCKS = 128;
+__device__ __forceinline__ void sum_all_partials(const double* __restrict__ partial, int nblocks, int T, double* red, double* out) {
+  const int rpp = 256 / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
+  double s = 0.0;
+  if (myrow < rpp)
+    for (int b = myrow; b < nblocks; b += rpp) s += partial[(int64_t)b * MAX_COLS + col];
+  red[tid] = s;
+  __syncthreads();
+  if (tid < T) {
+    for (int k = 1; k < rpp; ++k) s += red[k * T + tid];
+    out[tid] = s;
+  }
+  __syncthreads();
 }
 
 // X += D diag(alpha); R -= Q diag(alpha)   (alpha stays in fp64: rounding it to fp32 would scale the whole
@@ -214,19 +232,36 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
 template <typename VT>
 __global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* R, const VT* Rin,
                                                         const VT* __restrict__ D, const VT* __restrict__ Q,
-                                                        const VT* __restrict__ B, const PcgState* __restrict__ st,
-                                                        int64_t n, int T, int first, double* __restrict__ partial) {
+                                                        const VT* __restrict__ B, PcgState* __restrict__ st,
+                                                        int64_t n, int T, int first, double* __restrict__ partial,
+                                                        const double* __restrict__ dqs, int iter, double* __restrict__ alog) {
   __shared__ double red[2][256];
+  __shared__ double al[MAX_COLS];
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
+  if (dqs) {                                   // the step of k_pcg_alpha (a column the first workgroup stops here has a = 0 anyway)
+    sum_all_partials(dqs, (int)gridDim.x, T, &red[0][0], al);
+    if (tid < T) {
+      const double dq = al[tid];
+      const bool act = st->active[tid] != 0;
+      const double a = act && dq > 0.0 ? st->rho[iter & 1][tid] / dq : 0.0;
+      al[tid] = a;
+      if (blockIdx.x == 0) {
+        if (act && !(dq > 0.0)) { st->indef[tid] = 1; st->active[tid] = 0; }
+        st->alpha[tid] = a;
+        alog[(int64_t)iter * MAX_COLS + tid] = a;
+      }
+    }
+    __syncthreads();
+  }
   const int64_t rows_per_block = (n + gridDim.x - 1) / gridDim.x;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
   const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
   double s0 = 0.0, s1 = 0.0;
   if (live) {
-    const double a = st->alpha[col];
+    const double a = dqs ? al[col] : st->alpha[col];
     for (int64_t r = r0 + myrow; r < r1; r += rpp) {
       const int64_t idx = r * T + col;
       const VT xn = first ? (VT)(a * (double)D[idx]) : (VT)fma(a, (double)D[idx], (double)X[idx]);
@@ -252,13 +287,32 @@ __global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* 
 // D = Z + D diag(beta) for active columns, 0 for stopped ones
 template <typename VT>
 __global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT* __restrict__ Z,
-                                                  const PcgState* __restrict__ st, int64_t n, int T) {
+                                                  PcgState* __restrict__ st, int64_t n, int T,
+                                                  const double* __restrict__ rzs, int nblocks, int iter, double* __restrict__ blog) {
+  __shared__ double red[256];
+  __shared__ double be[MAX_COLS];
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
+  if (rzs) {                                   // the step of k_pcg_beta; a negative value marks a stopped column
+    sum_all_partials(rzs, nblocks, T, red, be);
+    if (tid < T) {
+      const double rz = be[tid];
+      const bool act = st->active[tid] != 0, go = act && rz > 0.0;
+      const double b = go ? rz / st->rho[iter & 1][tid] : 0.0;
+      be[tid] = go ? b : -1.0;
+      if (blockIdx.x == 0) {
+        if (act && !go) { st->active[tid] = 0; st->indef[tid] = 1; }
+        if (go) st->rho[(iter + 1) & 1][tid] = rz;
+        st->beta[tid] = b;
+        blog[(int64_t)iter * MAX_COLS + tid] = b;
+      }
+    }
+    __syncthreads();
+  }
   if (myrow >= rpp) return;
-  const double bta = st->beta[col];
-  const bool act = st->active[col] != 0;
+  const double bta = rzs ? be[col] : st->beta[col];
+  const bool act = rzs ? bta >= 0.0 : st->active[col] != 0;
   for (int64_t r = (int64_t)blockIdx.x * rpp + myrow; r < n; r += (int64_t)gridDim.x * rpp) {
     const int64_t idx = r * T + col;
     D[idx] = act ? (VT)fma(bta, (double)Din[idx], (double)Z[idx]) : (VT)0;
@@ -383,7 +437,12 @@ __global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const V
 }
 
 static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D = nullptr, double* dq_partial = nullptr,
-                      float* Q32 = nullptr);
+                      float* Q32 = nullptr, int parts = 1);
+// How many column slabs of P the expansion adds up itself: all of them with the one-hot basis while the extra gathers
+// (n T values from every slab after the first, out of L2) cost less than the launch they save (4 - 5 us)
+static int fold_parts(const nugpr_ctx* c, int T) {
+  return c->onehot && (double)c->L.n * T * (c->L.nsP - 1) <= 3e6 ? c->L.nsP : 1;
+}
 
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial, bool* dq_done,
                const float* D32, float* Q32) {
@@ -424,11 +483,12 @@ int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, doubl
     k2.A = c->Clo; k2.accumulate = 1;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
-  if (L.nsP > 1 && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s))) return rc;
+  const int parts = fold_parts(c, T);
+  if (L.nsP > parts && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s))) return rc;
   // Q_i += W_i P_i (and, on request, the partial sums of <d, q> in the same pass)
   const bool fuse = dq_partial && c->onehot;
   if (dq_done) *dq_done = fuse;
-  if ((rc = run_expand(c, Q, T, s, fuse ? D : nullptr, fuse ? dq_partial : nullptr, Q32))) return rc;
+  if ((rc = run_expand(c, Q, T, s, fuse ? D : nullptr, fuse ? dq_partial : nullptr, Q32, parts))) return rc;
   if (s_known && shortcuts && c->build_gen == c->factor_gen && c->q0_gen != c->build_gen) {
     const size_t bytes = (size_t)L.n * T * (c->acc64 ? sizeof(double) : sizeof(float));
     NUGPR_HIP(hipMemcpyAsync(c->Q0v, Q, bytes, hipMemcpyDeviceToDevice, s));
@@ -511,17 +571,24 @@ __global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ 
 }
 
 // out = Q + W P: out is Q itself, or the caller's fp32 block (the narrowing then costs no pass of its own)
+// (parts: the column slabs of P = C S, a stride apart, are added up here instead of in a pass of their own)
+template <typename VT>
+__device__ __forceinline__ double coupling_value(const VT* __restrict__ P, int64_t at, int parts, uint64_t stride) {
+  VT s = P[at];
+  for (int p = 1; p < parts; ++p) s += P[(uint64_t)p * stride + at];
+  return (double)s;
+}
 template <typename VT, typename OT>
 __global__ __launch_bounds__(256) void k_onehot_expand(const VT* Q, const VT* __restrict__ P,
                                                        const int32_t* __restrict__ assign, int64_t n, int T,
-                                                       OT* out) {
+                                                       OT* out, int parts, uint64_t stride) {
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   if (myrow >= rpp) return;
   for (int64_t p = (int64_t)blockIdx.x * rpp + myrow; p < n; p += (int64_t)gridDim.x * rpp) {
     const int64_t idx = p * T + col;
-    out[idx] = (OT)((double)Q[idx] + (double)P[(int64_t)assign[p] * T + col]);
+    out[idx] = (OT)((double)Q[idx] + coupling_value(P, (int64_t)assign[p] * T + col, parts, stride));
   }
 }
 
@@ -531,7 +598,7 @@ template <typename VT>
 __global__ __launch_bounds__(256) void k_onehot_expand_dot(VT* __restrict__ Q, const VT* __restrict__ P,
                                                            const int32_t* __restrict__ assign,
                                                            const VT* __restrict__ D, int64_t n, int T,
-                                                           double* __restrict__ partial) {
+                                                           double* __restrict__ partial, int parts, uint64_t stride) {
   __shared__ double red[256];
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
@@ -544,7 +611,7 @@ __global__ __launch_bounds__(256) void k_onehot_expand_dot(VT* __restrict__ Q, c
   if (live) {
     for (int64_t p = r0 + myrow; p < r1; p += rpp) {
       const int64_t idx = p * T + col;
-      const VT qn = (VT)((double)Q[idx] + (double)P[(int64_t)assign[p] * T + col]);
+      const VT qn = (VT)((double)Q[idx] + coupling_value(P, (int64_t)assign[p] * T + col, parts, stride));
       Q[idx] = qn;
       s0 = fma((double)D[idx], (double)qn, s0);
     }
@@ -590,21 +657,22 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
 }
 
 // Q += W P with P the first slab of Ppart; with Q32 (one-hot basis, fp64 mode) the sum goes to that fp32 array instead
-static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D, double* dq_partial, float* Q32) {
+static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D, double* dq_partial, float* Q32, int parts) {
   const Layout& L = c->L;
+  const uint64_t stride = (uint64_t)L.ncr * T;
   if (Q32 && !(c->onehot && c->acc64 && !dq_partial)) { set_error("internal: fused narrowing needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot && dq_partial) {
     const int nb = L.n_dot_blocks;
-    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), dim3(nb), dim3(256), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial);
-    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), dim3(nb), dim3(256), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial);
+    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), dim3(nb), dim3(256), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride);
+    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), dim3(nb), dim3(256), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
   if (c->onehot) {
     const int grid = elementwise_grid(L.n, T);
-    if (Q32) hipLaunchKernelGGL((k_onehot_expand<double, float>), dim3(grid), dim3(256), 0, s, (const double*)Q, (const double*)c->Ppart, c->assign, (int64_t)L.n, T, Q32);
-    else if (c->acc64) hipLaunchKernelGGL((k_onehot_expand<double, double>), dim3(grid), dim3(256), 0, s, (const double*)Q, (const double*)c->Ppart, c->assign, (int64_t)L.n, T, (double*)Q);
-    else hipLaunchKernelGGL((k_onehot_expand<float, float>), dim3(grid), dim3(256), 0, s, (const float*)Q, (const float*)c->Ppart, c->assign, (int64_t)L.n, T, (float*)Q);
+    if (Q32) hipLaunchKernelGGL((k_onehot_expand<double, float>), dim3(grid), dim3(256), 0, s, (const double*)Q, (const double*)c->Ppart, c->assign, (int64_t)L.n, T, Q32, parts, stride);
+    else if (c->acc64) hipLaunchKernelGGL((k_onehot_expand<double, double>), dim3(grid), dim3(256), 0, s, (const double*)Q, (const double*)c->Ppart, c->assign, (int64_t)L.n, T, (double*)Q, parts, stride);
+    else hipLaunchKernelGGL((k_onehot_expand<float, float>), dim3(grid), dim3(256), 0, s, (const float*)Q, (const float*)c->Ppart, c->assign, (int64_t)L.n, T, (float*)Q, parts, stride);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -759,6 +827,13 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
   PcgState* hs = reinterpret_cast<PcgState*>(c->h_buf + 2 * cnt);
   double* hdot = c->h_buf + 2 * cnt + (sizeof(PcgState) + sizeof(double) - 1) / sizeof(double);
   const bool want_logs = alpha || beta;
+  // partial sums: sets 0 and 1 belong to the update kernel (|r|^2, <b, x>), 2 to <d, q>, 3 to <r, z>
+  double *const dq_sums = c->dotpart + (size_t)2 * nb * MAX_COLS, *const rz_sums = c->dotpart + (size_t)3 * nb * MAX_COLS;
+  const bool fuse = nb <= FUSE_BLOCKS;
+  // Iterations every one of the last three solves of this kind needed are issued without waiting for their stop
+  // tests: should a column, or all of them, be done earlier, its steps are zero from there on and change nothing.
+  const int* rec = c->recent_iters[plain ? 1 : 0];
+  const int sure = fuse ? std::min(rec[0], std::min(rec[1], rec[2])) : 1;
   // The end-of-solve report (k_pcg_tail) is issued INSIDE the iteration that is expected to be the last
   // one, right behind its stop test, so that it is already on the host when the stop test says "done";
   // a solve that ends earlier or later than the previous one of its kind gets the report after the loop.
@@ -774,17 +849,17 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
     return NUGPR_OK;
   };
   bool tail_current = false;
-  while (it < max_iter && c->h_flags->n_active > 0) {
+  while (it < max_iter) {
     bool dq_done = false;
-    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : run_matvec(c, Dcur, Q, T, s, c->dotpart, &dq_done))) return rc;
+    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : run_matvec(c, Dcur, Q, T, s, dq_sums, &dq_done))) return rc;
     if (!dq_done)
-      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, c->dotpart);
-    hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, c->dotpart, nb, it, c->alog);
+      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums);
+    if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
     // the update, fused with ||r||^2 for the stop test and, in the iteration expected to be the last, <b, x>
     const bool report = it + 1 >= expect || it + 1 >= max_iter;
     hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb), dim3(256), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
-                       c->dotpart);
+                       c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog);
     first = false;
     // stop test first: when every column has converged the preconditioner apply is not needed
     c->flag_seq += 1;
@@ -796,21 +871,20 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
       if ((rc = issue_tail(it + 1, true))) return rc;
       tail_current = true;
     }
-    if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq, s))) return rc;
     const int j = it++;
-    if (c->h_flags->indefinite) indefinite = true;
-    if (c->h_flags->n_active == 0 || it >= max_iter) break;
+    if (it >= sure || it >= max_iter) {
+      if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq, s))) return rc;
+      if (c->h_flags->indefinite) indefinite = true;
+      if (c->h_flags->n_active == 0 || it >= max_iter) break;
+    }
     if (!plain && (rc = run_precond(c, R, Z, T, s))) return rc;
-    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, c->dotpart);
-    hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, c->dotpart, nb, j, c->blog);
-    hipLaunchKernelGGL((k_update_d<VT>), dim3(eg), dim3(256), 0, s, D, Dcur, Zr, c->d_state, n, T);
+    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums);
+    if (!fuse) hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, rz_sums, nb, j, c->blog);
+    hipLaunchKernelGGL((k_update_d<VT>), dim3(fuse ? std::min(eg, 512) : eg), dim3(256), 0, s, D, Dcur, Zr, c->d_state, n, T,
+                       fuse ? rz_sums : (const double*)nullptr, nb, j, c->blog);
     NUGPR_HIP(hipGetLastError());
     Dcur = D;
   }
-  c->expect_iters[plain ? 1 : 0] = it > 0 ? it : 1;
-  c->stats.pcg_solves += 1;
-  c->stats.pcg_iterations += it;
-  c->stats.pcg_iterations_max = std::max<int64_t>(c->stats.pcg_iterations_max, it);
   if (!tail_current && (rc = issue_tail(it, false))) return rc;
   if ((rc = wait_seq(&c->h_flags->tail_seq, c->tail_seq, s))) return rc;
   bool all_conv = true;
@@ -822,6 +896,13 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
     if (hs->indef[col]) indefinite = true;
   }
   if (max_it_used) *max_it_used = mx;
+  const int needed = mx > 0 && mx < it ? mx : it;             // (iterations issued past the last active column's are none)
+  c->expect_iters[plain ? 1 : 0] = std::max(needed, 1);
+  int* recent = c->recent_iters[plain ? 1 : 0];
+  recent[2] = recent[1]; recent[1] = recent[0]; recent[0] = std::max(needed, 1);
+  c->stats.pcg_solves += 1;
+  c->stats.pcg_iterations += needed;
+  c->stats.pcg_iterations_max = std::max<int64_t>(c->stats.pcg_iterations_max, needed);
   if (extras) {
     for (int col = 0; col < T; ++col) {
       extras->bx[col] = hdot[col];
