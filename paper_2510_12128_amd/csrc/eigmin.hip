@@ -15,7 +15,7 @@
 //   (theta, y) = smallest eigenpair of H = V^T C V;  x = V y;  res = C x - theta x;
 //   t = T res with T = blockdiag(B_k + mu I)^-1, B_k the 128 x 128 diagonal blocks of C recomputed in fp64
 //       from the representatives and Cholesky-factored once per assembly (mu = 1e-10 alpha);
-//   t is orthogonalised against V (modified Gram-Schmidt, twice), normalised and appended; C t is computed.
+//   t is orthogonalised against V (Gram-Schmidt, twice), normalised and appended; C t is computed.
 // All vector work of a step runs in single workgroups with fixed-order reductions, so lambda_0 is reproducible
 // to the bit.  Stop: the Ritz value theta is safe when min(|res|, 4 |res|^2 / gap) <= tol (gap: distance to the
 // second Ritz value, used when it is clearly separate), or when |theta| <= tol: a kernel matrix is positive
@@ -46,15 +46,20 @@ struct BlockKernelArgs {
   int n, d;
 };
 
-// Cholesky factor (lower, row-major EB x EB doubles per block, unit rows past the end) of B_k + mu I, where
-// B_k = k(R_k, R_k) for the representatives 128 k .. 128 k + 127, evaluated in fp64 with direct differences.
-__global__ __launch_bounds__(256) void k_block_factor(BlockKernelArgs a, const float* __restrict__ reps,
-                                                      double* __restrict__ Lout) {
-  extern __shared__ __attribute__((aligned(16))) double M[];      // EB rows of EBP
+// Inverse L^-1 of the Cholesky factor (lower, row-major EB x EB doubles per block, unit rows past the end) of
+// B_k + mu I, where B_k = k(R_k, R_k) for the representatives 128 k .. 128 k + 127, evaluated in fp64 with direct
+// differences.  Once per assembly; the explicit triangular inverse turns the two substitutions of every step, 256
+// dependent rounds, into two products.  1024 threads: a pivot's trailing update is the serial part, and a thread keeps
+// its column (256 threads with a division per element: 493 us; now 267 us, inverse included, 2048 representatives).
+constexpr int BF_THREADS = 1024;
+__global__ __launch_bounds__(BF_THREADS) void k_block_factor(BlockKernelArgs a, const float* __restrict__ reps,
+                                                             double* __restrict__ Lout) {
+  extern __shared__ __attribute__((aligned(16))) double M[];      // EB rows of EBP, then EB values
+  double* dj = M + EB * EBP;
   const int blk = blockIdx.x, tid = threadIdx.x;
   const int i0 = blk * EB;
   const int nb = min(EB, a.n - i0);
-  for (int idx = tid; idx < EB * EB; idx += 256) {
+  for (int idx = tid; idx < EB * EB; idx += BF_THREADS) {
     const int i = idx / EB, j = idx % EB;
     double v = (i == j) ? 1.0 : 0.0;
     if (i < nb && j < nb && j <= i) {
@@ -71,57 +76,73 @@ __global__ __launch_bounds__(256) void k_block_factor(BlockKernelArgs a, const f
   }
   __syncthreads();
   // right-looking elimination on the lower triangle; a pivot that rounding pushed below the shift is replaced by it
+  const int col = tid & (EB - 1), part = tid >> 7;
   for (int j = 0; j < nb; ++j) {
-    if (tid == 0) {
-      double p = M[j * EBP + j];
-      if (!(p > 1e-3 * a.mu)) p = 1e-3 * a.mu;
-      M[j * EBP + j] = sqrt(p);
+    double p = M[j * EBP + j];
+    if (!(p > 1e-3 * a.mu)) p = 1e-3 * a.mu;
+    const double ljj = sqrt(p);
+    __syncthreads();                                  // every thread has the pivot
+    if (tid < nb && tid > j) M[tid * EBP + j] /= ljj;
+    if (tid == j) { M[j * EBP + j] = ljj; dj[j] = 1.0 / ljj; }
+    __syncthreads();
+    if (col > j && col < nb) {
+      const double lc = M[col * EBP + j];
+      for (int i = col + part; i < nb; i += BF_THREADS / EB) M[i * EBP + col] = fma(-M[i * EBP + j], lc, M[i * EBP + col]);
     }
     __syncthreads();
-    const double ljj = M[j * EBP + j];
-    for (int i = j + 1 + tid; i < nb; i += 256) M[i * EBP + j] /= ljj;
+  }
+  // inverse in place, row by row: Y[i][c] = -(sum over c <= k < i of L[i][k] Y[k][c]) / L[i][i]; rows above i hold Y
+  __shared__ double part_sum[BF_THREADS];
+  for (int i = 0; i < nb; ++i) {
+    double s = 0.0;
+    if (col < i)
+      for (int k = col + part; k < i; k += BF_THREADS / EB) s = fma(M[i * EBP + k], M[k * EBP + col], s);
+    part_sum[tid] = s;
     __syncthreads();
-    const int m = nb - j - 1;                       // trailing rows / columns
-    for (int idx = tid; idx < m * m; idx += 256) {
-      const int i = j + 1 + idx / m, k = j + 1 + idx % m;
-      if (k <= i) M[i * EBP + k] = fma(-M[i * EBP + j], M[k * EBP + j], M[i * EBP + k]);
+    if (tid < EB && col <= i) {
+      for (int q = 1; q < BF_THREADS / EB; ++q) s += part_sum[tid + q * EB];
+      M[i * EBP + col] = col == i ? dj[i] : -s * dj[i];
     }
     __syncthreads();
   }
   double* out = Lout + (uint64_t)blk * EB * EB;
-  for (int idx = tid; idx < EB * EB; idx += 256) {
+  for (int idx = tid; idx < EB * EB; idx += BF_THREADS) {
     const int i = idx / EB, j = idx % EB;
     out[idx] = j <= i ? M[i * EBP + j] : 0.0;
   }
 }
 
-// t = blockdiag(L_k L_k^T)^-1 res: forward and back substitution inside each block, one workgroup per block
-__global__ __launch_bounds__(128) void k_block_solve(const double* __restrict__ Lall, const double* __restrict__ res,
-                                                     double* __restrict__ t, int n) {
-  extern __shared__ __attribute__((aligned(16))) double Ls[];     // EB x EB factor, then EB values
-  double* x = Ls + EB * EBP;
-  const int blk = blockIdx.x, tid = threadIdx.x;
+// t = blockdiag(Y_k^T Y_k) res with Y_k = L_k^-1: two triangular products per block, one workgroup per block.
+// Rows by waves (shuffles), then columns by threads: 72 us as two substitutions, 9.5 us now (2048 representatives).
+__global__ __launch_bounds__(1024) void k_block_solve(const double* __restrict__ Yall, const double* __restrict__ res,
+                                                      double* __restrict__ t, int n) {
+  __shared__ double x[EB], z[EB], part_sum[1024];
+  const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i0 = blk * EB;
   const int nb = min(EB, n - i0);
-  const double* L = Lall + (uint64_t)blk * EB * EB;
-  for (int idx = tid; idx < EB * EB; idx += 128) Ls[(idx / EB) * EBP + idx % EB] = L[idx];
-  double b = tid < nb ? res[i0 + tid] : 0.0;
+  const double* Y = Yall + (uint64_t)blk * EB * EB;
+  if (tid < EB) x[tid] = tid < nb ? res[i0 + tid] : 0.0;
   __syncthreads();
-  for (int j = 0; j < nb; ++j) {                    // L z = res
-    if (tid == j) x[j] = b / Ls[j * EBP + j];
-    __syncthreads();
-    if (tid > j && tid < nb) b = fma(-Ls[tid * EBP + j], x[j], b);
+  const double x0 = x[lane], x1 = x[lane + 64];
+#pragma unroll
+  for (int q = 0; q < EB / 16; ++q) {                 // rows wave, wave + 16, ..
+    const int i = wave + 16 * q;
+    double s = fma(Y[i * EB + lane], x0, Y[i * EB + lane + 64] * x1);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if (lane == 0) z[i] = s;
   }
   __syncthreads();
-  b = tid < nb ? x[tid] : 0.0;
+  const int col = tid & (EB - 1), part = tid >> 7;
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < EB / 8; ++q) s = fma(Y[(part + 8 * q) * EB + col], z[part + 8 * q], s);
+  part_sum[tid] = s;
   __syncthreads();
-  for (int j = nb - 1; j >= 0; --j) {               // L^T t = z
-    if (tid == j) x[j] = b / Ls[j * EBP + j];
-    __syncthreads();
-    if (tid < j) b = fma(-Ls[j * EBP + tid], x[j], b);
+  if (tid < nb) {
+    for (int q = 1; q < 8; ++q) s += part_sum[tid + q * EB];
+    t[i0 + tid] = s;
   }
-  __syncthreads();
-  if (tid < nb) t[i0 + tid] = x[tid];
 }
 
 // v_0: a fixed +-1 pattern (integer hash of the index), normalised
@@ -149,11 +170,44 @@ __device__ __forceinline__ double block_sum_1024(double x, double* red) {
 
 struct Coef { double y[DAV_MAX_BASIS]; };
 
+// out[k] = <V[k], w>, k = 0 .. m - 1, for all k in one pass: shuffles inside each wave, then the 16 wave totals through
+// LDS in a fixed order (one vector after the other, ten barriers each: the orthogonalisation took 56 us a step instead of 33, the
+// new row 30 instead of 24)
+__device__ __forceinline__ void block_dots(const double* V, const double* w, int m, int n, int ld,
+                                           double (*part)[16], double* out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double acc[DAV_MAX_BASIS];
+#pragma unroll
+  for (int k = 0; k < DAV_MAX_BASIS; ++k) acc[k] = 0.0;
+  for (int i = tid; i < n; i += 1024) {
+    const double wi = w[i];
+#pragma unroll
+    for (int k = 0; k < DAV_MAX_BASIS; ++k)
+      if (k < m) acc[k] = fma(V[(uint64_t)k * ld + i], wi, acc[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < DAV_MAX_BASIS; ++k)
+    if (k < m) {
+      double s = acc[k];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+      if (lane == 0) part[k][wave] = s;
+    }
+  __syncthreads();
+  if (tid < m) {
+    double s = part[tid][0];
+    for (int q = 1; q < 16; ++q) s += part[tid][q];
+    out[tid] = s;
+  }
+  __syncthreads();
+}
+
 // AV[m] = sum of the column-slab partial sums of C V[m]; h[i] = <V[i], AV[m]>, i = 0 .. m
 __global__ __launch_bounds__(1024) void k_eig_newrow(const double* __restrict__ parts, int nparts, uint64_t stride,
                                                      const double* __restrict__ V, double* __restrict__ AV, int m,
                                                      int n, int ld, double* __restrict__ out) {
-  __shared__ double red[1024];
+  __shared__ double part[DAV_MAX_BASIS][16];
+  __shared__ double h[DAV_MAX_BASIS];
   const int tid = threadIdx.x;
   double* av = AV + (uint64_t)m * ld;
   for (int i = tid; i < n; i += 1024) {
@@ -162,13 +216,8 @@ __global__ __launch_bounds__(1024) void k_eig_newrow(const double* __restrict__ 
     av[i] = w;
   }
   __syncthreads();
-  for (int k = 0; k <= m; ++k) {
-    const double* v = V + (uint64_t)k * ld;
-    double acc = 0.0;
-    for (int i = tid; i < n; i += 1024) acc = fma(v[i], av[i], acc);
-    const double s = block_sum_1024(acc, red);
-    if (tid == 0) out[k] = s;
-  }
+  block_dots(V, av, m + 1, n, ld, part, h);
+  if (tid <= m) out[tid] = h[tid];
 }
 
 // x = V y, res = AV y - theta x (m vectors); out[0] = |res|^2.  x is not kept: only the residual is needed.
@@ -192,26 +241,30 @@ __global__ __launch_bounds__(1024) void k_eig_residual(const double* __restrict_
   if (tid == 0) out[0] = s;
 }
 
-// V[m] = t orthogonalised against V[0 .. m-1] (modified Gram-Schmidt, two passes) and normalised;
-// out[0] = its norm before the normalisation
-__global__ __launch_bounds__(1024) void k_eig_orth(double* __restrict__ V, const double* __restrict__ t, int m, int n,
+// V[m] = t orthogonalised against V[0 .. m-1] (classical Gram-Schmidt, two passes: orthogonal to rounding, as the
+// modified form, and all coefficients of a pass at once) and normalised; out[0] = its norm before the normalisation
+__global__ __launch_bounds__(1024) void k_eig_orth(double* V, const double* __restrict__ t, int m, int n,
                                                    int ld, double* __restrict__ out) {
   __shared__ double red[1024];
+  __shared__ double part[DAV_MAX_BASIS][16];
+  __shared__ double h[DAV_MAX_BASIS];
   const int tid = threadIdx.x;
   double* vn = V + (uint64_t)m * ld;
   for (int i = tid; i < n; i += 1024) vn[i] = t[i];
   __syncthreads();
-  for (int pass = 0; pass < 2; ++pass)
-    for (int k = 0; k < m; ++k) {
-      const double* v = V + (uint64_t)k * ld;
-      double acc = 0.0;
-      for (int i = tid; i < n; i += 1024) acc = fma(v[i], vn[i], acc);
-      const double s = block_sum_1024(acc, red);
-      for (int i = tid; i < n; i += 1024) vn[i] = fma(-s, v[i], vn[i]);
-      __syncthreads();
-    }
   double acc = 0.0;
-  for (int i = tid; i < n; i += 1024) acc = fma(vn[i], vn[i], acc);
+  for (int pass = 0; pass < 2; ++pass) {
+    block_dots(V, vn, m, n, ld, part, h);
+    for (int i = tid; i < n; i += 1024) {
+      double v = vn[i];
+#pragma unroll
+      for (int k = 0; k < DAV_MAX_BASIS; ++k)
+        if (k < m) v = fma(-h[k], V[(uint64_t)k * ld + i], v);
+      vn[i] = v;
+      if (pass == 1) acc = fma(v, v, acc);
+    }
+    __syncthreads();
+  }
   const double nrm = sqrt(block_sum_1024(acc, red));
   const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
   for (int i = tid; i < n; i += 1024) vn[i] *= inv;
@@ -263,10 +316,11 @@ static void small_sym_eigen(std::vector<double>& A, int m, std::vector<double>& 
     for (int i = 0; i < m; ++i)
       for (int j = 0; j < m; ++j) (i == j ? diag : off) += A[(size_t)i * m + j] * A[(size_t)i * m + j];
     if (off <= 1e-32 * diag) break;
+    const double none = 1e-33 * diag / ((double)m * m);      // entries this small, all together, pass the test above
     for (int p = 0; p < m; ++p)
       for (int q = p + 1; q < m; ++q) {
         const double apq = A[(size_t)p * m + q];
-        if (apq == 0.0) continue;
+        if (apq * apq <= none) continue;
         const double tau = (A[(size_t)q * m + q] - A[(size_t)p * m + p]) / (2.0 * apq);
         const double t = (tau >= 0.0 ? 1.0 : -1.0) / (std::fabs(tau) + std::sqrt(1.0 + tau * tau));
         const double cs = 1.0 / std::sqrt(1.0 + t * t), sn = t * cs;
@@ -311,18 +365,14 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
   const int nblk = (n + EB - 1) / EB;
   double *V = c->dav, *AV = V + (size_t)DAV_MAX_BASIS * ld, *res = AV + (size_t)DAV_MAX_BASIS * ld, *tvec = res + ld,
          *small = tvec + ld, *Lblk = small + 64;
-  static const hipError_t lds_attr = []() {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_block_factor), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       EB * EBP * (int)sizeof(double));
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_block_solve), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (EB * EBP + EB) * (int)sizeof(double));
-  }();
+  constexpr int factor_lds = (EB * EBP + EB) * (int)sizeof(double);
+  static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_block_factor),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, factor_lds);
   NUGPR_HIP(lds_attr);
   BlockKernelArgs ba;
   for (int k = 0; k < MAX_D; ++k) ba.inv_ell[k] = k < L.d ? 1.0 / (iso ? theta[0] : theta[k]) : 0.0;
   ba.alpha = alpha; ba.mu = 1e-10 * alpha; ba.n = n; ba.d = L.d;
-  hipLaunchKernelGGL(k_block_factor, dim3(nblk), dim3(256), EB * EBP * sizeof(double), s, ba, c->reps, Lblk);
+  hipLaunchKernelGGL(k_block_factor, dim3(nblk), dim3(BF_THREADS), factor_lds, s, ba, c->reps, Lblk);
   hipLaunchKernelGGL(k_eig_start, dim3(64), dim3(256), 0, s, V, n);
   NUGPR_HIP(hipGetLastError());
   const uint64_t stride = (uint64_t)n;            // one column: a slab of the partial sums is n doubles
@@ -380,7 +430,7 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
     for (int k = 0; k < DAV_MAX_BASIS; ++k) cf.y[k] = k < m ? Y[(size_t)k * m + 0] : 0.0;
     hipLaunchKernelGGL(k_eig_residual, dim3(1), dim3(1024), 0, s, (const double*)V, (const double*)AV, cf, thetaR, m, n, ld,
                        res, small);
-    hipLaunchKernelGGL(k_block_solve, dim3(nblk), dim3(128), (EB * EBP + EB) * sizeof(double), s, (const double*)Lblk,
+    hipLaunchKernelGGL(k_block_solve, dim3(nblk), dim3(1024), 0, s, (const double*)Lblk,
                        (const double*)res, tvec, n);
     hipLaunchKernelGGL(k_eig_orth, dim3(1), dim3(1024), 0, s, V, (const double*)tvec, m, n, ld, small + 1);
     NUGPR_HIP(hipGetLastError());
