@@ -166,13 +166,15 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
     last = (atomicAdd(&st->check_count, 1) == T - 1);
   }
   __syncthreads();
-  if (last && tid == 0) {
+  if (last && tid < 64) {                      // one wave, a lane per column (one after the other: 4 us)
     __threadfence();
-    int n_active = 0, indef = 0;
-    for (int k = 0; k < T; ++k) {
-      n_active += *reinterpret_cast<volatile int32_t*>(&st->active[k]);
-      indef |= *reinterpret_cast<volatile int32_t*>(&st->indef[k]);
+    int act = 0, ind = 0;
+    if (tid < T) {
+      act = *reinterpret_cast<volatile int32_t*>(&st->active[tid]);
+      ind = *reinterpret_cast<volatile int32_t*>(&st->indef[tid]);
     }
+    const int n_active = __popcll(__ballot(act != 0)), indef = __ballot(ind != 0) != 0 ? 1 : 0;
+    if (tid != 0) return;
     st->check_count = 0;
     st->n_active = n_active;
     st->indefinite = indef;
