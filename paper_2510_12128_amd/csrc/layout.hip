@@ -85,7 +85,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
     want = (2048 + strips_P - 1) / strips_P;
     L.nsP = std::max(1, std::min({want, 16, L.ldc / TILE}));
   }
-  L.n_dot_blocks = (int)std::min<int64_t>(1024, (L.n + 255) / 256);
+  L.n_dot_blocks = (int)std::min<int64_t>(1024, (L.n + 127) / 128);
 
   size_t cur = 0;
   const size_t f = sizeof(float);

@@ -209,9 +209,9 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
 }
 
 // Problems of up to FUSE_BLOCKS partial sums per column (32768 points): the kernels that apply alpha and beta sum them
-// up themselves, every workgroup in the same fixed order (17 KB of L2 reads a workgroup at 128 x 17), and the first
+// up themselves, every workgroup in the same fixed order (35 KB of L2 reads a workgroup at 256 x 17), and the first
 // one keeps the records.  That saves a launch of 3 - 5 us each; with 1024 partial sums every workgroup would read 139 KB.
-constexpr int FUSE_BLOCKS = 128;
+constexpr int FUSE_BLOCKS = 256;
 __device__ __forceinline__ void sum_all_partials(const double* __restrict__ partial, int nblocks, int T, double* red, double* out) {
   const int rpp = 256 / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
   double s = 0.0;
