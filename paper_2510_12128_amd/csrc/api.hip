@@ -227,12 +227,10 @@ void build_tables(const Layout& L, Tables& t) {
   arrange_for_dies(t.lowL);
 }
 
-int upload_table(const std::vector<StripItem>& v, StripItem*& cursor, StripTable& tab, hipStream_t s) {
+int upload_table(const std::vector<StripItem>& v, uint64_t matrix_elems, StripItem*& cursor, StripTable& tab, hipStream_t s) {
   tab.dev = cursor;
   tab.count = (int)v.size();
-  tab.sym = false;
-  tab.rowmajor = !v.empty() && v[0].blocked == 0;
-  for (const StripItem& it : v) tab.sym = tab.sym || (it.blocked & 2u) != 0;
+  tab.kind = strip_kind(v, matrix_elems * sizeof(float));
   if (!v.empty())
     NUGPR_HIP(hipMemcpyAsync(cursor, v.data(), v.size() * sizeof(StripItem), hipMemcpyHostToDevice, s));
   cursor += v.size();
@@ -361,15 +359,15 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   const size_t total_items = t.WtD.size() + t.KC.size() + t.Conly.size() + t.WP.size() + t.lowG.size() + t.upG.size() + t.lowL.size();
   if (total_items * sizeof(StripItem) > L.items_bytes) { set_error("internal: strip table overflow"); return fail(NUGPR_ERR_INVALID); }
   StripItem* cur = reinterpret_cast<StripItem*>(w + L.o_items);
-  if ((rc = upload_table(t.WtD, cur, c->tab_WtD, s))) return fail(rc);
-  if ((rc = upload_table(t.KC, cur, c->tab_KC, s))) return fail(rc);
+  if ((rc = upload_table(t.WtD, L.wt_elems, cur, c->tab_WtD, s))) return fail(rc);
+  if ((rc = upload_table(t.KC, L.kd_elems, cur, c->tab_KC, s))) return fail(rc);
   c->c_paired = false;
   for (const StripItem& it : t.KC) c->c_paired = c->c_paired || (it.port == 1 && (it.blocked & 2u) != 0);
-  if ((rc = upload_table(t.Conly, cur, c->tab_C, s))) return fail(rc);
-  if ((rc = upload_table(t.WP, cur, c->tab_WP, s))) return fail(rc);
-  if ((rc = upload_table(t.lowG, cur, c->tab_lowG, s))) return fail(rc);
-  if ((rc = upload_table(t.upG, cur, c->tab_upG, s))) return fail(rc);
-  if ((rc = upload_table(t.lowL, cur, c->tab_lowL, s))) return fail(rc);
+  if ((rc = upload_table(t.Conly, (uint64_t)L.ldc * L.ldc, cur, c->tab_C, s))) return fail(rc);
+  if ((rc = upload_table(t.WP, (uint64_t)L.n * L.ldw, cur, c->tab_WP, s))) return fail(rc);
+  if ((rc = upload_table(t.lowG, L.kd_elems, cur, c->tab_lowG, s))) return fail(rc);
+  if ((rc = upload_table(t.upG, L.kd_elems, cur, c->tab_upG, s))) return fail(rc);
+  if ((rc = upload_table(t.lowL, L.kd_elems, cur, c->tab_lowL, s))) return fail(rc);
   e = hipStreamSynchronize(s);          // host vectors go out of scope below
   if (e != hipSuccess) return fail(hip_fail(e, "sync after table upload"));
   if ((rc = launch_setup(c, pb->reps, pb->W, s))) return fail(rc);

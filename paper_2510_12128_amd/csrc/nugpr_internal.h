@@ -107,8 +107,7 @@ struct StripArgs {
 struct StripTable {
   StripItem* dev = nullptr;
   int count = 0;
-  bool rowmajor = false; // the items' matrix is stored row-major (all of them, or none)
-  bool sym = false;      // some items are strips of symmetric blocks (StripItem::blocked bit 1)
+  int kind = 0;          // which instantiation of the strip kernel serves it (strip_kind)
 };
 
 // ---------------------------------------------------------------------------
@@ -315,7 +314,9 @@ int coupling_set_diag(nugpr_ctx* c, double value, hipStream_t s);
 int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64,
                  hipStream_t s);
 
-// name of the kernel instantiation launch_strip picks for such a table and width (profilers' spelling, no namespace)
+// the instantiation for a table of these items over a matrix of that size
+int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes);
+// its name for such a table and width (profilers' spelling, no namespace), valid until the thread's next call
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64);
 
 int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64_t stride, bool acc64,

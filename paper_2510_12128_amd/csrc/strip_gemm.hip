@@ -20,7 +20,8 @@
 // Operands: the matrix goes from memory straight into registers, STAGES steps ahead (7 KiB a step and wave); the
 // step's 16 vector rows arrive as contiguous 16-byte loads and take their operand order through a piece of LDS that
 // belongs to the wave.  Loads past the last tile are issued out of range instead of being skipped: the number in
-// flight is what the waits count.
+// flight is what the waits count.  Such a load still costs the address unit its 25 - 30 cycles, so the loop refills
+// only while a whole turn of it remains, and a strip of few tiles wants few stages.
 //
 // What bounds it.  fp64: the matrix cores and the vector ALUs share one pipe (16 MFMAs x 64 cycles and 32 vector
 // instructions a step: 550 ns at the sustained clock, measured without any memory access); 1 - 17 columns also the
@@ -32,6 +33,13 @@
 // Tried and not kept: vector operands loaded in operand order from memory (the address unit takes 25 - 30 cycles
 // for a load whatever its width: 640 us); workgroups that stay and take item after item (741 us), or whose start is
 // staggered (580 us): both take the partner strips below out of step.
+// Short triangular strips (clusters of up to about 1024 points) spend their time at the two ends, so what counts is how
+// many workgroups a compute unit holds: two stages, the vector operands made ready when they are needed, and with two
+// column groups two row groups a wave, which leaves four waves per SIMD in place of two.  With the long strips' two waves
+// x four stages and streaming loads for every size, clusters this small were slower than under the loader wave.
+// Preconditioner apply, fp64, 17 columns, loader wave / two waves x four stages / now: 2000 clusters of 64 points
+// 48 / 60 / 46 us, 600 uneven ones of 100 35 / 48 / 37, 300 uneven ones of 200 41 / 53 / 43, 256 x 512 94 / 108 / 89,
+// 32 x 1024 49 / 52 / 46; 33 columns 69 / 83 / 64, 50 / 63 / 51, 57 / 71 / 61, 146 / 154 / 131, 77 / 77 / 76.
 //
 // Two arithmetic modes, same data movement:
 //   ACC64 = true   vector blocks are fp64; the fp32 matrix entries are widened in
@@ -55,6 +63,7 @@
 // LDS: each lane fetches the 16-byte piece (row 4 ((l / 4) % 4) + l / 16, columns 4 (l % 4) ..) of the stored
 // fragment, which puts element (4 kg + i, m) at float 64 i + 16 kg + m, so both accesses have unit stride.
 #include <algorithm>
+#include <cstdio>
 #include <type_traits>
 
 #include "nugpr_internal.h"
@@ -62,6 +71,7 @@
 namespace nugpr {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 template <bool ACC64> struct VecT { typedef float type; };
@@ -75,41 +85,54 @@ __device__ __forceinline__ int acc_row(int lane, int i) {
 }
 
 constexpr int NW = 4;                  // waves of a workgroup
-enum { STRIP_PLAIN = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2 };      // what the items of a table are
+// What the items of a table are.  STRIP_STREAMED (added to the first and the last): matrix loads with the streaming hint.
+enum { STRIP_LONG = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2, STRIP_SHORT = 3, STRIP_STREAMED = 4 };
 template <int NG, bool ACC64, int KIND> struct WaveCfg {
   typedef typename VecT<ACC64>::type VT;
+  static constexpr int BASE = KIND & 3;
+  static constexpr bool SHORT = BASE == STRIP_SHORT;
   // Waves per SIMD and steps in flight, as the registers allow.  Symmetric strips in fp64 with one column group: 3
-  // waves x 3 stages 500 us, 2 x 4 527 us (workload in the file's head); strips without partners, which stream from
-  // HBM: 2 x 4 108 us, 3 x 3 117 us.
-  static constexpr int WAVES_PER_EU = KIND == STRIP_SYM && ACC64 && NG == 1 ? 3 : 2;
-  static constexpr int STAGES = NG == 2 && !ACC64 ? 2 : (WAVES_PER_EU == 3 || NG == 2 ? 3 : 4);
+  // waves x 3 stages 500 us, 2 x 4 527 us (workload in the file's head); long strips without partners, which stream from
+  // HBM: 2 x 4 108 us, 3 x 3 117 us.  Short strips: see the file's head.
+  static constexpr int WAVES_PER_EU = SHORT ? (NG == 1 && !ACC64 ? 3 : 4) : BASE == STRIP_SYM && ACC64 && NG == 1 ? 3 : 2;
+  static constexpr int STAGES = SHORT || (NG == 2 && !ACC64) ? 2 : (WAVES_PER_EU == 3 || NG == 2 ? 3 : 4);
+  // Row groups of a wave: all four with a quarter of a tile's columns, or two with half of them (short strips of two
+  // column groups: half the accumulators, so that four waves fit; the vector rows are then read twice)
+  static constexpr int ROW_GROUPS = SHORT && NG == 2 ? 2 : 4;
+  // the vector operands of the next step are made ready while the matrix cores work on the present one
+  static constexpr bool AHEAD = !SHORT;
   static constexpr int NB = NG > 0 ? NG : 1;
-  // 16-byte loads per lane that cover the vector rows of a step (16 rows of at most 16 NG + 1 columns)
-  static constexpr int NV = NG > 0 ? (16 * (16 * NG + 1) * (int)sizeof(VT) + 1023) / 1024 : 1;
-  static constexpr int WAVE_LDS = 4096 + NV * 1024;            // a wave's LDS: a tile on its way to its transpose, vector rows
+  // 16-byte loads per lane that cover the vector rows of a step (16 rows of at most 16 NG + 1 columns; with one column the
+  // lane's own four rows, which are contiguous)
+  static constexpr int NV = NG > 0 ? (16 * (16 * NG + 1) * (int)sizeof(VT) + 1023) / 1024 : (int)sizeof(VT) / 4;
+  static constexpr int TURN_LDS = BASE == STRIP_SYM ? 4096 : 0;  // a wave's LDS: a tile on its way to its transpose,
+  static constexpr int WAVE_LDS = TURN_LDS + NV * 1024;          // vector rows
 };
 
 template <int NG, bool ACC64, int KIND>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCfg<NG, ACC64, KIND>::WAVES_PER_EU)))) void k_strip(const StripArgs a) {
   typedef WaveCfg<NG, ACC64, KIND> Cfg;
   typedef typename Cfg::VT VT;
-  constexpr bool RM = KIND == STRIP_ROWMAJOR, SYM = KIND == STRIP_SYM;
-  constexpr int ST = Cfg::STAGES, NB = Cfg::NB, NV = Cfg::NV;
+  constexpr bool RM = Cfg::BASE == STRIP_ROWMAJOR, SYM = Cfg::BASE == STRIP_SYM, TRI = !RM && !SYM;
+  constexpr int ST = Cfg::STAGES, NB = Cfg::NB, NV = Cfg::NV, RG = Cfg::ROW_GROUPS;
+  constexpr int KP = RG, SP = 4 / RG;                        // waves that share a row's columns; steps of a wave in a tile
+  constexpr int HINT = (KIND & STRIP_STREAMED) ? 2 : 0;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
   const int T = a.T;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 15, kg = lane >> 4;
-  const int sub = wave;                                      // which 16 columns of every 64-column tile are this wave's
+  // which 16 SP columns of every 64-column tile are this wave's, and its first row group
+  const int part = KP == NW ? wave : wave % KP, g0 = KP == NW ? 0 : wave / KP * RG;
   const uint32_t rowbytes = (uint32_t)T * (uint32_t)sizeof(VT);
 
-  // What the loops need to know of an item.  Tile numbers p = 0 .. nb - 1 run from the item's first column on.  The
-  // diagonal tile of a triangular item is masked and comes first, the others are taken in turn (tile_of).
+  // What the loops need to know of an item.  Tile numbers p = 0 .. nb - 1 run from the item's first column on and are
+  // visited in a rotating order (tile_of): a triangular item begins with its diagonal tile, which is masked.
   struct Strip {
     const char *A, *V;         // matrix (strip row 0, column 0) and the vector row of the item's first column
     uint32_t lda, vbytes;
-    int c_begin, nrows, mode, p_lo, p_diag, cnt, jm, thr, tbj, j_abs;
+    int c_begin, nrows, mode, cnt, jm, thr, tbj, j_abs;
   } S;
   auto setup = [&](const StripItem& it) {
     const StripPort& pt = a.port[it.port];
@@ -122,12 +145,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     S.j_abs = (int)it.row_in_block >> 6;
     const int jr = ((fl >> 4) & 0x7ffu) ? (int)((fl >> 15) & 0x7ffu) : S.j_abs - tb;
     S.mode = (int)it.mode;
-    int p_hi = nb;
-    S.p_lo = 0; S.p_diag = -1;
-    if (KIND == STRIP_PLAIN && nb > 0 && S.mode == 1) { p_hi -= 1; S.p_diag = p_hi; }
-    if (KIND == STRIP_PLAIN && nb > 0 && S.mode == 2) { S.p_lo = 1; S.p_diag = 0; }
-    S.cnt = p_hi - S.p_lo;
-    S.jm = !sym || S.cnt <= 0 ? 0 : (jr < S.cnt ? jr : jr % S.cnt);
+    S.cnt = nb;
+    // (the diagonal tile is the last one of mode 1 and the first one of mode 2)
+    S.jm = TRI ? (S.mode == 1 ? 1 : 0) : !sym || nb <= 0 ? 0 : (jr < nb ? jr : jr % nb);
     S.thr = !sym || kind == 1 ? 0x7fffffff : (kind == 2 ? -1 : jr);      // tiles past it are read transposed
     S.tbj = tb - S.j_abs;
     S.A = reinterpret_cast<const char*>(pt.A + it.a_off);
@@ -137,7 +157,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     S.c_begin = c_begin;
     S.nrows = (int)it.nrows;
   };
-  auto tile_of = [&](const int u) { int p = min(u, S.cnt - 1) - S.jm; p += p < 0 ? S.cnt : 0; return S.p_lo + p; };
+  auto tile_of = [&](const int u) { int p = min(u, S.cnt - 1) - S.jm; p += p < 0 ? S.cnt : 0; return p; };
   auto turned = [&](const int p) { return SYM && p > S.thr; };
 
   // Buffer loads: the address is a scalar base + a lane offset that never changes, so the loop computes no vector
@@ -155,7 +175,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     for (int n = 0; n < NB; ++n) boff[n][j] = yoff[j] + (uint32_t)min(1 + 16 * n + m, T - 1) * (uint32_t)sizeof(VT);
   }
 
-  auto load_a = [&](v4f (&ra)[4], const int p, const bool valid) {
+  auto load_a = [&](v4f (&ra)[RG], const int p, const int sub, const bool valid) {
     const int c = S.c_begin + TILE * p;                      // first column of the tile
     // transposed: fragments (row group sub, columns 16 g ..) of the stored tile (column tile of p, tile row of the strip)
     const bool tr = turned(p);
@@ -164,17 +184,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     const auto res = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(S.A + (tr ? far : own) * 4), 0, valid ? 0x7fffffff : 0, 0x00027000);
     const uint32_t off = tr ? toff : ooff;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int so = RM || !valid ? 0 : (tr ? ((g >> 1) * (TILE * BLK_COLS) + (g & 1) * FRAG) * 4 : g * 2 * FRAG * 4);
-      const uint32_t ro = RM ? (uint32_t)min(16 * g + m, S.nrows - 1) * S.lda * 4u + 16u * (uint32_t)kg : off;
-      ra[g] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(res, ro, so, SYM ? 0 : 2));
+    for (int g = 0; g < RG; ++g) {
+      const int so = RM || !valid ? 0 : (tr ? ((g >> 1) * (TILE * BLK_COLS) + (g & 1) * FRAG) * 4 : (g0 + g) * 2 * FRAG * 4);
+      const uint32_t ro = RM ? (uint32_t)min(16 * (g0 + g) + m, S.nrows - 1) * S.lda * 4u + 16u * (uint32_t)kg : off;
+      ra[g] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(res, ro, so, HINT));
     }
   };
-  struct VRegs { typename std::conditional<(NG > 0), v4f, VT>::type q[NG > 0 ? NV : 4]; };
+  struct VRegs { v4f q[NV]; };
   // (valid = false: past the wave's last tile; every load is out of range and touches no memory, so that the number of
   // loads in flight stays what the loop's waits count on)
-  auto load = [&](v4f (&ra)[4], VRegs& rv, const int p, const bool valid) {
-    load_a(ra, p, valid);
+  auto load = [&](v4f (&ra)[RG], VRegs& rv, const int u, const bool valid) {
+    const int p = tile_of(SP == 1 ? u : u / SP), sub = SP == 1 ? part : part * SP + u % SP;
+    load_a(ra, p, sub, valid);
     const auto vres = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(S.V), 0, (int)S.vbytes, 0x00027000);
     const int so = valid ? (int)min((uint32_t)(TILE * p + 16 * sub) * rowbytes, S.vbytes) : (int)S.vbytes;
     if constexpr (NG > 0) {
@@ -185,24 +206,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
                       1024u * i < 16u * rowbytes ? (int)min((uint32_t)(so + 1024 * i), S.vbytes) : (int)S.vbytes, 0));
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if constexpr (ACC64) rv.q[j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vres, yoff[j], so, 0));
-        else rv.q[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vres, yoff[j], so, 0));
-      }
+      for (int i = 0; i < NV; ++i)
+        rv.q[i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(vres, yoff[0] + 16u * i, so, 0));
     }
   };
 
   // accumulators: fp64 running sums; in the fp32 mode the matrix cores fill a fresh fp32 chain every 16 columns
-  v4d acc[4][NB];
-  double accy[4];
+  v4d acc[RG][NB];
+  double accy[RG];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < RG; ++g) {
     accy[g] = 0.0;
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[g][n] = (v4d){0.0, 0.0, 0.0, 0.0};
   }
   float* tr_lds = reinterpret_cast<float*>(lds + wave * Cfg::WAVE_LDS);
-  unsigned char* v_lds = lds + wave * Cfg::WAVE_LDS + 4096;
+  unsigned char* v_lds = lds + wave * Cfg::WAVE_LDS + Cfg::TURN_LDS;
   // vector rows of a step: through the wave's LDS into operand order
   auto spread = [&](const VRegs& rv, VT (&rb)[NB][4], VT (&ry)[4]) {
     if constexpr (NG > 0) {
@@ -221,126 +240,128 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
       __builtin_amdgcn_wave_barrier();
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) ry[j] = rv.q[j];
+      for (int j = 0; j < 4; ++j) {
+        if constexpr (ACC64) ry[j] = __builtin_bit_cast(v2d, rv.q[j >> 1])[j & 1];
+        else ry[j] = rv.q[0][j];
+      }
     }
   };
   // the operand of a transposed tile passes the wave's own piece of LDS (a wave's LDS accesses are served in order)
-  auto turn = [&](v4f (&ra)[4]) {
+  auto turn = [&](v4f (&ra)[RG]) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) reinterpret_cast<v4f*>(tr_lds)[g * 64 + lane] = ra[g];
+    for (int g = 0; g < RG; ++g) reinterpret_cast<v4f*>(tr_lds)[g * 64 + lane] = ra[g];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < RG; ++g)
 #pragma unroll
       for (int i = 0; i < 4; ++i) ra[g][i] = tr_lds[g * 256 + 64 * i + lane];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  auto compute = [&](const v4f (&ra)[4], const VT (&rb)[NB][4], const VT (&ry)[4]) {
+  auto compute = [&](const v4f (&ra)[RG], const VT (&rb)[NB][4], const VT (&ry)[4]) {
     if constexpr (ACC64) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        double ad[4];
+        double ad[RG];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) ad[g] = (double)ra[g][j];
+        for (int g = 0; g < RG; ++g) ad[g] = (double)ra[g][j];
         if (NG > 0) {
 #pragma unroll
           for (int n = 0; n < NB; ++n)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) acc[g][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[g], rb[n][j], acc[g][n], 0, 0, 0);
+            for (int g = 0; g < RG; ++g) acc[g][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[g], rb[n][j], acc[g][n], 0, 0, 0);
         }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) accy[g] = fma(ad[g], ry[j], accy[g]);
+        for (int g = 0; g < RG; ++g) accy[g] = fma(ad[g], ry[j], accy[g]);
       }
     } else {
       if (NG > 0) {
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
           if (n > 0) __builtin_amdgcn_sched_barrier(0);     // one column group's chains at a time: registers
-          v4f f[4];
+          v4f f[RG];
 #pragma unroll
-          for (int g = 0; g < 4; ++g) f[g] = (v4f){0.f, 0.f, 0.f, 0.f};
+          for (int g = 0; g < RG; ++g) f[g] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) f[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[g][j], rb[n][j], f[g], 0, 0, 0);
+            for (int g = 0; g < RG; ++g) f[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(ra[g][j], rb[n][j], f[g], 0, 0, 0);
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
+          for (int g = 0; g < RG; ++g)
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[g][n][i] += (double)f[g][i];
         }
       }
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int g = 0; g < RG; ++g)
         accy[g] += (double)fmaf(ra[g][3], ry[3], fmaf(ra[g][2], ry[2], fmaf(ra[g][1], ry[1], ra[g][0] * ry[0])));
     }
     // pins the y sums to this place: the compiler otherwise moves them behind the loop's last use and keeps every
     // operand alive until then
 #pragma unroll
-    for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(accy[g]));
+    for (int g = 0; g < RG; ++g) asm volatile("" : "+v"(accy[g]));
   };
 
-  v4f sa[ST][4];
+  v4f sa[ST][RG];
   VRegs sv[ST];
   VT cb[2][NB][4], cy[2][4];                                 // vector operands of the step at hand and of the next one
   auto ready = [&](auto s_c, const int u) {                  // operands of sequence number u, held by stage s
     constexpr int s = decltype(s_c)::value;
     if (turned(tile_of(u))) turn(sa[s % ST]);
-    spread(sv[s % ST], cb[s & 1], cy[s & 1]);
-  };
-  // the diagonal tile passes through the last stage's registers before the loop needs them
-  auto start = [&]() {
-    if (S.p_diag >= 0) load(sa[ST - 1], sv[ST - 1], S.p_diag, true);
-#pragma unroll
-    for (int s = 0; s + 1 < ST; ++s) load(sa[s], sv[s], tile_of(s), s < S.cnt);
+    spread(sv[s % ST], cb[Cfg::AHEAD ? s & 1 : 0], cy[Cfg::AHEAD ? s & 1 : 0]);
   };
   const StripItem& it = a.items[blockIdx.x];
   setup(it);
-  start();
+  const int cnt = SP * S.cnt;                                // steps of a wave
   {
-    if (S.p_diag >= 0) {
-      const int q0 = 16 * sub + 4 * kg;                      // column of this lane's first element inside the tile
+    if (cnt > 0) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int s = 0; s + 1 < ST; ++s) load(sa[s], sv[s], s, s < cnt);
+      __builtin_amdgcn_sched_barrier(0);
+      load(sa[ST - 1], sv[ST - 1], ST - 1, ST - 1 < cnt);
+      if (TRI && S.mode != 0) {                              // the diagonal tile: the wave's first SP steps
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool keep = S.mode == 1 ? q0 + i <= 16 * g + m : q0 + i >= 16 * g + m;
-          sa[ST - 1][g][i] = keep ? sa[ST - 1][g][i] : 0.f;
+        for (int s = 0; s < SP; ++s) {
+          const int q0 = 16 * (part * SP + s) + 4 * kg;      // column of this lane's first element inside the tile
+#pragma unroll
+          for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int row = 16 * (g0 + g) + m;
+              sa[s][g][i] = (S.mode == 1 ? q0 + i <= row : q0 + i >= row) ? sa[s][g][i] : 0.f;
+            }
         }
-      spread(sv[ST - 1], cb[1], cy[1]);
-      compute(sa[ST - 1], cb[1], cy[1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (S.cnt > 0) {
-      load(sa[ST - 1], sv[ST - 1], tile_of(ST - 1), ST - 1 < S.cnt);
+      }
       int i = 0;
-      ready(std::integral_constant<int, 0>(), 0);
+      if constexpr (Cfg::AHEAD) ready(std::integral_constant<int, 0>(), 0);
       constexpr int UN = ST % 2 == 0 ? ST : 2 * ST;          // the operand buffers alternate: an even number of steps
       auto step = [&](auto s_c, const bool refill) {
         constexpr int s = decltype(s_c)::value;
-        ready(std::integral_constant<int, s + 1>(), i + s + 1);
-        compute(sa[s % ST], cb[s & 1], cy[s & 1]);
+        if constexpr (Cfg::AHEAD) ready(std::integral_constant<int, s + 1>(), i + s + 1);
+        else ready(s_c, i + s);
+        compute(sa[s % ST], cb[Cfg::AHEAD ? s & 1 : 0], cy[Cfg::AHEAD ? s & 1 : 0]);
         __builtin_amdgcn_sched_barrier(0);
-        if (refill) load(sa[s % ST], sv[s % ST], tile_of(i + s + ST), i + s + ST < S.cnt);
+        if (refill) load(sa[s % ST], sv[s % ST], i + s + ST, i + s + ST < cnt);
         __builtin_amdgcn_sched_barrier(0);
       };
-      for (; i + UN <= S.cnt; i += UN) {
+      for (; i + UN < cnt; i += UN) {
         step(std::integral_constant<int, 0>(), true);
         step(std::integral_constant<int, 1>(), true);
         if constexpr (UN > 2) { step(std::integral_constant<int, 2>(), true); step(std::integral_constant<int, 3>(), true); }
         if constexpr (UN > 4) { step(std::integral_constant<int, 4>(), true); step(std::integral_constant<int, 5>(), true); }
       }
-      const int rem = S.cnt - i;                             // < UN; with UN = 2 ST the first steps still refill
-      if (rem > 0) step(std::integral_constant<int, 0>(), UN > ST);
+      const int rem = cnt - i;                               // 1 .. UN; with UN = 2 ST the first steps still refill
+      step(std::integral_constant<int, 0>(), UN > ST);
+      if (rem > 1) step(std::integral_constant<int, 1>(), UN > ST);
       if constexpr (UN > 2) {
-        if (rem > 1) step(std::integral_constant<int, 1>(), UN > ST);
-        if (rem > 2) step(std::integral_constant<int, 2>(), false);
+        if (rem > 2) step(std::integral_constant<int, 2>(), UN > ST);
+        if (rem > 3) step(std::integral_constant<int, 3>(), false);
       }
       if constexpr (UN > 4) {
-        if (rem > 3) step(std::integral_constant<int, 3>(), false);
         if (rem > 4) step(std::integral_constant<int, 4>(), false);
+        if (rem > 5) step(std::integral_constant<int, 5>(), false);
       }
     }
 
@@ -352,29 +373,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     const bool accumulate = pt.accumulate != 0;
     // ---- the waves' sums are added in a fixed order ----
     __syncthreads();                                         // every wave is done with its own piece of LDS
-    double* red = reinterpret_cast<double*>(lds) + (size_t)wave * per;
+    double* red = reinterpret_cast<double*>(lds) + (size_t)part * per;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < RG; ++g) {
       if (NG > 0) {
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
           const int col = 1 + 16 * n + m;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (col < T) red[(16 * g + acc_row<ACC64>(lane, i)) * T + col] = acc[g][n][i];
+            if (col < T) red[(16 * (g0 + g) + acc_row<ACC64>(lane, i)) * T + col] = acc[g][n][i];
           acc[g][n] = (v4d){0.0, 0.0, 0.0, 0.0};
         }
       }
       double y = accy[g];
       y += __shfl_xor(y, 16);
       y += __shfl_xor(y, 32);
-      if (kg == 0) red[(16 * g + m) * T] = y;
+      if (kg == 0) red[(16 * (g0 + g) + m) * T] = y;
       accy[g] = 0.0;
     }
     __syncthreads();
     const double* all = reinterpret_cast<const double*>(lds);
     for (int e = tid; e < total; e += 64 * NW) {
-      double v = (all[e] + all[per + e]) + (all[2 * per + e] + all[3 * per + e]);
+      double v = KP == 2 ? all[e] + all[per + e] : (all[e] + all[per + e]) + (all[2 * per + e] + all[3 * per + e]);
       v *= scale;
       if (dadd != 0.0) v = fma(dadd, (double)din[e], v);
       if (accumulate) v += (double)out[e];
@@ -385,8 +406,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
 
 template <int NG, bool ACC64, int KIND>
 static int launch_kind(int count, int T, hipStream_t s, const StripArgs& a) {
-  constexpr int wl = NW * WaveCfg<NG, ACC64, KIND>::WAVE_LDS, rl = NW * TILE * (16 * NG + 1) * (int)sizeof(double);
-  const size_t lds = std::max<size_t>(wl, (size_t)NW * TILE * T * sizeof(double));
+  typedef WaveCfg<NG, ACC64, KIND> Cfg;
+  // LDS: the waves' own pieces in the loop, then the partial sums (one set for each wave that shares a row's columns)
+  constexpr int wl = NW * Cfg::WAVE_LDS, per_col = Cfg::ROW_GROUPS * TILE * (int)sizeof(double), rl = per_col * (16 * NG + 1);
+  const size_t lds = std::max<size_t>(wl, (size_t)per_col * T);
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_strip<NG, ACC64, KIND>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, std::max(wl, rl));
   NUGPR_HIP(attr);
@@ -426,15 +449,45 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
 }
 
 // Tables with strips of symmetric blocks take the instantiation that pairs their tiles, strips of a basis the caller
-// supplied the row-major one, triangular strips the plain one (streaming loads: each tile is used once).
-static int strip_kind(const StripTable& tab) { return tab.rowmajor ? STRIP_ROWMAJOR : tab.sym ? STRIP_SYM : STRIP_PLAIN; }
+// supplied the row-major one, triangular strips the short or the long one by their mean number of tiles.
+// Short: up to 10 tiles a strip on average.  Preconditioner apply, fp64, 17 columns, short against long: 256 clusters of
+// 512 points (4.5 tiles) 91 / 109 us, 32 x 1024 (8.5) 46 / 48, 32 x 1280 (10.5) 61 / 61, 64 x 2048 (16.5) 258 / 264 but
+// 3 x 4096 95 / 91; 33 columns: 131 / 165, 73 / 74, 100 / 93, 24 uneven clusters of 1536 on average 217 / 168.
+// The streaming hint (each tile is used once).  A solver applies the K_ii and the factor, equally large, in turn, so it pays
+// from the size on at which the two no longer fit the memory-side cache (256 MB) together.  Batched solve, 17 columns,
+// without / with it: 64 x 512 points (64 MB each) 385 / 392 us, 96 x 512 (96 MB) 431 / 441, 128 x 512 (128 MB) 513 / 508,
+// 48 x 1024 (192 MB) 550 / 530, 64 x 2048 (1 GB) 1614 / 1555; the apply by itself could do without up to 256 MB (48 x 1024:
+// 60 / 66).  Row-major strips never gain: the basis is small beside the K_ii (96 x 2048 points, rank 256: 848 / 865 us).
+int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
+  uint64_t tiles = 0;
+  bool sym = false;
+  for (const StripItem& it : items) {
+    sym = sym || (it.blocked & 2u) != 0;
+    tiles += it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0;
+  }
+  if (sym) return STRIP_SYM;
+  if (!items.empty() && items[0].blocked == 0) return STRIP_ROWMAJOR;
+  return (tiles <= 10 * items.size() ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
+}
 
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64) {
-  static const char* const names[3][2][3] = {
-      {{"k_strip<0, false, 0>", "k_strip<0, false, 1>", "k_strip<0, false, 2>"}, {"k_strip<0, true, 0>", "k_strip<0, true, 1>", "k_strip<0, true, 2>"}},
-      {{"k_strip<1, false, 0>", "k_strip<1, false, 1>", "k_strip<1, false, 2>"}, {"k_strip<1, true, 0>", "k_strip<1, true, 1>", "k_strip<1, true, 2>"}},
-      {{"k_strip<2, false, 0>", "k_strip<2, false, 1>", "k_strip<2, false, 2>"}, {"k_strip<2, true, 0>", "k_strip<2, true, 1>", "k_strip<2, true, 2>"}}};
-  return names[(T - 1 + 15) / 16][acc64 ? 1 : 0][strip_kind(tab)];
+  static thread_local char name[32];
+  std::snprintf(name, sizeof(name), "k_strip<%d, %s, %d>", (T - 1 + 15) / 16, acc64 ? "true" : "false", tab.kind);
+  return name;
+}
+
+template <bool ACC64>
+static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, const StripArgs& a) {
+  switch (tab.kind) {
+    case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, tab.count, T, s, a);
+    case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, tab.count, T, s, a);
+    case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, tab.count, T, s, a);
+    case STRIP_ROWMAJOR: return launch_width<ACC64, STRIP_ROWMAJOR>(ng, tab.count, T, s, a);
+    case STRIP_LONG + STRIP_STREAMED: return launch_width<ACC64, STRIP_LONG + STRIP_STREAMED>(ng, tab.count, T, s, a);
+    case STRIP_SHORT + STRIP_STREAMED: return launch_width<ACC64, STRIP_SHORT + STRIP_STREAMED>(ng, tab.count, T, s, a);
+  }
+  set_error("internal: strip table of an unknown kind");
+  return NUGPR_ERR_INVALID;
 }
 
 int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64,
@@ -447,11 +500,7 @@ int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1
   a.items = tab.dev;
   a.T = T;
   const int ng = (T - 1 + 15) / 16;
-  switch (strip_kind(tab)) {
-    case STRIP_ROWMAJOR: return acc64 ? launch_width<true, STRIP_ROWMAJOR>(ng, tab.count, T, s, a) : launch_width<false, STRIP_ROWMAJOR>(ng, tab.count, T, s, a);
-    case STRIP_SYM: return acc64 ? launch_width<true, STRIP_SYM>(ng, tab.count, T, s, a) : launch_width<false, STRIP_SYM>(ng, tab.count, T, s, a);
-    default: return acc64 ? launch_width<true, STRIP_PLAIN>(ng, tab.count, T, s, a) : launch_width<false, STRIP_PLAIN>(ng, tab.count, T, s, a);
-  }
+  return acc64 ? launch_table<true>(tab, ng, T, s, a) : launch_table<false>(tab, ng, T, s, a);
 }
 
 }  // namespace nugpr
