@@ -346,7 +346,8 @@ double nugpr_profile_bytes(const nugpr_ctx* ctx, int32_t ncols);
 int nugpr_profile_kernel_name(const nugpr_ctx* ctx, int32_t ncols, char* buf /*HOST*/, int32_t len);
 
 /* Work counters of a context since nugpr_create or the last reset (host bookkeeping, no GPU work):
- * what the calls so far did in units of the path's steps (Algorithm 1 / ComputeLoss). */
+ * what the calls so far did in units of the path's steps (Algorithm 1 / ComputeLoss).  An iteration that the solver
+ * issued ahead of the stop test that ended the solve is not counted, nor its product and apply. */
 typedef struct {
   int64_t loss_evals;        /* loss evaluations that returned a value (nugpr_mll, nugpr_train_step)     */
   int64_t pcg_solves;        /* batched PCG solves                                                        */

@@ -127,6 +127,7 @@ struct PcgState {
   int32_t indefinite;
   int32_t bad_cluster;    // Cholesky: lowest failing cluster index, or INT_MAX
   int32_t tail_count;     // workgroups of the end-of-solve report that are done (returns to 0)
+  int32_t steps;          // iterations until a stop test found no column active (or all that were made)
   int32_t check_count;    // workgroups of the stop test that are done (returns to 0)
   int32_t nonfinite_mark; // mark of the last assembly that met NaN / Inf coordinates (nugpr_ctx::assembly_mark)
   // <b, b> and <b, z_0> of the two right-hand-side blocks the context owns ([y | L Z] with z_0 = M^-1 b,
@@ -228,7 +229,9 @@ struct nugpr_ctx {
   nugpr::HostFlags* h_flags = nullptr;   // pinned
   uint64_t flag_seq = 0, tail_seq = 0;   // last numbers handed to the device
   int expect_iters[2] = {1, 1};          // iterations the last solve of each system took (when to report early)
-  int recent_iters[2][3] = {{1, 1, 1}, {1, 1, 1}};   // and the last three (how many to issue without asking in between)
+  // the last three solves of a kind (the context's own right-hand sides, the Pade system, any other block, a single
+  // column) and width: how many iterations to issue one ahead of the stop test
+  struct IterationRecord { int ncols = 0, last[3] = {1, 1, 1}; } recent_iters[4];
   double* h_buf = nullptr;               // pinned scratch for small device->host reads
   size_t h_buf_doubles = 0;
   float diag_residual = 0.f;             // (alpha + sigma^2) - float(alpha + sigma^2) of the stored blocks

@@ -176,6 +176,7 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
     const int n_active = __popcll(__ballot(act != 0)), indef = __ballot(ind != 0) != 0 ? 1 : 0;
     if (tid != 0) return;
     st->check_count = 0;
+    if (iter == 0 || st->n_active != 0) st->steps = iter + 1;       // (n_active: what the test before this one found)
     st->n_active = n_active;
     st->indefinite = indef;
     out->n_active = n_active;
@@ -355,15 +356,15 @@ __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, con
   }
 }
 
-// Waits until the device has stored `want` in a pinned sequence slot: a short poll (the usual case:
-// microseconds after the kernel ends), then an ordinary stream synchronisation.
+// Waits until the device has stored `want`, or a later number, in a pinned sequence slot: a short poll (the usual
+// case: microseconds after the kernel ends), then an ordinary stream synchronisation.
 static int wait_seq(const volatile uint64_t* slot, uint64_t want, hipStream_t s) {
   for (int spin = 0; spin < 200000; ++spin) {
-    if (*slot == want) return NUGPR_OK;
+    if (*slot >= want) return NUGPR_OK;
     __builtin_ia32_pause();
   }
   NUGPR_HIP(hipStreamSynchronize(s));
-  if (*slot != want) { set_error("the device did not report the end of a solver step"); return NUGPR_ERR_HIP; }
+  if (*slot < want) { set_error("the device did not report the end of a solver step"); return NUGPR_ERR_HIP; }
   return NUGPR_OK;
 }
 
@@ -832,10 +833,15 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
   // partial sums: sets 0 and 1 belong to the update kernel (|r|^2, <b, x>), 2 to <d, q>, 3 to <r, z>
   double *const dq_sums = c->dotpart + (size_t)2 * nb * MAX_COLS, *const rz_sums = c->dotpart + (size_t)3 * nb * MAX_COLS;
   const bool fuse = nb <= FUSE_BLOCKS;
-  // Iterations every one of the last three solves of this kind needed are issued without waiting for their stop
-  // tests: should a column, or all of them, be done earlier, its steps are zero from there on and change nothing.
-  const int* rec = c->recent_iters[plain ? 1 : 0];
-  const int sure = fuse ? std::min(rec[0], std::min(rec[1], rec[2])) : 1;
+  // Up to as many iterations as each of the last three solves of this kind and width needed, the host issues an
+  // iteration while the device still works on the one before it, whose stop test it has not seen.  Should that test end
+  // the solve, ONE iteration was issued in vain: every column's steps are zero in it and change nothing.  A loss gains
+  // 8 - 12 us by it whatever its size (24576 points 342 us, 352 without; 131072 points 1272 / 1284), but an iteration in
+  // vain costs what an iteration costs, so larger problems wait for every test.
+  nugpr_ctx::IterationRecord& rec = c->recent_iters[plain ? 1 : own ? 0 : T == 1 ? 3 : 2];
+  if (rec.ncols != T) { rec.ncols = T; rec.last[0] = rec.last[1] = rec.last[2] = 1; }
+  const int sure = fuse ? std::min(rec.last[0], std::min(rec.last[1], rec.last[2])) : 1;
+  nugpr_stats counted = c->stats, counted_before = c->stats;      // after the product of the present iteration, and the last
   // The end-of-solve report (k_pcg_tail) is issued INSIDE the iteration that is expected to be the last
   // one, right behind its stop test, so that it is already on the host when the stop test says "done";
   // a solve that ends earlier or later than the previous one of its kind gets the report after the loop.
@@ -874,8 +880,11 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
       tail_current = true;
     }
     const int j = it++;
-    if (it >= sure || it >= max_iter) {
-      if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq, s))) return rc;
+    counted_before = counted;
+    counted = c->stats;
+    const bool ahead = it < sure && it < max_iter;                // the stop test to wait for: this one's, or the last one's
+    if (!ahead || it > 1) {
+      if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq - (ahead ? 1 : 0), s))) return rc;
       if (c->h_flags->indefinite) indefinite = true;
       if (c->h_flags->n_active == 0 || it >= max_iter) break;
     }
@@ -898,10 +907,11 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
     if (hs->indef[col]) indefinite = true;
   }
   if (max_it_used) *max_it_used = mx;
-  const int needed = mx > 0 && mx < it ? mx : it;             // (iterations issued past the last active column's are none)
-  c->expect_iters[plain ? 1 : 0] = std::max(needed, 1);
-  int* recent = c->recent_iters[plain ? 1 : 0];
-  recent[2] = recent[1]; recent[1] = recent[0]; recent[0] = std::max(needed, 1);
+  // the counters leave out the iteration issued in vain, if there was one
+  const int needed = std::min(std::max(hs->steps, 1), it);
+  if (needed < it) c->stats = counted_before;
+  c->expect_iters[plain ? 1 : 0] = needed;
+  rec.last[2] = rec.last[1]; rec.last[1] = rec.last[0]; rec.last[0] = needed;
   c->stats.pcg_solves += 1;
   c->stats.pcg_iterations += needed;
   c->stats.pcg_iterations_max = std::max<int64_t>(c->stats.pcg_iterations_max, needed);
