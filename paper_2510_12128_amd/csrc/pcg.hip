@@ -294,16 +294,18 @@ __global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT
                                                   const double* __restrict__ rzs, int nblocks, int iter, double* __restrict__ blog) {
   __shared__ double red[256];
   __shared__ double be[MAX_COLS];
+  __shared__ int goes_on[MAX_COLS];
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
-  if (rzs) {                                   // the step of k_pcg_beta; a negative value marks a stopped column
+  if (rzs) {                                   // the step of k_pcg_beta (beta itself can be negative: rho_0 may be, by rounding)
     sum_all_partials(rzs, nblocks, T, red, be);
     if (tid < T) {
       const double rz = be[tid];
       const bool act = st->active[tid] != 0, go = act && rz > 0.0;
       const double b = go ? rz / st->rho[iter & 1][tid] : 0.0;
-      be[tid] = go ? b : -1.0;
+      be[tid] = b;
+      goes_on[tid] = go;
       if (blockIdx.x == 0) {
         if (act && !go) { st->active[tid] = 0; st->indef[tid] = 1; }
         if (go) st->rho[(iter + 1) & 1][tid] = rz;
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT
   }
   if (myrow >= rpp) return;
   const double bta = rzs ? be[col] : st->beta[col];
-  const bool act = rzs ? bta >= 0.0 : st->active[col] != 0;
+  const bool act = rzs ? goes_on[col] != 0 : st->active[col] != 0;
   for (int64_t r = (int64_t)blockIdx.x * rpp + myrow; r < n; r += (int64_t)gridDim.x * rpp) {
     const int64_t idx = r * T + col;
     D[idx] = act ? (VT)fma(bta, (double)Din[idx], (double)Z[idx]) : (VT)0;

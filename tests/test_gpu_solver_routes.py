@@ -1,4 +1,6 @@
-"""Solves whose iterations are issued ahead of the stop test: after three solves of one kind and width the host no longer
+"""The solver's two ways up to 32768 points and beyond.
+
+Solves whose iterations are issued ahead of the stop test: after three solves of one kind and width the host no longer
 waits for each test, so a solve that then ends sooner must give what it gives on a fresh context, to the bit, and count the
 same iterations, products and preconditioner applies."""
 import numpy as np
@@ -75,3 +77,57 @@ def test_a_solve_that_ends_sooner_than_the_last_three(lib, ncols, then, acc_fp32
             assert np.array_equal(out[k], want[k]), k
     ctx.close()
     ref_ctx.close()
+
+
+def test_a_negative_first_rho_takes_the_same_way_at_every_size(lib):
+    """<b, M^-1 b> can come out negative by rounding: right-hand sides of a few hundred units of the smallest fp32 number
+    do it on purpose (every rounding is then to a whole unit).  Problems whose update kernels add up the dot products
+    themselves (up to 32768 points) must take the same steps as larger ones, which have separate kernels for it."""
+    from paper_2510_12128_amd import binding as B
+    rng = np.random.default_rng(0)
+    Xa = rng.standard_normal((4, 2)).astype(np.float32)
+    theta = np.array([3.0, 3.0, 1e4, 10.0])
+    unit = 2.0 ** -149
+
+    def solver(n_more):
+        """The cluster Xa and others of 64 points, out of reach of it."""
+        sizes = [4] + [64] * n_more
+        off = np.concatenate([[0], np.cumsum(sizes)])
+        X = np.concatenate([Xa, 5000.0 + np.float32(3.0) * rng.standard_normal((64 * n_more, 2)).astype(np.float32)])
+        probes = 2.0 * rng.integers(0, 2, (len(X), 1)) - 1.0
+        ctx = lib.Context(X, np.zeros(len(X), np.float32), off, probes, 1, tol=1e-6, max_iter=6, acc_fp32=True)
+        ctx.nugpr_build_blocks(theta)
+        assert ctx.nugpr_precond_factor()[0] == 0
+        return ctx
+
+    small = solver(1)
+    Y = small.nugpr_export(B.EXPORT_LINV, 0).cpu().numpy().astype(np.float64)
+    K = small.nugpr_export(B.EXPORT_K, 0).cpu().numpy().astype(np.float64)
+
+    def apply(A, k):
+        """A k in whole units, rounded after every term as the kernel does."""
+        out = np.rint(A[:, 0][None, :] * k[:, :1])
+        for j in range(1, 4):
+            out = np.rint(A[:, j][None, :] * k[:, j:j + 1] + out)
+        return out
+
+    k = rng.integers(-60, 61, (400000, 4)).astype(np.float64)
+    z = apply(Y.T, apply(Y, k))
+    rho, dq = (k * z).sum(1), (z * apply(K, z)).sum(1)
+    pick = np.flatnonzero((rho < 0) & (dq > 0))
+    assert len(pick) > 20
+    large = solver(520)
+    assert large.n > 32768
+    seen = 0
+    for i in pick[:20]:
+        runs = []
+        for ctx in (small, large):
+            b = np.zeros((ctx.n, 1), np.float32)
+            b[:4, 0] = (k[i] * unit).astype(np.float32)
+            code, x, iters, alpha, beta = ctx.nugpr_pcg_solve(b)
+            runs.append((code, int(iters[0]), alpha[:, 0].tolist(), beta[:, 0].tolist(), x[:4, 0].cpu().numpy().tolist()))
+        assert runs[0] == runs[1], (i, runs)
+        seen += min(runs[1][3]) < 0.0
+    assert seen > 0                                   # the case did occur
+    small.close()
+    large.close()
