@@ -482,7 +482,7 @@ int nugpr_destroy(nugpr_ctx* c) {
 
 int nugpr_build_blocks(nugpr_ctx* c, const double* theta, void* stream) {
   if (!c) { set_error("ctx is null"); return NUGPR_ERR_INVALID; }
-  return launch_build(c, theta, as_stream(stream), false);
+  return launch_build(c, theta, as_stream(stream));
 }
 
 int nugpr_set_nystrom_basis(nugpr_ctx* c, const double* theta, double jitter, void* stream) {
@@ -629,7 +629,7 @@ static int set_operator(nugpr_ctx* c, const double* theta, bool allow_reuse, hip
   bool same = allow_reuse && c->built && (int)c->theta_built.size() == L.p &&
               !(c->params.flags & NUGPR_NO_SHORTCUTS);
   for (int k = 0; same && k < nl; ++k) same = (theta[k] == c->theta_built[k]);
-  if (!same) return launch_build(c, theta, s, false);
+  if (!same) return launch_build(c, theta, s);
   for (int i = 0; i < L.p; ++i)
     if (!(theta[i] > 0.0) || !std::isfinite(theta[i])) { set_error("theta entries must be finite and > 0"); return NUGPR_ERR_INVALID; }
   const double a0 = c->theta_built[L.p - 2], s0 = c->theta_built[L.p - 1];
@@ -795,7 +795,7 @@ int nugpr_train_step(nugpr_ctx* c, double* log_theta, double* adam_m, double* ad
     const double tp = std::exp(log_theta[i] + h), tm = std::exp(log_theta[i] - h);
     const bool pair = pairs && i < p - 2;
     if (pair) {
-      rc = launch_build_pair(c, theta.data(), i, h, tp, tm, as_stream(stream), false);
+      rc = launch_build_pair(c, theta.data(), i, h, tp, tm, as_stream(stream));
       if (rc) return rc;
     }
     theta[i] = tp;

@@ -21,8 +21,8 @@
 //                   group), and the squared norms;
 //   k_build_tile    one workgroup = one 64 x 64 tile of a lower triangle.  Each wave owns a
 //                   16-column slice: operands come from the scaled array (512-byte contiguous
-//                   loads, served by L2), the mirror image is stored straight from registers
-//                   and the tile itself through a wave-private LDS staging area, both with
+//                   loads, served by L2), the mirror image, where one is wanted, is stored
+//                   straight from registers and the tile itself through a wave-private LDS staging area, both with
 //                   16-byte stores.
 #include <algorithm>
 #include <cmath>
@@ -128,7 +128,7 @@ __device__ __forceinline__ void kernel_values(const double (&arg)[W], const doub
 }
 
 // One workgroup = one 64 x 64 tile (tr, tc), tc <= tr, of one square symmetric matrix (a cluster's
-// K_ii, or the coupling C) and its mirror image.
+// K_ii, or the coupling C) and, on request, its mirror image.
 //
 // Wave w computes columns 16 w .. 16 w + 15 with four 16 x 16 fp64 MFMA accumulators (one per
 // 16-row group); the row operands of the tile are shared through LDS, the column operands go
@@ -478,7 +478,7 @@ int launch_setup(nugpr_ctx* c, const float* user_reps, const float* user_W, hipS
 // pair_param < 0: one assembly at theta.  Otherwise theta holds the centre of a central difference in
 // lengthscale pair_param with step h on its logarithm: ell e^{+h} goes to the blocks in force (Kd, C),
 // ell e^{-h} to the spare ones (Kd2, C2); theta_built / theta_spare record which is which.
-static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, bool need_upper, int pair_param, double h,
+static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, int pair_param, double h,
                       double value_plus, double value_minus) {
   const Layout& L = c->L;
   if (!theta) { set_error("theta is null"); return NUGPR_ERR_INVALID; }
@@ -497,7 +497,7 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, bool nee
   PanelArgs a;
   for (int k = 0; k < EXP2_TERMS; ++k) a.coef[k] = alpha * EXP2_COEF[k];
   a.diag_val = (float)(alpha + sigma2);
-  a.mirror = need_upper ? 1 : 0;
+  a.mirror = 0;                                      // the products read the lower tiles of the K_ii only
   a.kd = pair_kd(L.d);
   a.keep_same = 0;
   a.g[0] = a.g[1] = 0.0;
@@ -512,8 +512,9 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, bool nee
   }
   c->diag_residual = (float)((alpha + sigma2) - (double)a.diag_val);
   PanelArgs ac = a;                                  // the coupling launch
-  // the upper tiles of C can be left out only if its strips pair up in the product (and nothing else reads them)
-  const bool need_c_upper = need_upper || L.compensate || !c->c_paired;
+  // The upper tiles of C are written unless its strips pair up in the product.  (Under the compensation they are written
+  // all the same, for the residual Clo, which is formed over the whole square; the products read the lower ones of both.)
+  const bool need_c_upper = L.compensate || !c->c_paired;
   ac.mirror = need_c_upper ? 1 : 0;
   const bool host_lambda = L.compensate && L.ncr <= COMPENSATE_HOST_MAX;
   if (L.compensate && !host_lambda) {
@@ -594,26 +595,25 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, bool nee
     c->theta_spare[pair_param] = value_minus;
   }
   if (pair) c->lf_valid = false;              // the second matrix of the pair has just overwritten the Cholesky factor
-  c->spare_upper_valid = pair && need_upper;
   c->c_upper_valid = need_c_upper;
   c->spare_c_upper_valid = pair && need_c_upper;
   c->op_scale = 1.0;
   c->op_shift = (double)c->diag_residual;
   c->built = true;
-  c->kd_upper_valid = need_upper;
+  c->kd_upper_valid = false;
   c->build_gen += 1;
   c->stats.assembly_passes += 1;
   c->stats.matrices_assembled += pair ? 2 : 1;
   return NUGPR_OK;
 }
 
-int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s, bool need_upper) {
-  return build_impl(c, theta, s, need_upper, -1, 0.0, 0.0, 0.0);
+int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s) {
+  return build_impl(c, theta, s, -1, 0.0, 0.0, 0.0);
 }
 
 int launch_build_pair(nugpr_ctx* c, const double* theta, int param, double h, double value_plus, double value_minus,
-                      hipStream_t s, bool need_upper) {
-  return build_impl(c, theta, s, need_upper, param, h, value_plus, value_minus);
+                      hipStream_t s) {
+  return build_impl(c, theta, s, param, h, value_plus, value_minus);
 }
 
 int swap_pair(nugpr_ctx* c) {
@@ -622,7 +622,7 @@ int swap_pair(nugpr_ctx* c) {
   std::swap(c->C, c->C2);
   c->theta_built.swap(c->theta_spare);
   c->theta_spare.clear();               // the blocks left behind are not used again
-  c->kd_upper_valid = c->spare_upper_valid;
+  c->kd_upper_valid = false;
   c->c_upper_valid = c->spare_c_upper_valid;
   c->build_gen += 1;
   return NUGPR_OK;

@@ -383,7 +383,7 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
   std::vector<double> H((size_t)DAV_MAX_BASIS * DAV_MAX_BASIS, 0.0);
   auto extend = [&](int m) -> int {             // V[m] exists: AV[m] = C V[m], H[m][0..m]
     StripPort p{};
-    p.A = c->C; p.in = V + (size_t)m * ld; p.nin = 1; p.out = parts; p.out_part_stride = stride; p.diag_add = alpha;
+    p.A = c->C; p.in = V + (size_t)m * ld; p.out = parts; p.out_part_stride = stride; p.diag_add = alpha;
     if ((rc = launch_strip(c->tab_C, p, p, 1, true, s))) return rc;
     StripPort q = p;
     q.A = c->Clo; q.accumulate = 1; q.diag_add = 0.0;

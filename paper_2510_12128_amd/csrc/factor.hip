@@ -630,7 +630,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     else
       hipLaunchKernelGGL((k_probes_to_block<float>), dim3(1024), dim3(256), 0, s, c->probes, (float*)c->Pv, (int64_t)L.n, L.t);
     StripPort p0{};
-    p0.A = c->Lf; p0.in = c->Pv; p0.out = c->Bv; p0.nin = 1;
+    p0.A = c->Lf; p0.in = c->Pv; p0.out = c->Bv;
     int rc = launch_strip(c->tab_lowL, p0, p0, L.T, c->acc64, s);
     if (rc) return rc;
   }

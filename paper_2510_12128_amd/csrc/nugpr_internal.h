@@ -88,11 +88,9 @@ static_assert(sizeof(StripItem) == 48, "StripItem layout");
 
 struct StripPort {
   const float* A;            // matrix base (always fp32)
-  const void* in;            // input vector block(s), fp32 or fp64 by the arithmetic mode
+  const void* in;            // input vector block, fp32 or fp64 by the arithmetic mode
   void* out;                 // output vector block(s), same type
-  uint64_t in_part_stride;   // elements between the nin input slabs (summed on load)
   uint64_t out_part_stride;  // elements between output slabs
-  int32_t nin;
   int32_t accumulate;        // out += result instead of out = result
   double scale = 1.0;        // the product is multiplied by this before anything is added
   double diag_add = 0.0;     // scalar added on the diagonal of items that ask for it
@@ -251,7 +249,7 @@ struct nugpr_ctx {
   int32_t assembly_mark = 0;
   // The assembly leaves out the strictly upper tiles of the K_ii (the product reads the lower ones only, see
   // k_strip); the export of a whole block calls ensure_kd_upper first.
-  bool kd_upper_valid = false, spare_upper_valid = false;
+  bool kd_upper_valid = false;
   // the same for the coupling matrix, whose strips pair up when c_paired (set with the work tables)
   bool c_upper_valid = false, spare_c_upper_valid = false, c_paired = false;
   // K' z_0 of the factored blocks, kept from the base loss: the output-scale and noise evaluations apply
@@ -290,12 +288,11 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L);
 
 // build_blocks.hip ----------------------------------------------------------
 int launch_setup(nugpr_ctx* c, const float* user_reps, const float* user_W, hipStream_t s);
-// need_upper = false: the strictly upper tiles of the K_ii are not written (kd_upper_valid records it)
-int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s, bool need_upper = false);
+int launch_build(nugpr_ctx* c, const double* theta, hipStream_t s);
 // The two assemblies of a central difference in lengthscale `param` (step h on its logarithm) in one pass:
 // ell e^{+h} into the blocks in force, ell e^{-h} into the spare ones; swap_pair puts the spare ones in force.
 int launch_build_pair(nugpr_ctx* c, const double* theta, int param, double h, double value_plus, double value_minus,
-                      hipStream_t s, bool need_upper);
+                      hipStream_t s);
 int swap_pair(nugpr_ctx* c);
 // fills the strictly upper tiles of the K_ii from the lower ones if the last assembly left them out
 int ensure_kd_upper(nugpr_ctx* c, hipStream_t s);

@@ -474,8 +474,8 @@ int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, doubl
   if (!s_known && (rc = run_project(c, D, T, s, D32))) return rc;
   // Q_i = K_ii D_i   and   P = C_offdiag S (column slabs), one launch
   StripPort k0{}, k1{};
-  k0.A = c->Kd; k0.in = D; k0.out = Q; k0.nin = 1; k0.scale = c->op_scale; k0.diag_add = c->op_shift;
-  k1.A = c->C; k1.in = s_known ? c->S0v : c->Spart; k1.nin = 1; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
+  k0.A = c->Kd; k0.in = D; k0.out = Q; k0.scale = c->op_scale; k0.diag_add = c->op_shift;
+  k1.A = c->C; k1.in = s_known ? c->S0v : c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
   const bool timed = c->prof_on && (size_t)(2 * c->prof_used + 1) < c->prof_ev.size();
   if (timed) NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used], s));
   if ((rc = launch_strip(c->tab_KC, k0, k1, T, c->acc64, s))) return rc;
@@ -655,7 +655,7 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
   int rc;
   const uint64_t spart = (uint64_t)L.ncr * T;
   StripPort s0{};
-  s0.A = c->Wt; s0.in = D; s0.out = c->Spart; s0.nin = 1; s0.out_part_stride = spart;
+  s0.A = c->Wt; s0.in = D; s0.out = c->Spart; s0.out_part_stride = spart;
   if ((rc = launch_strip(c->tab_WtD, s0, s0, T, c->acc64, s))) return rc;
   if (L.nsS > 1 && (rc = launch_sum_parts(c->Spart, c->Spart, (int64_t)spart, L.nsS, spart, c->acc64, s))) return rc;
   return NUGPR_OK;
@@ -682,7 +682,7 @@ static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D
     return NUGPR_OK;
   }
   StripPort w0{};
-  w0.A = c->Wd; w0.in = c->Ppart; w0.nin = 1; w0.out = Q; w0.accumulate = 1;
+  w0.A = c->Wd; w0.in = c->Ppart; w0.out = Q; w0.accumulate = 1;
   return launch_strip(c->tab_WP, w0, w0, T, c->acc64, s);
 }
 
@@ -693,7 +693,7 @@ static int run_lowrank_accumulate(nugpr_ctx* c, const void* D, void* Q, int T, h
   const uint64_t ppart = (uint64_t)L.ncr * T;
   if ((rc = run_project(c, D, T, s))) return rc;
   StripPort k1{};
-  k1.A = c->C; k1.in = c->Spart; k1.nin = 1; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
+  k1.A = c->C; k1.in = c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
   if ((rc = launch_strip(c->tab_C, k1, k1, T, c->acc64, s))) return rc;
   if (L.compensate) {
     StripPort k2 = k1;
@@ -712,12 +712,12 @@ int run_split_op(nugpr_ctx* c, const void* D, void* out, int T, hipStream_t s) {
   int rc;
   const int64_t cnt = c->L.n * T;
   StripPort up{};
-  up.A = c->G; up.in = D; up.out = c->Vv; up.nin = 1;
+  up.A = c->G; up.in = D; up.out = c->Vv;
   if ((rc = launch_strip(c->tab_upG, up, up, T, c->acc64, s))) return rc;                 // U = Y^T D
   const bool identity = c->build_gen == c->factor_gen && !c->general_route &&
                         !(c->params.flags & (NUGPR_NO_SHORTCUTS | NUGPR_PRECOND_COMPENSATED));
   StripPort lo{};
-  lo.A = c->G; lo.in = c->Uv; lo.out = out; lo.nin = 1;
+  lo.A = c->G; lo.in = c->Uv; lo.out = out;
   if (!identity) {
     if ((rc = run_matvec(c, c->Vv, c->Uv, T, s))) return rc;                              // K' U
   } else {
@@ -749,10 +749,10 @@ int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s) {
   int rc;
   c->stats.precond_applies += 1;
   StripPort a{};
-  a.A = c->G; a.in = R; a.out = c->Vv; a.nin = 1;
+  a.A = c->G; a.in = R; a.out = c->Vv;
   if ((rc = launch_strip(c->tab_lowG, a, a, T, c->acc64, s))) return rc;
   StripPort b{};
-  b.A = c->G; b.in = c->Vv; b.out = Z; b.nin = 1;
+  b.A = c->G; b.in = c->Vv; b.out = Z;
   return launch_strip(c->tab_upG, b, b, T, c->acc64, s);
 }
 
