@@ -192,8 +192,8 @@ const char* nugpr_last_error_string(void);
  *   K_ii[p,q] = alpha exp(-1/2 sum_k ((x_pk - x_qk)/ell_k)^2) + sigma^2 [p = q]
  *   C[(i,a),(j,c)] = alpha exp(-1/2 sum_k ((R_iak - R_jck)/ell_k)^2), i != j (no noise).
  * Overwrites the stored K_diag and C; never touches the preconditioner.  Both are symmetric
- * and the tiles above their diagonals may be left unwritten until an operation needs them
- * (nugpr_export and the products on widths that read whole rows fill them in first). */
+ * and every product reads the tiles on and below their diagonals only; the tiles above may be
+ * left unwritten until nugpr_export needs them, which fills them in first. */
 int nugpr_build_blocks(nugpr_ctx* ctx, const double* theta /*HOST*/, void* stream);
 
 /* Replaces the basis W by Nystrom weights at theta (Section 3.3 defines the rank-1 block 1 1^T and leaves higher

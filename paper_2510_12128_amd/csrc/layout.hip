@@ -85,9 +85,10 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
     want = (2048 + strips_P - 1) / strips_P;
     L.nsP = std::max(1, std::min({want, 16, L.ldc / TILE}));
   }
-  // workgroups (= partial sums per column) of the kernels with dot products: 64 rows each while that is at most 128 of
-  // them (2048 points: training step 1226 us, 1287 with 128 rows), 128 rows beyond (32768 points: 5946 us, 6057 with 64:
-  // more partial sums to add up, 6408 with 256: half of the chip idle)
+  // workgroups (= partial sums per column) of the kernels with dot products: 64 rows each up to 8192 points (a loss at
+  // 4096 points 161 us, with 128 rows 169; at 8192 points 260 / 281), 128 beyond (training step at 32768 points 5821 us,
+  // 6408 with 256: half of the chip idle).  The line could lie higher: with 64 rows a loss at 12288 points takes 275 us in
+  // place of 295, at 16384 298 / 318, and that training step 5566, though its sums are then too many for FUSE_BLOCKS.
   L.n_dot_blocks = L.n <= 8192 ? (int)((L.n + 63) / 64) : (int)std::min<int64_t>(1024, (L.n + 127) / 128);
 
   size_t cur = 0;

@@ -5,9 +5,13 @@
 // All T columns advance in lock step.  Vector blocks are n x T row-major, fp64 or fp32
 // according to the context's arithmetic mode (VT below); every reduction that feeds a CG
 // coefficient (the paper's batched dot products) is accumulated in fp64 in a fixed order:
-// per-workgroup partial sums, then one small kernel that adds them, computes alpha / beta
-// per column and updates the convergence mask on the device.  The host reads back one
-// 16-byte flag record per iteration (O(1) traffic, Section 4).
+// per-workgroup partial sums, which up to FUSE_BLOCKS of them (32768 points) are added up by
+// every workgroup of the kernel that applies alpha or beta, and beyond by a small kernel of one
+// workgroup per column (k_pcg_alpha, k_pcg_beta).  The stop test (k_pcg_check) is such a kernel
+// at every size; it keeps the convergence mask on the device and stores a 16-byte flag record
+// into pinned host memory (O(1) traffic, Section 4), which the host polls once per iteration,
+// on problems of up to FUSE_BLOCKS partial sums one iteration late while a solve is expected to
+// go on (pcg_t).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -73,7 +77,7 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
   return r;
 }
 
-// The three scalar kernels run one workgroup per column (grid = T); the cross-column
+// The scalar kernels run one workgroup per column (grid = T); the cross-column
 // bookkeeping (how many columns are still active, did any meet negative curvature) is
 // gathered by the last workgroup of the stop test (k_pcg_check).
 
@@ -212,6 +216,8 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
 // Problems of up to FUSE_BLOCKS partial sums per column (32768 points): the kernels that apply alpha and beta sum them
 // up themselves, every workgroup in the same fixed order (35 KB of L2 reads a workgroup at 256 x 17), and the first
 // one keeps the records.  That saves a launch of 3 - 5 us each; with 1024 partial sums every workgroup would read 139 KB.
+// The line: a loss with them in the kernels / with launches of their own takes 254 / 261 us at 24576 points (192 sums),
+// 271 / 273 at 32768 (256), 304 / 302 at 40960 (320), 372 / 351 at 65536 (512), 664 / 579 at 131072 (1024).
 constexpr int FUSE_BLOCKS = 256;
 __device__ __forceinline__ void sum_all_partials(const double* __restrict__ partial, int nblocks, int T, double* red, double* out) {
   const int rpp = 256 / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
@@ -444,7 +450,8 @@ __global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const V
 static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D = nullptr, double* dq_partial = nullptr,
                       float* Q32 = nullptr, int parts = 1);
 // How many column slabs of P the expansion adds up itself: all of them with the one-hot basis while the extra gathers
-// (n T values from every slab after the first, out of L2) cost less than the launch they save (4 - 5 us)
+// (n T values from every slab after the first, out of L2) cost less than the launch they save.  A product with that
+// launch / without it: 20.6 / 17.9 us at 0.02e6 gathers, 23.5 / 21.8 at 1e6, 42.5 / 41.2 at 2.1e6, 48.8 / 52.7 at 8.4e6.
 static int fold_parts(const nugpr_ctx* c, int T) {
   return c->onehot && (double)c->L.n * T * (c->L.nsP - 1) <= 3e6 ? c->L.nsP : 1;
 }
@@ -526,14 +533,16 @@ static int scaled_copy(void* out, const void* x, double a, int64_t count, hipStr
 }
 
 // One-hot basis (every point belongs to exactly one representative): S = W^T D is the sum of the rows of
-// D over each representative's points, taken in ascending point order; Q += W P adds row assign[p] of P to
-// row p.  Neither streams the dense W.
+// D over each representative's points, in a fixed order; Q += W P adds row assign[p] of P to row p.
+// Neither streams the dense W.
 // ST: type of the block that is read.  Dwide (may be null): every point belongs to exactly one representative,
 // so the gather visits every row of D once and can leave a copy of it in the solver's own type on the way
 // (the widening of a caller's fp32 block, which the strip kernels then read, costs no pass of its own).
-// A representative's points are dealt to `parts` threads per column (8 to 16 points each, see project_shape), whose
-// sums are added in a fixed order: the gathers are dependent pairs of loads (point index, then row), so one thread per
-// representative and column spent 125 us at 128 points each, and 1 ms and more with few representatives of large clusters.
+// A representative's points are dealt in turn to `parts` threads per column (run_project: 4 to 8 points each on average,
+// more where the workgroup has no more threads or a representative more than its share), whose sums, each in ascending
+// point order, are added in a fixed order: the gathers are dependent pairs of loads (point index, then row), so one thread
+// per representative and column spent 125 us at 128 points each (42 us now), and the product on 8 clusters of 4096 points
+// with one representative each took 722 us (117 us now).
 template <typename VT, typename ST>
 __global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ D, VT* __restrict__ Dwide,
                                                          const int32_t* __restrict__ rep_ptr,
@@ -638,8 +647,8 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
   const Layout& L = c->L;
   if (D32 && !(c->onehot && c->acc64)) { set_error("internal: fused widening needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot) {
-    // threads per representative and column: as many as leave each about eight points (one round of gathers); large
-    // workgroups once that is more than an ordinary one holds
+    // threads per representative and column: the power of two that leaves each at most eight points on average (one round
+    // of gathers), as far as the workgroup has them; large workgroups once an ordinary one has not
     const int64_t want = (L.n + 8 * (int64_t)L.ncr - 1) / (8 * (int64_t)L.ncr);
     const int block = want > 256 / T ? 1024 : 256, rpp = block / T;
     int parts = 1;

@@ -106,10 +106,10 @@ def test_matvec_matches_oracle(lib, case):
 
 
 @pytest.mark.parametrize("case", ["ragged-halves", "many-reps"])
-def test_upper_tiles_are_filled_in_when_a_product_needs_them(lib, case):
-    """An assembly for a context whose products read the lower tiles of the K_ii (and of the coupling matrix,
-    when its strips pair up) leaves the upper tiles out; products of other widths (whole strips) and the export must still see the full blocks, after
-    every assembly."""
+def test_upper_tiles_are_left_out_by_products_and_filled_in_for_the_export(lib, case):
+    """The assembly leaves out the upper tiles of the K_ii (and of the coupling matrix, when its strips pair up): the
+    products of every width read the lower ones only, right after the first assembly and over the upper tiles that an
+    export of the blocks before has left, and the export must see the full blocks after every assembly."""
     w = CASES[case]()
     print("case", w.name, flush=True)
     ctx = make_ctx(lib, w)
@@ -120,7 +120,7 @@ def test_upper_tiles_are_filled_in_when_a_product_needs_them(lib, case):
         theta[:-2] *= scale
         ctx.nugpr_build_blocks(theta)
         op = prob.operator(theta)
-        for ncols in (w.n_probes + 1, 1, 2):              # paired tiles, whole strips, paired tiles again
+        for ncols in (w.n_probes + 1, 1, 2):              # matrix cores and vector ALU, vector ALU only, both
             D = rng.standard_normal((w.n, ncols)).astype(np.float32)
             Q = ctx.nugpr_matvec(D).cpu().numpy().astype(np.float64)
             assert relmax(Q, op(D.astype(np.float64))) < 1e-5, (scale, ncols)
@@ -202,9 +202,8 @@ def test_pcg_solve_and_mll_match_oracle(lib, case):
 GRAD_FLOOR = {"tiny": 1e-3}
 
 
-# ragged-t32: 33 columns (two column groups: whole strips are read, so the upper tiles the pair assembly left out
-# are filled in first); ragged-halves / many-reps: pair assembly with the lower-only coupling matrix and strips
-# that pair up over super-blocks of unequal size
+# ragged-t32: 33 columns (two column groups); ragged-halves / many-reps: pair assembly with the lower-only coupling
+# matrix and strips that pair up over super-blocks of unequal size
 @pytest.mark.parametrize("case", ["ragged-t8", "ragged-t32", "ragged-halves", "many-reps", "tiny", "iso-d1", "C1",
                                   "C1-wide"])
 def test_train_step_gradient_matches_oracle(lib, case):
