@@ -27,9 +27,10 @@
 // instructions a step: 550 ns at the sustained clock, measured without any memory access); 1 - 17 columns also the
 // traffic behind the L2s.  Before (a loader wave feeding an LDS ring with one workgroup barrier per 32 columns, the
 // strip's rows split among the waves) the barrier -> LDS -> MFMA chain left a fifth of the issue slots empty.
-// 128 clusters of 2048 points, 128 representatives each, 17 columns: 556 -> 500 us; 64 uneven clusters of 4096
-// points on average, 33 columns: 2297 -> 1870 us; preconditioner strips, 64 x 2048, 17 columns: 112 -> 108 us
-// (4.9 TB/s of HBM); fp32 mode, 64 x 2048, 17 columns: whole squares -> lower tiles (see below).
+// 128 clusters of 2048 points, 128 representatives each, 17 columns: 556 -> 500 us, and the whole product 550 -> 534 us
+// since the loop no longer refills past its last turn; 64 uneven clusters of 4096 points on average, 33 columns:
+// 2297 -> 1870 us; preconditioner strips, 64 x 2048, 17 columns: 112 -> 108 us (4.9 TB/s of HBM); fp32 mode, 64 x 2048,
+// 17 columns: whole squares -> lower tiles (see below).
 // Tried and not kept: vector operands loaded in operand order from memory (the address unit takes 25 - 30 cycles
 // for a load whatever its width: 640 us); workgroups that stay and take item after item (741 us), or whose start is
 // staggered (580 us): both take the partner strips below out of step.

@@ -12,7 +12,7 @@ SIZES = {
     "around-a-tile": [63, 65, 129],
     "tiny": [5, 3, 1],
     "many-tiles": [200, 257, 64, 90, 33, 640],
-    # one for each: its points are shared out among many threads (16 a column at 33 columns, 512 at one)
+    # one for each: its points are shared out among many threads (16 a column at 33 columns, 256 at one)
     "few-representatives": [1700, 900],
     "wide-coupling": [150] * 11,         # 11 x 65 representatives: row groups of the coupling matrix of unequal size
     "long-strips": [1900, 1610],         # more than 10 tiles a strip on average
