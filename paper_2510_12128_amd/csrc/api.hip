@@ -102,7 +102,26 @@ void arrange_for_dies(std::vector<StripItem>& v) {
   v.swap(out);
 }
 
-// The same for whole groups of items that must run together (the strips of one cluster; the two sets of
+// The strips of a launch that is resident all at once, or nearly (four workgroups of short strips and two of long ones on
+// each of the 256 compute units), reach the units in rounds, longest first: one unit would get the longest strip of every
+// round, another one the shortest.  Every second round goes in reverse; an item keeps its die (its position modulo 8).
+// nugpr_precond_apply, fp64, 17 columns, as dealt / with this: 300 uneven clusters of 200 points on average (1200 strips)
+// 43 / 42 us, 33 columns 62 / 58 (57 under the loader wave); 128 uneven ones of 512 73 / 68; 32 x 1024 points 48 / 42;
+// 8 x 4096 (512 long strips) 136 / 114.  Launches of several rounds fill the gaps by themselves and are left as they are:
+// 64 x 2048 (2048 long strips) 249 / 253, 32 uneven clusters of 2048 (1024) 176 / 179, 1024 x 256 (4096 short) 118 / 118.
+void alternate_rounds(std::vector<StripItem>& v) {
+  constexpr size_t ROUND = 256;
+  if (v.size() > (short_strips(v) ? 5 : 2) * ROUND) return;
+  for (size_t from = ROUND; from < v.size(); from += 2 * ROUND) {
+    const size_t rows = std::min(ROUND, v.size() - from) / NUM_XCD;        // what is left of a last, partial row stays
+    for (size_t x = 0, y = rows; x + 1 < y; ++x) {
+      --y;
+      std::swap_ranges(v.begin() + from + x * NUM_XCD, v.begin() + from + (x + 1) * NUM_XCD, v.begin() + from + y * NUM_XCD);
+    }
+  }
+}
+
+// Dealing to the dies for whole groups of items that must run together (the strips of one cluster; the two sets of
 // strips that share the tiles of a pair of super-blocks of the coupling matrix): the groups go to the dies
 // in turn, in the order given, each die works through its groups in order, and a die whose queue has run
 // dry takes from the fullest one.
@@ -225,6 +244,9 @@ void build_tables(const Layout& L, Tables& t) {
   arrange_for_dies(t.lowG);
   arrange_for_dies(t.upG);
   arrange_for_dies(t.lowL);
+  alternate_rounds(t.lowG);
+  alternate_rounds(t.upG);
+  alternate_rounds(t.lowL);
 }
 
 int upload_table(const std::vector<StripItem>& v, uint64_t matrix_elems, StripItem*& cursor, StripTable& tab, hipStream_t s) {

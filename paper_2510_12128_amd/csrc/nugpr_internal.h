@@ -314,6 +314,8 @@ int coupling_set_diag(nugpr_ctx* c, double value, hipStream_t s);
 int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64,
                  hipStream_t s);
 
+// up to 10 tiles an item on average
+bool short_strips(const std::vector<StripItem>& items);
 // the instantiation for a table of these items over a matrix of that size
 int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes);
 // its name for such a table and width (profilers' spelling, no namespace), valid until the thread's next call

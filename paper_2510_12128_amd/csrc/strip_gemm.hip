@@ -39,8 +39,8 @@
 // column groups two row groups a wave, which leaves four waves per SIMD in place of two.  With the long strips' two waves
 // x four stages and streaming loads for every size, clusters this small were slower than under the loader wave.
 // Preconditioner apply, fp64, 17 columns, loader wave / two waves x four stages / now: 2000 clusters of 64 points
-// 48 / 60 / 46 us, 600 uneven ones of 100 35 / 48 / 37, 300 uneven ones of 200 41 / 53 / 43, 256 x 512 94 / 108 / 89,
-// 32 x 1024 49 / 52 / 46; 33 columns 69 / 83 / 64, 50 / 63 / 51, 57 / 71 / 61, 146 / 154 / 131, 77 / 77 / 76.
+// 48 / 60 / 46 us, 600 uneven ones of 100 35 / 48 / 38, 300 uneven ones of 200 41 / 53 / 42, 256 x 512 94 / 108 / 90,
+// 32 x 1024 50 / 52 / 42; 33 columns 69 / 83 / 64, 50 / 63 / 52, 57 / 71 / 58, 146 / 154 / 126, 78 / 77 / 77.
 //
 // Two arithmetic modes, same data movement:
 //   ACC64 = true   vector blocks are fp64; the fp32 matrix entries are widened in
@@ -449,6 +449,12 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
   return NUGPR_OK;
 }
 
+bool short_strips(const std::vector<StripItem>& items) {
+  uint64_t tiles = 0;
+  for (const StripItem& it : items) tiles += it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0;
+  return tiles <= 10 * items.size();
+}
+
 // Tables with strips of symmetric blocks take the instantiation that pairs their tiles, strips of a basis the caller
 // supplied the row-major one, triangular strips the short or the long one by their mean number of tiles.
 // Short: up to 10 tiles a strip on average.  Preconditioner apply, fp64, 17 columns, short against long: 256 clusters of
@@ -460,15 +466,10 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
 // 48 x 1024 (192 MB) 550 / 530, 64 x 2048 (1 GB) 1614 / 1555; the apply by itself could do without up to 256 MB (48 x 1024:
 // 60 / 66).  Row-major strips never gain: the basis is small beside the K_ii (96 x 2048 points, rank 256: 848 / 865 us).
 int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
-  uint64_t tiles = 0;
-  bool sym = false;
-  for (const StripItem& it : items) {
-    sym = sym || (it.blocked & 2u) != 0;
-    tiles += it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0;
-  }
-  if (sym) return STRIP_SYM;
+  for (const StripItem& it : items)
+    if (it.blocked & 2u) return STRIP_SYM;
   if (!items.empty() && items[0].blocked == 0) return STRIP_ROWMAJOR;
-  return (tiles <= 10 * items.size() ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
+  return (short_strips(items) ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
 }
 
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64) {
