@@ -472,15 +472,25 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
   return (short_strips(items) ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
 }
 
+// Up to 512 strips leave a compute unit two workgroups at most, so four waves per SIMD are no use to them; what two row
+// groups a wave cost is then felt, and two column groups in fp64 run as long strips (three stages, four row groups).
+// Preconditioner apply, 33 columns, short / long: 4 uneven clusters of 700 points on average 73 / 64 us, 24 x 1000 (384
+// strips) 67 / 60, 64 x 300 (320) 33 / 35, 100 uneven ones of 300 (560) 53 / 54.  The other widths and the fp32 mode gain
+// as much by the shorter start as they lose (17 columns: 4 of 700 40 / 39, 24 x 1000 38 / 40).
+static int kind_at(const StripTable& tab, int T, bool acc64) {
+  const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && tab.count <= 512;
+  return as_long ? tab.kind - STRIP_SHORT + STRIP_LONG : tab.kind;
+}
+
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64) {
   static thread_local char name[32];
-  std::snprintf(name, sizeof(name), "k_strip<%d, %s, %d>", (T - 1 + 15) / 16, acc64 ? "true" : "false", tab.kind);
+  std::snprintf(name, sizeof(name), "k_strip<%d, %s, %d>", (T - 1 + 15) / 16, acc64 ? "true" : "false", kind_at(tab, T, acc64));
   return name;
 }
 
 template <bool ACC64>
 static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, const StripArgs& a) {
-  switch (tab.kind) {
+  switch (kind_at(tab, T, ACC64)) {
     case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, tab.count, T, s, a);
     case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, tab.count, T, s, a);
     case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, tab.count, T, s, a);

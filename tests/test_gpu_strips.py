@@ -15,6 +15,7 @@ SIZES = {
     # one for each: its points are shared out among many threads (16 a column at 33 columns, 256 at one)
     "few-representatives": [1700, 900],
     "wide-coupling": [150] * 11,         # 11 x 65 representatives: row groups of the coupling matrix of unequal size
+    "many-short": [90 + k % 60 for k in range(240)],  # more than 512 strips of few tiles
     "long-strips": [1900, 1610],         # more than 10 tiles a strip on average
     "long-streamed": [4800, 4730],       # the same, and more than 128 MB of K_ii
     "short-streamed": [500 + k % 13 for k in range(130)],  # more than 128 MB in strips of few tiles
