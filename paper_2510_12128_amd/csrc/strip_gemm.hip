@@ -40,7 +40,7 @@
 // x four stages and streaming loads for every size, clusters this small were slower than under the loader wave.
 // Preconditioner apply, fp64, 17 columns, loader wave / two waves x four stages / now: 2000 clusters of 64 points
 // 48 / 60 / 46 us, 600 uneven ones of 100 35 / 48 / 38, 300 uneven ones of 200 41 / 53 / 42, 256 x 512 94 / 108 / 90,
-// 32 x 1024 50 / 52 / 42; 33 columns 69 / 83 / 64, 50 / 63 / 52, 57 / 71 / 58, 146 / 154 / 126, 78 / 77 / 77.
+// 32 x 1024 50 / 52 / 42; 33 columns 69 / 83 / 64, 50 / 63 / 52, 57 / 71 / 58, 146 / 154 / 126, 77 / 76 / 66.
 //
 // Two arithmetic modes, same data movement:
 //   ACC64 = true   vector blocks are fp64; the fp32 matrix entries are widened in
