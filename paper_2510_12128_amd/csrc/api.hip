@@ -351,6 +351,7 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->S0v = w + L.o_S0;
   c->assign = reinterpret_cast<int32_t*>(w + L.o_assign);
   c->rep_ptr = reinterpret_cast<int32_t*>(w + L.o_rep_ptr);
+  c->d_rows_before = reinterpret_cast<uint32_t*>(w + L.o_rows_before);
   c->rep_pts = reinterpret_cast<int32_t*>(w + L.o_rep_pts);
   c->Pv = w + L.o_P;
   c->Spart = w + L.o_Spart;
@@ -376,6 +377,8 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   if (e != hipSuccess) return fail(hip_fail(e, "clear solver state"));
   e = hipMemcpyAsync(c->d_cl, L.cl.data(), sizeof(ClusterInfo) * L.nc, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return fail(hip_fail(e, "upload cluster table"));
+  e = hipMemcpyAsync(c->d_rows_before, L.rows_before.data(), L.rows_before.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return fail(hip_fail(e, "upload the factorisation's work lists"));
   Tables t;
   build_tables(L, t);
   const size_t total_items = t.WtD.size() + t.KC.size() + t.Conly.size() + t.WP.size() + t.lowG.size() + t.upG.size() + t.lowL.size();

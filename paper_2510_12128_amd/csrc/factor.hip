@@ -3,21 +3,21 @@
 // paper applies the factor as an explicit inverse followed by batched products, Table 2),
 // log det of the preconditioner, and the right-hand sides B = [y | L Z].
 //
-// Everything is tiled in 64 x 64 fp32 tiles whose products run on the matrix cores
-// (v_mfma_f32_16x16x4_f32, four waves per tile, each 32 x 32).
-//   Cholesky: left-looking over tile columns.  Step k: every tile (m, k), m >= k, gets
+// Everything runs on the fp32 matrix cores (v_mfma_f32_16x16x4_f32), products in blocks of 128 x 128, four waves of 64 x 64.
+//   Cholesky: left-looking over block columns.  Step k: every block (m, k), m >= k, gets
 //     A[m,k] - sum_{j<k} L[m,j] L[k,j]^T in one batched launch over clusters (most of
-//     the sum one step ahead, see k_potrf_update); the workgroup that owns the diagonal
-//     tile factors and inverts it in registers; a second launch multiplies the tiles
+//     the sum one step ahead, see k_potrf_step); the workgroup that owns the diagonal
+//     block factors and inverts it; a second launch multiplies the blocks
 //     below by that inverse.
 //   Inverse: the binary-tree identity
 //     [L11 0; L21 L22]^-1 = [Y11 0; -Y22 L21 Y11, Y22]
 //     applied bottom-up over tile ranges, two batched products per level
 //     (T = L21 Y11, kept transposed in the still unused upper triangle; Y21 = -Y22 T).
-//   The inverse is finally mirrored into the upper triangle so that both halves of the
+//   The inverse is stored with its mirror image so that both halves of the
 //   preconditioner apply, tril(G) r and triu(G) v, stream row-major strips.
 // log det of the preconditioner is taken from the STORED inverse, -2 sum log Y_pp, so the
 // split of eq. (logdet) holds exactly for the operator PCG really applies.
+#include <algorithm>
 #include <climits>
 #include <cmath>
 
@@ -26,143 +26,6 @@
 namespace nugpr {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-constexpr int KS = 32;          // contraction depth per LDS stage (two 16-deep halves per thread)
-constexpr int SP = KS + 1;      // padded LDS row
-
-struct Frag {          // one thread's share of a 64 x 32 operand stage: four elements of each 16-deep half
-  float v[8];
-};
-
-// Logical operand Op[r][k]; memory is element (r, k) (TRANS = false) or (k, r) of a matrix stored in blocks of
-// 16 x 16 fragments (blocked_index): the four elements a thread loads are consecutive in a fragment row, and the
-// 64 threads of a wave load one whole fragment, 1 KiB in one piece.
-// tri: 0 none, 1 keep k <= r, 2 keep k >= r (r, k are coordinates inside the same square block).
-template <bool TRANS>
-__device__ __forceinline__ Frag fetch(const float* __restrict__ base, uint32_t ld, int r0, int k0, int rmax,
-                                      int tri, int tid) {
-  Frag f;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float* v = f.v + 4 * h;
-    if (!TRANS) {
-      const int r = r0 + (tid >> 2), k = k0 + 16 * h + (tid & 3) * 4;
-      if (r < rmax) {
-        const float4 x = *reinterpret_cast<const float4*>(base + blocked_index(ld, r, k));
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-      } else {
-        v[0] = v[1] = v[2] = v[3] = 0.f;
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (tri == 1 && k + j > r) v[j] = 0.f;
-        if (tri == 2 && k + j < r) v[j] = 0.f;
-      }
-    } else {
-      const int k = k0 + 16 * h + (tid >> 4), r = r0 + (tid & 15) * 4;
-      const float4 x = *reinterpret_cast<const float4*>(base + blocked_index(ld, k, r));
-      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (r + j >= rmax) v[j] = 0.f;
-        if (tri == 1 && k > r + j) v[j] = 0.f;
-        if (tri == 2 && k < r + j) v[j] = 0.f;
-      }
-    }
-  }
-  return f;
-}
-
-template <bool TRANS>
-__device__ __forceinline__ void commit(float (*s)[SP], const Frag& f, int tid) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (!TRANS) {
-      const int r = tid >> 2, k = 16 * h + (tid & 3) * 4;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[r][k + j] = f.v[4 * h + j];
-    } else {
-      const int k = 16 * h + (tid >> 4), r = (tid & 15) * 4;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[r + j][k] = f.v[4 * h + j];
-    }
-  }
-}
-
-struct Operand {
-  const float* base;
-  uint32_t ld;
-  int r0;      // first logical row of the 64-row tile
-  int rmax;    // rows >= rmax read as zero
-  int tri;
-};
-
-// acc[i][j] += OpA[64 x K] * OpB[64 x K]^T over k in [k0, k1), k0/k1 multiples of 32 (all callers pass tile boundaries).
-// The operands enter the matrix instruction in swapped roles (OpB as its row operand), which transposes the
-// 16 x 16 result inside the registers: lane l holds C[row l & 15][columns 4 (l >> 4) .. + 3], four consecutive
-// columns of one row, i.e. 16 bytes of a row-major fragment, and the 64 lanes of a wave one whole fragment
-// (1 KiB in one piece): tiles are read and written with one 16-byte access per lane and fragment.
-template <bool TA, bool TB>
-__device__ __forceinline__ void tile_gemm(v4f (&acc)[2][2], const Operand& A, const Operand& B, int k0, int k1,
-                                          float (*sA)[SP], float (*sB)[SP], int tid) {
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wy = wave >> 1, wx = wave & 1;
-  const int m = lane & 15, kk = lane >> 4;
-  if (k0 >= k1) return;
-  Frag fa = fetch<TA>(A.base, A.ld, A.r0, k0, A.rmax, A.tri, tid);
-  Frag fb = fetch<TB>(B.base, B.ld, B.r0, k0, B.rmax, B.tri, tid);
-  for (int k = k0; k < k1; k += KS) {
-    __syncthreads();
-    commit<TA>(sA, fa, tid);
-    commit<TB>(sB, fb, tid);
-    __syncthreads();
-    if (k + KS < k1) {
-      fa = fetch<TA>(A.base, A.ld, A.r0, k + KS, A.rmax, A.tri, tid);
-      fb = fetch<TB>(B.base, B.ld, B.r0, k + KS, B.rmax, B.tri, tid);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS / 4; ++ks) {
-      const float a0 = sA[wy * 32 + m][4 * ks + kk];
-      const float a1 = sA[wy * 32 + 16 + m][4 * ks + kk];
-      const float b0 = sB[wx * 32 + m][4 * ks + kk];
-      const float b1 = sB[wx * 32 + 16 + m][4 * ks + kk];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0, a0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, a0, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0, a1, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, a1, acc[1][1], 0, 0, 0);
-    }
-  }
-}
-
-__device__ __forceinline__ void zero_acc(v4f (&acc)[2][2]) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-}
-
-// visit every accumulator element with its (row, col) inside the 64 x 64 tile
-template <class F>
-__device__ __forceinline__ void for_each_acc(v4f (&acc)[2][2], int tid, F f) {
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wy = wave >> 1, wx = wave & 1;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        f(wy * 32 + 16 * i + (lane & 15), wx * 32 + 16 * j + 4 * (lane >> 4) + v, acc[i][j][v]);
-}
-// the same, four consecutive columns at a time: f(row, first column (a multiple of 4), the four values)
-template <class F>
-__device__ __forceinline__ void for_each_acc4(v4f (&acc)[2][2], int tid, F f) {
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wy = wave >> 1, wx = wave & 1;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) f(wy * 32 + 16 * i + (lane & 15), wx * 32 + 16 * j + 4 * (lane >> 4), acc[i][j]);
-}
 
 // Blocked storage seen tile by tile: element (r, q) of the 64 x 64 tile (tr, tc) of a square block lies at
 // tile_base(ld, tr, tc) + tile_offset(r, q) (= blocked_index(ld, 64 tr + r, 64 tc + q)).  The base is uniform over a
@@ -175,283 +38,606 @@ __device__ __forceinline__ uint32_t tile_offset(int r, int q) {
   return (uint32_t)((q >> 5) * (TILE * BLK_COLS) + (((r >> 4) * 2 + ((q & 31) >> 4)) * FRAG) + (r & 15) * 16 + (q & 15));
 }
 
-// Workgroup -> (cluster, item) for a launch of `per` items for each of `nc` clusters: a 1-D grid of
-// die_grid(per, nc) workgroups.  Workgroups go round-robin to the 8 dies, each with an L2 of its own: with
-// the cluster as the slow index of a plain grid the tiles of one cluster, which all read the same panel,
-// would be spread over every die and the panel fetched eight times.  With nc > 0 die d takes the clusters
-// d, d + 8, .. one after the other (the grid is rounded up to whole groups of 8 clusters; workgroups that
-// fall past the last cluster return at once).  That ties a cluster's work to one die: with clusters of
-// very different sizes the dies would finish far apart, and the host then passes -nc for the plain order
-// (cluster = slow index), which spreads every cluster over all dies (configuration 5: 302 against 353 ms).
+// Workgroup -> (cluster, item) for a launch with a different number of items for every cluster.  The items of all clusters,
+// the largest cluster first, form one list, and each of the 8 dies, to which workgroups go round-robin and which have an
+// L2 of their own each, takes a contiguous piece of it: the tiles of a cluster all read the same panel, which then is
+// fetched into one L2 (or two, where a piece ends) and not into eight.  The pieces are cut by work, so it makes no difference
+// whether the clusters are alike.  (Before: one die per cluster for similar clusters, 14.9 -> 12.8 ms at 128 x 2048 points, and
+// every cluster over all dies, workgroups past the end of a cluster leaving at once, for uneven ones, where the last level of
+// the inverse of 64 uneven clusters of 4096 points ran at half the rate of the one before it: the valid rows of a block of
+// tiles fell on the first dies.)
 constexpr int NUM_DIES = 8;
-static inline unsigned die_grid(int per, int nc) {
-  const int n = nc < 0 ? -nc : nc;
-  return (unsigned)per * NUM_DIES * ((n + NUM_DIES - 1) / NUM_DIES);
-}
-__device__ __forceinline__ bool die_local_item(int per, int nc, int& cluster, int& item, int id = (int)blockIdx.x) {
-  if (nc < 0) {
-    cluster = id / per;
-    item = id % per;
-    return cluster < -nc;
+struct Pieces {
+  uint32_t from[NUM_DIES + 1];        // die d takes the items from[d] .. from[d + 1] - 1
+  unsigned grid() const {
+    uint32_t most = 0;
+    for (int d = 0; d < NUM_DIES; ++d) most = std::max(most, from[d + 1] - from[d]);
+    return most * NUM_DIES;
   }
-  const int die = id % NUM_DIES, slot = id / NUM_DIES;
-  cluster = die + NUM_DIES * (slot / per);
-  item = slot % per;
-  return cluster < nc;
+};
+// The clusters come in the order of ClusterInfo::by_size; the one of rank i has the items first[i] - i sub .. first[i + 1] -
+// (i + 1) sub - 1 (n ranks with items).  rank, item (inside the cluster): uniform over the workgroup.
+// An item may be shared by `parts` workgroups, which follow one another (part: which of them this one is).
+__device__ __forceinline__ bool list_item(const Pieces& pieces, const uint32_t* __restrict__ first, uint32_t sub, int n, int id, int& rank, int& item,
+                                          uint32_t parts, int& part) {
+  const uint32_t die = (uint32_t)id % NUM_DIES;
+  uint32_t g = pieces.from[die] + (uint32_t)id / NUM_DIES;
+  if (g >= pieces.from[die + 1]) return false;
+  part = (int)(g % parts);
+  g /= parts;
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;                          // the rank lies in lo .. hi - 1: 64 places of it are looked at at a time
+  while (hi - lo > 1) {
+    const int stride = (hi - lo + 63) / 64, at = lo + lane * stride;
+    const bool before = at < hi && first[at] - (uint32_t)at * sub <= g;
+    lo += (__popcll(__ballot(before)) - 1) * stride;
+    hi = min(hi, lo + stride);
+  }
+  rank = __builtin_amdgcn_readfirstlane(lo);
+  item = (int)__builtin_amdgcn_readfirstlane(g - (first[rank] - (uint32_t)rank * sub));
+  return true;
+}
+
+// ---------------------------------------------------------------------------
+// Block products: a workgroup computes 128 x 128, each of its four waves one 64 x 64 tile
+// ---------------------------------------------------------------------------
+// acc += OpA[128 x K] OpB[128 x K]^T: wave w works on row tile w / 2 of OpA and w % 2 of OpB.  A step is 16 columns: sixteen
+// fragments of 1 KiB, four a wave, go from memory straight into a stage of an LDS ring (16-byte pieces, one instruction a
+// fragment), two steps ahead; for one workgroup barrier a wave reads its eight fragments, 16 bytes a lane, and issues 64
+// matrix instructions.  Lane (m, kg) holds (row m, columns 4 kg ..) of either operand, so component i of both feeds one
+// instruction whose contraction index is kg.  The roles are swapped (OpB is the row operand of the instruction): lane l ends
+// up with C[row l & 15][columns 4 (l >> 4) .. + 3] of each fragment, 16 bytes of a row.
+// The fragments of step q + 1 are read in the middle of step q's instructions, so neither the barrier nor the LDS is waited for
+// with idle matrix cores: without that 104 TFLOP/s at the last level of the inverse of 128 x 2048 points, with it 115.
+// What bounds it: the matrix cores, and the ends of a workgroup.  With 64 x 64 per workgroup (16 flop per byte through L2, two
+// barriers for 32 matrix instructions a wave) the two products of the tree took 4.27 + 0.5 ms there with the mirroring that
+// followed, now 3.85, and 31 + 1.2 ms on 64 uneven clusters of 4096 points, now 21.5 (the work lists below have their part in it).
+constexpr int RING_STAGES = 3, RING_STAGE = 16 * 1024, RING = RING_STAGES * RING_STAGE;
+constexpr uint32_t waitcnt_vm(uint32_t n) {      // s_waitcnt immediate: vmcnt(n), the other counters unconstrained
+  return (n & 15u) | ((n >> 4) << 14) | 0x0F70u;
+}
+// Steps s0 .. s1 - 1 (whole tiles).  mine: first element of the strip (64 rows of a square block) that this wave loads:
+// row tile 0 / 1 of OpA, 0 / 1 of OpB for wave 0 .. 3.  TRI (of OpA): 0 none; 1 / 2: the tile of column tile diag is
+// triangular (column <= row / >= row is kept) and the tiles past it / before it count as zero whatever is stored there.
+template <int TRI, bool SWAP = false>
+__device__ __forceinline__ void block_gemm(v4f (&acc)[4][4], const float* mine, int s0, int s1, int diag, unsigned char* ring) {
+#if __HIP_DEVICE_COMPILE__
+  typedef __attribute__((address_space(3))) const v4f* lds_v4f;
+  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+  const int lane = threadIdx.x & 63, m = lane & 15, kg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t piece = (uint32_t)(m * 16 + 4 * kg) * 4u;      // (scalar base + 32-bit lane offset: one address register)
+  const int n = s1 - s0;
+  auto issue = [&](int q) {
+    const int step = s0 + q;
+    const float* at = mine + (uint64_t)(step >> 1) * (TILE * BLK_COLS) + (step & 1) * FRAG;
+    unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + 4 * w * 1024;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(at + g * 2 * FRAG) + piece, (lds_ptr)(st + g * 1024), 16, 0, 0);
+  };
+  v4f a[2][4], b[2][4];
+  // step q into the registers of its parity, once every wave's share of it has landed.  The barrier also says that every
+  // wave has read step q - 1, whose stage then takes step q - 1 + RING_STAGES.
+  auto fetch_step = [&](int q, v4f (&fa)[4], v4f (&fb)[4]) {
+    if (q + RING_STAGES - 2 <= n - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 * (RING_STAGES - 2)));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + lane * 16;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) fa[g] = *(lds_v4f)(st + (4 * (w >> 1) + g) * 1024);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) fb[g] = *(lds_v4f)(st + (8 + 4 * (w & 1) + g) * 1024);
+    if (q > 0 && q - 1 + RING_STAGES < n) issue(q - 1 + RING_STAGES);
+  };
+  auto mult = [&](const v4f (&fa)[4], const v4f (&fb)[4], int i) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[g][j] = SWAP ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[g][i], fb[j][i], acc[g][j], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][i], fa[g][i], acc[g][j], 0, 0, 0);
+  };
+  auto step_of = [&](int q, v4f (&fa)[4], v4f (&fb)[4], v4f (&na)[4], v4f (&nb)[4]) {
+    const int step = s0 + q, tile = step >> 2;
+    const bool counts = !((TRI == 1 && tile > diag) || (TRI == 2 && tile < diag));
+    // (the step's reads are waited for here, where nothing younger is in flight, and not at a use behind a branch)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(fa[g]), "+v"(fb[g]));
+    if (TRI != 0 && tile == diag) {
+      const int k = 16 * (step & 3) + 4 * kg;
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool keep = TRI == 1 ? k + i <= 16 * g + m : k + i >= 16 * g + m;
+          fa[g][i] = keep ? fa[g][i] : 0.f;
+        }
+    }
+    if (counts) { mult(fa, fb, 0); mult(fa, fb, 1); }
+    __builtin_amdgcn_sched_barrier(0);
+    if (q + 1 < n) fetch_step(q + 1, na, nb);
+    __builtin_amdgcn_sched_barrier(0);
+    if (counts) { mult(fa, fb, 2); mult(fa, fb, 3); }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int q = 0; q < RING_STAGES; ++q)
+    if (q < n) issue(q);
+  fetch_step(0, a[0], b[0]);
+#pragma unroll 1
+  for (int q = 0; q < n; q += 2) {
+    step_of(q, a[0], b[0], a[1], b[1]);
+    step_of(q + 1, a[1], b[1], a[0], b[0]);
+  }
+#endif
+}
+__device__ __forceinline__ void zero_block(v4f (&acc)[4][4]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[g][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+}
+// this lane's four values of fragment (g, j) of a 64 x 64 tile (a uniform pointer and a 32-bit lane offset)
+__device__ __forceinline__ v4f* fragment(float* tile, int g, int j) {
+  const uint32_t lane = threadIdx.x & 63, at = (lane & 15) * 64 + (lane >> 4) * 16;
+  return reinterpret_cast<v4f*>(reinterpret_cast<char*>(tile + ((j >> 1) * (TILE * BLK_COLS) + (g * 2 + (j & 1)) * FRAG)) + at);
+}
+__device__ __forceinline__ const v4f* fragment(const float* tile, int g, int j) { return fragment(const_cast<float*>(tile), g, j); }
+// keeps an address where it is used: per-lane addresses computed ahead of the products cost registers that these need
+template <typename P> __device__ __forceinline__ P* here(P* p) {
+#if __HIP_DEVICE_COMPILE__
+  __attribute__((address_space(1))) P* g = (__attribute__((address_space(1))) P*)p;
+  asm volatile("" : "+s"(g));
+  p = (P*)g;
+#endif
+  return p;
+}
+// (four fragments at a time: with the whole tile's loads in flight at once the accumulators would not stay in registers)
+__device__ __forceinline__ void add_tile(v4f (&acc)[4][4], const float* tile) {
+  tile = here(tile);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[g][j] += *fragment(tile, g, j);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+__device__ __forceinline__ void put_difference(const float* from, const v4f (&acc)[4][4], float* tile) {
+  from = here(from);
+  tile = here(tile);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *fragment(tile, g, j) = *fragment(from, g, j) - acc[g][j];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+__device__ __forceinline__ void put_tile(const v4f (&acc)[4][4], float* tile) {
+  tile = here(tile);
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *fragment(tile, g, j) = acc[g][j];
+}
+// element offset of fragment (g, j)'s first value of this lane in the transposed tile
+__device__ __forceinline__ uint32_t block_at_mirrored(int g, int j) {
+  const int lane = threadIdx.x & 63;
+  return tile_offset(16 * j + 4 * (lane >> 4), 16 * g + (lane & 15));
+}
+
+// ---------------------------------------------------------------------------
+// Cholesky factor and inverse of one 64 x 64 tile in LDS (256 threads)
+// ---------------------------------------------------------------------------
+// This is the critical path of a step's launch (the next one needs its result), and it shares its compute unit with
+// workgroups that keep the matrix cores busy, which slows every instruction it issues.  So the serial part is small: the
+// tile is taken in four panels of 16 columns, a panel is factored by ONE wave in registers (lane = row; pivots and pivot
+// rows reach the other lanes by v_readlane, no LDS and no barrier between the pivots), and everything else is 16 x 16 blocks
+// on the matrix cores, a block per wave: the left-looking update of a panel's column of blocks, and the blocks of
+// L^-1 = [Y11 0; -Y22 L21 Y11, Y22] over blocks, then pairs of blocks.
+// Panel, elimination without square roots (A = Lu D Lu^T): pivot j: m_i = a_ij / d_j (i > j), a_ic -= m_i a_cj (c > j);
+// then L = Lu D^1/2.  A pivot that is not positive and finite is replaced by 1 and reported.
+// Before: 64 pivots of one LDS round trip and one barrier each, the inverse carried along: a step of four clusters of 512
+// points (this and one short product) 34 us, now 17.
+constexpr int LT = TILE + 1;                    // row stride of a tile in LDS
+constexpr int IP = 17;                          // and of an inverted diagonal block
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+// sT: the tile (lower triangle read), replaced by L; block (i, j), i > j, of L^-1 is left where block (j, i) of L would be.
+// inv: four 16 x IP inverted diagonal blocks; rdiag: 64 values.  Returns whether a pivot was bad (true for wave 0's threads).
+__device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* rdiag) {
+  const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  bool bad = false;
+#pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
+    if (p > 0) {                                // block (w, p) -= sum over the panels before of L(w, q) L(p, q)^T
+      if (w >= p) {
+        v4f acc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = sT[16 * w + 4 * kg + i][16 * p + m];
+        for (int q = 0; q < p; ++q)
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-sT[16 * w + m][16 * q + 4 * s + kg], sT[16 * p + m][16 * q + 4 * s + kg], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sT[16 * w + 4 * kg + i][16 * p + m] = acc[i];
+      }
+      __syncthreads();
+    }
+    if (w == 0) {
+      float a[16], d = 1.f;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) a[u] = sT[lane][16 * p + u];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        float dj = lane_value(a[j], 16 * p + j);
+        if (!(dj > 0.f) || !(dj < INFINITY)) { bad = true; dj = 1.f; }
+        d = lane == 16 * p + j ? dj : d;
+        const float mi = lane > 16 * p + j ? a[j] * (1.f / dj) : 0.f;
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) a[c] = fmaf(-mi, lane_value(a[j], 16 * p + c), a[c]);
+      }
+      const float sd = sqrtf(d), rs = 1.f / sd;
+      if (lane >= 16 * p) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sT[lane][16 * p + u] = lane == 16 * p + u ? sd : (lane > 16 * p + u ? a[u] * lane_value(rs, 16 * p + u) : 0.f);
+        if (lane < 16 * p + 16) rdiag[lane] = rs;
+      }
+    }
+    __syncthreads();
+  }
+  {                                             // inverse of diagonal block w: lane m holds column m of it
+    float l[16], y[16];
+    const float r = rdiag[16 * w + m];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      l[u] = sT[16 * w + m][16 * w + u];
+      y[u] = u == m ? 1.f : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      y[q] *= lane_value(r, q);
+#pragma unroll
+      for (int i = q + 1; i < 16; ++i) y[i] = fmaf(-lane_value(l[q], i), y[q], y[i]);
+    }
+    if (kg == 0) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) inv[(16 * w + u) * IP + m] = y[u];
+    }
+  }
+  __syncthreads();
+  // acc += X Y for blocks: X row-major at x, Y row-major at y; a product's result enters the next one as its right factor
+  // as it stands (component i of lane (m, kg) is element (4 kg + i, m), contraction index 4 kg + i)
+  auto mult = [&](const float* x, int ldx, const float* y, int ldy, v4f acc) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[m * ldx + 4 * kg + i], y[(4 * kg + i) * ldy + m], acc, 0, 0, 0);
+    return acc;
+  };
+  auto mult_reg = [&](const float* x, int ldx, const v4f& y, v4f acc) {      // acc -= X Y
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(-x[m * ldx + 4 * kg + i], y[i], acc, 0, 0, 0);
+    return acc;
+  };
+  const v4f zero = (v4f){0.f, 0.f, 0.f, 0.f};
+  auto put = [&](int i, int j, const v4f& v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sT[16 * j + 4 * kg + e][16 * i + m] = v[e];
+  };
+  if (w < 2) {                                  // blocks (1, 0) and (3, 2)
+    const int j = 2 * w, i = j + 1;
+    const v4f t = mult(&sT[16 * i][16 * j], LT, inv + 16 * j * IP, IP, zero);
+    put(i, j, mult_reg(inv + 16 * i * IP, IP, t, zero));
+  }
+  __syncthreads();
+  if (w < 2) {                                  // blocks (2, w) and (3, w)
+    v4f t2 = mult(&sT[32][16 * w], LT, inv + 16 * w * IP, IP, zero), t3 = mult(&sT[48][16 * w], LT, inv + 16 * w * IP, IP, zero);
+    if (w == 0) {
+      t2 = mult(&sT[32][16], LT, &sT[0][16], LT, t2);
+      t3 = mult(&sT[48][16], LT, &sT[0][16], LT, t3);
+    }
+    const v4f y2 = mult_reg(inv + 32 * IP, IP, t2, zero);
+    const v4f y3 = mult_reg(&sT[32][48], LT, t2, mult_reg(inv + 48 * IP, IP, t3, zero));
+    put(2, w, y2);
+    put(3, w, y3);
+  }
+  __syncthreads();
+  return bad;
 }
 
 // ---------------------------------------------------------------------------
 // Cholesky, step k
 // ---------------------------------------------------------------------------
-// Left-looking, with the bulk of every tile's update done one step ahead.  The launch of step k has two
-// kinds of workgroups:
-//   diagonal  tile (k, k): subtract the contribution of column k - 1 (the only one that was not final when the
-//             bulk of this tile was computed), then factor and invert the tile
-//   row m > k two tiles of the same block row, one after the other:
-//             finish (m, k): subtract the contribution of column k - 1, as above;
-//             bulk (m, k + 1): L <- A - sum over the columns < k, all final by now
-// The factorisation of the diagonal tile is serial and keeps one workgroup per cluster busy for tens of
+// Left-looking over columns of blocks of 128 x 128 (two tiles by two; the last one of a cluster may be one tile), with the
+// bulk of every block's update done one step ahead.  The launch of step k has two kinds of workgroups:
+//   diagonal  block (k, k): subtract the contribution of block column k - 1 (the only one that was not final when the bulk of
+//             this block was computed), then factor and invert the block
+//   row m > k two blocks of the same block row, one after the other:
+//             finish (m, k): subtract the contribution of block column k - 1, as above;
+//             bulk (m, k + 1): L <- A - sum over the block columns < k, all final by now
+//             Where there are too few blocks for the chip, the sum is shared by `parts` workgroups of k / parts columns each: the
+//             first one as above, the others leave their sums in blocks of the inverse's row m that it does not need yet, in
+//             turn even and odd columns, and the finish of the next step adds them up.
+// The factorisation of the diagonal block is serial and keeps one workgroup per cluster busy for tens of
 // microseconds; with the long products of the NEXT column in the same launch the rest of the chip has work
-// meanwhile, where a launch that only finished column k would idle behind its diagonal tiles.
-// Grid order = start order (workgroups are handed out in index order, a few thousand take tens of
-// microseconds): the diagonal tiles of all clusters first, since the launch cannot end before they do.  Finish
+// meanwhile, where a launch that only finished column k would idle behind its diagonal blocks.
+// Grid order = start order: the diagonal blocks of all clusters first, since the launch cannot end before they do.  Finish
 // and bulk of a block row share a workgroup because, as workgroups of their own, the short finish ones either
-// delay the start of the long ones or wait behind them for a free slot: measured 25 us per launch.
-__global__ __launch_bounds__(256) void k_potrf_update(const ClusterInfo* __restrict__ cl, const float* Kd,
-                                                      float* Lf, float* __restrict__ G, int k,
-                                                      int n_rows, int grid_diag, int nc, PcgState* __restrict__ st) {
-  // the operand stages and, once the products are done, the tile on its way into the registers of the
-  // factorisation (then its exchange buffers) share one piece of LDS: 16.5 KB per workgroup
-  static_assert(2 * TILE * SP >= TILE * (TILE + 1), "the tile to be factored must fit in the operand stages");
-  __shared__ __attribute__((aligned(16))) float stage[2 * TILE * SP];
-  float (*sA)[SP] = reinterpret_cast<float (*)[SP]>(stage);
-  float (*sB)[SP] = reinterpret_cast<float (*)[SP]>(stage + TILE * SP);
-  float (*sT)[TILE + 1] = reinterpret_cast<float (*)[TILE + 1]>(stage);
-  const int id = (int)blockIdx.x;
-  const bool diag = id < grid_diag;
-  int ci, item;
-  if (diag) {
-    if (!die_local_item(1, nc, ci, item, id)) return;
-  } else {
-    if (!die_local_item(n_rows, nc, ci, item, id - grid_diag)) return;
-    item += 1;
-  }
-  const ClusterInfo c = cl[ci];
-  const int mt = k + item;                     // block row of this workgroup
-  if (mt >= (int)c.nt) return;
-  const int tid = threadIdx.x;
-  const int b = (int)c.b;
-  const float* A = Kd + c.koff;
-  float* L = Lf + c.koff;
-  v4f acc[2][2];
-  zero_acc(acc);
-  Operand oa{L, c.ld, mt * TILE, b, 0};
-  Operand ob{L, c.ld, k * TILE, b, 0};
-  if (k > 0) tile_gemm<false, false>(acc, oa, ob, (k - 1) * TILE, k * TILE, sA, sB, tid);
-  // what the products are subtracted from: the assembled block, or the bulk result of the step before
-  const float* base = k == 0 ? A : L;
-  if (!diag) {
-    {
-      const uint64_t tb = tile_base(c.ld, mt, k);
-      const float* bt = base + tb;
-      float* lt = L + tb;
-      for_each_acc4(acc, tid, [&](int r, int q, const v4f& v) {
-        const uint32_t at = tile_offset(r, q);
-        const float4 x = *reinterpret_cast<const float4*>(bt + at);
-        *reinterpret_cast<float4*>(lt + at) = make_float4(x.x - v[0], x.y - v[1], x.z - v[2], x.w - v[3]);
-      });
-    }
-    zero_acc(acc);
-    Operand oc{L, c.ld, (k + 1) * TILE, b, 0};
-    if (k > 0) tile_gemm<false, false>(acc, oa, oc, 0, k * TILE, sA, sB, tid);
-    {
-      const uint64_t tb = tile_base(c.ld, mt, k + 1);
-      const float* at_ = A + tb;
-      float* lt = L + tb;
-      for_each_acc4(acc, tid, [&](int r, int q, const v4f& v) {
-        const uint32_t at = tile_offset(r, q);
-        const float4 x = *reinterpret_cast<const float4*>(at_ + at);
-        *reinterpret_cast<float4*>(lt + at) = make_float4(x.x - v[0], x.y - v[1], x.z - v[2], x.w - v[3]);
-      });
-    }
-    return;
-  }
-  // ---- diagonal tile: factor and invert it; rows/cols past the cluster end behave as identity ----
-  // This workgroup is the critical path of the whole launch (the next launch needs its result) and shares its
-  // compute unit with workgroups that keep the matrix cores busy, which slows every instruction it issues: so
-  // the tile lives in REGISTERS and a pivot costs one LDS round trip and one barrier.  Wave w owns the columns
-  // 16 w .. 16 w + 15 of all 64 rows, lane i the row i: a[u] = A[i][16 w + u], y[u] = Y[i][16 w + u].
-  // Elimination without square roots (A = Lu D Lu^T, Lu unit lower) applied to [A | I]:
-  //   pivot j:  m_i = a_ij / d_j (i > j);  a_ic -= m_i a_cj (c > j);  y_ic -= m_i y_jc (c <= j)
-  // leaves a_ic = (Lu D)_ic below the diagonal, d on it, and Y = Lu^-1; then L = Lu D^1/2, L^-1 = D^-1/2 Lu^-1.
-  // Per pivot the owners publish column j of A (one value per row) and row j of Y in LDS, double-buffered so
-  // that one barrier per pivot is enough.
-  __syncthreads();                              // every wave is done reading the operand stages
-  const int valid = min(TILE, b - k * TILE);
-  const float* bkk = base + tile_base(c.ld, k, k);
-  for_each_acc4(acc, tid, [&](int r, int q, const v4f& v) {
-    const float4 b4 = *reinterpret_cast<const float4*>(bkk + tile_offset(r, q));
-    const float x[4] = {b4.x - v[0], b4.y - v[1], b4.z - v[2], b4.w - v[3]};
-#pragma unroll
-    for (int u = 0; u < 4; ++u) sT[r][q + u] = (r >= valid || q + u >= valid) ? (r == q + u ? 1.f : 0.f) : x[u];
-  });
-  __syncthreads();
-  const int w = tid >> 6, i = tid & 63;
-  float a[16], y[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    a[u] = sT[i][16 * w + u];
-    y[u] = (16 * w + u == i) ? 1.f : 0.f;
-  }
-  __syncthreads();                              // sT is dead from here on: its memory holds the exchange buffers
-  float* colbuf = stage;                        // [2][64]  column j of A, by row
-  float* rowbuf = stage + 2 * TILE;             // [2][64]  row j of Y
-  float* dvec = stage + 4 * TILE;               // [64]     the pivots d_j
-  bool bad = false;
-#pragma unroll 1
-  for (int jb = 0; jb < 4; ++jb) {
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-      const int j = 16 * jb + jj;
-      float* cb = colbuf + (j & 1) * TILE;
-      float* rb = rowbuf + (j & 1) * TILE;
-      if (w == jb) cb[i] = a[jj];
-      if (i == j) {
-#pragma unroll
-        for (int u = 0; u < 16; u += 4) *reinterpret_cast<float4*>(rb + 16 * w + u) = make_float4(y[u], y[u + 1], y[u + 2], y[u + 3]);
-      }
-      __syncthreads();
-      float dj = cb[j];
-      if (!(dj > 0.f) || !(dj < INFINITY)) { bad = true; dj = 1.f; }
-      if (tid == 0) dvec[j] = dj;
-      const float mi = i > j ? cb[i] / dj : 0.f;
-      if (w > jb) {                             // all 16 columns of this wave lie right of the pivot
-#pragma unroll
-        for (int u = 0; u < 16; u += 4) {
-          const float4 cj = *reinterpret_cast<const float4*>(cb + 16 * w + u);
-          a[u] = fmaf(-mi, cj.x, a[u]); a[u + 1] = fmaf(-mi, cj.y, a[u + 1]);
-          a[u + 2] = fmaf(-mi, cj.z, a[u + 2]); a[u + 3] = fmaf(-mi, cj.w, a[u + 3]);
-        }
-      } else if (w == jb) {
-#pragma unroll
-        for (int u = jj + 1; u < 16; ++u) a[u] = fmaf(-mi, cb[16 * w + u], a[u]);
-      }
-      if (w <= jb) {                            // Y_j is zero right of column j
-#pragma unroll
-        for (int u = 0; u < 16; u += 4) {
-          const float4 yj = *reinterpret_cast<const float4*>(rb + 16 * w + u);
-          y[u] = fmaf(-mi, yj.x, y[u]); y[u + 1] = fmaf(-mi, yj.y, y[u + 1]);
-          y[u + 2] = fmaf(-mi, yj.z, y[u + 2]); y[u + 3] = fmaf(-mi, yj.w, y[u + 3]);
-        }
-      }
-    }
-  }
-  __syncthreads();                              // dvec complete
-  if (bad && tid == 0) atomicMin(&st->bad_cluster, ci);
-  // L_ic = a_ic / sqrt(d_c) (c < i), sqrt(d_i) on the diagonal;  (L^-1)_ic = y_ic / sqrt(d_i) (c <= i)
-  const float rsi = 1.f / sqrtf(dvec[i]);
-  float* Y = G + c.koff;
-  const uint64_t at = tile_base(c.ld, k, k) + tile_offset(i, 16 * w);     // one fragment row: 16 floats
+// delay the start of the long ones or wait behind them for a free slot.
+// A second launch multiplies the blocks below the diagonal by its inverse.
+// What bounds it: the matrix cores, half idle where a launch is one or two rounds of workgroups; 82 TFLOP/s on 64 uneven
+// clusters of 4096 points (23.7 + 2 ms; with tiles of 64 31.6 + 1.6 ms), 85 on 128 x 2048 (4.3 + 0.7 ms; 4.4 + 0.6 ms).  A block
+// column of 128 needs half as many steps as one of 64, reads the panel L[m, 0:k] half as often, and its diagonal workgroup
+// (47 us on an idle chip) is still done before the rows are.
+// (Rows past the end of a cluster: zero in the assembled blocks and therefore zero in L; identity in the diagonal tile.)
+// the tile in LDS and its inverse (factor_tile) to memory: L lower, the inverse with its mirror image
+__device__ __forceinline__ void store_factored(const float (*sT)[LT], const float* inv, float* l, float* y) {
+  const int w = threadIdx.x >> 6, i = threadIdx.x & 63;
+  const uint32_t at = tile_offset(i, 16 * w);     // one fragment row: 16 floats
 #pragma unroll
   for (int u = 0; u < 16; u += 4) {
     float lo[4], yo[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int cc = 16 * w + u + v;
-      const float sc = sqrtf(dvec[cc]);
-      lo[v] = cc < i ? a[u + v] / sc : (cc == i ? sc : 0.f);
-      yo[v] = cc <= i ? y[u + v] * rsi : 0.f;
+      lo[v] = cc <= i ? sT[i][cc] : 0.f;
+      const int r = max(i, cc), q = min(i, cc);
+      yo[v] = (r >> 4) == (q >> 4) ? inv[r * IP + (q & 15)] : sT[(q & ~15) + (r & 15)][(r & ~15) + (q & 15)];
     }
-    *reinterpret_cast<float4*>(L + at + u) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-    *reinterpret_cast<float4*>(Y + at + u) = make_float4(yo[0], yo[1], yo[2], yo[3]);
+    *reinterpret_cast<float4*>(l + at + u) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+    *reinterpret_cast<float4*>(y + at + u) = make_float4(yo[0], yo[1], yo[2], yo[3]);
   }
 }
 
-// tiles below the diagonal: L[m,k] <- L[m,k] * inv(L[k,k])^T
-__global__ __launch_bounds__(256) void k_potrf_trsm(const ClusterInfo* __restrict__ cl, float* __restrict__ Lf,
-                                                    const float* __restrict__ G, int k, int per, int nc) {
-  __shared__ __attribute__((aligned(16))) float sA[TILE][SP];
-  __shared__ __attribute__((aligned(16))) float sB[TILE][SP];
-  int ci, item;
-  if (!die_local_item(per, nc, ci, item)) return;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, float* G, int k, int n_diag, int grid_diag,
+                  Pieces pieces, const uint32_t* __restrict__ first, int n_rows, int parts, int parts_before, PcgState* __restrict__ st) {
+  // the ring of the products and, once these are done, the tiles of the diagonal block share one piece of LDS
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
+  static_assert((2 * TILE * LT + 4 * 16 * IP + TILE) * sizeof(float) <= RING, "two tiles and the inverted blocks must fit");
+  const int id = (int)blockIdx.x;
+  const bool diag = id < grid_diag;
+  int rank = id, item = 0, part = 0;
+  if (diag) {
+    if (id >= n_diag) return;
+    __builtin_amdgcn_s_setprio(3);
+  } else {
+    if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, id - grid_diag, rank, item, (uint32_t)parts, part)) return;
+  }
+  const int ci = (int)cl[rank].by_size;
   const ClusterInfo c = cl[ci];
-  const int mt = k + 1 + item;
-  if (mt >= (int)c.nt) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), ia = w >> 1, jb = w & 1;
+  const int m = diag ? k : k + 1 + item;       // block row of this workgroup
+  const int last = (int)c.nt - 1;
+  const float* A = Kd + c.koff;
   float* L = Lf + c.koff;
-  const float* Y = G + c.koff;
-  v4f acc[2][2];
-  zero_acc(acc);
-  Operand oa{L, c.ld, mt * TILE, (int)c.b, 0};
-  Operand ob{Y, c.ld, k * TILE, (int)c.ld, 1};          // Y_kk[c][j], lower triangular
-  tile_gemm<false, false>(acc, oa, ob, k * TILE, (k + 1) * TILE, sA, sB, tid);
+  float* Y = G + c.koff;
+  // where part p (1, 2, ..) of the sum for tile (ia, jb) of the block of row m and an even / odd column of blocks waits
+  auto part_tile = [&](int column, int p) { return Y + tile_base(c.ld, 2 * m + ia, 2 * (2 * (p - 1) + (column & 1)) + jb); };
+  auto strip = [&](int t) { return (const float*)(L + (uint64_t)min(t, last) * TILE * c.ld); };
+  v4f acc[4][4];
+  zero_block(acc);
+#pragma unroll 1
+  for (int ahead = part > 0 ? 1 : 0; k > 0; ahead = 1) {      // the block of column k, then (rows) that of column k + 1
+    const int col = 2 * (k + ahead) + jb, row = 2 * m + ia;
+    zero_block(acc);
+    block_gemm<0>(acc, strip(w < 2 ? 2 * m + w : 2 * (k + ahead) + w - 2), ahead ? 8 * (k * part / parts) : 8 * (k - 1),
+                  ahead ? 8 * (k * (part + 1) / parts) : 8 * k, 0, ring);
+    if (!ahead && row <= last)
+      for (int p = 1; p < parts_before; ++p) add_tile(acc, part_tile(k, p));
+    if (diag) break;
+    if (row <= last && col <= row) {           // (tiles above the diagonal are not part of the factor)
+      const uint64_t tb = tile_base(c.ld, row, col);
+      // what the products are subtracted from: the bulk result of the step before where there is one, or the assembled block
+      if (part > 0) put_tile(acc, part_tile(k + 1, part));
+      else put_difference((!ahead && k > 1 ? L : A) + tb, acc, L + tb);
+    }
+    if (ahead) return;
+    __syncthreads();                           // the ring starts over
+  }
+  if (!diag) return;                           // (k = 0: k_potrf_solve reads the assembled block)
+  // ---- diagonal block [A00 .; A10 A11]: L00, L00^-1 = Y00;  L10 = A10 Y00^T;  A11 -= L10 L10^T;  L11, Y11;  Y10 = -Y11 L10 Y00 ----
+  float (*sT)[LT] = reinterpret_cast<float (*)[LT]>(ring);
+  float (*sX)[LT] = sT + TILE;
+  float *inv = &sX[TILE][0], *rdiag = inv + 4 * 16 * IP;
+  const int lane = tid & 63, mm = lane & 15, kg = lane >> 4;
+  const int b = (int)c.b;
+  const bool two = 2 * k + 1 <= last;
+  __syncthreads();                             // every wave is done with the ring
+  const float* base = k > 1 ? L : A;
+  if (jb <= ia && 2 * k + ia <= last) {        // wave 0: A00, wave 2: A10, wave 3: A11, which waits in memory
+    const uint64_t tb = tile_base(c.ld, 2 * k + ia, 2 * k + jb);
+    const int valid = w == 0 ? min(TILE, b - 2 * k * TILE) : TILE;       // (the rows of A10 past the end are zero)
+    float (*s)[LT] = w == 0 ? sT : sX;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const v4f x = *fragment(base + tb, g, j) - acc[g][j];
+        if (w == 3) *fragment(L + tb, g, j) = x;
+        else {
+          const int r = 16 * g + mm, q = 16 * j + 4 * kg;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[r][q + e] = r >= valid || q + e >= valid ? (r == q + e ? 1.f : 0.f) : x[e];
+        }
+        if (j == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+  }
   __syncthreads();
-  float* lt = L + tile_base(c.ld, mt, k);
-  for_each_acc4(acc, tid, [&](int r, int q, const v4f& v) {
-    *reinterpret_cast<float4*>(lt + tile_offset(r, q)) = make_float4(v[0], v[1], v[2], v[3]);
-  });
+  bool bad = factor_tile(sT, inv, rdiag);
+  {
+    const uint64_t tb = tile_base(c.ld, 2 * k, 2 * k);
+    store_factored(sT, inv, L + tb, Y + tb);
+  }
+  if (two) {
+    // blocks of 16 x 16: element (r, q) of block (i, j) of the inverse left by factor_tile
+    auto yb = [&](int i, int j) { return i == j ? inv + 16 * i * IP : &sT[16 * j][16 * i]; };
+    auto ldy = [&](int i, int j) { return i == j ? IP : LT; };
+    v4f l10[4];                                // L10(w, j) = sum over q <= j of A10(w, q) Y00(j, q)^T
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      l10[j] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q <= j; ++q) {
+        const float* y = yb(j, q);
+        const int ld = ldy(j, q);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          l10[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(sX[16 * w + mm][16 * q + 4 * s + kg], y[mm * ld + 4 * s + kg], l10[j], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sX[16 * w + 4 * kg + e][16 * j + mm] = l10[j][e];
+    __syncthreads();
+    {
+      float* lt = L + tile_base(c.ld, 2 * k + 1, 2 * k) + tile_offset(lane, 16 * w);
+#pragma unroll
+      for (int u = 0; u < 16; u += 4)
+        *reinterpret_cast<float4*>(lt + u) = make_float4(sX[lane][16 * w + u], sX[lane][16 * w + u + 1], sX[lane][16 * w + u + 2], sX[lane][16 * w + u + 3]);
+    }
+    v4f t[4];                                  // column w of blocks of L10 Y00
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int q = w; q < 4; ++q) {
+      const float* y = yb(q, w);
+      const int ld = ldy(q, w);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sX[16 * i + mm][16 * q + 4 * s + kg], y[(4 * s + kg) * ld + mm], t[i], 0, 0, 0);
+    }
+    __syncthreads();
+    {                                          // A11; rows / columns past the cluster's end behave as identity
+      const float* from = L + tile_base(c.ld, 2 * k + 1, 2 * k + 1) + tile_offset(lane, 16 * w);
+      const int valid = min(TILE, b - (2 * k + 1) * TILE);
+#pragma unroll
+      for (int u = 0; u < 16; u += 4) {
+        const v4f x = *reinterpret_cast<const v4f*>(from + u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int q = 16 * w + u + e;
+          sT[lane][q] = lane >= valid || q >= valid ? (lane == q ? 1.f : 0.f) : x[e];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int j = 0; j <= w; ++j) {             // row w of blocks of A11
+      v4f x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = sT[16 * w + 4 * kg + e][16 * j + mm];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          x = __builtin_amdgcn_mfma_f32_16x16x4f32(-sX[16 * w + mm][16 * q + 4 * s + kg], sX[16 * j + mm][16 * q + 4 * s + kg], x, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sT[16 * w + 4 * kg + e][16 * j + mm] = x[e];
+    }
+    __syncthreads();
+    if (factor_tile(sT, inv, rdiag)) bad = true;
+    {
+      const uint64_t tb = tile_base(c.ld, 2 * k + 1, 2 * k + 1);
+      store_factored(sT, inv, L + tb, Y + tb);
+    }
+    // column w of blocks of Y10 = -Y11 (L10 Y00), and its mirror image
+    float *yl = Y + tile_base(c.ld, 2 * k + 1, 2 * k), *yu = Y + tile_base(c.ld, 2 * k, 2 * k + 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v4f x = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q <= i; ++q) {
+        const float* y = yb(i, q);
+        const int ld = ldy(i, q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x = __builtin_amdgcn_mfma_f32_16x16x4f32(-y[mm * ld + 4 * kg + e], t[q][e], x, 0, 0, 0);
+      }
+      *reinterpret_cast<v4f*>(yu + tile_offset(16 * w + mm, 16 * i + 4 * kg)) = x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) yl[tile_offset(16 * i + 4 * kg + e, 16 * w + mm)] = x[e];
+    }
+  }
+  if (bad && tid == 0) atomicMin(&st->bad_cluster, ci);
+}
+
+// blocks below the diagonal: L[m,k] <- L[m,k] inv(L[k,k])^T
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, const float* G, int k, Pieces pieces,
+                   const uint32_t* __restrict__ first, int n_rows) {
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
+  int rank, item, part;
+  if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, (int)blockIdx.x, rank, item, 1u, part)) return;
+  const ClusterInfo c = cl[cl[rank].by_size];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ia = w >> 1, jb = w & 1;
+  const int m = k + 1 + item, last = (int)c.nt - 1;
+  float* L = Lf + c.koff;
+  const float* from = k == 0 ? Kd + c.koff : L;
+  v4f acc[4][4];
+  zero_block(acc);
+  // OpA = the inverse (columns of the result), OpB = the block's rows
+  block_gemm<1, true>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + w) * TILE * c.ld : from + (uint64_t)min(2 * m + w - 2, last) * TILE * c.ld,
+                      8 * k, 8 * (k + 1), 2 * k + ia, ring);
+  if (2 * m + jb > last) return;
+  float* lt = L + tile_base(c.ld, 2 * m + jb, 2 * k + ia);
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = acc[g][j];
 }
 
 // ---------------------------------------------------------------------------
 // triangular inverse, one tree level (half = tiles per child)
 // ---------------------------------------------------------------------------
-// stage 1: T = L21 * Y11, stored transposed in the mirror block (upper triangle of G)
-__global__ __launch_bounds__(256) void k_trtri_stage1(const ClusterInfo* __restrict__ cl, const float* __restrict__ Lf,
-                                                      float* __restrict__ G, int half, int per, int nc) {
-  __shared__ __attribute__((aligned(16))) float stage[2 * TILE * SP];   // operand stages, then the tile on its way to the mirror block
-  float (*sA)[SP] = reinterpret_cast<float (*)[SP]>(stage);
-  float (*sB)[SP] = reinterpret_cast<float (*)[SP]>(stage + TILE * SP);
-  float (*sT)[TILE + 1] = reinterpret_cast<float (*)[TILE + 1]>(stage);
-  int ci, item;
-  if (!die_local_item(per, nc, ci, item)) return;
-  const ClusterInfo c = cl[ci];
-  const int node = item / (half * half), within = item % (half * half);
+// T = L21 Y11 and Y21 = -Y22 T, T kept transposed in the upper triangle of L's storage, which nothing else uses, and Y21
+// written with its mirror image: the next level reads Y11 transposed, and both operands of every product are then
+// row-major strips.  Blocks of 128 x 128 (half is even, so a block's columns are whole; its second row tile may be missing).
+// STAGE 1: T^T[n][m] over the columns tn ..; longest products (small tn) first.  STAGE 2: Y21[m][n] over the columns up to
+// tm; longest (large tm) first.
+template <int STAGE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int half, Pieces pieces,
+                   const uint32_t* __restrict__ first, int n) {
+  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
+  int rank, item, part;
+  if (!list_item(pieces, first, 0u, n, (int)blockIdx.x, rank, item, 1u, part)) return;
+  const ClusterInfo c = cl[cl[rank].by_size];
+  const int hb = half / 2, node = item / (hb * hb), within = item % (hb * hb), last = (int)c.nt - 1;
   const int start = node * 2 * half, mid = start + half;
-  const int tm = mid + within / half, tn = start + within % half;
-  if (mid >= (int)c.nt || tm >= (int)c.nt) return;
-  const int tid = threadIdx.x;
-  const float* L = Lf + c.koff;
+  const int rows = min(hb, (last - mid) / 2 + 1);                 // block rows of this node
+  const int tm = mid + 2 * (STAGE == 1 ? within % rows : rows - 1 - within / hb), tn = start + 2 * (STAGE == 1 ? within / rows : within % hb);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ia = w >> 1, jb = w & 1;
+  float* L = Lf + c.koff;
   float* Y = G + c.koff;
-  v4f acc[2][2];
-  zero_acc(acc);
-  Operand oa{L, c.ld, tm * TILE, (int)c.b, 0};          // L21[m][k]
-  Operand ob{Y, c.ld, tn * TILE, (int)c.ld, 2};         // OpB[n][k] = Y11[k][n], nonzero for k >= n
-  tile_gemm<false, true>(acc, oa, ob, tn * TILE, mid * TILE, sA, sB, tid);
-  __syncthreads();                              // every wave is done reading the operand stages
-  for_each_acc(acc, tid, [&](int r, int q, float v) { sT[r][q] = v; });
-  __syncthreads();
-  // mirror block: rows = columns of T (tile tn), columns = rows of T (tile tm)
-
-  float* yt = Y + tile_base(c.ld, tn, tm);
-  for (int idx = tid; idx < TILE * TILE; idx += 256) {
-    const int q = idx >> 6, r = idx & 63;
-    yt[tile_offset(q, r)] = sT[r][q];
+  auto strip = [&](const float* base, int t) { return base + (uint64_t)min(t, last) * TILE * c.ld; };
+  v4f acc[4][4];
+  zero_block(acc);
+  if (STAGE == 1) {
+    block_gemm<2>(acc, w < 2 ? strip(Y, tn + w) : strip(L, tm + w - 2), 4 * tn, 4 * mid, tn + ia, ring);
+    if (tm + jb > last) return;
+    put_tile(acc, L + tile_base(c.ld, tn + ia, tm + jb));
+  } else {
+    block_gemm<1>(acc, w < 2 ? strip(Y, tm + w) : strip(L, tn + w - 2), 4 * mid, 4 * (min(tm + 1, last) + 1), tm + ia, ring);
+    if (tm + ia > last) return;
+    float *yl = Y + tile_base(c.ld, tm + ia, tn + jb), *yu = Y + tile_base(c.ld, tn + jb, tm + ia);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        *fragment(yl, g, j) = -acc[g][j];
+        float* to = yu + block_at_mirrored(g, j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) to[16 * i] = -acc[g][j][i];
+      }
   }
-}
-
-// stage 2: Y21 = -Y22 * T
-__global__ __launch_bounds__(256) void k_trtri_stage2(const ClusterInfo* __restrict__ cl, float* __restrict__ G,
-                                                      int half, int per, int nc) {
-  __shared__ __attribute__((aligned(16))) float sA[TILE][SP];
-  __shared__ __attribute__((aligned(16))) float sB[TILE][SP];
-  int ci, item;
-  if (!die_local_item(per, nc, ci, item)) return;
-  const ClusterInfo c = cl[ci];
-  const int node = item / (half * half), within = item % (half * half);
-  const int start = node * 2 * half, mid = start + half;
-  const int tm = mid + within / half, tn = start + within % half;
-  if (mid >= (int)c.nt || tm >= (int)c.nt) return;
-  const int tid = threadIdx.x;
-  float* Y = G + c.koff;
-  v4f acc[2][2];
-  zero_acc(acc);
-  Operand oa{Y, c.ld, tm * TILE, (int)c.b, 1};          // Y22[m][k], nonzero for k <= m
-  Operand ob{Y, c.ld, tn * TILE, (int)c.ld, 0};         // OpB[n][k] = T[k][n], read from the mirror block
-  tile_gemm<false, false>(acc, oa, ob, mid * TILE, (tm + 1) * TILE, sA, sB, tid);
-  float* yt = Y + tile_base(c.ld, tm, tn);
-  for_each_acc4(acc, tid, [&](int r, int q, const v4f& v) {
-    *reinterpret_cast<float4*>(yt + tile_offset(r, q)) = make_float4(-v[0], -v[1], -v[2], -v[3]);
-  });
 }
 
 // upper triangle <- transpose of the lower triangle (tile list of the assembly kernels)
@@ -585,13 +771,26 @@ __global__ __launch_bounds__(256) void k_compensated_blocks(const ClusterInfo* _
   }
 }
 
+// How many workgroups share the bulk of a block (k_potrf_step's parts).  The chip holds 768 workgroups, three on a compute
+// unit, which then share its matrix cores; what counts is how full the last round is.  A workgroup alone on its unit leaves
+// the matrix cores idle for three eighths of the time, two for a fifth, three for a tenth; the block of column k and both ends
+// of a workgroup cost as much as 14 steps of 16 columns.  Steps of the factorisation of 128 x 2048 points (15 - k blocks of every
+// cluster below the diagonal), one workgroup a block / three or four: k = 8 423 / 393 us, 11 239 / 311, 13 160 / 219; of 64 uneven
+// clusters of 4096 points: k = 40 351 / 252, 53 447 / 84.
+static int bulk_parts(uint64_t items, int k) {
+  int best = 1;
+  double least = 0.0;
+  for (int p = 1; p <= 8 && (p == 1 || 2 * p <= k); ++p) {
+    const uint64_t n = items * (uint64_t)p, left = (n % 768 + 255) / 256;
+    const double units = 3.3 * (double)(n / 768) + (left == 0 ? 0.0 : left == 1 ? 1.6 : left == 2 ? 2.5 : 3.3);
+    const double cost = units * (8.0 * k / p + 14.0);
+    if (p == 1 || cost < least) { best = p; least = cost; }
+  }
+  return best;
+}
+
 int launch_factor(nugpr_ctx* c, hipStream_t s) {
   const Layout& L = c->L;
-  // clusters of similar size: one die per cluster; otherwise every cluster over all dies (see die_local_item)
-  uint64_t tiles_sum = 0;
-  for (const ClusterInfo& ci : L.cl) tiles_sum += ci.nt;
-  const bool even = (uint64_t)L.ntmax * (uint64_t)L.nc * 4 <= tiles_sum * 5;
-  const int ncm = even ? L.nc : -L.nc;
   c->Lf = c->Kd2;                 // the factor goes into the spare blocks (see nugpr_ctx::lf_valid)
   c->lf_valid = true;
   // what is factored: the assembled K_ii, or (NUGPR_PRECOND_COMPENSATED) the diagonal blocks of K'' formed in the
@@ -604,23 +803,29 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     Afac = c->Kd2;
   }
   hipLaunchKernelGGL(k_reset_bad, dim3(1), dim3(1), 0, s, c->d_state);
-  for (int k = 0; k < L.ntmax; ++k) {
-    const int n_rows = L.ntmax - k - 1;         // block rows below the diagonal tile
-    const unsigned grid_diag = die_grid(1, ncm), grid_rows = n_rows > 0 ? die_grid(n_rows, ncm) : 0u;
-    hipLaunchKernelGGL(k_potrf_update, dim3(grid_diag + grid_rows), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k,
-                       n_rows, (int)grid_diag, ncm, c->d_state);
-    if (k + 1 < L.ntmax)
-      hipLaunchKernelGGL(k_potrf_trsm, dim3(die_grid(L.ntmax - k - 1, ncm)), dim3(256), 0, s, c->d_cl, c->Lf, c->G, k,
-                         L.ntmax - k - 1, ncm);
+  // (ranks are by size: the clusters with more than k block columns are the first ones)
+  const int n_blocks = (L.ntmax + 1) / 2;
+  auto with_blocks = [&](int least) {
+    return (int)(std::partition_point(L.blocks_by_rank.begin(), L.blocks_by_rank.end(), [&](uint32_t nb) { return (int)nb >= least; }) - L.blocks_by_rank.begin());
+  };
+  int parts_before = 1;
+  for (int k = 0; k < n_blocks; ++k) {
+    const int n_diag = with_blocks(k + 1), grid_diag = (n_diag + NUM_DIES - 1) / NUM_DIES * NUM_DIES, n_rows = with_blocks(k + 2);
+    const uint64_t items = L.rows_before[n_rows] - (uint64_t)n_rows * (uint64_t)(k + 1);
+    const int parts = items ? bulk_parts(items, k) : 1;
+    Pieces pr, ps;
+    for (int d = 0; d <= NUM_DIES; ++d) { pr.from[d] = (uint32_t)(items * parts * d / NUM_DIES); ps.from[d] = (uint32_t)(items * d / NUM_DIES); }
+    hipLaunchKernelGGL(k_potrf_step, dim3((unsigned)grid_diag + (k > 0 ? pr.grid() : 0u)), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k,
+                       n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, c->d_state);
+    if (items) hipLaunchKernelGGL(k_potrf_solve, dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+    parts_before = parts;
   }
-  for (int half = 1; half < L.ntmax; half *= 2) {
-    const int nodes = (L.ntmax + 2 * half - 1) / (2 * half);
-    const int per = half * half * nodes;
-    dim3 grid(die_grid(per, ncm));
-    hipLaunchKernelGGL(k_trtri_stage1, grid, dim3(256), 0, s, c->d_cl, c->Lf, c->G, half, per, ncm);
-    hipLaunchKernelGGL(k_trtri_stage2, grid, dim3(256), 0, s, c->d_cl, c->G, half, per, ncm);
+  for (const TreeLevel& t : L.tree) {
+    Pieces p1, p2;
+    for (int d = 0; d <= NUM_DIES; ++d) { p1.from[d] = t.from1[d]; p2.from[d] = t.from2[d]; }
+    hipLaunchKernelGGL((k_trtri_block<1>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, c->d_rows_before + t.at, t.ranks);
+    hipLaunchKernelGGL((k_trtri_block<2>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, c->d_rows_before + t.at, t.ranks);
   }
-  hipLaunchKernelGGL(k_mirror, dim3((unsigned)L.n_diag_tiles), dim3(256), 0, s, c->d_cl, c->d_tiles, c->G);
   hipLaunchKernelGGL(k_logdet, dim3(L.nc), dim3(256), 0, s, c->d_cl, c->G, c->d_logdet);
   NUGPR_HIP(hipGetLastError());
   // right-hand sides B = [y | L Z]

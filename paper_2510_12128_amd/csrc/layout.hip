@@ -26,6 +26,60 @@ static size_t take(size_t& cursor, size_t bytes) {
   return at;
 }
 
+// Work lists of the factorisation (factor.hip).  A cluster of nt tiles has ceil(nt / 2) block columns.  A node of the tree
+// inverse with children of `half` tiles takes (half / 2) x (block rows of its second child) workgroups in either product; in
+// the first one a workgroup's contraction is as long as the first child on average half over, in the second one as the second.
+static void plan_factor(Layout& L) {
+  L.blocks_by_rank.clear();
+  L.tree.clear();
+  L.rows_before.assign(1, 0u);
+  for (int i = 0; i < L.nc; ++i) {
+    const uint32_t nb = (L.cl[L.cl[i].by_size].nt + 1) / 2;
+    L.blocks_by_rank.push_back(nb);
+    L.rows_before.push_back(L.rows_before.back() + nb);
+  }
+  for (int half = 2; half < L.ntmax; half *= 2) {
+    TreeLevel t;
+    t.half = half;
+    t.at = (uint32_t)L.rows_before.size();
+    const uint32_t hb = (uint32_t)half / 2;
+    std::vector<double> work1(1, 0.0), work2(1, 0.0);
+    uint32_t before = 0;
+    L.rows_before.push_back(0u);
+    for (int i = 0; i < L.nc; ++i) {
+      const uint32_t nt = L.cl[L.cl[i].by_size].nt;
+      if (nt <= (uint32_t)half) break;
+      uint32_t count = 0;
+      double w1 = 0.0, w2 = 0.0;
+      for (uint32_t mid = (uint32_t)half; mid < nt; mid += 2 * (uint32_t)half) {
+        const uint32_t rows = std::min(hb, (nt - mid + 1) / 2);
+        count += hb * rows;
+        w1 += (double)hb * rows * (half + 2);
+        w2 += (double)hb * rows * (2 * rows + 2);
+      }
+      before += count;
+      L.rows_before.push_back(before);
+      work1.push_back(work1.back() + w1);
+      work2.push_back(work2.back() + w2);
+      t.ranks += 1;
+    }
+    // cut the list where the work of both products is an eighth each, a cluster's work spread evenly over its workgroups
+    auto cut = [&](const std::vector<double>& work, uint32_t (&from)[9]) {
+      for (int d = 0; d <= 8; ++d) {
+        const double goal = work.back() * d / 8;
+        int i = 0;
+        while (i + 1 < t.ranks && work[i + 1] <= goal) ++i;
+        const double part = (goal - work[i]) / (work[i + 1] - work[i]);
+        const uint32_t lo = L.rows_before[t.at + i], hi = L.rows_before[t.at + i + 1];
+        from[d] = d == 8 ? before : lo + (uint32_t)(std::min(1.0, part) * (hi - lo));
+      }
+    };
+    cut(work1, t.from1);
+    cut(work2, t.from2);
+    L.tree.push_back(t);
+  }
+}
+
 int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   if (!pb || !pb->cluster_offsets) { set_error("null problem or cluster_offsets"); return NUGPR_ERR_INVALID; }
   if (pb->n <= 0 || pb->n > (int64_t)0x7fff0000) { set_error("n out of range"); return NUGPR_ERR_INVALID; }
@@ -59,12 +113,18 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
     c.koff = koff;
     c.wtoff = wtoff;
     c.prow = (uint32_t)prow;
-    c.pad_ = 0;
     prow += c.ld;
     koff += (uint64_t)c.ld * c.ld;
     wtoff += (uint64_t)L.r * c.ld;
     L.ntmax = std::max<int>(L.ntmax, (int)c.nt);
     L.n_diag_tiles += (uint64_t)c.nt * (c.nt + 1) / 2;
+  }
+  {
+    std::vector<uint32_t> order(L.nc);
+    for (int i = 0; i < L.nc; ++i) order[i] = (uint32_t)i;
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return L.cl[a].b > L.cl[b].b; });
+    for (int i = 0; i < L.nc; ++i) L.cl[i].by_size = order[i];
+    plan_factor(L);
   }
   L.kd_elems = koff;
   L.rows_pad = prow;
@@ -119,6 +179,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_assign = take(cur, (size_t)L.n * sizeof(int32_t));
   L.o_rep_ptr = take(cur, ((size_t)L.ncr + 1) * sizeof(int32_t));
   L.o_rep_pts = take(cur, (size_t)L.n * sizeof(int32_t));
+  L.o_rows_before = take(cur, L.rows_before.size() * sizeof(uint32_t));
   L.o_B = take(cur, vec);
   L.o_X = take(cur, vec);
   L.o_R = take(cur, vec);

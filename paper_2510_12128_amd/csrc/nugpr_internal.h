@@ -33,7 +33,7 @@ struct ClusterInfo {
   uint32_t ld;      // leading dimension of its square blocks: b rounded up to 64
   uint32_t nt;      // number of 64-wide tiles per side: ld / 64
   uint32_t prow;    // first row of the cluster in the padded row numbering (sum of ld of the clusters before it)
-  uint32_t pad_;
+  uint32_t by_size; // (no property of this cluster:) index of the cluster that comes at this place when the largest come first
 };
 
 // Work item of the block assembly: tile (tr, tc0) of the lower triangle of one square symmetric
@@ -146,6 +146,15 @@ struct HostFlags {
   uint64_t tail_seq;   // the end-of-solve record in the pinned buffer belongs to report number `tail_seq`
 };
 
+// One level of the tree inverse (factor.hip): children of `half` tiles.  The clusters that have a node at this level are the
+// first `ranks` by size; the numbers of workgroups before each of them start at element `at` of the device list, and the
+// pieces of the work that the dies take in the two products are cut at from1 / from2.
+struct TreeLevel {
+  int half = 0, ranks = 0;
+  uint32_t at = 0;
+  uint32_t from1[9] = {}, from2[9] = {};
+};
+
 struct Layout {
   // geometry
   int64_t n = 0;
@@ -155,6 +164,10 @@ struct Layout {
   int nsS = 1, nsP = 1;
   bool compensate = false;    // SPD compensation: full coupling matrix minus lambda_0 I, with an fp32 residual matrix
   std::vector<ClusterInfo> cl;
+  // factorisation: block columns (two tiles each) of the clusters in the order of their size, and their running sum;
+  // then, in rows_before, the running sums of the tree levels
+  std::vector<uint32_t> blocks_by_rank, rows_before;
+  std::vector<TreeLevel> tree;
   uint64_t kd_elems = 0, wt_elems = 0;
   uint64_t rows_pad = 0;      // sum of ld over the clusters
   // byte offsets into the workspace
@@ -166,7 +179,7 @@ struct Layout {
   size_t o_theta = 0, o_logdet = 0, o_tiles = 0, o_items = 0;
   size_t o_Xs = 0, o_Xn = 0, o_Rs = 0, o_Rn = 0;
   size_t o_x0 = 0, o_Z0 = 0, o_P = 0, o_Clo = 0, o_S0 = 0, o_dav = 0;
-  size_t o_assign = 0, o_rep_ptr = 0, o_rep_pts = 0;
+  size_t o_assign = 0, o_rep_ptr = 0, o_rep_pts = 0, o_rows_before = 0;
   size_t items_bytes = 0;
   int n_dot_blocks = 0;
   int max_iter = 0;
@@ -215,6 +228,7 @@ struct nugpr_ctx {
   bool acc64 = true;                     // arithmetic mode of the operator applications
   double *dotpart = nullptr, *alog = nullptr, *blog = nullptr, *d_theta = nullptr, *d_logdet = nullptr;
   nugpr::PcgState* d_state = nullptr;
+  uint32_t* d_rows_before = nullptr; // Layout::rows_before
   uint64_t* d_tiles = nullptr;       // packed (cluster, tile row, tile col) list of the diagonal blocks
   nugpr::BuildItem* d_pan_diag = nullptr;    // work items of the K_ii assembly
   nugpr::BuildItem* d_pan_c = nullptr;       // work items of the coupling assembly

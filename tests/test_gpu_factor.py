@@ -1,0 +1,50 @@
+"""The factorisation at the edges of its tiles (64), blocks (128), tree levels and shared sums, against float64 on the exported
+matrices: backward error of L, residual of the stored inverse, log det."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SIZES = {
+    "one-tile": [64, 1, 63],
+    "around-a-block": [65, 127, 128, 129, 191, 192, 193],
+    "around-a-level": [256, 257, 320, 385, 513, 575],
+    # few block rows and many columns: the sums of a block are shared by several workgroups
+    "one-long": [2113],
+    "long-and-short": [1665, 70, 1024, 3, 1471],
+    "uneven-many": [64 * (1 + k % 7) + k for k in range(70)],          # more clusters than lanes look at in one go
+}
+
+
+@pytest.mark.parametrize("name", list(SIZES))
+def test_factor_and_inverse_at_block_edges(lib, name):
+    import torch
+    from paper_2510_12128_amd import binding as B
+    sizes = SIZES[name]
+    n, d = sum(sizes), 3
+    rng = np.random.default_rng(5)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    ctx = lib.Context(X, rng.standard_normal(n).astype(np.float32), off, 2.0 * rng.integers(0, 2, (n, 2)) - 1.0, 1)
+    for theta in (np.array([2.0, 1.4, 0.8, 2.1, 0.3]), np.array([1.2, 0.9, 1.5, 1.3, 0.2])):      # the second time over what the first left
+        ctx.nugpr_build_blocks(theta)
+        code, logdet, bad = ctx.nugpr_precond_factor()
+        assert code == 0 and bad == -1
+        want = 0.0
+        for i, b in enumerate(sizes):
+            K = ctx.nugpr_export(B.EXPORT_K, i).double()
+            L = ctx.nugpr_export(B.EXPORT_L, i).double()
+            Y = ctx.nugpr_export(B.EXPORT_LINV, i).double()
+            # element-wise backward error of a Cholesky factorisation of order b: (b + 1) u |L| |L|^T, u = 2^-24; what goes
+            # through a block's explicit inverse also meets the condition number of the block's factor, at these theta at most
+            # sqrt(1 + 128 alpha / sigma^2) = 31, in both of its uses: 64 u
+            u = 2.0 ** -24
+            err = (L @ L.T - K).abs() / (L.abs() @ L.abs().T)
+            assert float(err.max()) <= (b + 1 + 64) * u, (name, i, float(err.max()) / u)
+            # residual of an inverse by blocks, likewise relative to |Y| |L|
+            res = (Y @ L - torch.eye(b, device=L.device, dtype=L.dtype)).abs() / (Y.abs() @ L.abs()).clamp_min(1.0)
+            assert float(res.max()) <= (b + 1 + 64) * u, (name, i, float(res.max()) / u)
+            assert float(L.triu(1).abs().max()) == 0.0 and float(Y.triu(1).abs().max()) == 0.0
+            want -= 2.0 * float(torch.log(Y.diagonal()).sum())
+        assert abs(logdet - want) <= 1e-12 * n + 1e-10 * abs(want)
+    ctx.close()
