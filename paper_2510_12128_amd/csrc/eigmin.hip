@@ -16,7 +16,7 @@
 //   t = T res with T = blockdiag(B_k + mu I)^-1, B_k the 128 x 128 diagonal blocks of C recomputed in fp64
 //       from the representatives and Cholesky-factored once per assembly (mu = 1e-10 alpha);
 //   t is orthogonalised against V (Gram-Schmidt, twice), normalised and appended; C t is computed.
-// All vector work of a step runs in single workgroups with fixed-order reductions, so lambda_0 is reproducible
+// All sums of a step are taken in a fixed order, so lambda_0 is reproducible
 // to the bit.  Stop: the Ritz value theta is safe when min(|res|, 4 |res|^2 / gap) <= tol (gap: distance to the
 // second Ritz value, used when it is clearly separate), or when |theta| <= tol: a kernel matrix is positive
 // semi-definite, so lambda_min lies in [0, theta].  Ritz values approach lambda_min from above, so
@@ -112,39 +112,6 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factor(BlockKernelArgs a, 
   }
 }
 
-// t = blockdiag(Y_k^T Y_k) res with Y_k = L_k^-1: two triangular products per block, one workgroup per block.
-// Rows by waves (shuffles), then columns by threads: 72 us as two substitutions, 9.5 us now (2048 representatives).
-__global__ __launch_bounds__(1024) void k_block_solve(const double* __restrict__ Yall, const double* __restrict__ res,
-                                                      double* __restrict__ t, int n) {
-  __shared__ double x[EB], z[EB], part_sum[1024];
-  const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int i0 = blk * EB;
-  const int nb = min(EB, n - i0);
-  const double* Y = Yall + (uint64_t)blk * EB * EB;
-  if (tid < EB) x[tid] = tid < nb ? res[i0 + tid] : 0.0;
-  __syncthreads();
-  const double x0 = x[lane], x1 = x[lane + 64];
-#pragma unroll
-  for (int q = 0; q < EB / 16; ++q) {                 // rows wave, wave + 16, ..
-    const int i = wave + 16 * q;
-    double s = fma(Y[i * EB + lane], x0, Y[i * EB + lane + 64] * x1);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if (lane == 0) z[i] = s;
-  }
-  __syncthreads();
-  const int col = tid & (EB - 1), part = tid >> 7;
-  double s = 0.0;
-#pragma unroll
-  for (int q = 0; q < EB / 8; ++q) s = fma(Y[(part + 8 * q) * EB + col], z[part + 8 * q], s);
-  part_sum[tid] = s;
-  __syncthreads();
-  if (tid < nb) {
-    for (int q = 1; q < 8; ++q) s += part_sum[tid + q * EB];
-    t[i0 + tid] = s;
-  }
-}
-
 // v_0: a fixed +-1 pattern (integer hash of the index), normalised
 __global__ void k_eig_start(double* __restrict__ v, int n) {
   const double s = 1.0 / sqrt((double)n);
@@ -155,120 +122,184 @@ __global__ void k_eig_start(double* __restrict__ v, int n) {
   }
 }
 
-__device__ __forceinline__ double block_sum_1024(double x, double* red) {
-  const int tid = threadIdx.x;
-  red[tid] = x;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  const double r = red[0];
-  __syncthreads();
-  return r;
-}
-
 struct Coef { double y[DAV_MAX_BASIS]; };
 
-// out[k] = <V[k], w>, k = 0 .. m - 1, for all k in one pass: shuffles inside each wave, then the 16 wave totals through
-// LDS in a fixed order (one vector after the other, ten barriers each: the orthogonalisation took 56 us a step instead of 33, the
-// new row 30 instead of 24)
-__device__ __forceinline__ void block_dots(const double* V, const double* w, int m, int n, int ld,
-                                           double (*part)[16], double* out) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double acc[DAV_MAX_BASIS];
+// The vector work of a step.  One workgroup per block of 128 rows (the preconditioner's blocks), eight threads a row; sums
+// over all rows are left as one partial sum per workgroup and added up, in a fixed order, by every workgroup of the kernel
+// that needs them.  (In single workgroups, each kernel alone on one compute unit, a step of 2048 rows took 33 us for the
+// orthogonalisation, 25 for the new row, 9 + 9 for residual and correction.)
+__device__ __forceinline__ double wave_total(double s) {
 #pragma unroll
-  for (int k = 0; k < DAV_MAX_BASIS; ++k) acc[k] = 0.0;
-  for (int i = tid; i < n; i += 1024) {
-    const double wi = w[i];
-#pragma unroll
-    for (int k = 0; k < DAV_MAX_BASIS; ++k)
-      if (k < m) acc[k] = fma(V[(uint64_t)k * ld + i], wi, acc[k]);
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  return s;                                           // (lane 0)
+}
+// partial[k][workgroup] = <V[k], x> over this workgroup's rows, k < m (x in LDS, zero past the end; a wave takes every 16th k)
+__device__ __forceinline__ void row_dots(const double* __restrict__ V, const double* x, int m, int i0, int nb, int ld, double* __restrict__ partial) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int k = wave; k < m; k += 16) {
+    const double* v = V + (uint64_t)k * ld + i0;
+    double s = lane < nb ? v[lane] * x[lane] : 0.0;
+    if (lane + 64 < nb) s = fma(v[lane + 64], x[lane + 64], s);
+    s = wave_total(s);
+    if (lane == 0) partial[(uint64_t)k * gridDim.x + blockIdx.x] = s;
   }
-#pragma unroll
-  for (int k = 0; k < DAV_MAX_BASIS; ++k)
-    if (k < m) {
-      double s = acc[k];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-      if (lane == 0) part[k][wave] = s;
-    }
-  __syncthreads();
-  if (tid < m) {
-    double s = part[tid][0];
-    for (int q = 1; q < 16; ++q) s += part[tid][q];
-    out[tid] = s;
+}
+// h[k] = the sum of partial[k][..], k < m, in LDS (complete after the next barrier)
+__device__ __forceinline__ void add_partials(const double* __restrict__ partial, int m, int nblk, double* h) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int k = wave; k < m; k += 16) {
+    double s = 0.0;
+    for (int q = lane; q < nblk; q += 64) s += partial[(uint64_t)k * nblk + q];
+    s = wave_total(s);
+    if (lane == 0) h[k] = s;
   }
-  __syncthreads();
 }
 
-// AV[m] = sum of the column-slab partial sums of C V[m]; h[i] = <V[i], AV[m]>, i = 0 .. m
-__global__ __launch_bounds__(1024) void k_eig_newrow(const double* __restrict__ parts, int nparts, uint64_t stride,
-                                                     const double* __restrict__ V, double* __restrict__ AV, int m,
-                                                     int n, int ld, double* __restrict__ out) {
-  __shared__ double part[DAV_MAX_BASIS][16];
-  __shared__ double h[DAV_MAX_BASIS];
-  const int tid = threadIdx.x;
-  double* av = AV + (uint64_t)m * ld;
-  for (int i = tid; i < n; i += 1024) {
-    double w = parts[i];
-    for (int p = 1; p < nparts; ++p) w += parts[(uint64_t)p * stride + i];
-    av[i] = w;
-  }
-  __syncthreads();
-  block_dots(V, av, m + 1, n, ld, part, h);
-  if (tid <= m) out[tid] = h[tid];
-}
-
-// x = V y, res = AV y - theta x (m vectors); out[0] = |res|^2.  x is not kept: only the residual is needed.
-__global__ __launch_bounds__(1024) void k_eig_residual(const double* __restrict__ V, const double* __restrict__ AV,
-                                                       Coef c, double theta, int m, int n, int ld,
-                                                       double* __restrict__ res, double* __restrict__ out) {
-  __shared__ double red[1024];
-  const int tid = threadIdx.x;
-  double acc = 0.0;
-  for (int i = tid; i < n; i += 1024) {
-    double x = 0.0, ax = 0.0;
-    for (int k = 0; k < m; ++k) {
-      x = fma(c.y[k], V[(uint64_t)k * ld + i], x);
-      ax = fma(c.y[k], AV[(uint64_t)k * ld + i], ax);
+// res = AV y - theta V y;  t = blockdiag(Y_k^T Y_k) res with Y_k = L_k^-1, two triangular products per block: rows by waves
+// (shuffles), then columns by threads.  Partial sums of |res|^2 and of <V[k], t>.
+__global__ __launch_bounds__(1024) void k_eig_correct(const double* __restrict__ V, const double* __restrict__ AV, Coef c, double theta, int m,
+                                                      int n, int ld, const double* __restrict__ Yall, double* __restrict__ t,
+                                                      double* __restrict__ res2, double* __restrict__ dots) {
+  __shared__ double x[EB], z[EB], sums[1024], two[2];
+  const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row = tid & (EB - 1), part = tid >> 7;
+  const int i0 = blk * EB, nb = min(EB, n - i0);
+  double s = 0.0;
+  if (row < nb)
+    for (int k = part; k < m; k += 8) {
+      const uint64_t at = (uint64_t)k * ld + i0 + row;
+      s = fma(c.y[k], fma(-theta, V[at], AV[at]), s);
     }
-    const double r = fma(-theta, x, ax);
-    res[i] = r;
-    acc = fma(r, r, acc);
-  }
-  const double s = block_sum_1024(acc, red);
-  if (tid == 0) out[0] = s;
-}
-
-// V[m] = t orthogonalised against V[0 .. m-1] (classical Gram-Schmidt, two passes: orthogonal to rounding, as the
-// modified form, and all coefficients of a pass at once) and normalised; out[0] = its norm before the normalisation
-__global__ __launch_bounds__(1024) void k_eig_orth(double* V, const double* __restrict__ t, int m, int n,
-                                                   int ld, double* __restrict__ out) {
-  __shared__ double red[1024];
-  __shared__ double part[DAV_MAX_BASIS][16];
-  __shared__ double h[DAV_MAX_BASIS];
-  const int tid = threadIdx.x;
-  double* vn = V + (uint64_t)m * ld;
-  for (int i = tid; i < n; i += 1024) vn[i] = t[i];
+  sums[tid] = s;
   __syncthreads();
-  double acc = 0.0;
-  for (int pass = 0; pass < 2; ++pass) {
-    block_dots(V, vn, m, n, ld, part, h);
-    for (int i = tid; i < n; i += 1024) {
-      double v = vn[i];
+  if (tid < EB) {
+    for (int q = 1; q < 8; ++q) s += sums[tid + q * EB];
+    x[tid] = s;
+    const double r2 = wave_total(s * s);
+    if (lane == 0) two[wave] = r2;
+  }
+  __syncthreads();
+  if (tid == 0) res2[blk] = two[0] + two[1];
+  const double* Y = Yall + (uint64_t)blk * EB * EB;
+  const double x0 = x[lane], x1 = x[lane + 64];
 #pragma unroll
-      for (int k = 0; k < DAV_MAX_BASIS; ++k)
-        if (k < m) v = fma(-h[k], V[(uint64_t)k * ld + i], v);
-      vn[i] = v;
-      if (pass == 1) acc = fma(v, v, acc);
+  for (int q = 0; q < EB / 16; ++q) {                 // rows wave, wave + 16, ..
+    const int i = wave + 16 * q;
+    const double v = wave_total(fma(Y[i * EB + lane], x0, Y[i * EB + lane + 64] * x1));
+    if (lane == 0) z[i] = v;
+  }
+  __syncthreads();
+  s = 0.0;
+#pragma unroll
+  for (int q = 0; q < EB / 8; ++q) s = fma(Y[(part + 8 * q) * EB + row], z[part + 8 * q], s);
+  sums[tid] = s;
+  __syncthreads();
+  if (tid < EB) {
+    for (int q = 1; q < 8; ++q) s += sums[tid + q * EB];
+    x[tid] = tid < nb ? s : 0.0;
+    if (tid < nb) t[i0 + tid] = s;
+  }
+  __syncthreads();
+  row_dots(V, x, m, i0, nb, ld, dots);
+}
+
+// One pass of classical Gram-Schmidt, all coefficients at once: t <- t - sum h_k V[k], h_k the sums of dots_in.  Two passes are
+// orthogonal to rounding, as the modified form.  The first leaves the partial sums of <V[k], t>; the second (LAST) writes t as
+// V[m], not yet normalised, and leaves the partial sums of |t|^2.
+template <bool LAST>
+__global__ __launch_bounds__(1024) void k_eig_orth(double* V, double* t, int m, int n, int ld, const double* __restrict__ dots_in,
+                                                   double* __restrict__ dots_out) {
+  __shared__ double x[EB], sums[1024], h[DAV_MAX_BASIS], two[2];
+  const int tid = threadIdx.x, lane = tid & 63, row = tid & (EB - 1), part = tid >> 7;
+  const int i0 = (int)blockIdx.x * EB, nb = min(EB, n - i0);
+  double v[DAV_MAX_BASIS / 8];
+#pragma unroll
+  for (int q = 0; q < DAV_MAX_BASIS / 8; ++q) v[q] = row < nb && part + 8 * q < m ? V[(uint64_t)(part + 8 * q) * ld + i0 + row] : 0.0;
+  add_partials(dots_in, m, (int)gridDim.x, h);
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < DAV_MAX_BASIS / 8; ++q)
+    if (part + 8 * q < m) s = fma(h[part + 8 * q], v[q], s);
+  sums[tid] = s;
+  __syncthreads();
+  if (tid < EB) {
+    for (int q = 1; q < 8; ++q) s += sums[tid + q * EB];
+    const double r = tid < nb ? t[i0 + tid] - s : 0.0;
+    x[tid] = r;
+    if (tid < nb) (LAST ? V + (uint64_t)m * ld : t)[i0 + tid] = r;
+    if (LAST) {
+      const double r2 = wave_total(r * r);
+      if (lane == 0) two[tid >> 6] = r2;
     }
+  }
+  __syncthreads();
+  if (LAST) {
+    if (tid == 0) dots_out[blockIdx.x] = two[0] + two[1];
+  } else {
+    row_dots(V, x, m, i0, nb, ld, dots_out);
+  }
+}
+
+// V[m] <- V[m] / |V[m]| (norm2: partial sums of the square; null: it is normalised), AV[m] = the sum of the column-slab partial sums of C V[m]
+// over the same norm.  The workgroup that finishes last adds up what the host waits for, into pinned memory: out[0] = |res|^2
+// (from res2, may be null), out[1] = the norm, out[8 + k] = <V[k], AV[m]>, k <= m; then, behind a system-scope fence, the
+// sequence number.
+__global__ __launch_bounds__(1024) void k_eig_newrow(const double* __restrict__ parts, int nparts, uint64_t stride, double* V,
+                                                     double* __restrict__ AV, int m, int n, int ld, const double* __restrict__ norm2,
+                                                     const double* __restrict__ res2, double* dots, double* __restrict__ out,
+                                                     PcgState* __restrict__ st, HostFlags* __restrict__ flags, uint64_t seq) {
+  __shared__ double x[EB], vm[EB], sums[1024], h[DAV_MAX_BASIS + 2];
+  __shared__ int last;
+  const int tid = threadIdx.x, row = tid & (EB - 1), part = tid >> 7, nblk = (int)gridDim.x;
+  const int i0 = (int)blockIdx.x * EB, nb = min(EB, n - i0);
+  double s = 0.0;
+  if (row < nb)
+    for (int p = part; p < nparts; p += 8) s += parts[(uint64_t)p * stride + i0 + row];
+  sums[tid] = s;
+  if (norm2) add_partials(norm2, 1, nblk, h);
+  __syncthreads();
+  const double nrm = norm2 ? sqrt(h[0]) : 1.0, inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+  if (tid < EB) {
+    for (int q = 1; q < 8; ++q) s += sums[tid + q * EB];
+    x[tid] = s * inv;
+    vm[tid] = 0.0;
+    if (tid < nb) {
+      AV[(uint64_t)m * ld + i0 + tid] = s * inv;
+      vm[tid] = V[(uint64_t)m * ld + i0 + tid] * inv;
+      V[(uint64_t)m * ld + i0 + tid] = vm[tid];
+    }
+  }
+  __syncthreads();
+  row_dots(V, x, m, i0, nb, ld, dots);
+  if (tid < 64) {                                     // <V[m], AV[m]>, from this workgroup's own copy
+    const double d = wave_total(fma(vm[tid], x[tid], vm[tid + 64] * x[tid + 64]));
+    if (tid == 0) dots[(uint64_t)m * nblk + blockIdx.x] = d;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    __threadfence();
+    last = atomicAdd(&st->check_count, 1) == nblk - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  add_partials(dots, m + 1, nblk, h);
+  __syncthreads();
+  if (tid <= m) out[8 + tid] = h[tid];
+  if (res2) {
     __syncthreads();
+    add_partials(res2, 1, nblk, h);
+    __syncthreads();
+    if (tid == 0) out[0] = h[0];
   }
-  const double nrm = sqrt(block_sum_1024(acc, red));
-  const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-  for (int i = tid; i < n; i += 1024) vn[i] *= inv;
-  if (tid == 0) out[0] = nrm;
+  if (tid == 0) {
+    out[1] = nrm;
+    st->check_count = 0;
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (tid == 0) *reinterpret_cast<volatile uint64_t*>(&flags->seq) = seq;
 }
 
 // restart: V <- V Y, AV <- AV Y for the `keep` coefficient columns in c (column q at y[q * m ..]); element-wise, in place
@@ -353,9 +384,103 @@ static void small_sym_eigen(std::vector<double>& A, int m, std::vector<double>& 
   Y.swap(Ys);
 }
 
+// The two lowest eigenvalues and the eigenvector y of the lowest one, for the steps that need no more: Householder reduction
+// to tridiagonal form, eigenvalues by the QL iteration, the vector by inverse iteration there (Gaussian elimination with
+// row exchanges) and back.  H: m x m, row stride DAV_MAX_BASIS.  At 24 x 24 39 us; all eigenvectors by Jacobi rotations 220.
+static int lowest_eigenpair(const std::vector<double>& H, int m, double& e0, double& e1, double* y) {
+  constexpr int S = DAV_MAX_BASIS;
+  y[0] = 1.0;
+  e0 = H[0];
+  e1 = INFINITY;
+  if (m == 1) return 0;
+  double A[S][S], beta[S] = {};
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < m; ++j) A[i][j] = H[(size_t)i * S + j];
+  std::vector<double> d(m), e(m, 0.0), z;
+  for (int k = 0; k + 2 < m; ++k) {                   // the reflector's vector stays in row k
+    double norm2 = 0.0, tail = 0.0;
+    for (int i = k + 1; i < m; ++i) norm2 += A[k][i] * A[k][i];
+    for (int i = k + 2; i < m; ++i) tail += std::fabs(A[k][i]);
+    if (tail == 0.0) { e[k] = A[k][k + 1]; continue; }
+    const double a = A[k][k + 1] > 0.0 ? -std::sqrt(norm2) : std::sqrt(norm2);
+    e[k] = a;
+    A[k][k + 1] -= a;
+    beta[k] = -1.0 / (a * A[k][k + 1]);               // 2 / |v|^2
+    double p[S], pv = 0.0;
+    for (int i = k + 1; i < m; ++i) {
+      double s = 0.0;
+      for (int j = k + 1; j < m; ++j) s += A[i][j] * A[k][j];
+      p[i] = beta[k] * s;
+      pv += p[i] * A[k][i];
+    }
+    for (int i = k + 1; i < m; ++i) p[i] -= 0.5 * beta[k] * pv * A[k][i];
+    for (int i = k + 1; i < m; ++i)
+      for (int j = k + 1; j < m; ++j) A[i][j] -= A[k][i] * p[j] + p[i] * A[k][j];
+  }
+  e[m - 2] = A[m - 2][m - 1];
+  for (int i = 0; i < m; ++i) d[i] = A[i][i];
+  std::vector<double> ev = d, off = e;
+  if (tridiag_eigen_first_row(ev, off, z)) return 1;
+  std::nth_element(ev.begin(), ev.begin() + 1, ev.end());
+  e0 = ev[0];
+  e1 = ev[1];
+  double scale = 0.0;
+  for (int i = 0; i < m; ++i) scale = std::max(scale, std::fabs(d[i]) + std::fabs(e[i]));
+  const double tiny = std::max(2.3e-16 * scale, 1e-300);
+  // T - e0 I = P^T L U: diagonal u0, first and second upper diagonals u1, u2
+  double u0[S], u1[S] = {}, u2[S] = {}, mult[S] = {};
+  bool swapped[S] = {};
+  double p0 = d[0] - e0, p1 = e[0];
+  for (int i = 0; i + 1 < m; ++i) {
+    const double l = e[i], q0 = d[i + 1] - e0, q1 = i + 2 < m ? e[i + 1] : 0.0;
+    if (std::fabs(l) > std::fabs(p0)) {
+      swapped[i] = true;
+      mult[i] = p0 / l;
+      u0[i] = l; u1[i] = q0; u2[i] = q1;
+      p0 = p1 - mult[i] * q0;
+      p1 = -mult[i] * q1;
+    } else {
+      if (std::fabs(p0) < tiny) p0 = tiny;
+      mult[i] = l / p0;
+      u0[i] = p0; u1[i] = p1;
+      p0 = q0 - mult[i] * p1;
+      p1 = q1;
+    }
+  }
+  u0[m - 1] = std::fabs(p0) < tiny ? tiny : p0;
+  for (int i = 0; i < m; ++i) y[i] = 1.0 + 0.01 * i;
+  for (int it = 0; it < 3; ++it) {
+    for (int i = 0; i + 1 < m; ++i) {
+      if (swapped[i]) std::swap(y[i], y[i + 1]);
+      y[i + 1] -= mult[i] * y[i];
+    }
+    double norm = 0.0;
+    for (int i = m - 1; i >= 0; --i) {
+      double s = y[i];
+      if (i + 1 < m) s -= u1[i] * y[i + 1];
+      if (i + 2 < m) s -= u2[i] * y[i + 2];
+      y[i] = s / u0[i];
+      norm = std::max(norm, std::fabs(y[i]));
+    }
+    if (!(norm > 0.0) || !std::isfinite(norm)) return 1;
+    double sq = 0.0;
+    for (int i = 0; i < m; ++i) { y[i] /= norm; sq += y[i] * y[i]; }
+    sq = 1.0 / std::sqrt(sq);
+    for (int i = 0; i < m; ++i) y[i] *= sq;
+  }
+  for (int k = m - 3; k >= 0; --k) {
+    if (beta[k] == 0.0) continue;
+    double s = 0.0;
+    for (int i = k + 1; i < m; ++i) s += A[k][i] * y[i];
+    s *= beta[k];
+    for (int i = k + 1; i < m; ++i) y[i] -= s * A[k][i];
+  }
+  return 0;
+}
+
 // lambda_min of the matrix whose off-diagonal part is stored in (c->C, c->Clo) (diagonal entries of both zero)
 // and whose diagonal is the scalar alpha = theta[p - 2].  Scratch: the partial-sum slabs of the coupling product
-// and the Davidson area of the workspace.  Synchronises the stream once per step.
+// and the Davidson area of the workspace.  The host waits for the device once per step.
 int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double* lambda_out, int* steps_out) {
   const Layout& L = c->L;
   const int n = L.ncr, ld = L.ldc;
@@ -363,8 +488,11 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
   const bool iso = (c->params.flags & NUGPR_ISOTROPIC) != 0;
   const double alpha = theta[L.p - 2];
   const int nblk = (n + EB - 1) / EB;
-  double *V = c->dav, *AV = V + (size_t)DAV_MAX_BASIS * ld, *res = AV + (size_t)DAV_MAX_BASIS * ld, *tvec = res + ld,
-         *small = tvec + ld, *Lblk = small + 64;
+  // (the partial sums: two sets of DAV_MAX_BASIS and one of DAV_MAX_BASIS + 1 dot products, two of squares, a value per
+  // block of 128 rows: at most n doubles, as n is larger than COMPENSATE_HOST_MAX)
+  double *V = c->dav, *AV = V + (size_t)DAV_MAX_BASIS * ld, *sums = AV + (size_t)DAV_MAX_BASIS * ld, *tvec = sums + ld, *Lblk = tvec + ld + 64;
+  static_assert((COMPENSATE_HOST_MAX + EB) / EB * (3 * DAV_MAX_BASIS + 3) <= COMPENSATE_HOST_MAX, "room for the partial sums");
+  double *res2 = sums, *norm2 = res2 + nblk, *dots1 = norm2 + nblk, *dots2 = dots1 + DAV_MAX_BASIS * nblk, *dots3 = dots2 + DAV_MAX_BASIS * nblk;
   constexpr int factor_lds = (EB * EBP + EB) * (int)sizeof(double);
   static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_block_factor),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, factor_lds);
@@ -388,11 +516,11 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
     StripPort q = p;
     q.A = c->Clo; q.accumulate = 1; q.diag_add = 0.0;
     if ((rc = launch_strip(c->tab_C, q, q, 1, true, s))) return rc;
-    hipLaunchKernelGGL(k_eig_newrow, dim3(1), dim3(1024), 0, s, (const double*)parts, L.nsP, stride, (const double*)V, AV, m, n,
-                       ld, small + 8);
+    c->flag_seq += 1;
+    hipLaunchKernelGGL(k_eig_newrow, dim3(nblk), dim3(1024), 0, s, (const double*)parts, L.nsP, stride, V, AV, m, n, ld,
+                       m > 0 ? norm2 : (const double*)nullptr, m > 0 ? res2 : (const double*)nullptr, dots3, c->h_buf, c->d_state, c->h_flags, c->flag_seq);
     NUGPR_HIP(hipGetLastError());
-    NUGPR_HIP(hipMemcpyAsync(c->h_buf, small, (size_t)(8 + DAV_MAX_BASIS) * sizeof(double), hipMemcpyDeviceToHost, s));
-    NUGPR_HIP(hipStreamSynchronize(s));
+    if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq, s))) return rc;
     for (int k = 0; k <= m; ++k) {
       const double h = c->h_buf[8 + k];
       if (!std::isfinite(h)) { set_error("lambda_0: the projected matrix is not finite"); return NUGPR_ERR_INVALID; }
@@ -406,13 +534,18 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
   bool done = false;
   std::vector<double> A, ev, Y;
   for (; step < DAV_MAX_STEPS; ++step) {
-    A.assign((size_t)m * m, 0.0);
-    for (int i = 0; i < m; ++i)
-      for (int j = 0; j < m; ++j) A[(size_t)i * m + j] = H[(size_t)i * DAV_MAX_BASIS + j];
-    small_sym_eigen(A, m, ev, Y);
-    thetaR = ev[0];
-    if (m == DAV_MAX_BASIS) {
+    Coef cf = {};
+    double second = INFINITY;
+    if (m < DAV_MAX_BASIS) {
+      if (lowest_eigenpair(H, m, thetaR, second, cf.y)) { set_error("lambda_0: the projected eigen-solve did not converge"); return NUGPR_ERR_INVALID; }
+    } else {
       // thick restart: the lowest Ritz vectors become the basis, H their (diagonal) Rayleigh quotients
+      A.assign((size_t)m * m, 0.0);
+      for (int i = 0; i < m; ++i)
+        for (int j = 0; j < m; ++j) A[(size_t)i * m + j] = H[(size_t)i * DAV_MAX_BASIS + j];
+      small_sym_eigen(A, m, ev, Y);
+      thetaR = ev[0];
+      second = ev[1];
       RestartCoef rcf;
       for (int q = 0; q < DAV_KEEP; ++q)
         for (int k = 0; k < m; ++k) rcf.y[q * m + k] = Y[(size_t)k * m + q];
@@ -420,26 +553,20 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
       NUGPR_HIP(hipGetLastError());
       std::fill(H.begin(), H.end(), 0.0);
       for (int q = 0; q < DAV_KEEP; ++q) H[(size_t)q * DAV_MAX_BASIS + q] = ev[q];
-      std::vector<double> ev2(ev.begin(), ev.begin() + DAV_KEEP);
       m = DAV_KEEP;
-      Y.assign((size_t)m * m, 0.0);
-      for (int q = 0; q < m; ++q) Y[(size_t)q * m + q] = 1.0;
-      ev = ev2;
+      cf.y[0] = 1.0;
     }
-    Coef cf;
-    for (int k = 0; k < DAV_MAX_BASIS; ++k) cf.y[k] = k < m ? Y[(size_t)k * m + 0] : 0.0;
-    hipLaunchKernelGGL(k_eig_residual, dim3(1), dim3(1024), 0, s, (const double*)V, (const double*)AV, cf, thetaR, m, n, ld,
-                       res, small);
-    hipLaunchKernelGGL(k_block_solve, dim3(nblk), dim3(1024), 0, s, (const double*)Lblk,
-                       (const double*)res, tvec, n);
-    hipLaunchKernelGGL(k_eig_orth, dim3(1), dim3(1024), 0, s, V, (const double*)tvec, m, n, ld, small + 1);
+    hipLaunchKernelGGL(k_eig_correct, dim3(nblk), dim3(1024), 0, s, (const double*)V, (const double*)AV, cf, thetaR, m, n, ld,
+                       (const double*)Lblk, tvec, res2, dots1);
+    hipLaunchKernelGGL((k_eig_orth<false>), dim3(nblk), dim3(1024), 0, s, V, tvec, m, n, ld, (const double*)dots1, dots2);
+    hipLaunchKernelGGL((k_eig_orth<true>), dim3(nblk), dim3(1024), 0, s, V, tvec, m, n, ld, (const double*)dots2, norm2);
     NUGPR_HIP(hipGetLastError());
     if ((rc = extend(m))) return rc;              // (also brings |res|^2 and the norm of the new direction)
     const double rn = std::sqrt(std::max(c->h_buf[0], 0.0)), tn = c->h_buf[1];
     if (!std::isfinite(rn)) { set_error("lambda_0: residual not finite"); return NUGPR_ERR_INVALID; }
     est = rn;
     if (m > 1) {
-      const double gap = ev[1] - ev[0];
+      const double gap = second - thetaR;
       if (gap > 10.0 * rn) est = std::min(est, 4.0 * rn * rn / gap);
     }
     if (est <= tol || std::fabs(thetaR) <= tol) { done = true; break; }

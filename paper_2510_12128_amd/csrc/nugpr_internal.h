@@ -366,6 +366,8 @@ int run_pcg(nugpr_ctx* c, const void* B, void* X, int T, int32_t* iters, double*
             int* max_it_used, hipStream_t s, PcgExtras* extras = nullptr, int system = PCG_KPRIME);
 // A D = Y K' Y^T D (eq. (RKR)); with the linear relations of eqs. (linear1)-(linear3) when they apply
 int run_split_op(nugpr_ctx* c, const void* D, void* out, int T, hipStream_t s);
+// waits until the device has stored `want`, or a later number, in a pinned sequence slot
+int wait_seq(const volatile uint64_t* slot, uint64_t want, hipStream_t s);
 int run_dot2(nugpr_ctx* c, const void* A0, const void* B0, const void* A1, const void* B1, int T, double* out0,
              double* out1, hipStream_t s);
 int store_known_starts(nugpr_ctx* c, hipStream_t s);

@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, con
 
 // Waits until the device has stored `want`, or a later number, in a pinned sequence slot: a short poll (the usual
 // case: microseconds after the kernel ends), then an ordinary stream synchronisation.
-static int wait_seq(const volatile uint64_t* slot, uint64_t want, hipStream_t s) {
+int wait_seq(const volatile uint64_t* slot, uint64_t want, hipStream_t s) {
   for (int spin = 0; spin < 200000; ++spin) {
     if (*slot >= want) return NUGPR_OK;
     __builtin_ia32_pause();
