@@ -329,24 +329,56 @@ struct CouplingArgs {
   double alpha, lambda0;
   int n, d;
   uint32_t ld;
+  int lower;              // the products read the tiles on and below the diagonal only: leave the others alone
 };
+// One workgroup per 64 x 64 tile (all of them, or the lower triangle row by row), the coordinates of its rows and columns in
+// LDS.  2048 representatives in 8 dimensions: one thread per entry, its place found by a 64-bit division and its coordinates
+// in memory, 68 us whether or not the upper half was left out; the lower tiles now 15.
 __global__ __launch_bounds__(256) void k_coupling_residual(CouplingArgs a, const float* __restrict__ reps,
                                                            const float* __restrict__ Chi, float* __restrict__ Clo) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (uint64_t)a.ld * a.ld) return;
-  const int i = (int)(idx / a.ld), j = (int)(idx - (uint64_t)i * a.ld);
-  float lo = 0.f;
-  if (i < a.n && j < a.n) {
-    double q = 0.0;
-    for (int k = 0; k < a.d; ++k) {
-      const double t = ((double)reps[(uint64_t)i * a.d + k] - (double)reps[(uint64_t)j * a.d + k]) * a.inv_ell[k];
-      q = fma(t, t, q);
-    }
-    double v = a.alpha * exp(-0.5 * q);
-    if (i == j) v -= a.lambda0;
-    lo = (float)(v - (double)Chi[blocked_index(a.ld, i, j)]);
+  extern __shared__ float pts[];                   // [d][64] of the rows, then of the columns
+  const int nt = (int)(a.ld / TILE);
+  int tr, tc;
+  if (a.lower) {                                   // tile number tr (tr + 1) / 2 + tc
+    const int id = (int)blockIdx.x;
+    tr = (int)((sqrt(8.0 * id + 1.0) - 1.0) * 0.5);
+    if (tr * (tr + 1) / 2 > id) --tr;
+    if ((tr + 1) * (tr + 2) / 2 <= id) ++tr;
+    tc = id - tr * (tr + 1) / 2;
+  } else {
+    tr = (int)blockIdx.x / nt;
+    tc = (int)blockIdx.x % nt;
   }
-  Clo[blocked_index(a.ld, i, j)] = lo;             // same blocked storage as the matrix it completes
+  const int tid = threadIdx.x;
+  for (int e = tid; e < 2 * TILE * a.d; e += 256) {
+    const int side = e / (TILE * a.d), at = e % (TILE * a.d), p = at / a.d, k = at % a.d, row = (side ? tc : tr) * TILE + p;
+    pts[(side * a.d + k) * TILE + p] = row < a.n ? reps[(uint64_t)row * a.d + k] : 0.f;
+  }
+  __syncthreads();
+  const int q = tid & 63, j = tc * TILE + q;
+  for (int r0 = tid >> 6; r0 < TILE; r0 += 16) {   // four rows at a time
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < a.d; ++k) {
+      const double y = (double)pts[(a.d + k) * TILE + q], w = a.inv_ell[k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double t = ((double)pts[k * TILE + r0 + 4 * e] - y) * w;
+        s[e] = fma(t, t, s[e]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = tr * TILE + r0 + 4 * e;
+      const uint64_t at = blocked_index(a.ld, (uint32_t)i, (uint32_t)j);      // same blocked storage as the matrix it completes
+      float lo = 0.f;
+      if (i < a.n && j < a.n) {
+        double v = a.alpha * exp(-0.5 * s[e]);
+        if (i == j) v -= a.lambda0;
+        lo = (float)(v - (double)Chi[at]);
+      }
+      Clo[at] = lo;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -512,9 +544,9 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, int pair
   }
   c->diag_residual = (float)((alpha + sigma2) - (double)a.diag_val);
   PanelArgs ac = a;                                  // the coupling launch
-  // The upper tiles of C are written unless its strips pair up in the product.  (Under the compensation they are written
-  // all the same, for the residual Clo, which is formed over the whole square; the products read the lower ones of both.)
-  const bool need_c_upper = L.compensate || !c->c_paired;
+  // The upper tiles of C, and under the compensation of its residual Clo, are written unless the strips of C pair up in the
+  // product.
+  const bool need_c_upper = !c->c_paired;
   ac.mirror = need_c_upper ? 1 : 0;
   const bool host_lambda = L.compensate && L.ncr <= COMPENSATE_HOST_MAX;
   if (L.compensate && !host_lambda) {
@@ -573,9 +605,10 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, int pair
     CouplingArgs ca;
     for (int k = 0; k < MAX_D; ++k) ca.inv_ell[k] = k < L.d ? 1.0 / (iso ? theta[0] : theta[k]) : 0.0;
     // (large coupling: the diagonal is zero for now, in both terms)
-    ca.alpha = alpha; ca.lambda0 = host_lambda ? c->lambda0 : alpha; ca.n = L.ncr; ca.d = L.d; ca.ld = (uint32_t)L.ldc;
-    const unsigned blocks = (unsigned)(((uint64_t)L.ldc * L.ldc + 255) / 256);
-    hipLaunchKernelGGL(k_coupling_residual, dim3(blocks), dim3(256), 0, s, ca, c->reps, c->C, c->Clo);
+    ca.alpha = alpha; ca.lambda0 = host_lambda ? c->lambda0 : alpha; ca.n = L.ncr; ca.d = L.d; ca.ld = (uint32_t)L.ldc; ca.lower = !need_c_upper;
+    const unsigned nt = (unsigned)(L.ldc / TILE);
+    hipLaunchKernelGGL(k_coupling_residual, dim3(ca.lower ? nt * (nt + 1) / 2 : nt * nt), dim3(256), (size_t)2 * TILE * L.d * sizeof(float), s,
+                       ca, c->reps, c->C, c->Clo);
     NUGPR_HIP(hipGetLastError());
     if (!host_lambda) {
       double lam0 = 0.0;

@@ -34,6 +34,7 @@
 
 namespace nugpr {
 
+typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int EB = 128;               // order of the preconditioner's diagonal blocks
 constexpr int EBP = EB + 1;           // row stride of a block in LDS (odd: column accesses spread over the banks)
 constexpr int DAV_MAX_BASIS = 24;     // basis vectors kept before a restart
@@ -49,14 +50,60 @@ struct BlockKernelArgs {
 // Inverse L^-1 of the Cholesky factor (lower, row-major EB x EB doubles per block, unit rows past the end) of
 // B_k + mu I, where B_k = k(R_k, R_k) for the representatives 128 k .. 128 k + 127, evaluated in fp64 with direct
 // differences.  Once per assembly; the explicit triangular inverse turns the two substitutions of every step, 256
-// dependent rounds, into two products.  1024 threads: a pivot's trailing update is the serial part, and a thread keeps
-// its column (256 threads with a division per element: 493 us; now 267 us, inverse included, 2048 representatives).
+// dependent rounds, into two products.
+// One workgroup per block, so what counts is the serial chain: eight panels of 16 columns, each factored by one wave in
+// registers (a lane holds rows l and l + 64; pivots and pivot rows reach the other lanes by v_readlane), the rest in 16 x 16
+// blocks on the matrix cores, a block row or column per wave: the left-looking update before a panel, and the inverse by
+// [L11 0; L21 L22]^-1 = [Y11 0; -Y22 L21 Y11, Y22] over blocks, pairs and fours of them.  2048 representatives: 267 us with a
+// pivot's trailing update by all threads (three barriers a pivot, two a row of the inverse), now 87.
 constexpr int BF_THREADS = 1024;
+constexpr int BI = 16 * 17;           // an inverted diagonal block in LDS, row stride 17
+constexpr int BF_LDS = (EB * EBP + EB / 16 * BI + EB) * (int)sizeof(double);
+__device__ __forceinline__ double lane_double(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane), hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+// column j of blocks of -Y22 L21 Y11 for the node of 2 H blocks from block s0 on; block (i, j) of the inverse lies where block
+// (j, i) of the matrix was.  A product enters the next one as its right factor as it stands in the registers.
+template <int H>
+__device__ __forceinline__ void block_inverse_column(double* M, const double* inv, int s0, int j) {
+  const int lane = threadIdx.x & 63, m = lane & 15, kg = lane >> 4, mid = s0 + H;
+  auto yb = [&](int i, int q) { return i == q ? inv + i * BI : M + (16 * q) * EBP + 16 * i; };
+  auto ldy = [&](int i, int q) { return i == q ? 17 : EBP; };
+  v4d t[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) t[i] = (v4d){0.0, 0.0, 0.0, 0.0};
+  for (int q = j; q < mid; ++q) {
+    const double* y = yb(q, j);
+    const int ld = ldy(q, j);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double b = y[(4 * e + kg) * ld + m];
+#pragma unroll
+      for (int i = 0; i < H; ++i)
+        t[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(M[(16 * (mid + i) + m) * EBP + 16 * q + 4 * e + kg], b, t[i], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    v4d x = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q <= i; ++q) {
+      const double* y = yb(mid + i, mid + q);
+      const int ld = ldy(mid + i, mid + q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x = __builtin_amdgcn_mfma_f64_16x16x4f64(-y[m * ld + 4 * e + kg], t[q][e], x, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) M[(16 * j + kg + 4 * e) * EBP + 16 * (mid + i) + m] = x[e];
+  }
+}
 __global__ __launch_bounds__(BF_THREADS) void k_block_factor(BlockKernelArgs a, const float* __restrict__ reps,
                                                              double* __restrict__ Lout) {
-  extern __shared__ __attribute__((aligned(16))) double M[];      // EB rows of EBP, then EB values
-  double* dj = M + EB * EBP;
-  const int blk = blockIdx.x, tid = threadIdx.x;
+  extern __shared__ __attribute__((aligned(16))) double M[];      // EB rows of EBP, eight inverted blocks, EB values
+  double *inv = M + EB * EBP, *rdiag = inv + EB / 16 * BI;
+  const int blk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, m = lane & 15, kg = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i0 = blk * EB;
   const int nb = min(EB, a.n - i0);
   for (int idx = tid; idx < EB * EB; idx += BF_THREADS) {
@@ -75,40 +122,92 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factor(BlockKernelArgs a, 
     M[i * EBP + j] = v;
   }
   __syncthreads();
-  // right-looking elimination on the lower triangle; a pivot that rounding pushed below the shift is replaced by it
-  const int col = tid & (EB - 1), part = tid >> 7;
-  for (int j = 0; j < nb; ++j) {
-    double p = M[j * EBP + j];
-    if (!(p > 1e-3 * a.mu)) p = 1e-3 * a.mu;
-    const double ljj = sqrt(p);
-    __syncthreads();                                  // every thread has the pivot
-    if (tid < nb && tid > j) M[tid * EBP + j] /= ljj;
-    if (tid == j) { M[j * EBP + j] = ljj; dj[j] = 1.0 / ljj; }
-    __syncthreads();
-    if (col > j && col < nb) {
-      const double lc = M[col * EBP + j];
-      for (int i = col + part; i < nb; i += BF_THREADS / EB) M[i * EBP + col] = fma(-M[i * EBP + j], lc, M[i * EBP + col]);
+#pragma unroll 1
+  for (int p = 0; p < EB / 16; ++p) {
+    if (p > 0) {                                      // block (w, p) -= sum over the panels before of L(w, q) L(p, q)^T
+      if (w >= p && w < EB / 16) {
+        v4d x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = M[(16 * w + kg + 4 * e) * EBP + 16 * p + m];
+        for (int q = 0; q < p; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            x = __builtin_amdgcn_mfma_f64_16x16x4f64(-M[(16 * w + m) * EBP + 16 * q + 4 * e + kg], M[(16 * p + m) * EBP + 16 * q + 4 * e + kg], x, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) M[(16 * w + kg + 4 * e) * EBP + 16 * p + m] = x[e];
+      }
+      __syncthreads();
+    }
+    if (w == 0) {
+      // elimination without square roots; a pivot that rounding pushed below the shift is replaced by it
+      double r0[16], r1[16], d0 = 1.0, d1 = 1.0;
+      const bool lower = 16 * p >= 64;                // the pivots are among the rows lane + 64
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        r0[u] = M[lane * EBP + 16 * p + u];
+        r1[u] = M[(lane + 64) * EBP + 16 * p + u];
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int row = 16 * p + j;
+        const double pv = lower ? r1[j] : r0[j];
+        double dj = lane_double(pv, row & 63);
+        if (!(dj > 1e-3 * a.mu)) dj = 1e-3 * a.mu;
+        d0 = lane == row ? dj : d0;
+        d1 = lane + 64 == row ? dj : d1;
+        const double rd = 1.0 / dj;
+        const double m0 = lane > row ? r0[j] * rd : 0.0, m1 = lane + 64 > row ? r1[j] * rd : 0.0;
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) {
+          const double x = lane_double(pv, (16 * p + c) & 63);
+          r0[c] = fma(-m0, x, r0[c]);
+          r1[c] = fma(-m1, x, r1[c]);
+        }
+      }
+      const double s0 = sqrt(d0), s1 = sqrt(d1), q0 = 1.0 / s0, q1 = 1.0 / s1, qp = lower ? q1 : q0;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int col = 16 * p + u;
+        const double sc = lane_double(qp, col & 63);
+        if (lane >= 16 * p) M[lane * EBP + col] = lane == col ? s0 : (lane > col ? r0[u] * sc : 0.0);
+        if (lane + 64 >= 16 * p) M[(lane + 64) * EBP + col] = lane + 64 == col ? s1 : (lane + 64 > col ? r1[u] * sc : 0.0);
+      }
+      if (lower ? lane + 64 >= 16 * p && lane + 64 < 16 * p + 16 : lane >= 16 * p && lane < 16 * p + 16) rdiag[lower ? lane + 64 : lane] = qp;
     }
     __syncthreads();
   }
-  // inverse in place, row by row: Y[i][c] = -(sum over c <= k < i of L[i][k] Y[k][c]) / L[i][i]; rows above i hold Y
-  __shared__ double part_sum[BF_THREADS];
-  for (int i = 0; i < nb; ++i) {
-    double s = 0.0;
-    if (col < i)
-      for (int k = col + part; k < i; k += BF_THREADS / EB) s = fma(M[i * EBP + k], M[k * EBP + col], s);
-    part_sum[tid] = s;
-    __syncthreads();
-    if (tid < EB && col <= i) {
-      for (int q = 1; q < BF_THREADS / EB; ++q) s += part_sum[tid + q * EB];
-      M[i * EBP + col] = col == i ? dj[i] : -s * dj[i];
+  if (w < EB / 16) {                                  // inverse of diagonal block w: lane m holds column m of it
+    double l[16], y[16];
+    const double r = rdiag[16 * w + m];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      l[u] = M[(16 * w + m) * EBP + 16 * w + u];
+      y[u] = u == m ? 1.0 : 0.0;
     }
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      y[q] *= lane_double(r, q);
+#pragma unroll
+      for (int i = q + 1; i < 16; ++i) y[i] = fma(-lane_double(l[q], i), y[q], y[i]);
+    }
+    if (kg == 0) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) inv[w * BI + u * 17 + m] = y[u];
+    }
   }
+  __syncthreads();
+  if (w < 4) block_inverse_column<1>(M, inv, 2 * w, 2 * w);
+  __syncthreads();
+  if (w < 4) block_inverse_column<2>(M, inv, 4 * (w >> 1), 4 * (w >> 1) + (w & 1));
+  __syncthreads();
+  if (w < 4) block_inverse_column<4>(M, inv, 0, w);
+  __syncthreads();
   double* out = Lout + (uint64_t)blk * EB * EB;
   for (int idx = tid; idx < EB * EB; idx += BF_THREADS) {
-    const int i = idx / EB, j = idx % EB;
-    out[idx] = j <= i ? M[i * EBP + j] : 0.0;
+    const int i = idx / EB, j = idx % EB, bi = i >> 4, bj = j >> 4;
+    double v = 0.0;
+    if (j <= i) v = bi == bj ? inv[bi * BI + (i & 15) * 17 + (j & 15)] : M[(16 * bj + (i & 15)) * EBP + 16 * bi + (j & 15)];
+    out[idx] = v;
   }
 }
 
@@ -493,7 +592,7 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
   double *V = c->dav, *AV = V + (size_t)DAV_MAX_BASIS * ld, *sums = AV + (size_t)DAV_MAX_BASIS * ld, *tvec = sums + ld, *Lblk = tvec + ld + 64;
   static_assert((COMPENSATE_HOST_MAX + EB) / EB * (3 * DAV_MAX_BASIS + 3) <= COMPENSATE_HOST_MAX, "room for the partial sums");
   double *res2 = sums, *norm2 = res2 + nblk, *dots1 = norm2 + nblk, *dots2 = dots1 + DAV_MAX_BASIS * nblk, *dots3 = dots2 + DAV_MAX_BASIS * nblk;
-  constexpr int factor_lds = (EB * EBP + EB) * (int)sizeof(double);
+  constexpr int factor_lds = BF_LDS;
   static const hipError_t lds_attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_block_factor),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, factor_lds);
   NUGPR_HIP(lds_attr);
