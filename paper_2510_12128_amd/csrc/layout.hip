@@ -181,6 +181,16 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_rep_pts = take(cur, (size_t)L.n * sizeof(int32_t));
   L.o_rows_before = take(cur, L.rows_before.size() * sizeof(uint32_t));
   L.o_B = take(cur, vec);
+  L.o_x0 = take(cur, (size_t)L.n * sizeof(double));
+  L.o_Z0 = take(cur, vec);
+  L.o_P = take(cur, vec);
+  L.o_Q0 = take(cur, vec);
+  L.o_S0 = take(cur, (size_t)L.ncr * L.T * sizeof(double));
+  // The blocks of a solve, once per system that can be taken side by side.  Up to 32768 points (256 partial sums a dot product):
+  // there a launch of one system leaves most of the chip idle.
+  L.slots = L.n_dot_blocks <= 256 ? MAX_SLOTS : 1;
+  cur = align_up(cur, 256);
+  const size_t slot0 = cur;
   L.o_X = take(cur, vec);
   L.o_R = take(cur, vec);
   L.o_Z = take(cur, vec);
@@ -188,17 +198,15 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_Q = take(cur, vec);
   L.o_V = take(cur, vec);
   L.o_U = take(cur, vec);
-  L.o_x0 = take(cur, (size_t)L.n * sizeof(double));
-  L.o_Z0 = take(cur, vec);
-  L.o_P = take(cur, vec);
-  L.o_Q0 = take(cur, vec);
-  L.o_S0 = take(cur, (size_t)L.ncr * L.T * sizeof(double));
   L.o_Spart = take(cur, (size_t)L.nsS * L.ncr * L.T * sizeof(double));
   L.o_Ppart = take(cur, (size_t)L.nsP * L.ncr * L.T * sizeof(double));
   L.o_dot = take(cur, (size_t)4 * L.n_dot_blocks * MAX_COLS * sizeof(double));
   L.o_state = take(cur, sizeof(PcgState));
   L.o_alog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
   L.o_blog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
+  cur = align_up(cur, 256);
+  L.slot_bytes = cur - slot0;
+  cur = slot0 + L.slots * L.slot_bytes;
   L.o_logdet = take(cur, (size_t)L.nc * sizeof(double));
   // tile list of the diagonal blocks (mirroring) + row-panel work items of the two assembly launches
   // tile list of the diagonal blocks + the assembly work items (32 bytes each, at most one per tile)

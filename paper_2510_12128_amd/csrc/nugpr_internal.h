@@ -15,6 +15,9 @@ constexpr int TILE = 64;        // rows per strip / edge of the square tiles
 constexpr int MAX_COLS = 33;    // widest vector block (1 + 32 probes)
 constexpr int MAX_D = 64;
 constexpr int MAX_ITER_CAP = 4096;
+// Systems that the solver takes side by side, in one set of launches (small problems, whose launches leave most of the chip
+// idle): each has a slot of the workspace for its vector blocks, sums and scalars.
+constexpr int MAX_SLOTS = 4;
 constexpr int COMPENSATE_HOST_MAX = 512;     // lambda_0 of eq. (krep): dense host eigen-solve up to this n_c r, iteration on the device beyond
 constexpr double EIGMIN_REL_TOL = 2e-11;     // stopping tolerance of that iteration on lambda_0, relative to alpha
 constexpr double EIGMIN_PSD_TOL = 1e-5;      // at its step cap a Ritz value below this (times alpha) is accepted: lambda_min lies in [0, theta]
@@ -78,7 +81,7 @@ struct StripItem {
   uint32_t out_row0;     // vector-block row of strip row 0
   uint32_t row_in_block; // index of strip row 0 inside its square block (diagonal position)
   uint16_t out_part;     // which partial-output slab this item writes
-  uint8_t port;          // 0 / 1: which (matrix, in, out) triple of the launch
+  uint8_t port;          // which (matrix, in, out) triple of the launch
   uint8_t mode;          // 0 full, 1 lower triangle (col <= row), 2 upper triangle (col >= row)
   float diag_add;        // 1 for square diagonal blocks: out += port.diag_add * in[row]; else 0
   uint32_t blocked;      // bit 0: the matrix is stored in blocks of operand fragments (blocked_index), else row-major;
@@ -97,9 +100,12 @@ struct StripPort {
 };
 
 struct StripArgs {
-  StripPort port[2];
+  StripPort port[2 * MAX_SLOTS];
   const StripItem* items;
   int32_t T;                 // columns of the vector blocks (row stride)
+  // 2^sys_log2 systems side by side: every row of eight items (one per die) once for each of them, with ports sys_ports
+  // further a system, so that strips of two systems that read the same matrix meet in one die's L2
+  int32_t sys_log2, sys_ports, count;
 };
 
 struct StripTable {
@@ -181,6 +187,8 @@ struct Layout {
   size_t o_x0 = 0, o_Z0 = 0, o_P = 0, o_Clo = 0, o_S0 = 0, o_dav = 0;
   size_t o_assign = 0, o_rep_ptr = 0, o_rep_pts = 0, o_rows_before = 0;
   size_t items_bytes = 0;
+  int slots = 1;                     // MAX_SLOTS, or 1 on large problems
+  size_t slot_bytes = 0;             // from a block of one slot (X .. blog) to that of the next
   int n_dot_blocks = 0;
   int max_iter = 0;
   uint64_t n_diag_tiles = 0, n_c_tiles = 0;
@@ -234,11 +242,12 @@ struct nugpr_ctx {
   nugpr::BuildItem* d_pan_c = nullptr;       // work items of the coupling assembly
   int n_pan_diag = 0, n_pan_c = 0;
   nugpr::StripTable tab_WtD, tab_KC, tab_C, tab_WP, tab_lowG, tab_upG, tab_lowL;
+  int slots = 1;                         // systems the solver can take side by side (1, 2 or 4)
   // optional event timing of the K_diag / C streaming launch
   bool prof_on = false;
   std::vector<hipEvent_t> prof_ev;       // start/stop pairs
   int prof_used = 0;                     // pairs recorded since the last read
-  nugpr::HostFlags* h_flags = nullptr;   // pinned
+  nugpr::HostFlags* h_flags = nullptr;   // pinned, one per slot
   uint64_t flag_seq = 0, tail_seq = 0;   // last numbers handed to the device
   int expect_iters[2] = {1, 1};          // iterations the last solve of each system took (when to report early)
   // the last three solves of a kind (the context's own right-hand sides, the Pade system, any other block, a single
@@ -325,8 +334,12 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
 int coupling_set_diag(nugpr_ctx* c, double value, hipStream_t s);
 
 // strip_gemm.hip ------------------------------------------------------------
-int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64,
-                 hipStream_t s);
+// (nsys = 1, 2 or 4 systems side by side, the same number of ports for each, one system after the other)
+int launch_strip(const StripTable& tab, const StripPort* ports, int nports, int T, bool acc64, hipStream_t s, int nsys = 1);
+inline int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64, hipStream_t s) {
+  const StripPort ports[2] = {p0, p1};
+  return launch_strip(tab, ports, 2, T, acc64, s);
+}
 
 // up to 10 tiles an item on average
 bool short_strips(const std::vector<StripItem>& items);
@@ -335,8 +348,9 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes);
 // its name for such a table and width (profilers' spelling, no namespace), valid until the thread's next call
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64);
 
+// (nsys > 1: the same for several systems, slot bytes apart)
 int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64_t stride, bool acc64,
-                     hipStream_t s);
+                     hipStream_t s, int nsys = 1, uint64_t slot = 0);
 
 // factor.hip ----------------------------------------------------------------
 int launch_factor(nugpr_ctx* c, hipStream_t s);
@@ -350,7 +364,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s);
 // one, Q holding the block-diagonal part only: a caller's fp32 blocks then cost no conversion passes)
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial = nullptr,
                bool* dq_done = nullptr, const float* D32 = nullptr, float* Q32 = nullptr);
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s);
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys = 1);
 // What a loss evaluation needs besides the solution, fetched with the solve's last synchronisation:
 // <b_c, x_c> per column and rho_0 = <r_0, M^-1 r_0>.
 // Which system a batched CG run solves.
@@ -364,6 +378,29 @@ struct PcgExtras {
 };
 int run_pcg(nugpr_ctx* c, const void* B, void* X, int T, int32_t* iters, double* alpha, double* beta,
             int* max_it_used, hipStream_t s, PcgExtras* extras = nullptr, int system = PCG_KPRIME);
+// The operator scale (K_ii, C) + shift I of one system, and what a solve of it gave (iters, alpha, beta, extras: where the caller
+// wants them, or null, alike for all systems of a call; the rest is filled in: alog and blog, on request (logs), the rows of
+// MAX_COLS alphas and betas in the pinned buffer, until the context's next call).
+struct Operator {
+  const float *Kd, *C;
+  double scale, shift;
+};
+struct PcgOutcome {
+  int32_t* iters;
+  double *alpha, *beta;
+  PcgExtras* extras;
+  bool logs;
+  int max_it, status;
+  const double *alog, *blog;
+};
+// Several systems in lock step, to the bit what run_pcg gives for each: nsys = 1, or 2 or 4 up to the context's slots (one-hot
+// basis, no compensation, no Pade system).  B: the context's own right-hand sides, shared by all, or a block of slot 0; X a block
+// of slot 0.  A system that is done before the others keeps them company with zero steps.
+int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system = PCG_KPRIME);
+// a system's part of the pinned buffer: logs of alpha and beta, final state, <b, x>
+inline size_t host_record_doubles(int max_iter) {
+  return (size_t)2 * max_iter * MAX_COLS + (sizeof(PcgState) + sizeof(double) - 1) / sizeof(double) + MAX_COLS;
+}
 // A D = Y K' Y^T D (eq. (RKR)); with the linear relations of eqs. (linear1)-(linear3) when they apply
 int run_split_op(nugpr_ctx* c, const void* D, void* out, int T, hipStream_t s);
 // waits until the device has stored `want`, or a later number, in a pinned sequence slot

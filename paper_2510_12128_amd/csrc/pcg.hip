@@ -20,14 +20,28 @@
 
 namespace nugpr {
 
+// Several systems side by side (blockIdx.y = which one): every kernel of the solver finds the blocks of system y at a fixed
+// number of bytes from those of system 0 (the solver slots of the workspace), or, with 0, shares them.
+template <typename P>
+__device__ __forceinline__ P* of_system(P* p, uint64_t stride) {
+  return reinterpret_cast<P*>(reinterpret_cast<char*>(p) + (uint64_t)blockIdx.y * stride);
+}
+template <typename P>
+__device__ __forceinline__ const P* of_system(const P* p, uint64_t stride) {
+  return reinterpret_cast<const P*>(reinterpret_cast<const char*>(p) + (uint64_t)blockIdx.y * stride);
+}
+
 // ---------------------------------------------------------------------------
 // per-column dot products: partial[which][block][col] = sum over the block's rows
 // ---------------------------------------------------------------------------
 template <int NP, typename VT>
 __global__ __launch_bounds__(256) void k_dot(const VT* __restrict__ A0, const VT* __restrict__ B0,
                                              const VT* __restrict__ A1, const VT* __restrict__ B1,
-                                             int64_t n, int T, double* __restrict__ partial) {
+                                             int64_t n, int T, double* __restrict__ partial, uint64_t sa, uint64_t sb, uint64_t sys) {
   __shared__ double red[NP][256];
+  A0 = of_system(A0, sa); B0 = of_system(B0, sb);
+  A1 = of_system(A1, sa); B1 = of_system(B1, sb);
+  partial = of_system(partial, sys);
   const int rpp = 256 / T;                      // rows per pass
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -83,9 +97,11 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
 
 // start of a solve: ||b||^2 and rho_0 = <r_0, z_0>
 __global__ __launch_bounds__(256) void k_pcg_begin(PcgState* __restrict__ st, const double* __restrict__ partial,
-                                                   int nblocks) {
+                                                   int nblocks, uint64_t sys) {
   __shared__ double red[256];
   const int tid = threadIdx.x, c = blockIdx.x;
+  st = of_system(st, sys);
+  partial = of_system(partial, sys);
   const double bb = sum_partials(partial, nblocks, c, red, tid);
   const double rz = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
   if (tid == 0) {
@@ -103,10 +119,11 @@ __global__ __launch_bounds__(256) void k_pcg_begin(PcgState* __restrict__ st, co
 }
 
 // the same from the values kept with the factor (which = 0: [y | L Z], 1: the probe block)
-__global__ void k_pcg_begin_known(PcgState* __restrict__ st, int which, int T) {
+__global__ void k_pcg_begin_known(PcgState* st, int which, int T, uint64_t sys) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= T) return;
-  const double bb = st->known_bb[which][c], rz = st->known_rz[which][c];
+  const double bb = st->known_bb[which][c], rz = st->known_rz[which][c];      // (kept by system 0)
+  st = of_system(st, sys);
   const bool act = bb > 0.0 && rz == rz;
   st->bnorm2[c] = bb;
   st->rho[0][c] = rz;
@@ -150,10 +167,13 @@ __global__ __launch_bounds__(256) void k_pcg_alpha(PcgState* __restrict__ st, co
 // curvature) and publishes it to the host: the flags, a system-scope fence, then the sequence number.
 __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, const double* __restrict__ partial,
                                                    int nblocks, int iter, double tol2, int T,
-                                                   HostFlags* __restrict__ out, uint64_t seq) {
+                                                   HostFlags* __restrict__ out, uint64_t seq, uint64_t sys) {
   __shared__ double red[256];
   __shared__ int last;
   const int tid = threadIdx.x, c = blockIdx.x;
+  st = of_system(st, sys);
+  partial = of_system(partial, sys);
+  out += blockIdx.y;
   const double rr = sum_partials(partial, nblocks, c, red, tid);
   if (tid == 0) {
     if (st->active[c]) {
@@ -243,9 +263,15 @@ __global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* 
                                                         const VT* __restrict__ D, const VT* __restrict__ Q,
                                                         const VT* __restrict__ B, PcgState* __restrict__ st,
                                                         int64_t n, int T, int first, double* __restrict__ partial,
-                                                        const double* __restrict__ dqs, int iter, double* __restrict__ alog) {
+                                                        const double* __restrict__ dqs, int iter, double* __restrict__ alog,
+                                                        uint64_t sys, uint64_t s_in, uint64_t s_d, uint64_t s_b) {
   __shared__ double red[2][256];
   __shared__ double al[MAX_COLS];
+  X = of_system(X, sys); R = of_system(R, sys); Q = of_system(Q, sys);
+  Rin = of_system(Rin, s_in); D = of_system(D, s_d);
+  if (B) B = of_system(B, s_b);
+  st = of_system(st, sys); partial = of_system(partial, sys); alog = of_system(alog, sys);
+  if (dqs) dqs = of_system(dqs, sys);
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -297,7 +323,11 @@ __global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* 
 template <typename VT>
 __global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT* __restrict__ Z,
                                                   PcgState* __restrict__ st, int64_t n, int T,
-                                                  const double* __restrict__ rzs, int nblocks, int iter, double* __restrict__ blog) {
+                                                  const double* __restrict__ rzs, int nblocks, int iter, double* __restrict__ blog,
+                                                  uint64_t sys, uint64_t s_d) {
+  D = of_system(D, sys); Din = of_system(Din, s_d); Z = of_system(Z, sys);
+  st = of_system(st, sys); blog = of_system(blog, sys);
+  if (rzs) rzs = of_system(rzs, sys);
   __shared__ double red[256];
   __shared__ double be[MAX_COLS];
   __shared__ int goes_on[MAX_COLS];
@@ -339,10 +369,13 @@ __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, con
                                                   const double* __restrict__ blog, int rows,
                                                   PcgState* __restrict__ h_state, double* __restrict__ h_bx,
                                                   double* __restrict__ h_alog, double* __restrict__ h_blog,
-                                                  HostFlags* __restrict__ flags, uint64_t seq) {
+                                                  HostFlags* __restrict__ flags, uint64_t seq, uint64_t sys, uint64_t hsys) {
   __shared__ double red[256];
   __shared__ int last;
   const int tid = threadIdx.x, c = blockIdx.x;
+  st = of_system(st, sys); partial = of_system(partial, sys); alog = of_system(alog, sys); blog = of_system(blog, sys);
+  h_state = of_system(h_state, hsys); h_bx = of_system(h_bx, hsys); h_alog = of_system(h_alog, hsys); h_blog = of_system(h_blog, hsys);
+  flags += blockIdx.y;
   if (want_bx) {
     const double v = sum_partials(partial, nblocks, c, red, tid);
     if (tid == 0) h_bx[c] = v;
@@ -381,7 +414,9 @@ int wait_seq(const volatile uint64_t* slot, uint64_t want, hipStream_t s) {
 // during the solve.)
 template <typename VT>
 __global__ void k_pcg_init(VT* __restrict__ X, VT* __restrict__ R, const VT* __restrict__ B,
-                           const VT* __restrict__ Z0, VT* __restrict__ D, int64_t count) {
+                           const VT* __restrict__ Z0, VT* __restrict__ D, int64_t count, uint64_t sys, uint64_t s_b) {
+  X = of_system(X, sys); R = of_system(R, sys); D = of_system(D, sys); B = of_system(B, s_b);
+  if (Z0) Z0 = of_system(Z0, s_b);
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
   if (Z0) {
     for (int64_t i = i0; i < count; i += stride) { X[i] = (VT)0; R[i] = B[i]; D[i] = Z0[i]; }
@@ -413,14 +448,18 @@ int from_internal(nugpr_ctx* c, const void* src, float* dst, int64_t count, hipS
 // ---------------------------------------------------------------------------
 // operator applications on internal vector blocks
 // ---------------------------------------------------------------------------
-static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const float* D32 = nullptr);
+static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const float* D32 = nullptr, int nsys = 1, uint64_t s_d = 0);
 // Q = a Q0 + b D with the reduction that follows a product in the solver (partial as in
 // k_onehot_expand_dot; may be null)
+struct Combination { double a[MAX_SLOTS], b[MAX_SLOTS]; };
 template <typename VT>
 __global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const VT* __restrict__ Q0,
-                                                     const VT* __restrict__ D, double a, double b, int64_t n, int T,
-                                                     double* __restrict__ partial) {
+                                                     const VT* __restrict__ D, Combination of, int64_t n, int T,
+                                                     double* __restrict__ partial, uint64_t sys) {
   __shared__ double red[256];
+  const double a = of.a[blockIdx.y], b = of.b[blockIdx.y];
+  Q = of_system(Q, sys);
+  if (partial) partial = of_system(partial, sys);
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -448,7 +487,7 @@ __global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const V
 }
 
 static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D = nullptr, double* dq_partial = nullptr,
-                      float* Q32 = nullptr, int parts = 1);
+                      float* Q32 = nullptr, int parts = 1, int nsys = 1, uint64_t s_d = 0);
 // How many column slabs of P the expansion adds up itself: all of them with the one-hot basis while the extra gathers
 // (n T values from every slab after the first, out of L2) cost less than the launch they save.  A product with that
 // launch / without it: 20.6 / 17.9 us at 0.02e6 gathers, 23.5 / 21.8 at 1e6, 42.5 / 41.2 at 2.1e6, 48.8 / 52.7 at 8.4e6.
@@ -456,9 +495,14 @@ static int fold_parts(const nugpr_ctx* c, int T) {
   return c->onehot && (double)c->L.n * T * (c->L.nsP - 1) <= 3e6 ? c->L.nsP : 1;
 }
 
-int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial, bool* dq_done,
-               const float* D32, float* Q32) {
+template <typename P> static P* slot_of(P* p, uint64_t stride, int e) { return (P*)((uintptr_t)p + (uint64_t)e * stride); }
+
+// The product of `nsys` systems side by side, each with its operator; D and Q those of system 0, the others a slot further
+// (the kept direction z_0 is shared).  More than one (2 or 4): one-hot basis, no compensation.
+static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, void* Q, int T, hipStream_t s, double* dq_partial,
+                   bool* dq_done, const float* D32, float* Q32) {
   const Layout& L = c->L;
+  const uint64_t sys = L.slot_bytes;
   int rc;
   const uint64_t ppart = (uint64_t)L.ncr * T;
   // S_j = W_j^T D_j (dense W: in column slabs of W_j^T that are then added up); the projection of z_0, the
@@ -468,40 +512,50 @@ int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, doubl
   // operator is s K_0 + shift I for some other (s, shift), and the product a combination of what is kept.
   const bool shortcuts = !(c->params.flags & NUGPR_NO_SHORTCUTS);
   if (s_known && shortcuts && c->q0_gen == c->build_gen && Q != c->Q0v) {
-    const double a = c->op_scale / c->q0_scale, b = c->op_shift - a * c->q0_shift;
-    const int nb = L.n_dot_blocks;
-    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), dim3(nb), dim3(256), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, a, b, (int64_t)L.n, T, dq_partial);
-    else hipLaunchKernelGGL((k_lincomb_dot<float>), dim3(nb), dim3(256), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, a, b, (int64_t)L.n, T, dq_partial);
+    Combination of = {};
+    for (int e = 0; e < nsys; ++e) {
+      of.a[e] = ops[e].scale / c->q0_scale;
+      of.b[e] = ops[e].shift - of.a[e] * c->q0_shift;
+    }
+    const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
+    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), nb, dim3(256), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, of, (int64_t)L.n, T, dq_partial, sys);
+    else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(256), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
     NUGPR_HIP(hipGetLastError());
     if (dq_done) *dq_done = dq_partial != nullptr;
-    c->stats.products_reused += 1;
+    c->stats.products_reused += nsys;
     return NUGPR_OK;
   }
-  c->stats.products += 1;
-  if (!s_known && (rc = run_project(c, D, T, s, D32))) return rc;
+  c->stats.products += nsys;
+  const bool d_shared = D == c->Z0v;
+  const uint64_t s_d = d_shared ? 0 : sys;
+  if (!s_known && (rc = run_project(c, D, T, s, D32, nsys, s_d))) return rc;
   // Q_i = K_ii D_i   and   P = C_offdiag S (column slabs), one launch
-  StripPort k0{}, k1{};
-  k0.A = c->Kd; k0.in = D; k0.out = Q; k0.scale = c->op_scale; k0.diag_add = c->op_shift;
-  k1.A = c->C; k1.in = s_known ? c->S0v : c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
+  StripPort port[2 * MAX_SLOTS] = {};
+  for (int e = 0; e < nsys; ++e) {
+    StripPort &k0 = port[2 * e], &k1 = port[2 * e + 1];
+    k0.A = ops[e].Kd; k0.in = slot_of(D, s_d, e); k0.out = slot_of(Q, sys, e); k0.scale = ops[e].scale; k0.diag_add = ops[e].shift;
+    k1.A = ops[e].C; k1.in = s_known ? c->S0v : slot_of(c->Spart, sys, e); k1.out = slot_of(c->Ppart, sys, e);
+    k1.out_part_stride = ppart; k1.scale = ops[e].scale;
+  }
   const bool timed = c->prof_on && (size_t)(2 * c->prof_used + 1) < c->prof_ev.size();
   if (timed) NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used], s));
-  if ((rc = launch_strip(c->tab_KC, k0, k1, T, c->acc64, s))) return rc;
+  if ((rc = launch_strip(c->tab_KC, port, 2 * nsys, T, c->acc64, s, nsys))) return rc;
   if (timed) {
     NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used + 1], s));
     c->prof_used += 1;
   }
   if (L.compensate) {                     // the fp32 residual of C - lambda_0 I, added slab by slab
-    StripPort k2 = k1;
+    StripPort k2 = port[1];
     k2.A = c->Clo; k2.accumulate = 1;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
   const int parts = fold_parts(c, T);
-  if (L.nsP > parts && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s))) return rc;
+  if (L.nsP > parts && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s, nsys, sys))) return rc;
   // Q_i += W_i P_i (and, on request, the partial sums of <d, q> in the same pass)
   const bool fuse = dq_partial && c->onehot;
   if (dq_done) *dq_done = fuse;
-  if ((rc = run_expand(c, Q, T, s, fuse ? D : nullptr, fuse ? dq_partial : nullptr, Q32, parts))) return rc;
-  if (s_known && shortcuts && c->build_gen == c->factor_gen && c->q0_gen != c->build_gen) {
+  if ((rc = run_expand(c, Q, T, s, fuse ? D : nullptr, fuse ? dq_partial : nullptr, Q32, parts, nsys, s_d))) return rc;
+  if (nsys == 1 && s_known && shortcuts && c->build_gen == c->factor_gen && c->q0_gen != c->build_gen) {
     const size_t bytes = (size_t)L.n * T * (c->acc64 ? sizeof(double) : sizeof(float));
     NUGPR_HIP(hipMemcpyAsync(c->Q0v, Q, bytes, hipMemcpyDeviceToDevice, s));
     c->q0_gen = c->build_gen;
@@ -509,6 +563,14 @@ int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, doubl
     c->q0_shift = c->op_shift;
   }
   return NUGPR_OK;
+}
+
+static Operator operator_in_force(const nugpr_ctx* c) { return Operator{c->Kd, c->C, c->op_scale, c->op_shift}; }
+
+int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial, bool* dq_done,
+               const float* D32, float* Q32) {
+  const Operator op = operator_in_force(c);
+  return product(c, &op, 1, D, Q, T, s, dq_partial, dq_done, D32, Q32);
 }
 
 // out = a * x  (elementwise over a vector block)
@@ -547,8 +609,10 @@ template <typename VT, typename ST>
 __global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ D, VT* __restrict__ Dwide,
                                                          const int32_t* __restrict__ rep_ptr,
                                                          const int32_t* __restrict__ rep_pts, VT* __restrict__ S,
-                                                         int ncr, int T, int parts) {
+                                                         int ncr, int T, int parts, uint64_t s_d, uint64_t sys) {
   __shared__ double red[1024];
+  D = of_system(D, s_d);
+  S = of_system(S, sys);
   const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -612,8 +676,10 @@ template <typename VT>
 __global__ __launch_bounds__(256) void k_onehot_expand_dot(VT* __restrict__ Q, const VT* __restrict__ P,
                                                            const int32_t* __restrict__ assign,
                                                            const VT* __restrict__ D, int64_t n, int T,
-                                                           double* __restrict__ partial, int parts, uint64_t stride) {
+                                                           double* __restrict__ partial, int parts, uint64_t stride, uint64_t sys, uint64_t s_d) {
   __shared__ double red[256];
+  Q = of_system(Q, sys); P = of_system(P, sys); partial = of_system(partial, sys);
+  D = of_system(D, s_d);
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -643,7 +709,7 @@ static int elementwise_grid(int64_t n, int T);
 
 // S = W^T D into the first slab of Spart (summed over the column slabs when W is dense).  D32 (one-hot basis,
 // fp64 mode only): the block is read from this fp32 array and its widened copy is written to D on the way.
-static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const float* D32) {
+static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const float* D32, int nsys, uint64_t s_d) {
   const Layout& L = c->L;
   if (D32 && !(c->onehot && c->acc64)) { set_error("internal: fused widening needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot) {
@@ -654,10 +720,11 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
     int parts = 1;
     while (2 * parts <= rpp && parts < want) parts *= 2;
     const int reps = rpp / parts;
-    const dim3 grid((unsigned)((L.ncr + reps - 1) / reps)), blk((unsigned)block);
-    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), grid, blk, 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts);
-    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), grid, blk, 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts);
-    else hipLaunchKernelGGL((k_onehot_project<float, float>), grid, blk, 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T, parts);
+    const dim3 grid((unsigned)((L.ncr + reps - 1) / reps), (unsigned)nsys), blk((unsigned)block);
+    const uint64_t sys = L.slot_bytes;
+    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), grid, blk, 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys);
+    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), grid, blk, 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys);
+    else hipLaunchKernelGGL((k_onehot_project<float, float>), grid, blk, 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T, parts, s_d, sys);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -671,14 +738,15 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
 }
 
 // Q += W P with P the first slab of Ppart; with Q32 (one-hot basis, fp64 mode) the sum goes to that fp32 array instead
-static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D, double* dq_partial, float* Q32, int parts) {
+static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D, double* dq_partial, float* Q32, int parts, int nsys, uint64_t s_d) {
   const Layout& L = c->L;
   const uint64_t stride = (uint64_t)L.ncr * T;
   if (Q32 && !(c->onehot && c->acc64 && !dq_partial)) { set_error("internal: fused narrowing needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot && dq_partial) {
-    const int nb = L.n_dot_blocks;
-    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), dim3(nb), dim3(256), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride);
-    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), dim3(nb), dim3(256), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride);
+    const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
+    const uint64_t sys = L.slot_bytes;
+    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), nb, dim3(256), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
+    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), nb, dim3(256), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -754,15 +822,18 @@ static int run_pade_q(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s
   return NUGPR_OK;
 }
 
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s) {
+// (nsys > 1: R and Z of system 0, the others a slot further)
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys) {
   int rc;
-  c->stats.precond_applies += 1;
-  StripPort a{};
-  a.A = c->G; a.in = R; a.out = c->Vv;
-  if ((rc = launch_strip(c->tab_lowG, a, a, T, c->acc64, s))) return rc;
-  StripPort b{};
-  b.A = c->G; b.in = c->Vv; b.out = Z;
-  return launch_strip(c->tab_upG, b, b, T, c->acc64, s);
+  const uint64_t sys = c->L.slot_bytes;
+  c->stats.precond_applies += nsys;
+  StripPort a[MAX_SLOTS] = {}, b[MAX_SLOTS] = {};
+  for (int e = 0; e < nsys; ++e) {
+    a[e].A = c->G; a[e].in = slot_of(R, sys, e); a[e].out = slot_of(c->Vv, sys, e);
+    b[e].A = c->G; b[e].in = a[e].out; b[e].out = slot_of(Z, sys, e);
+  }
+  if ((rc = launch_strip(c->tab_lowG, a, nsys, T, c->acc64, s, nsys))) return rc;
+  return launch_strip(c->tab_upG, b, nsys, T, c->acc64, s, nsys);
 }
 
 static int elementwise_grid(int64_t n, int T) {
@@ -776,7 +847,7 @@ static int dot2_t(nugpr_ctx* c, const VT* A0, const VT* B0, const VT* A1, const 
                   double* out1, hipStream_t s) {
   const Layout& L = c->L;
   const int nb = L.n_dot_blocks;
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart);
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart, (uint64_t)0, (uint64_t)0, (uint64_t)0);
   NUGPR_HIP(hipGetLastError());
   NUGPR_HIP(hipMemcpyAsync(c->h_buf, c->dotpart, (size_t)2 * nb * MAX_COLS * sizeof(double), hipMemcpyDeviceToHost, s));
   NUGPR_HIP(hipStreamSynchronize(s));
@@ -800,9 +871,11 @@ int run_dot2(nugpr_ctx* c, const void* A0, const void* B0, const void* A1, const
 }
 
 template <typename VT>
-static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double* alpha, double* beta,
-                 int* max_it_used, hipStream_t s, PcgExtras* extras, int system) {
+static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system) {
   const Layout& L = c->L;
+  const uint64_t sys = L.slot_bytes;
+  const unsigned ny = (unsigned)nsys;
+  const bool extras = out[0].extras != nullptr;
   const int64_t n = L.n;
   const int nb = L.n_dot_blocks;
   const int eg = elementwise_grid(n, T);
@@ -818,29 +891,32 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
   // the first update reads b in the place of r and writes x without reading it, and the first direction
   // is z_0 where it lies.
   const bool own = T == L.T && c->z0_ready && (const void*)B == (plain ? (const void*)c->Pv : (const void*)c->Bv);
+  // systems side by side: their own blocks lie a slot apart; the context's right-hand sides and z_0 are shared
+  const uint64_t s_b = own ? 0 : sys;
+  uint64_t s_d = own ? 0 : sys;
   const VT* Dcur = D;                    // the direction the operator is applied to
   if (own) {
-    hipLaunchKernelGGL(k_pcg_begin_known, dim3(1), dim3(64), 0, s, c->d_state, plain ? 1 : 0, T);
+    hipLaunchKernelGGL(k_pcg_begin_known, dim3(1, ny), dim3(64), 0, s, c->d_state, plain ? 1 : 0, T, sys);
     Dcur = plain ? B : (const VT*)c->Z0v;
   } else {
     // x_0 = 0, r_0 = b, d_0 = z_0 = M^-1 r_0 written straight into D
-    hipLaunchKernelGGL((k_pcg_init<VT>), dim3(1024), dim3(256), 0, s, X, R, B, plain ? B : (const VT*)nullptr, D, n * T);
-    if (!plain && (rc = run_precond(c, R, D, T, s))) return rc;
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart);
-    hipLaunchKernelGGL(k_pcg_begin, dim3(T), dim3(256), 0, s, c->d_state, c->dotpart, nb);
+    hipLaunchKernelGGL((k_pcg_init<VT>), dim3(1024, ny), dim3(256), 0, s, X, R, B, plain ? B : (const VT*)nullptr, D, n * T, sys, s_b);
+    if (!plain && (rc = run_precond(c, R, D, T, s, nsys))) return rc;
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(256), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
+    hipLaunchKernelGGL(k_pcg_begin, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, sys);
   }
   NUGPR_HIP(hipGetLastError());
   bool first = own;
   int it = 0;
-  bool indefinite = false;
   // The first iteration is issued without asking the device whether any column is active: columns
   // that start inactive (zero right-hand side) are skipped by every kernel on their own flag, and
   // the host learns the count at the first stop test.
-  c->h_flags->n_active = 1;
+  for (int e = 0; e < nsys; ++e) c->h_flags[e].n_active = 1;
   const size_t cnt = (size_t)max_iter * MAX_COLS;
   PcgState* hs = reinterpret_cast<PcgState*>(c->h_buf + 2 * cnt);
   double* hdot = c->h_buf + 2 * cnt + (sizeof(PcgState) + sizeof(double) - 1) / sizeof(double);
-  const bool want_logs = alpha || beta;
+  const uint64_t hsys = host_record_doubles(max_iter) * sizeof(double);      // a system's part of the pinned buffer
+  const bool want_logs = out[0].alpha || out[0].beta || out[0].logs;
   // partial sums: sets 0 and 1 belong to the update kernel (|r|^2, <b, x>), 2 to <d, q>, 3 to <r, z>
   double *const dq_sums = c->dotpart + (size_t)2 * nb * MAX_COLS, *const rz_sums = c->dotpart + (size_t)3 * nb * MAX_COLS;
   const bool fuse = nb <= FUSE_BLOCKS;
@@ -860,30 +936,30 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
   // (its <b, x> sums were left in the second partial set by the update kernel of the same iteration)
   auto issue_tail = [&](int rows, bool bx_ready) -> int {
     if (extras && !bx_ready)
-      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart);
+      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(256), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
     c->tail_seq += 1;
-    hipLaunchKernelGGL(k_pcg_tail, dim3(T), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, extras ? 1 : 0, c->alog,
-                       c->blog, want_logs ? rows : 0, hs, hdot, c->h_buf, c->h_buf + cnt, c->h_flags, c->tail_seq);
+    hipLaunchKernelGGL(k_pcg_tail, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, extras ? 1 : 0, c->alog,
+                       c->blog, want_logs ? rows : 0, hs, hdot, c->h_buf, c->h_buf + cnt, c->h_flags, c->tail_seq, sys, hsys);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   };
   bool tail_current = false;
   while (it < max_iter) {
     bool dq_done = false;
-    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : run_matvec(c, Dcur, Q, T, s, dq_sums, &dq_done))) return rc;
+    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : product(c, ops, nsys, Dcur, Q, T, s, dq_sums, &dq_done, nullptr, nullptr))) return rc;
     if (!dq_done)
-      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums);
+      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(256), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
     // the update, fused with ||r||^2 for the stop test and, in the iteration expected to be the last, <b, x>
     const bool report = it + 1 >= expect || it + 1 >= max_iter;
-    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb), dim3(256), 0, s, X, R, first ? B : (const VT*)R, Dcur,
+    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(256), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
-                       c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog);
+                       c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b);
     first = false;
     // stop test first: when every column has converged the preconditioner apply is not needed
     c->flag_seq += 1;
-    hipLaunchKernelGGL(k_pcg_check, dim3(T), dim3(256), 0, s, c->d_state, c->dotpart, nb, it, tol2, T, c->h_flags,
-                       c->flag_seq);
+    hipLaunchKernelGGL(k_pcg_check, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, it, tol2, T, c->h_flags,
+                       c->flag_seq, sys);
     NUGPR_HIP(hipGetLastError());
     tail_current = false;
     if (report) {
@@ -895,59 +971,73 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, int32_t* iters, double
     counted = c->stats;
     const bool ahead = it < sure && it < max_iter;                // the stop test to wait for: this one's, or the last one's
     if (!ahead || it > 1) {
-      if ((rc = wait_seq(&c->h_flags->seq, c->flag_seq - (ahead ? 1 : 0), s))) return rc;
-      if (c->h_flags->indefinite) indefinite = true;
-      if (c->h_flags->n_active == 0 || it >= max_iter) break;
+      int n_active = 0;
+      for (int e = 0; e < nsys; ++e) {
+        if ((rc = wait_seq(&c->h_flags[e].seq, c->flag_seq - (ahead ? 1 : 0), s))) return rc;
+        n_active += c->h_flags[e].n_active;
+      }
+      if (n_active == 0 || it >= max_iter) break;
     }
-    if (!plain && (rc = run_precond(c, R, Z, T, s))) return rc;
-    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb), dim3(256), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums);
+    if (!plain && (rc = run_precond(c, R, Z, T, s, nsys))) return rc;
+    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(256), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, rz_sums, nb, j, c->blog);
-    hipLaunchKernelGGL((k_update_d<VT>), dim3(fuse ? std::min(eg, 512) : eg), dim3(256), 0, s, D, Dcur, Zr, c->d_state, n, T,
-                       fuse ? rz_sums : (const double*)nullptr, nb, j, c->blog);
+    hipLaunchKernelGGL((k_update_d<VT>), dim3(fuse ? std::min(eg, 512) : eg, ny), dim3(256), 0, s, D, Dcur, Zr, c->d_state, n, T,
+                       fuse ? rz_sums : (const double*)nullptr, nb, j, c->blog, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     Dcur = D;
+    s_d = sys;
   }
   if (!tail_current && (rc = issue_tail(it, false))) return rc;
-  if ((rc = wait_seq(&c->h_flags->tail_seq, c->tail_seq, s))) return rc;
-  bool all_conv = true;
-  int mx = 0;
-  for (int col = 0; col < T; ++col) {
-    if (iters) iters[col] = hs->iters[col];
-    mx = std::max(mx, hs->iters[col]);
-    if (!hs->converged[col]) all_conv = false;
-    if (hs->indef[col]) indefinite = true;
-  }
-  if (max_it_used) *max_it_used = mx;
-  // the counters leave out the iteration issued in vain, if there was one
-  const int needed = std::min(std::max(hs->steps, 1), it);
-  if (needed < it) c->stats = counted_before;
-  c->expect_iters[plain ? 1 : 0] = needed;
-  rec.last[2] = rec.last[1]; rec.last[1] = rec.last[0]; rec.last[0] = needed;
-  c->stats.pcg_solves += 1;
-  c->stats.pcg_iterations += needed;
-  c->stats.pcg_iterations_max = std::max<int64_t>(c->stats.pcg_iterations_max, needed);
-  if (extras) {
+  for (int e = 0; e < nsys; ++e)
+    if ((rc = wait_seq(&c->h_flags[e].tail_seq, c->tail_seq, s))) return rc;
+  // NaN / Inf among the coordinates of the last assembly (found by its scaling kernel, which marks system 0's state)
+  const bool bad_points = c->assembly_mark != 0 && hs->nonfinite_mark == c->assembly_mark;
+  int longest = 0, in_vain = 0;
+  for (int e = 0; e < nsys; ++e) {
+    const PcgState* st = slot_of(hs, hsys, e);
+    const double *dot = slot_of(hdot, hsys, e), *ha = slot_of(c->h_buf, hsys, e);
+    PcgOutcome& o = out[e];
+    bool all_conv = true, indefinite = false, finite = !bad_points;
+    o.max_it = 0;
+    o.alog = ha;
+    o.blog = ha + cnt;
     for (int col = 0; col < T; ++col) {
-      extras->bx[col] = hdot[col];
-      extras->rho0[col] = hs->rho0[col];
-    }
-  }
-  if (alpha || beta) {
-    const double* ha = c->h_buf;
-    for (int j = 0; j < max_iter; ++j)
-      for (int col = 0; col < T; ++col) {                 // rows past the last iteration were never written: zero
-        if (alpha) alpha[(size_t)j * T + col] = j < it ? ha[(size_t)j * MAX_COLS + col] : 0.0;
-        // (no beta follows the last iteration)
-        if (beta) beta[(size_t)j * T + col] = j < it - 1 ? ha[cnt + (size_t)j * MAX_COLS + col] : 0.0;
+      if (o.iters) o.iters[col] = st->iters[col];
+      o.max_it = std::max(o.max_it, st->iters[col]);
+      if (!st->converged[col]) all_conv = false;
+      if (st->indef[col]) indefinite = true;
+      // or in a right-hand side: it shows in the first dot products of its column, <b, b> and <b, M^-1 b>
+      if (!std::isfinite(st->bnorm2[col]) || !std::isfinite(st->rho0[col])) finite = false;
+      if (o.extras) {
+        o.extras->bx[col] = dot[col];
+        o.extras->rho0[col] = st->rho0[col];
       }
+    }
+    const int needed = std::min(std::max(st->steps, 1), it);
+    longest = std::max(longest, needed);
+    in_vain += it - needed;
+    c->stats.pcg_solves += 1;
+    c->stats.pcg_iterations += needed;
+    c->stats.pcg_iterations_max = std::max<int64_t>(c->stats.pcg_iterations_max, needed);
+    for (int j = 0; j < max_iter && (o.alpha || o.beta); ++j)
+      for (int col = 0; col < T; ++col) {                 // rows past the last iteration were never written: zero
+        if (o.alpha) o.alpha[(size_t)j * T + col] = j < it ? ha[(size_t)j * MAX_COLS + col] : 0.0;
+        // (no beta follows the last iteration)
+        if (o.beta) o.beta[(size_t)j * T + col] = j < it - 1 ? ha[cnt + (size_t)j * MAX_COLS + col] : 0.0;
+      }
+    o.status = !finite ? NUGPR_NOT_FINITE : indefinite ? NUGPR_INDEFINITE : all_conv ? NUGPR_OK : NUGPR_NOT_CONVERGED;
   }
-  // NaN / Inf among the coordinates of the last assembly (found by its scaling kernel), or in a right-hand
-  // side: the latter shows in the first dot products of its column, <b, b> and <b, M^-1 b>
-  if (c->assembly_mark != 0 && hs->nonfinite_mark == c->assembly_mark) return NUGPR_NOT_FINITE;
-  for (int col = 0; col < T; ++col)
-    if (!std::isfinite(hs->bnorm2[col]) || !std::isfinite(hs->rho0[col])) return NUGPR_NOT_FINITE;
-  if (indefinite) return NUGPR_INDEFINITE;
-  return all_conv ? NUGPR_OK : NUGPR_NOT_CONVERGED;
+  // The counters leave out iterations that a system did not need: the one issued ahead of its stop test, if there was one, and
+  // those in which it only kept another one company.
+  if (nsys == 1) {
+    if (in_vain) { counted_before.pcg_solves = c->stats.pcg_solves; counted_before.pcg_iterations = c->stats.pcg_iterations; counted_before.pcg_iterations_max = c->stats.pcg_iterations_max; c->stats = counted_before; }
+  } else {
+    c->stats.products -= in_vain;
+    c->stats.precond_applies -= in_vain;
+  }
+  c->expect_iters[plain ? 1 : 0] = longest;
+  rec.last[2] = rec.last[1]; rec.last[1] = rec.last[0]; rec.last[0] = longest;
+  return NUGPR_OK;
 }
 
 template <typename VT>
@@ -955,10 +1045,11 @@ static int store_known_t(nugpr_ctx* c, hipStream_t s) {
   const Layout& L = c->L;
   const int nb = L.n_dot_blocks;
   const VT *B = (const VT*)c->Bv, *Z0 = (const VT*)c->Z0v, *P = (const VT*)c->Pv;
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart);
+  const uint64_t one = 0;                // (one system)
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart, one, one, one);
   hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 0);
   if (L.t > 0) {
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart);
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart, one, one, one);
     hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 1);
   }
   NUGPR_HIP(hipGetLastError());
@@ -975,10 +1066,20 @@ int store_known_starts(nugpr_ctx* c, hipStream_t s) {
   return c->acc64 ? store_known_t<double>(c, s) : store_known_t<float>(c, s);
 }
 
+int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system) {
+  if (c->acc64) return pcg_t<double>(c, (const double*)B, (double*)X, T, ops, nsys, out, s, system);
+  return pcg_t<float>(c, (const float*)B, (float*)X, T, ops, nsys, out, s, system);
+}
+
 int run_pcg(nugpr_ctx* c, const void* B, void* X, int T, int32_t* iters, double* alpha, double* beta,
             int* max_it_used, hipStream_t s, PcgExtras* extras, int system) {
-  if (c->acc64) return pcg_t<double>(c, (const double*)B, (double*)X, T, iters, alpha, beta, max_it_used, s, extras, system);
-  return pcg_t<float>(c, (const float*)B, (float*)X, T, iters, alpha, beta, max_it_used, s, extras, system);
+  const Operator op = operator_in_force(c);
+  PcgOutcome out{};
+  out.iters = iters; out.alpha = alpha; out.beta = beta; out.extras = extras;
+  const int rc = run_pcg_systems(c, B, X, T, &op, 1, &out, s, system);
+  if (rc) return rc;
+  if (max_it_used) *max_it_used = out.max_it;
+  return out.status;
 }
 
 }  // namespace nugpr

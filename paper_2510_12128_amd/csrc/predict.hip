@@ -24,7 +24,11 @@ struct CrossArgs {
 template <typename VT>
 __global__ __launch_bounds__(256) void k_cross_block(CrossArgs a, const float* __restrict__ X,
                                                      const float* __restrict__ Xt, int64_t j0, int cnt,
-                                                     int64_t n, int T, VT* __restrict__ U) {
+                                                     int64_t n, int T, VT* __restrict__ U, uint64_t sys) {
+  // (blockIdx.y: the block of this many columns further, in the next slot)
+  U = reinterpret_cast<VT*>(reinterpret_cast<char*>(U) + blockIdx.y * sys);
+  j0 += (int64_t)blockIdx.y * T;
+  cnt = min(T, cnt - (int)blockIdx.y * T);
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -51,8 +55,11 @@ __global__ __launch_bounds__(256) void k_cross_block(CrossArgs a, const float* _
 template <typename VT>
 __global__ __launch_bounds__(256) void k_predict_dots(const VT* __restrict__ U, const VT* __restrict__ u,
                                                       const VT* __restrict__ S, int64_t n, int T,
-                                                      double* __restrict__ partial) {
+                                                      double* __restrict__ partial, uint64_t sys) {
   __shared__ double red[2][256];
+  U = reinterpret_cast<const VT*>(reinterpret_cast<const char*>(U) + blockIdx.y * sys);
+  if (S) S = reinterpret_cast<const VT*>(reinterpret_cast<const char*>(S) + blockIdx.y * sys);
+  partial = reinterpret_cast<double*>(reinterpret_cast<char*>(partial) + blockIdx.y * sys);
   const int rpp = 256 / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
@@ -81,12 +88,13 @@ __global__ __launch_bounds__(256) void k_predict_dots(const VT* __restrict__ U, 
   }
 }
 
-// out[set * MAX_COLS + col] = the sum of that set's and column's partial sums (grid: T x 2), fixed order.  Copying the
+// out[(2 system + set) * MAX_COLS + col] = the sum of that set's and column's partial sums (grid: T x 2 x systems), fixed order.  Copying the
 // partial sums to the host (540 KB at 1024 workgroups) and adding them up there took longer, per batch of 17 test points
 // by 1 us at 2048 training points, 13 at 32768, 49 at 131072 and 47 at 262144.
-__global__ __launch_bounds__(256) void k_predict_sums(const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_predict_sums(const double* __restrict__ partial, int nblocks, double* __restrict__ out, uint64_t sys) {
   __shared__ double red[256];
   const int tid = threadIdx.x;
+  partial = reinterpret_cast<const double*>(reinterpret_cast<const char*>(partial) + blockIdx.z * sys);
   const double* p = partial + (int64_t)blockIdx.y * nblocks * MAX_COLS + blockIdx.x;
   double s = 0.0;
   for (int b = tid; b < nblocks; b += 256) s += p[(int64_t)b * MAX_COLS];
@@ -96,7 +104,7 @@ __global__ __launch_bounds__(256) void k_predict_sums(const double* __restrict__
     if (tid < w) red[tid] += red[tid + w];
     __syncthreads();
   }
-  if (tid == 0) out[blockIdx.y * MAX_COLS + blockIdx.x] = red[0];
+  if (tid == 0) out[(blockIdx.z * 2 + blockIdx.y) * MAX_COLS + blockIdx.x] = red[0];
 }
 
 template <typename VT>
@@ -126,27 +134,42 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
   const int nb = L.n_dot_blocks;
   const int rpp = 256 / T;
   const int grid = (int)std::min<int64_t>((n + rpp - 1) / rpp, 8192);
-  for (int64_t j0 = 0; j0 < m; j0 += T) {
-    const int cnt = (int)std::min<int64_t>(T, m - j0);
-    hipLaunchKernelGGL((k_cross_block<VT>), dim3(grid), dim3(256), 0, s, a, c->X, Xt, j0, cnt, n, T, U);
+  // Blocks of T columns side by side, two or four in one set of launches, where the context can (nugpr_ctx::slots).  200 test
+  // points with variances, 32768 training points, 17 columns: one after the other 5450 us, side by side 3500.
+  const bool together = c->slots > 1 && c->onehot && !L.compensate;
+  const uint64_t sys = L.slot_bytes;
+  const Operator op{c->Kd, c->C, c->op_scale, c->op_shift};
+  const Operator ops[MAX_SLOTS] = {op, op, op, op};
+  int nsys = 1;
+  for (int64_t j0 = 0; j0 < m; j0 += (int64_t)nsys * T) {
+    const int64_t left = (m - j0 + T - 1) / T;                  // blocks
+    nsys = !together || left == 1 ? 1 : left == 2 || c->slots < 4 ? 2 : 4;        // (three: the last of four is empty)
+    const unsigned ny = (unsigned)nsys;
+    const int cnt = (int)std::min<int64_t>((int64_t)nsys * T, m - j0);
+    hipLaunchKernelGGL((k_cross_block<VT>), dim3(grid, ny), dim3(256), 0, s, a, c->X, Xt, j0, cnt, n, T, U, sys);
     NUGPR_HIP(hipGetLastError());
     if (var) {
-      rc = run_pcg(c, U, S, T, nullptr, nullptr, nullptr, &mx, s);
-      if (rc < 0 || rc == NUGPR_INDEFINITE || rc == NUGPR_NOT_FINITE) return rc;
-      worst = std::max(worst, rc);
-      mx_all = std::max(mx_all, mx);
+      PcgOutcome out[MAX_SLOTS] = {};
+      if ((rc = run_pcg_systems(c, U, S, T, ops, nsys, out, s))) return rc;
+      for (int e = 0; e < nsys; ++e) {
+        rc = out[e].status;
+        if (rc == NUGPR_INDEFINITE || rc == NUGPR_NOT_FINITE) return rc;
+        worst = std::max(worst, rc);
+        mx_all = std::max(mx_all, out[e].max_it);
+      }
     }
-    hipLaunchKernelGGL((k_predict_dots<VT>), dim3(nb), dim3(256), 0, s, U, u, var ? S : (const VT*)nullptr, n, T,
-                       c->dotpart);
+    hipLaunchKernelGGL((k_predict_dots<VT>), dim3(nb, ny), dim3(256), 0, s, U, u, var ? S : (const VT*)nullptr, n, T,
+                       c->dotpart, sys);
     NUGPR_HIP(hipGetLastError());
-    double* sums = c->dotpart + (size_t)2 * nb * MAX_COLS;       // the sets of the solver's dot products are free now
-    hipLaunchKernelGGL(k_predict_sums, dim3(T, 2), dim3(256), 0, s, c->dotpart, nb, sums);
+    double* sums = c->alog;                                      // (the solver's logs are free now)
+    hipLaunchKernelGGL(k_predict_sums, dim3(T, 2, ny), dim3(256), 0, s, c->dotpart, nb, sums, sys);
     NUGPR_HIP(hipGetLastError());
-    NUGPR_HIP(hipMemcpyAsync(c->h_buf, sums, (size_t)2 * MAX_COLS * sizeof(double), hipMemcpyDeviceToHost, s));
+    NUGPR_HIP(hipMemcpyAsync(c->h_buf, sums, (size_t)nsys * 2 * MAX_COLS * sizeof(double), hipMemcpyDeviceToHost, s));
     NUGPR_HIP(hipStreamSynchronize(s));
-    for (int col = 0; col < cnt; ++col) {
-      mean[j0 + col] = c->h_buf[col];
-      if (var) var[j0 + col] = a.alpha - c->h_buf[MAX_COLS + col];
+    for (int q = 0; q < cnt; ++q) {
+      const double* of = c->h_buf + (size_t)(q / T) * 2 * MAX_COLS + q % T;
+      mean[j0 + q] = of[0];
+      if (var) var[j0 + q] = a.alpha - of[MAX_COLS];
     }
   }
   if (max_iters_used) *max_iters_used = mx_all;

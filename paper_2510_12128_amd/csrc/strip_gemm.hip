@@ -135,8 +135,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     uint32_t lda, vbytes;
     int c_begin, nrows, mode, cnt, jm, thr, tbj, j_abs;
   } S;
-  auto setup = [&](const StripItem& it) {
-    const StripPort& pt = a.port[it.port];
+  auto setup = [&](const StripItem& it, const StripPort& pt) {
     const int c_begin = (int)it.c_begin, c_end = (int)it.c_end;
     const int nb = c_end > c_begin ? (c_end - c_begin + TILE - 1) >> 6 : 0;
     const uint32_t fl = it.blocked;
@@ -313,8 +312,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     if (turned(tile_of(u))) turn(sa[s % ST]);
     spread(sv[s % ST], cb[Cfg::AHEAD ? s & 1 : 0], cy[Cfg::AHEAD ? s & 1 : 0]);
   };
-  const StripItem& it = a.items[blockIdx.x];
-  setup(it);
+  uint32_t id = blockIdx.x, first_port = 0;
+  if (a.sys_log2) {                                          // (the last row of items may be shorter than eight)
+    const uint32_t row = id >> (3 + a.sys_log2), len = min(8u, (uint32_t)a.count - 8 * row), at = id - (row << (3 + a.sys_log2));
+    const uint32_t e = at / len;
+    id = 8 * row + at - e * len;
+    first_port = e * (uint32_t)a.sys_ports;
+  }
+  const StripItem& it = a.items[id];
+  const StripPort& pt = a.port[first_port + it.port];
+  setup(it, pt);
   const int cnt = SP * S.cnt;                                // steps of a wave
   {
     if (cnt > 0) {
@@ -366,7 +373,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
       }
     }
 
-    const StripPort& pt = a.port[it.port];
     VT* __restrict__ out = static_cast<VT*>(pt.out) + (uint64_t)it.out_part * pt.out_part_stride + (uint64_t)it.out_row0 * T;
     const VT* __restrict__ din = reinterpret_cast<const VT*>(pt.in) + (uint64_t)(it.in_row0 + it.row_in_block) * T;
     const double dadd = (double)it.diag_add * pt.diag_add, scale = pt.scale;
@@ -428,7 +434,9 @@ static int launch_width(int ng, int count, int T, hipStream_t s, const StripArgs
 // out[i] = sum over `parts` slabs of in[part * stride + i]  (fixed order: deterministic)
 template <typename VT>
 __global__ void k_sum_parts(const VT* __restrict__ in, VT* __restrict__ out, int64_t count, int parts,
-                            uint64_t stride) {
+                            uint64_t stride, uint64_t slot) {
+  in = reinterpret_cast<const VT*>(reinterpret_cast<const char*>(in) + blockIdx.y * slot);
+  out = reinterpret_cast<VT*>(reinterpret_cast<char*>(out) + blockIdx.y * slot);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
     VT s = in[i];
     for (int p = 1; p < parts; ++p) s += in[(uint64_t)p * stride + i];
@@ -437,14 +445,14 @@ __global__ void k_sum_parts(const VT* __restrict__ in, VT* __restrict__ out, int
 }
 
 int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64_t stride, bool acc64,
-                     hipStream_t s) {
-  const int grid = (int)std::min<int64_t>((count + 255) / 256, 2048);
+                     hipStream_t s, int nsys, uint64_t slot) {
+  const dim3 grid((unsigned)std::min<int64_t>((count + 255) / 256, 2048), (unsigned)nsys);
   if (acc64)
-    hipLaunchKernelGGL((k_sum_parts<double>), dim3(grid), dim3(256), 0, s, (const double*)in, (double*)out, count,
-                       parts, stride);
+    hipLaunchKernelGGL((k_sum_parts<double>), grid, dim3(256), 0, s, (const double*)in, (double*)out, count,
+                       parts, stride, slot);
   else
-    hipLaunchKernelGGL((k_sum_parts<float>), dim3(grid), dim3(256), 0, s, (const float*)in, (float*)out, count,
-                       parts, stride);
+    hipLaunchKernelGGL((k_sum_parts<float>), grid, dim3(256), 0, s, (const float*)in, (float*)out, count,
+                       parts, stride, slot);
   NUGPR_HIP(hipGetLastError());
   return NUGPR_OK;
 }
@@ -477,40 +485,43 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
 // Preconditioner apply, 33 columns, short / long: 4 uneven clusters of 700 points on average 73 / 64 us, 24 x 1000 (384
 // strips) 67 / 60, 64 x 300 (320) 33 / 35, 100 uneven ones of 300 (560) 53 / 54.  The other widths and the fp32 mode gain
 // as much by the shorter start as they lose (17 columns: 4 of 700 40 / 39, 24 x 1000 38 / 40).
-static int kind_at(const StripTable& tab, int T, bool acc64) {
-  const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && tab.count <= 512;
+static int kind_at(const StripTable& tab, int count, int T, bool acc64) {
+  const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && count <= 512;
   return as_long ? tab.kind - STRIP_SHORT + STRIP_LONG : tab.kind;
 }
 
 const char* strip_kernel_name(const StripTable& tab, int T, bool acc64) {
   static thread_local char name[32];
-  std::snprintf(name, sizeof(name), "k_strip<%d, %s, %d>", (T - 1 + 15) / 16, acc64 ? "true" : "false", kind_at(tab, T, acc64));
+  std::snprintf(name, sizeof(name), "k_strip<%d, %s, %d>", (T - 1 + 15) / 16, acc64 ? "true" : "false", kind_at(tab, tab.count, T, acc64));
   return name;
 }
 
 template <bool ACC64>
 static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, const StripArgs& a) {
-  switch (kind_at(tab, T, ACC64)) {
-    case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, tab.count, T, s, a);
-    case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, tab.count, T, s, a);
-    case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, tab.count, T, s, a);
-    case STRIP_ROWMAJOR: return launch_width<ACC64, STRIP_ROWMAJOR>(ng, tab.count, T, s, a);
-    case STRIP_LONG + STRIP_STREAMED: return launch_width<ACC64, STRIP_LONG + STRIP_STREAMED>(ng, tab.count, T, s, a);
-    case STRIP_SHORT + STRIP_STREAMED: return launch_width<ACC64, STRIP_SHORT + STRIP_STREAMED>(ng, tab.count, T, s, a);
+  const int count = tab.count << a.sys_log2;
+  switch (kind_at(tab, count, T, ACC64)) {
+    case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, count, T, s, a);
+    case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, count, T, s, a);
+    case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, count, T, s, a);
+    case STRIP_ROWMAJOR: return launch_width<ACC64, STRIP_ROWMAJOR>(ng, count, T, s, a);
+    case STRIP_LONG + STRIP_STREAMED: return launch_width<ACC64, STRIP_LONG + STRIP_STREAMED>(ng, count, T, s, a);
+    case STRIP_SHORT + STRIP_STREAMED: return launch_width<ACC64, STRIP_SHORT + STRIP_STREAMED>(ng, count, T, s, a);
   }
   set_error("internal: strip table of an unknown kind");
   return NUGPR_ERR_INVALID;
 }
 
-int launch_strip(const StripTable& tab, const StripPort& p0, const StripPort& p1, int T, bool acc64,
-                 hipStream_t s) {
+int launch_strip(const StripTable& tab, const StripPort* ports, int nports, int T, bool acc64, hipStream_t s, int nsys) {
   if (tab.count == 0) return NUGPR_OK;
+  if (nports < 1 || nports > 2 * MAX_SLOTS || (nsys != 1 && nsys != 2 && nsys != 4) || nports % nsys) { set_error("internal: number of strip ports"); return NUGPR_ERR_INVALID; }
   if (T < 1 || T > MAX_COLS) { set_error("vector block wider than 33 columns"); return NUGPR_ERR_INVALID; }
-  StripArgs a;
-  a.port[0] = p0;
-  a.port[1] = p1;
+  StripArgs a{};
+  for (int i = 0; i < nports; ++i) a.port[i] = ports[i];
   a.items = tab.dev;
   a.T = T;
+  a.sys_log2 = nsys / 2;
+  a.sys_ports = nports / nsys;
+  a.count = tab.count;
   const int ng = (T - 1 + 15) / 16;
   return acc64 ? launch_table<true>(tab, ng, T, s, a) : launch_table<false>(tab, ng, T, s, a);
 }

@@ -1,0 +1,79 @@
+"""Solves side by side (both sides of a central difference; blocks of test points) against one after the other: the same results
+to the bit and the same counts.  A context whose iteration cap leaves room for one system's logs only takes them one after the
+other."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ALONE = 4096                       # iteration cap: one system at a time
+STATS = ("loss_evals", "pcg_solves", "pcg_iterations", "pcg_iterations_max", "products", "products_reused", "precond_applies", "assembly_passes",
+         "matrices_assembled", "factorisations")
+
+
+def _contexts(lib, sizes, t, caps, acc_fp32, iso, spacing=4.0):
+    rng = np.random.default_rng(3)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    d = 2
+    centres = np.stack([spacing * (np.arange(len(sizes)) % 3), spacing * (np.arange(len(sizes)) // 3)], 1)
+    X = (np.repeat(centres, sizes, axis=0) + 0.5 * rng.standard_normal((off[-1], d))).astype(np.float32)
+    y = np.sin(X).sum(1).astype(np.float32)
+    probes = 2.0 * rng.integers(0, 2, (off[-1], t)) - 1.0 if t else None
+    return X, [lib.Context(X, y, off, probes, 3, tol=1e-6, max_iter=cap, acc_fp32=acc_fp32, isotropic=iso) for cap in caps]
+
+
+@pytest.mark.parametrize("acc_fp32", [False, True])
+@pytest.mark.parametrize("name,sizes,t,iso,spacing", [
+    ("one-cluster", [70], 4, False, 4.0),
+    ("ragged", [64, 130, 97, 3, 200, 71], 8, False, 4.0),
+    ("ragged-iso-33", [64, 130, 97, 65], 32, True, 3.0),
+    ("close", [128, 129, 127], 16, False, 3.8),          # several iterations, the sides of a difference need not take as many
+    ("largest", [1024] * 32, 4, False, 7.0),             # 32768 points
+])
+def test_training_step_side_by_side(lib, name, sizes, t, iso, spacing, acc_fp32):
+    _, (alone, two, four) = _contexts(lib, sizes, t, (ALONE, 2048, 1024), acc_fp32, iso, spacing)
+    phi = np.log(np.array([0.9, 1.0, 0.3] if iso else [0.9, 1.1, 1.0, 0.3]))
+    zero = np.zeros_like(phi)
+    runs = []
+    for ctx in (alone, two, four):
+        outs = []
+        p, m, v = phi, zero, zero
+        for k in range(3):                                # Adam moves on: from the second step the solver issues iterations ahead
+            ctx.nugpr_stats_read(reset=True)
+            o = ctx.nugpr_train_step(p, m, v, k)
+            p, m, v = o["log_theta"], o["adam_m"], o["adam_v"]
+            outs.append((o["code"], o["nll0"], o["grad"].tolist(), p.tolist(), {k: x for k, x in ctx.nugpr_stats_read().items() if k in STATS}))
+        V = np.random.default_rng(1).standard_normal((sum(sizes), 3)).astype(np.float32)
+        outs.append(ctx.nugpr_matvec(V).cpu().numpy().tolist())          # the blocks that are in force afterwards
+        runs.append(outs)
+    assert runs[0][0][0] == 0
+    assert runs[1] == runs[0]
+    assert runs[2] == runs[0]
+    for ctx in (alone, two, four):
+        ctx.close()
+
+
+@pytest.mark.parametrize("acc_fp32", [False, True])
+@pytest.mark.parametrize("sizes,t,spacing", [([64, 130, 97, 3, 200, 71], 4, 4.0), ([128, 129, 127], 16, 3.8)])
+def test_prediction_side_by_side(lib, sizes, t, spacing, acc_fp32):
+    X, (alone, two, four) = _contexts(lib, sizes, t, (ALONE, 2048, 1024), acc_fp32, False, spacing)
+    theta = np.array([0.9, 1.1, 1.0, 0.3])
+    T = t + 1
+    rng = np.random.default_rng(7)
+    ctxs = (alone, two, four)
+    for ctx in ctxs:
+        ctx.nugpr_build_blocks(theta)
+        assert ctx.nugpr_precond_factor()[0] == 0
+    for m in (1, T, T + 1, 2 * T, 3 * T - 1, 4 * T, 5 * T + 2, 7 * T):
+        pts = (X[rng.integers(0, len(X), m)] + 0.3 * rng.standard_normal((m, 2))).astype(np.float32)
+        pts[::5] += 1e4                                   # out of reach of everything: zero right-hand sides
+        for var in (True, False):
+            outs = [ctx.nugpr_predict(theta, pts, variance=var) for ctx in ctxs]
+            assert outs[0]["code"] == 0
+            for o in outs[1:]:
+                assert o["code"] == 0
+                assert np.array_equal(np.asarray(o["mean"]), np.asarray(outs[0]["mean"]))
+                if var:
+                    assert np.array_equal(np.asarray(o["var"]), np.asarray(outs[0]["var"]))
+    for ctx in ctxs:
+        ctx.close()
