@@ -31,41 +31,70 @@ __device__ __forceinline__ const P* of_system(const P* p, uint64_t stride) {
   return reinterpret_cast<const P*>(reinterpret_cast<const char*>(p) + (uint64_t)blockIdx.y * stride);
 }
 
+// The vector kernels with dot products: workgroups of 512 threads, a thread owns one column of every (512 / T)-th row, four
+// rows at a time with all their loads ahead of the first use.  Up to 32768 points there is one workgroup a system on a compute
+// unit, so what bounds them is how many loads are in flight; beyond, HBM.  Update of two systems of 32768 x 17 values with 256
+// threads and a row at a time 22.0 us, now 13.9 (1024 threads: 18.9), of one of 131072 20.8 / 21.0 (28.6), of 262144 40 / 34; the
+// product's last pass 11.7 / 7.3, 14.9 / 13.2, 28 / 25.
+constexpr int VB = 512;
+constexpr int ROWS_AT_ONCE = 4;
+// sums[col] of the workgroup's VB values (thread = row of the pass times T + column), in a fixed order: eight groups of rows,
+// then the groups.  red holds the values; the result is valid for threads below T.
+__device__ __forceinline__ double column_sum(double* red, int T, int tid) {
+  const int rpp = VB / T, g = tid / T;
+  __syncthreads();
+  double s = 0.0;
+  if (g < 8) {
+    for (int k = g; k < rpp; k += 8) s += red[k * T + tid - g * T];
+  }
+  __syncthreads();
+  if (g < 8) red[tid] = s;
+  __syncthreads();
+  if (tid < T)
+    for (int k = 1; k < 8 && k < rpp; ++k) s += red[k * T + tid];
+  return s;
+}
+
 // ---------------------------------------------------------------------------
 // per-column dot products: partial[which][block][col] = sum over the block's rows
 // ---------------------------------------------------------------------------
 template <int NP, typename VT>
-__global__ __launch_bounds__(256) void k_dot(const VT* __restrict__ A0, const VT* __restrict__ B0,
-                                             const VT* __restrict__ A1, const VT* __restrict__ B1,
-                                             int64_t n, int T, double* __restrict__ partial, uint64_t sa, uint64_t sb, uint64_t sys) {
-  __shared__ double red[NP][256];
+__global__ __launch_bounds__(VB) void k_dot(const VT* __restrict__ A0, const VT* __restrict__ B0,
+                                            const VT* __restrict__ A1, const VT* __restrict__ B1,
+                                            int64_t n, int T, double* __restrict__ partial, uint64_t sa, uint64_t sb, uint64_t sys) {
+  __shared__ double red[NP][VB];
   A0 = of_system(A0, sa); B0 = of_system(B0, sb);
   A1 = of_system(A1, sa); B1 = of_system(B1, sb);
   partial = of_system(partial, sys);
-  const int rpp = 256 / T;                      // rows per pass
+  const int rpp = VB / T;                       // rows per pass
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
-  const bool live = myrow < rpp;
   const int64_t rows_per_block = (n + gridDim.x - 1) / gridDim.x;
   const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
   const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
   double s0 = 0.0, s1 = 0.0;
-  if (live) {
-    for (int64_t r = r0 + myrow; r < r1; r += rpp) {
-      const int64_t idx = r * T + col;
-      s0 = fma((double)A0[idx], (double)B0[idx], s0);
-      if (NP > 1) s1 = fma((double)A1[idx], (double)B1[idx], s1);
+  if (myrow < rpp) {
+    for (int64_t r = r0 + myrow; r < r1; r += ROWS_AT_ONCE * rpp) {
+      VT a0[ROWS_AT_ONCE], b0[ROWS_AT_ONCE], a1[ROWS_AT_ONCE], b1[ROWS_AT_ONCE];
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j) {
+        const int64_t idx = (r + j * rpp < r1 ? r + j * rpp : r) * T + col;
+        a0[j] = A0[idx]; b0[j] = B0[idx];
+        if (NP > 1) { a1[j] = A1[idx]; b1[j] = B1[idx]; }
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j)
+        if (r + j * rpp < r1) {
+          s0 = fma((double)a0[j], (double)b0[j], s0);
+          if (NP > 1) s1 = fma((double)a1[j], (double)b1[j], s1);
+        }
     }
   }
   red[0][tid] = s0;
   if (NP > 1) red[NP - 1][tid] = s1;
-  __syncthreads();
-  if (tid < T) {
-    for (int w = 0; w < NP; ++w) {
-      double s = 0.0;
-      for (int k = 0; k < rpp; ++k) s += red[w][k * T + tid];
-      partial[((int64_t)w * gridDim.x + blockIdx.x) * MAX_COLS + tid] = s;
-    }
+  for (int w = 0; w < NP; ++w) {
+    const double s = column_sum(red[w], T, tid);
+    if (tid < T) partial[((int64_t)w * gridDim.x + blockIdx.x) * MAX_COLS + tid] = s;
   }
 }
 
@@ -240,16 +269,15 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
 // 271 / 273 at 32768 (256), 304 / 302 at 40960 (320), 372 / 351 at 65536 (512), 664 / 579 at 131072 (1024).
 constexpr int FUSE_BLOCKS = 256;
 __device__ __forceinline__ void sum_all_partials(const double* __restrict__ partial, int nblocks, int T, double* red, double* out) {
-  const int rpp = 256 / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
+  const int rpp = VB / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
   double s = 0.0;
-  if (myrow < rpp)
+  if (myrow < rpp) {
+#pragma unroll 4
     for (int b = myrow; b < nblocks; b += rpp) s += partial[(int64_t)b * MAX_COLS + col];
-  red[tid] = s;
-  __syncthreads();
-  if (tid < T) {
-    for (int k = 1; k < rpp; ++k) s += red[k * T + tid];
-    out[tid] = s;
   }
+  red[tid] = s;
+  s = column_sum(red, T, tid);
+  if (tid < T) out[tid] = s;
   __syncthreads();
 }
 
@@ -259,20 +287,20 @@ __device__ __forceinline__ void sum_all_partials(const double* __restrict__ part
 // (the stop test) and, when B is given, partial[1] = sums of b x_new (the quadratic form of the end-of-solve
 // report).  Rows are split among the workgroups as in k_dot, so the sums are those k_dot would produce.
 template <typename VT>
-__global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* R, const VT* Rin,
+__global__ __launch_bounds__(VB) void k_update_xr_dots(VT* __restrict__ X, VT* R, const VT* Rin,
                                                         const VT* __restrict__ D, const VT* __restrict__ Q,
                                                         const VT* __restrict__ B, PcgState* __restrict__ st,
                                                         int64_t n, int T, int first, double* __restrict__ partial,
                                                         const double* __restrict__ dqs, int iter, double* __restrict__ alog,
                                                         uint64_t sys, uint64_t s_in, uint64_t s_d, uint64_t s_b) {
-  __shared__ double red[2][256];
+  __shared__ double red[2][VB];
   __shared__ double al[MAX_COLS];
   X = of_system(X, sys); R = of_system(R, sys); Q = of_system(Q, sys);
   Rin = of_system(Rin, s_in); D = of_system(D, s_d);
   if (B) B = of_system(B, s_b);
   st = of_system(st, sys); partial = of_system(partial, sys); alog = of_system(alog, sys);
   if (dqs) dqs = of_system(dqs, sys);
-  const int rpp = 256 / T;
+  const int rpp = VB / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -297,41 +325,49 @@ __global__ __launch_bounds__(256) void k_update_xr_dots(VT* __restrict__ X, VT* 
   double s0 = 0.0, s1 = 0.0;
   if (live) {
     const double a = dqs ? al[col] : st->alpha[col];
-    for (int64_t r = r0 + myrow; r < r1; r += rpp) {
-      const int64_t idx = r * T + col;
-      const VT xn = first ? (VT)(a * (double)D[idx]) : (VT)fma(a, (double)D[idx], (double)X[idx]);
-      const VT rn = (VT)fma(-a, (double)Q[idx], (double)Rin[idx]);
-      X[idx] = xn;
-      R[idx] = rn;
-      s0 = fma((double)rn, (double)rn, s0);
-      if (B) s1 = fma((double)B[idx], (double)xn, s1);
+    for (int64_t r = r0 + myrow; r < r1; r += ROWS_AT_ONCE * rpp) {
+      VT d[ROWS_AT_ONCE], q[ROWS_AT_ONCE], x[ROWS_AT_ONCE], b[ROWS_AT_ONCE], ri[ROWS_AT_ONCE];
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j) {
+        const int64_t idx = (r + j * rpp < r1 ? r + j * rpp : r) * T + col;
+        d[j] = D[idx]; q[j] = Q[idx]; ri[j] = Rin[idx];
+        if (!first) x[j] = X[idx];
+        if (B) b[j] = B[idx];
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j)
+        if (r + j * rpp < r1) {
+          const int64_t idx = (r + j * rpp) * T + col;
+          const VT xn = first ? (VT)(a * (double)d[j]) : (VT)fma(a, (double)d[j], (double)x[j]);
+          const VT rn = (VT)fma(-a, (double)q[j], (double)ri[j]);
+          X[idx] = xn;
+          R[idx] = rn;
+          s0 = fma((double)rn, (double)rn, s0);
+          if (B) s1 = fma((double)b[j], (double)xn, s1);
+        }
     }
   }
   red[0][tid] = s0;
   red[1][tid] = s1;
-  __syncthreads();
-  if (tid < T) {
-    for (int w = 0; w < 2; ++w) {
-      double sacc = 0.0;
-      for (int k = 0; k < rpp; ++k) sacc += red[w][k * T + tid];
-      partial[((int64_t)w * gridDim.x + blockIdx.x) * MAX_COLS + tid] = sacc;
-    }
+  for (int w = 0; w < 2; ++w) {
+    const double s = column_sum(red[w], T, tid);
+    if (tid < T) partial[((int64_t)w * gridDim.x + blockIdx.x) * MAX_COLS + tid] = s;
   }
 }
 
 // D = Z + D diag(beta) for active columns, 0 for stopped ones
 template <typename VT>
-__global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT* __restrict__ Z,
+__global__ __launch_bounds__(VB) void k_update_d(VT* D, const VT* Din, const VT* __restrict__ Z,
                                                   PcgState* __restrict__ st, int64_t n, int T,
                                                   const double* __restrict__ rzs, int nblocks, int iter, double* __restrict__ blog,
                                                   uint64_t sys, uint64_t s_d) {
   D = of_system(D, sys); Din = of_system(Din, s_d); Z = of_system(Z, sys);
   st = of_system(st, sys); blog = of_system(blog, sys);
   if (rzs) rzs = of_system(rzs, sys);
-  __shared__ double red[256];
+  __shared__ double red[VB];
   __shared__ double be[MAX_COLS];
   __shared__ int goes_on[MAX_COLS];
-  const int rpp = 256 / T;
+  const int rpp = VB / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   if (rzs) {                                   // the step of k_pcg_beta (beta itself can be negative: rho_0 may be, by rounding)
@@ -354,9 +390,17 @@ __global__ __launch_bounds__(256) void k_update_d(VT* D, const VT* Din, const VT
   if (myrow >= rpp) return;
   const double bta = rzs ? be[col] : st->beta[col];
   const bool act = rzs ? goes_on[col] != 0 : st->active[col] != 0;
-  for (int64_t r = (int64_t)blockIdx.x * rpp + myrow; r < n; r += (int64_t)gridDim.x * rpp) {
-    const int64_t idx = r * T + col;
-    D[idx] = act ? (VT)fma(bta, (double)Din[idx], (double)Z[idx]) : (VT)0;
+  const int64_t step = (int64_t)gridDim.x * rpp;
+  for (int64_t r = (int64_t)blockIdx.x * rpp + myrow; r < n; r += ROWS_AT_ONCE * step) {
+    VT z[ROWS_AT_ONCE], d[ROWS_AT_ONCE];
+#pragma unroll
+    for (int j = 0; j < ROWS_AT_ONCE; ++j) {
+      const int64_t idx = (r + j * step < n ? r + j * step : r) * T + col;
+      z[j] = Z[idx]; d[j] = Din[idx];
+    }
+#pragma unroll
+    for (int j = 0; j < ROWS_AT_ONCE; ++j)
+      if (r + j * step < n) D[(r + j * step) * T + col] = act ? (VT)fma(bta, (double)d[j], (double)z[j]) : (VT)0;
   }
 }
 
@@ -453,14 +497,14 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
 // k_onehot_expand_dot; may be null)
 struct Combination { double a[MAX_SLOTS], b[MAX_SLOTS]; };
 template <typename VT>
-__global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const VT* __restrict__ Q0,
+__global__ __launch_bounds__(VB) void k_lincomb_dot(VT* __restrict__ Q, const VT* __restrict__ Q0,
                                                      const VT* __restrict__ D, Combination of, int64_t n, int T,
                                                      double* __restrict__ partial, uint64_t sys) {
-  __shared__ double red[256];
+  __shared__ double red[VB];
   const double a = of.a[blockIdx.y], b = of.b[blockIdx.y];
   Q = of_system(Q, sys);
   if (partial) partial = of_system(partial, sys);
-  const int rpp = 256 / T;
+  const int rpp = VB / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -469,21 +513,25 @@ __global__ __launch_bounds__(256) void k_lincomb_dot(VT* __restrict__ Q, const V
   const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
   double s0 = 0.0;
   if (live) {
-    for (int64_t p = r0 + myrow; p < r1; p += rpp) {
-      const int64_t idx = p * T + col;
-      const double d = (double)D[idx];
-      const VT qn = (VT)fma(a, (double)Q0[idx], b * d);
-      Q[idx] = qn;
-      s0 = fma(d, (double)qn, s0);
+    for (int64_t p = r0 + myrow; p < r1; p += ROWS_AT_ONCE * rpp) {
+      VT d[ROWS_AT_ONCE], q[ROWS_AT_ONCE];
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j) {
+        const int64_t idx = (p + j * rpp < r1 ? p + j * rpp : p) * T + col;
+        d[j] = D[idx]; q[j] = Q0[idx];
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j)
+        if (p + j * rpp < r1) {
+          const VT qn = (VT)fma(a, (double)q[j], b * (double)d[j]);
+          Q[(p + j * rpp) * T + col] = qn;
+          s0 = fma((double)d[j], (double)qn, s0);
+        }
     }
   }
   red[tid] = s0;
-  __syncthreads();
-  if (partial && tid < T) {
-    double sacc = 0.0;
-    for (int k = 0; k < rpp; ++k) sacc += red[k * T + tid];
-    partial[(int64_t)blockIdx.x * MAX_COLS + tid] = sacc;
-  }
+  const double sum = column_sum(red, T, tid);
+  if (partial && tid < T) partial[(int64_t)blockIdx.x * MAX_COLS + tid] = sum;
 }
 
 static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D = nullptr, double* dq_partial = nullptr,
@@ -518,8 +566,8 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, v
       of.b[e] = ops[e].shift - of.a[e] * c->q0_shift;
     }
     const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
-    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), nb, dim3(256), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, of, (int64_t)L.n, T, dq_partial, sys);
-    else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(256), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
+    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), nb, dim3(VB), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, of, (int64_t)L.n, T, dq_partial, sys);
+    else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(VB), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
     NUGPR_HIP(hipGetLastError());
     if (dq_done) *dq_done = dq_partial != nullptr;
     c->stats.products_reused += nsys;
@@ -673,14 +721,14 @@ __global__ __launch_bounds__(256) void k_onehot_expand(const VT* Q, const VT* __
 // the same with the reduction that follows a product in the solver: partial = per-workgroup sums of d q_new
 // per column, rows split among the workgroups as in k_dot
 template <typename VT>
-__global__ __launch_bounds__(256) void k_onehot_expand_dot(VT* __restrict__ Q, const VT* __restrict__ P,
+__global__ __launch_bounds__(VB) void k_onehot_expand_dot(VT* __restrict__ Q, const VT* __restrict__ P,
                                                            const int32_t* __restrict__ assign,
                                                            const VT* __restrict__ D, int64_t n, int T,
                                                            double* __restrict__ partial, int parts, uint64_t stride, uint64_t sys, uint64_t s_d) {
-  __shared__ double red[256];
+  __shared__ double red[VB];
   Q = of_system(Q, sys); P = of_system(P, sys); partial = of_system(partial, sys);
   D = of_system(D, s_d);
-  const int rpp = 256 / T;
+  const int rpp = VB / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -689,20 +737,30 @@ __global__ __launch_bounds__(256) void k_onehot_expand_dot(VT* __restrict__ Q, c
   const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
   double s0 = 0.0;
   if (live) {
-    for (int64_t p = r0 + myrow; p < r1; p += rpp) {
-      const int64_t idx = p * T + col;
-      const VT qn = (VT)((double)Q[idx] + coupling_value(P, (int64_t)assign[p] * T + col, parts, stride));
-      Q[idx] = qn;
-      s0 = fma((double)D[idx], (double)qn, s0);
+    for (int64_t p = r0 + myrow; p < r1; p += ROWS_AT_ONCE * rpp) {
+      VT d[ROWS_AT_ONCE], q[ROWS_AT_ONCE];
+      int32_t a[ROWS_AT_ONCE];
+      double w[ROWS_AT_ONCE];
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j) {
+        const int64_t row = p + j * rpp < r1 ? p + j * rpp : p;
+        a[j] = assign[row];
+        d[j] = D[row * T + col]; q[j] = Q[row * T + col];
+      }
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j) w[j] = coupling_value(P, (int64_t)a[j] * T + col, parts, stride);
+#pragma unroll
+      for (int j = 0; j < ROWS_AT_ONCE; ++j)
+        if (p + j * rpp < r1) {
+          const VT qn = (VT)((double)q[j] + w[j]);
+          Q[(p + j * rpp) * T + col] = qn;
+          s0 = fma((double)d[j], (double)qn, s0);
+        }
     }
   }
   red[tid] = s0;
-  __syncthreads();
-  if (tid < T) {
-    double sacc = 0.0;
-    for (int k = 0; k < rpp; ++k) sacc += red[k * T + tid];
-    partial[(int64_t)blockIdx.x * MAX_COLS + tid] = sacc;
-  }
+  const double sum = column_sum(red, T, tid);
+  if (tid < T) partial[(int64_t)blockIdx.x * MAX_COLS + tid] = sum;
 }
 
 static int elementwise_grid(int64_t n, int T);
@@ -745,8 +803,8 @@ static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D
   if (c->onehot && dq_partial) {
     const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
     const uint64_t sys = L.slot_bytes;
-    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), nb, dim3(256), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
-    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), nb, dim3(256), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
+    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), nb, dim3(VB), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
+    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), nb, dim3(VB), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -847,7 +905,7 @@ static int dot2_t(nugpr_ctx* c, const VT* A0, const VT* B0, const VT* A1, const 
                   double* out1, hipStream_t s) {
   const Layout& L = c->L;
   const int nb = L.n_dot_blocks;
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart, (uint64_t)0, (uint64_t)0, (uint64_t)0);
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart, (uint64_t)0, (uint64_t)0, (uint64_t)0);
   NUGPR_HIP(hipGetLastError());
   NUGPR_HIP(hipMemcpyAsync(c->h_buf, c->dotpart, (size_t)2 * nb * MAX_COLS * sizeof(double), hipMemcpyDeviceToHost, s));
   NUGPR_HIP(hipStreamSynchronize(s));
@@ -878,7 +936,9 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   const bool extras = out[0].extras != nullptr;
   const int64_t n = L.n;
   const int nb = L.n_dot_blocks;
-  const int eg = elementwise_grid(n, T);
+  // workgroups of the direction update: four rows a thread, and where each of them adds up the partial sums first, no more than two
+  // on a compute unit
+  const int eg = (int)std::min<int64_t>((n + ROWS_AT_ONCE * (VB / T) - 1) / (ROWS_AT_ONCE * (VB / T)), nb <= FUSE_BLOCKS ? 512 : 4096);
   const double tol2 = c->params.tol * c->params.tol;
   const int max_iter = c->params.max_iter;
   int rc;
@@ -902,7 +962,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     // x_0 = 0, r_0 = b, d_0 = z_0 = M^-1 r_0 written straight into D
     hipLaunchKernelGGL((k_pcg_init<VT>), dim3(1024, ny), dim3(256), 0, s, X, R, B, plain ? B : (const VT*)nullptr, D, n * T, sys, s_b);
     if (!plain && (rc = run_precond(c, R, D, T, s, nsys))) return rc;
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(256), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
     hipLaunchKernelGGL(k_pcg_begin, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, sys);
   }
   NUGPR_HIP(hipGetLastError());
@@ -936,7 +996,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   // (its <b, x> sums were left in the second partial set by the update kernel of the same iteration)
   auto issue_tail = [&](int rows, bool bx_ready) -> int {
     if (extras && !bx_ready)
-      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(256), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
+      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
     c->tail_seq += 1;
     hipLaunchKernelGGL(k_pcg_tail, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, extras ? 1 : 0, c->alog,
                        c->blog, want_logs ? rows : 0, hs, hdot, c->h_buf, c->h_buf + cnt, c->h_flags, c->tail_seq, sys, hsys);
@@ -948,11 +1008,11 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     bool dq_done = false;
     if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : product(c, ops, nsys, Dcur, Q, T, s, dq_sums, &dq_done, nullptr, nullptr))) return rc;
     if (!dq_done)
-      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(256), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
+      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
     // the update, fused with ||r||^2 for the stop test and, in the iteration expected to be the last, <b, x>
     const bool report = it + 1 >= expect || it + 1 >= max_iter;
-    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(256), 0, s, X, R, first ? B : (const VT*)R, Dcur,
+    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(VB), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
                        c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b);
     first = false;
@@ -979,9 +1039,9 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
       if (n_active == 0 || it >= max_iter) break;
     }
     if (!plain && (rc = run_precond(c, R, Z, T, s, nsys))) return rc;
-    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(256), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
+    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, rz_sums, nb, j, c->blog);
-    hipLaunchKernelGGL((k_update_d<VT>), dim3(fuse ? std::min(eg, 512) : eg, ny), dim3(256), 0, s, D, Dcur, Zr, c->d_state, n, T,
+    hipLaunchKernelGGL((k_update_d<VT>), dim3(eg, ny), dim3(VB), 0, s, D, Dcur, Zr, c->d_state, n, T,
                        fuse ? rz_sums : (const double*)nullptr, nb, j, c->blog, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     Dcur = D;
@@ -1046,10 +1106,10 @@ static int store_known_t(nugpr_ctx* c, hipStream_t s) {
   const int nb = L.n_dot_blocks;
   const VT *B = (const VT*)c->Bv, *Z0 = (const VT*)c->Z0v, *P = (const VT*)c->Pv;
   const uint64_t one = 0;                // (one system)
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart, one, one, one);
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart, one, one, one);
   hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 0);
   if (L.t > 0) {
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(256), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart, one, one, one);
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart, one, one, one);
     hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 1);
   }
   NUGPR_HIP(hipGetLastError());
