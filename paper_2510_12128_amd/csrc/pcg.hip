@@ -125,35 +125,7 @@ __device__ __forceinline__ double sum_partials(const double* __restrict__ partia
 // gathered by the last workgroup of the stop test (k_pcg_check).
 
 // start of a solve: ||b||^2 and rho_0 = <r_0, z_0>
-__global__ __launch_bounds__(256) void k_pcg_begin(PcgState* __restrict__ st, const double* __restrict__ partial,
-                                                   int nblocks, uint64_t sys) {
-  __shared__ double red[256];
-  const int tid = threadIdx.x, c = blockIdx.x;
-  st = of_system(st, sys);
-  partial = of_system(partial, sys);
-  const double bb = sum_partials(partial, nblocks, c, red, tid);
-  const double rz = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
-  if (tid == 0) {
-    const bool act = bb > 0.0 && rz == rz;
-    st->bnorm2[c] = bb;
-    st->rho[0][c] = rz;
-    st->rho0[c] = rz;
-    st->alpha[c] = 0.0;
-    st->beta[c] = 0.0;
-    st->active[c] = act ? 1 : 0;
-    st->iters[c] = 0;
-    st->converged[c] = (bb == 0.0) ? 1 : 0;
-    st->indef[c] = 0;
-  }
-}
-
-// the same from the values kept with the factor (which = 0: [y | L Z], 1: the probe block)
-__global__ void k_pcg_begin_known(PcgState* st, int which, int T, uint64_t sys) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= T) return;
-  const double bb = st->known_bb[which][c], rz = st->known_rz[which][c];      // (kept by system 0)
-  st = of_system(st, sys);
-  const bool act = bb > 0.0 && rz == rz;
+__device__ __forceinline__ void begin_column(PcgState* st, int c, double bb, double rz, bool act) {
   st->bnorm2[c] = bb;
   st->rho[0][c] = rz;
   st->rho0[c] = rz;
@@ -163,6 +135,25 @@ __global__ void k_pcg_begin_known(PcgState* st, int which, int T, uint64_t sys) 
   st->iters[c] = 0;
   st->converged[c] = (bb == 0.0) ? 1 : 0;
   st->indef[c] = 0;
+}
+__global__ __launch_bounds__(256) void k_pcg_begin(PcgState* __restrict__ st, const double* __restrict__ partial,
+                                                   int nblocks, uint64_t sys) {
+  __shared__ double red[256];
+  const int tid = threadIdx.x, c = blockIdx.x;
+  st = of_system(st, sys);
+  partial = of_system(partial, sys);
+  const double bb = sum_partials(partial, nblocks, c, red, tid);
+  const double rz = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
+  if (tid == 0) begin_column(st, c, bb, rz, bb > 0.0 && rz == rz);
+}
+
+// the same from the values kept with the factor (which = 0: [y | L Z], 1: the probe block), where the update kernel does
+// not see to it
+__global__ void k_pcg_begin_known(PcgState* st, int which, int T) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= T) return;
+  const double bb = st->known_bb[which][c], rz = st->known_rz[which][c];
+  begin_column(st, c, bb, rz, bb > 0.0 && rz == rz);
 }
 
 __global__ __launch_bounds__(256) void k_store_known(PcgState* __restrict__ st, const double* __restrict__ partial,
@@ -191,12 +182,34 @@ __global__ __launch_bounds__(256) void k_pcg_alpha(PcgState* __restrict__ st, co
   }
 }
 
+// End-of-solve report, written by the device straight into pinned host memory: the per-column state, <b_c, x_c> summed from the
+// per-workgroup partials (fixed order), and the first `rows` rows of the alpha / beta logs.  It comes with the stop test of the
+// iteration that is expected to be the last (k_pcg_check; a kernel of its own, 5 - 7 us, otherwise: k_pcg_tail).
+struct Report {
+  uint64_t seq;                    // 0: none
+  int want_bx, rows;
+  const double *alog, *blog;       // (of system 0, as the host's)
+  PcgState* h_state;
+  double *h_bx, *h_alog, *h_blog;
+  uint64_t hsys;                   // bytes from a system's part of the host buffer to the next one's
+};
+// what state and logs a report holds, by `threads` threads; state read past what this workgroup has cached
+__device__ __forceinline__ void copy_report(const PcgState* st, const Report& r, uint64_t sys, int at, int threads) {
+  const int words = (int)(sizeof(PcgState) / sizeof(int32_t));
+  const volatile int32_t* src = reinterpret_cast<const volatile int32_t*>(st);
+  int32_t* dst = reinterpret_cast<int32_t*>(of_system(r.h_state, r.hsys));
+  for (int i = at; i < words; i += threads) dst[i] = src[i];
+  const double *alog = of_system(r.alog, sys), *blog = of_system(r.blog, sys);
+  double *h_alog = of_system(r.h_alog, r.hsys), *h_blog = of_system(r.h_blog, r.hsys);
+  for (int i = at; i < r.rows * MAX_COLS; i += threads) { h_alog[i] = alog[i]; h_blog[i] = blog[i]; }
+}
+
 // after the update: stop test on ||r_c|| (columns that meet it are frozen).  The workgroup that finishes
 // last gathers the cross-column bookkeeping (how many columns are still active, did any meet negative
 // curvature) and publishes it to the host: the flags, a system-scope fence, then the sequence number.
 __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, const double* __restrict__ partial,
                                                    int nblocks, int iter, double tol2, int T,
-                                                   HostFlags* __restrict__ out, uint64_t seq, uint64_t sys) {
+                                                   HostFlags* __restrict__ out, uint64_t seq, uint64_t sys, Report report) {
   __shared__ double red[256];
   __shared__ int last;
   const int tid = threadIdx.x, c = blockIdx.x;
@@ -204,6 +217,13 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
   partial = of_system(partial, sys);
   out += blockIdx.y;
   const double rr = sum_partials(partial, nblocks, c, red, tid);
+  if (report.seq && report.want_bx) {
+    const double bx = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
+    if (tid == 0) {
+      of_system(report.h_bx, report.hsys)[c] = bx;
+      __threadfence_system();
+    }
+  }
   if (tid == 0) {
     if (st->active[c]) {
       st->iters[c] = iter + 1;
@@ -219,7 +239,8 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
     last = (atomicAdd(&st->check_count, 1) == T - 1);
   }
   __syncthreads();
-  if (last && tid < 64) {                      // one wave, a lane per column (one after the other: 4 us)
+  if (!last) return;
+  if (tid < 64) {                              // one wave, a lane per column (one after the other: 4 us)
     __threadfence();
     int act = 0, ind = 0;
     if (tid < T) {
@@ -227,15 +248,28 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
       ind = *reinterpret_cast<volatile int32_t*>(&st->indef[tid]);
     }
     const int n_active = __popcll(__ballot(act != 0)), indef = __ballot(ind != 0) != 0 ? 1 : 0;
-    if (tid != 0) return;
-    st->check_count = 0;
-    if (iter == 0 || st->n_active != 0) st->steps = iter + 1;       // (n_active: what the test before this one found)
-    st->n_active = n_active;
-    st->indefinite = indef;
-    out->n_active = n_active;
-    out->indefinite = indef;
-    out->bad_cluster = st->bad_cluster;
-    __threadfence_system();
+    if (tid == 0) {
+      st->check_count = 0;
+      if (iter == 0 || st->n_active != 0) st->steps = iter + 1;     // (n_active: what the test before this one found)
+      st->n_active = n_active;
+      st->indefinite = indef;
+      out->n_active = n_active;
+      out->indefinite = indef;
+      out->bad_cluster = st->bad_cluster;
+      if (!report.seq) {
+        __threadfence_system();
+        *reinterpret_cast<volatile uint64_t*>(&out->seq) = seq;
+      }
+    }
+  }
+  if (!report.seq) return;
+  __threadfence();
+  __syncthreads();                             // the state is what the other workgroups and thread 0 left
+  copy_report(st, report, sys, tid, 256);
+  __threadfence_system();
+  __syncthreads();
+  if (tid == 0) {
+    *reinterpret_cast<volatile uint64_t*>(&out->tail_seq) = report.seq;
     *reinterpret_cast<volatile uint64_t*>(&out->seq) = seq;
   }
 }
@@ -292,8 +326,9 @@ __global__ __launch_bounds__(VB) void k_update_xr_dots(VT* __restrict__ X, VT* R
                                                         const VT* __restrict__ B, PcgState* __restrict__ st,
                                                         int64_t n, int T, int first, double* __restrict__ partial,
                                                         const double* __restrict__ dqs, int iter, double* __restrict__ alog,
-                                                        uint64_t sys, uint64_t s_in, uint64_t s_d, uint64_t s_b) {
+                                                        uint64_t sys, uint64_t s_in, uint64_t s_d, uint64_t s_b, int known) {
   __shared__ double red[2][VB];
+  const PcgState* st0 = st;                    // (system 0's: keeps the values of the context's own right-hand sides)
   __shared__ double al[MAX_COLS];
   X = of_system(X, sys); R = of_system(R, sys); Q = of_system(Q, sys);
   Rin = of_system(Rin, s_in); D = of_system(D, s_d);
@@ -308,10 +343,20 @@ __global__ __launch_bounds__(VB) void k_update_xr_dots(VT* __restrict__ X, VT* R
     sum_all_partials(dqs, (int)gridDim.x, T, &red[0][0], al);
     if (tid < T) {
       const double dq = al[tid];
-      const bool act = st->active[tid] != 0;
-      const double a = act && dq > 0.0 ? st->rho[iter & 1][tid] / dq : 0.0;
+      bool act;
+      double rho, bb = 0.0;
+      if (known >= 0) {                        // first step of such a solve: the start of k_pcg_begin_known as well
+        bb = st0->known_bb[known][tid];
+        rho = st0->known_rz[known][tid];
+        act = bb > 0.0 && rho == rho;
+      } else {
+        rho = st->rho[iter & 1][tid];
+        act = st->active[tid] != 0;
+      }
+      const double a = act && dq > 0.0 ? rho / dq : 0.0;
       al[tid] = a;
       if (blockIdx.x == 0) {
+        if (known >= 0) begin_column(st, tid, bb, rho, act);
         if (act && !(dq > 0.0)) { st->indef[tid] = 1; st->active[tid] = 0; }
         st->alpha[tid] = a;
         alog[(int64_t)iter * MAX_COLS + tid] = a;
@@ -404,32 +449,20 @@ __global__ __launch_bounds__(VB) void k_update_d(VT* D, const VT* Din, const VT*
   }
 }
 
-// End-of-solve report, written by the device straight into pinned host memory: the per-column state,
-// <b_c, x_c> summed from the per-workgroup partials (fixed order), and the first `rows` rows of the
-// alpha / beta logs.  One workgroup per column (each sums its column; they share the copies); the
+// The report by itself (partial: the sums of b x).  One workgroup per column (each sums its column; they share the copies); the
 // workgroup that finishes last publishes the sequence number.
 __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, const double* __restrict__ partial,
-                                                  int nblocks, int T, int want_bx, const double* __restrict__ alog,
-                                                  const double* __restrict__ blog, int rows,
-                                                  PcgState* __restrict__ h_state, double* __restrict__ h_bx,
-                                                  double* __restrict__ h_alog, double* __restrict__ h_blog,
-                                                  HostFlags* __restrict__ flags, uint64_t seq, uint64_t sys, uint64_t hsys) {
+                                                  int nblocks, int T, Report report, HostFlags* __restrict__ flags, uint64_t sys) {
   __shared__ double red[256];
   __shared__ int last;
   const int tid = threadIdx.x, c = blockIdx.x;
-  st = of_system(st, sys); partial = of_system(partial, sys); alog = of_system(alog, sys); blog = of_system(blog, sys);
-  h_state = of_system(h_state, hsys); h_bx = of_system(h_bx, hsys); h_alog = of_system(h_alog, hsys); h_blog = of_system(h_blog, hsys);
+  st = of_system(st, sys); partial = of_system(partial, sys);
   flags += blockIdx.y;
-  if (want_bx) {
+  if (report.want_bx) {
     const double v = sum_partials(partial, nblocks, c, red, tid);
-    if (tid == 0) h_bx[c] = v;
+    if (tid == 0) of_system(report.h_bx, report.hsys)[c] = v;
   }
-  const int words = (int)(sizeof(PcgState) / sizeof(int32_t));
-  const int32_t* src = reinterpret_cast<const int32_t*>(st);
-  int32_t* dst = reinterpret_cast<int32_t*>(h_state);
-  for (int i = c * 256 + tid; i < words; i += 256 * T) dst[i] = src[i];
-  const int cnt = rows * MAX_COLS;
-  for (int i = c * 256 + tid; i < cnt; i += 256 * T) { h_alog[i] = alog[i]; h_blog[i] = blog[i]; }
+  copy_report(st, report, sys, c * 256 + tid, 256 * T);
   __threadfence_system();
   __syncthreads();
   if (tid == 0) last = (atomicAdd(&st->tail_count, 1) == T - 1);
@@ -437,7 +470,7 @@ __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, con
   if (last && tid == 0) {
     st->tail_count = 0;
     __threadfence_system();
-    *reinterpret_cast<volatile uint64_t*>(&flags->tail_seq) = seq;
+    *reinterpret_cast<volatile uint64_t*>(&flags->tail_seq) = report.seq;
   }
 }
 
@@ -956,7 +989,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   uint64_t s_d = own ? 0 : sys;
   const VT* Dcur = D;                    // the direction the operator is applied to
   if (own) {
-    hipLaunchKernelGGL(k_pcg_begin_known, dim3(1, ny), dim3(64), 0, s, c->d_state, plain ? 1 : 0, T, sys);
+    if (nb > FUSE_BLOCKS) hipLaunchKernelGGL(k_pcg_begin_known, dim3(1), dim3(64), 0, s, c->d_state, plain ? 1 : 0, T);
     Dcur = plain ? B : (const VT*)c->Z0v;
   } else {
     // x_0 = 0, r_0 = b, d_0 = z_0 = M^-1 r_0 written straight into D
@@ -989,17 +1022,19 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   if (rec.ncols != T) { rec.ncols = T; rec.last[0] = rec.last[1] = rec.last[2] = 1; }
   const int sure = fuse ? std::min(rec.last[0], std::min(rec.last[1], rec.last[2])) : 1;
   nugpr_stats counted = c->stats, counted_before = c->stats;      // after the product of the present iteration, and the last
-  // The end-of-solve report (k_pcg_tail) is issued INSIDE the iteration that is expected to be the last
-  // one, right behind its stop test, so that it is already on the host when the stop test says "done";
+  // The end-of-solve report comes with the stop test of the iteration that is expected to be the last
+  // one, so that it is already on the host when the stop test says "done";
   // a solve that ends earlier or later than the previous one of its kind gets the report after the loop.
   const int expect = c->expect_iters[plain ? 1 : 0];
   // (its <b, x> sums were left in the second partial set by the update kernel of the same iteration)
-  auto issue_tail = [&](int rows, bool bx_ready) -> int {
-    if (extras && !bx_ready)
-      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
+  auto next_report = [&](int rows) {
     c->tail_seq += 1;
-    hipLaunchKernelGGL(k_pcg_tail, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, extras ? 1 : 0, c->alog,
-                       c->blog, want_logs ? rows : 0, hs, hdot, c->h_buf, c->h_buf + cnt, c->h_flags, c->tail_seq, sys, hsys);
+    return Report{c->tail_seq, extras ? 1 : 0, want_logs ? rows : 0, c->alog, c->blog, hs, hdot, c->h_buf, c->h_buf + cnt, hsys};
+  };
+  auto issue_tail = [&](int rows) -> int {
+    if (extras)
+      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
+    hipLaunchKernelGGL(k_pcg_tail, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, next_report(rows), c->h_flags, sys);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   };
@@ -1014,18 +1049,14 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     const bool report = it + 1 >= expect || it + 1 >= max_iter;
     hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(VB), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
-                       c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b);
+                       c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b, fuse && own && it == 0 ? (plain ? 1 : 0) : -1);
     first = false;
     // stop test first: when every column has converged the preconditioner apply is not needed
     c->flag_seq += 1;
     hipLaunchKernelGGL(k_pcg_check, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, it, tol2, T, c->h_flags,
-                       c->flag_seq, sys);
+                       c->flag_seq, sys, report ? next_report(it + 1) : Report{});
     NUGPR_HIP(hipGetLastError());
-    tail_current = false;
-    if (report) {
-      if ((rc = issue_tail(it + 1, true))) return rc;
-      tail_current = true;
-    }
+    tail_current = report;
     const int j = it++;
     counted_before = counted;
     counted = c->stats;
@@ -1047,7 +1078,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     Dcur = D;
     s_d = sys;
   }
-  if (!tail_current && (rc = issue_tail(it, false))) return rc;
+  if (!tail_current && (rc = issue_tail(it))) return rc;
   for (int e = 0; e < nsys; ++e)
     if ((rc = wait_seq(&c->h_flags[e].tail_seq, c->tail_seq, s))) return rc;
   // NaN / Inf among the coordinates of the last assembly (found by its scaling kernel, which marks system 0's state)

@@ -87,11 +87,12 @@ __device__ __forceinline__ int acc_row(int lane, int i) {
 
 constexpr int NW = 4;                  // waves of a workgroup
 // What the items of a table are.  STRIP_STREAMED (added to the first and the last): matrix loads with the streaming hint.
-enum { STRIP_LONG = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2, STRIP_SHORT = 3, STRIP_STREAMED = 4 };
+// STRIP_MANY (added to the symmetric ones): up to 16 tiles a strip, more workgroups than three on a compute unit.
+enum { STRIP_LONG = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2, STRIP_SHORT = 3, STRIP_STREAMED = 4, STRIP_MANY = 8 };
 template <int NG, bool ACC64, int KIND> struct WaveCfg {
   typedef typename VecT<ACC64>::type VT;
   static constexpr int BASE = KIND & 3;
-  static constexpr bool SHORT = BASE == STRIP_SHORT;
+  static constexpr bool SHORT = BASE == STRIP_SHORT || (KIND & STRIP_MANY) != 0;
   // Waves per SIMD and steps in flight, as the registers allow.  Symmetric strips in fp64 with one column group: 3
   // waves x 3 stages 500 us, 2 x 4 527 us (workload in the file's head); long strips without partners, which stream from
   // HBM: 2 x 4 108 us, 3 x 3 117 us.  Short strips: see the file's head.
@@ -99,7 +100,7 @@ template <int NG, bool ACC64, int KIND> struct WaveCfg {
   static constexpr int STAGES = SHORT || (NG == 2 && !ACC64) ? 2 : (WAVES_PER_EU == 3 || NG == 2 ? 3 : 4);
   // Row groups of a wave: all four with a quarter of a tile's columns, or two with half of them (short strips of two
   // column groups: half the accumulators, so that four waves fit; the vector rows are then read twice)
-  static constexpr int ROW_GROUPS = SHORT && NG == 2 ? 2 : 4;
+  static constexpr int ROW_GROUPS = BASE == STRIP_SHORT && NG == 2 ? 2 : 4;
   // the vector operands of the next step are made ready while the matrix cores work on the present one
   static constexpr bool AHEAD = !SHORT;
   static constexpr int NB = NG > 0 ? NG : 1;
@@ -457,11 +458,12 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
   return NUGPR_OK;
 }
 
-bool short_strips(const std::vector<StripItem>& items) {
+static bool mean_tiles_up_to(const std::vector<StripItem>& items, uint64_t most) {
   uint64_t tiles = 0;
   for (const StripItem& it : items) tiles += it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0;
-  return tiles <= 10 * items.size();
+  return tiles <= most * items.size();
 }
+bool short_strips(const std::vector<StripItem>& items) { return mean_tiles_up_to(items, 10); }
 
 // Tables with strips of symmetric blocks take the instantiation that pairs their tiles, strips of a basis the caller
 // supplied the row-major one, triangular strips the short or the long one by their mean number of tiles.
@@ -475,7 +477,7 @@ bool short_strips(const std::vector<StripItem>& items) {
 // 60 / 66).  Row-major strips never gain: the basis is small beside the K_ii (96 x 2048 points, rank 256: 848 / 865 us).
 int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
   for (const StripItem& it : items)
-    if (it.blocked & 2u) return STRIP_SYM;
+    if (it.blocked & 2u) return mean_tiles_up_to(items, 16) ? STRIP_SYM + STRIP_MANY : STRIP_SYM;
   if (!items.empty() && items[0].blocked == 0) return STRIP_ROWMAJOR;
   return (short_strips(items) ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
 }
@@ -485,7 +487,12 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
 // Preconditioner apply, 33 columns, short / long: 4 uneven clusters of 700 points on average 73 / 64 us, 24 x 1000 (384
 // strips) 67 / 60, 64 x 300 (320) 33 / 35, 100 uneven ones of 300 (560) 53 / 54.  The other widths and the fp32 mode gain
 // as much by the shorter start as they lose (17 columns: 4 of 700 40 / 39, 24 x 1000 38 / 40).
+// Symmetric strips in fp64 with one column group, more of them than the 768 that three workgroups a compute unit make: with two
+// stages a fourth workgroup fits, which pays while a strip has few tiles.  Product of 17 columns, three stages / two: 512 clusters
+// of 128 points 52.0 / 48.7 us, 256 x 256 86.7 / 82.9, 128 x 512 64.2 / 63.2, 256 x 512 137.7 / 134.8, 128 x 1024 140.7 / 139.6, but
+// 64 x 1536 126.2 / 130.5, 64 x 2048 198.0 / 208.6, and 2000 x 64, whose coupling strips are long, 212.9 / 219.7.
 static int kind_at(const StripTable& tab, int count, int T, bool acc64) {
+  if (tab.kind & STRIP_MANY) return acc64 && T > 1 && T <= 17 && count > 768 ? tab.kind : tab.kind - STRIP_MANY;
   const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && count <= 512;
   return as_long ? tab.kind - STRIP_SHORT + STRIP_LONG : tab.kind;
 }
@@ -501,6 +508,9 @@ static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, con
   const int count = tab.count << a.sys_log2;
   switch (kind_at(tab, count, T, ACC64)) {
     case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, count, T, s, a);
+    case STRIP_SYM + STRIP_MANY:
+      if constexpr (ACC64) return launch_kind<1, true, STRIP_SYM + STRIP_MANY>(count, T, s, a);
+      break;
     case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, count, T, s, a);
     case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, count, T, s, a);
     case STRIP_ROWMAJOR: return launch_width<ACC64, STRIP_ROWMAJOR>(ng, count, T, s, a);
