@@ -251,6 +251,7 @@ void build_tables(const Layout& L, Tables& t) {
 int upload_table(const std::vector<StripItem>& v, uint64_t matrix_elems, StripItem*& cursor, StripTable& tab, hipStream_t s) {
   tab.dev = cursor;
   tab.count = (int)v.size();
+  tab.tiles = (int64_t)strip_tiles(v);
   tab.kind = strip_kind(v, matrix_elems * sizeof(float));
   if (!v.empty())
     NUGPR_HIP(hipMemcpyAsync(cursor, v.data(), v.size() * sizeof(StripItem), hipMemcpyHostToDevice, s));

@@ -111,6 +111,7 @@ struct StripArgs {
 struct StripTable {
   StripItem* dev = nullptr;
   int count = 0;
+  int64_t tiles = 0;     // of all items
   int kind = 0;          // which instantiation of the strip kernel serves it (strip_kind)
 };
 
@@ -343,6 +344,7 @@ inline int launch_strip(const StripTable& tab, const StripPort& p0, const StripP
 
 // up to 10 tiles an item on average
 bool short_strips(const std::vector<StripItem>& items);
+uint64_t strip_tiles(const std::vector<StripItem>& items);
 // the instantiation for a table of these items over a matrix of that size
 int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes);
 // its name for such a table and width (profilers' spelling, no namespace), valid until the thread's next call

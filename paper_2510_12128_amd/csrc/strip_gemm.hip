@@ -88,19 +88,23 @@ __device__ __forceinline__ int acc_row(int lane, int i) {
 constexpr int NW = 4;                  // waves of a workgroup
 // What the items of a table are.  STRIP_STREAMED (added to the first and the last): matrix loads with the streaming hint.
 // STRIP_MANY (added to the symmetric ones): up to 16 tiles a strip, more workgroups than three on a compute unit.
-enum { STRIP_LONG = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2, STRIP_SHORT = 3, STRIP_STREAMED = 4, STRIP_MANY = 8 };
+// STRIP_QUARTERS (added to symmetric and short ones): four workgroups a strip, one for each of its 16-row groups, where the
+// strips are too few for the chip: a wave's serial chain of matrix instructions is a quarter as long.
+enum { STRIP_LONG = 0, STRIP_SYM = 1, STRIP_ROWMAJOR = 2, STRIP_SHORT = 3, STRIP_STREAMED = 4, STRIP_MANY = 8, STRIP_QUARTERS = 16 };
 template <int NG, bool ACC64, int KIND> struct WaveCfg {
   typedef typename VecT<ACC64>::type VT;
   static constexpr int BASE = KIND & 3;
-  static constexpr bool SHORT = BASE == STRIP_SHORT || (KIND & STRIP_MANY) != 0;
+  static constexpr bool SHORT = (BASE == STRIP_SHORT && !(KIND & STRIP_QUARTERS)) || (KIND & STRIP_MANY) != 0;
   // Waves per SIMD and steps in flight, as the registers allow.  Symmetric strips in fp64 with one column group: 3
   // waves x 3 stages 500 us, 2 x 4 527 us (workload in the file's head); long strips without partners, which stream from
   // HBM: 2 x 4 108 us, 3 x 3 117 us.  Short strips: see the file's head.
-  static constexpr int WAVES_PER_EU = SHORT ? (NG == 1 && !ACC64 ? 3 : 4) : BASE == STRIP_SYM && ACC64 && NG == 1 ? 3 : 2;
-  static constexpr int STAGES = SHORT || (NG == 2 && !ACC64) ? 2 : (WAVES_PER_EU == 3 || NG == 2 ? 3 : 4);
+  static constexpr bool QUARTERS = (KIND & STRIP_QUARTERS) != 0;
+  static constexpr int WAVES_PER_EU = QUARTERS ? 2 : SHORT ? (NG == 1 && !ACC64 ? 3 : 4) : BASE == STRIP_SYM && ACC64 && NG == 1 ? 3 : 2;
+  static constexpr int STAGES = QUARTERS ? 4 : SHORT || (NG == 2 && !ACC64) ? 2 : (WAVES_PER_EU == 3 || NG == 2 ? 3 : 4);
   // Row groups of a wave: all four with a quarter of a tile's columns, or two with half of them (short strips of two
   // column groups: half the accumulators, so that four waves fit; the vector rows are then read twice)
-  static constexpr int ROW_GROUPS = BASE == STRIP_SHORT && NG == 2 ? 2 : 4;
+  static constexpr int ROW_GROUPS = QUARTERS ? 1 : BASE == STRIP_SHORT && NG == 2 ? 2 : 4;
+  static constexpr int SHARES = ROW_GROUPS == 2 ? 2 : 4;         // waves that share a row's columns
   // the vector operands of the next step are made ready while the matrix cores work on the present one
   static constexpr bool AHEAD = !SHORT;
   static constexpr int NB = NG > 0 ? NG : 1;
@@ -117,7 +121,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
   typedef typename Cfg::VT VT;
   constexpr bool RM = Cfg::BASE == STRIP_ROWMAJOR, SYM = Cfg::BASE == STRIP_SYM, TRI = !RM && !SYM;
   constexpr int ST = Cfg::STAGES, NB = Cfg::NB, NV = Cfg::NV, RG = Cfg::ROW_GROUPS;
-  constexpr int KP = RG, SP = 4 / RG;                        // waves that share a row's columns; steps of a wave in a tile
+  constexpr int KP = Cfg::SHARES, SP = 4 / KP;               // waves that share a row's columns; steps of a wave in a tile
   constexpr int HINT = (KIND & STRIP_STREAMED) ? 2 : 0;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 15, kg = lane >> 4;
   // which 16 SP columns of every 64-column tile are this wave's, and its first row group
-  const int part = KP == NW ? wave : wave % KP, g0 = KP == NW ? 0 : wave / KP * RG;
+  const int part = KP == NW ? wave : wave % KP, g0 = Cfg::QUARTERS ? (int)(blockIdx.x & 3u) : KP == NW ? 0 : wave / KP * RG;
   const uint32_t rowbytes = (uint32_t)T * (uint32_t)sizeof(VT);
 
   // What the loops need to know of an item.  Tile numbers p = 0 .. nb - 1 run from the item's first column on and are
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     const uint32_t off = tr ? toff : ooff;
 #pragma unroll
     for (int g = 0; g < RG; ++g) {
-      const int so = RM || !valid ? 0 : (tr ? ((g >> 1) * (TILE * BLK_COLS) + (g & 1) * FRAG) * 4 : (g0 + g) * 2 * FRAG * 4);
+      const int so = RM || !valid ? 0 : (tr ? (((g0 + g) >> 1) * (TILE * BLK_COLS) + ((g0 + g) & 1) * FRAG) * 4 : (g0 + g) * 2 * FRAG * 4);
       const uint32_t ro = RM ? (uint32_t)min(16 * (g0 + g) + m, S.nrows - 1) * S.lda * 4u + 16u * (uint32_t)kg : off;
       ra[g] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(res, ro, so, HINT));
     }
@@ -313,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     if (turned(tile_of(u))) turn(sa[s % ST]);
     spread(sv[s % ST], cb[Cfg::AHEAD ? s & 1 : 0], cy[Cfg::AHEAD ? s & 1 : 0]);
   };
-  uint32_t id = blockIdx.x, first_port = 0;
+  uint32_t id = Cfg::QUARTERS ? blockIdx.x >> 2 : blockIdx.x, first_port = 0;
   if (a.sys_log2) {                                          // (the last row of items may be shorter than eight)
     const uint32_t row = id >> (3 + a.sys_log2), len = min(8u, (uint32_t)a.count - 8 * row), at = id - (row << (3 + a.sys_log2));
     const uint32_t e = at / len;
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     VT* __restrict__ out = static_cast<VT*>(pt.out) + (uint64_t)it.out_part * pt.out_part_stride + (uint64_t)it.out_row0 * T;
     const VT* __restrict__ din = reinterpret_cast<const VT*>(pt.in) + (uint64_t)(it.in_row0 + it.row_in_block) * T;
     const double dadd = (double)it.diag_add * pt.diag_add, scale = pt.scale;
-    const int per = TILE * T, total = (int)it.nrows * T;
+    const int per = TILE * T, total = (Cfg::QUARTERS ? min((int)it.nrows, 16 * g0 + 16) : (int)it.nrows) * T;
     const bool accumulate = pt.accumulate != 0;
     // ---- the waves' sums are added in a fixed order ----
     __syncthreads();                                         // every wave is done with its own piece of LDS
@@ -402,7 +406,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     }
     __syncthreads();
     const double* all = reinterpret_cast<const double*>(lds);
-    for (int e = tid; e < total; e += 64 * NW) {
+    for (int e = tid + (Cfg::QUARTERS ? 16 * g0 * T : 0); e < total; e += 64 * NW) {
       double v = KP == 2 ? all[e] + all[per + e] : (all[e] + all[per + e]) + (all[2 * per + e] + all[3 * per + e]);
       v *= scale;
       if (dadd != 0.0) v = fma(dadd, (double)din[e], v);
@@ -416,7 +420,7 @@ template <int NG, bool ACC64, int KIND>
 static int launch_kind(int count, int T, hipStream_t s, const StripArgs& a) {
   typedef WaveCfg<NG, ACC64, KIND> Cfg;
   // LDS: the waves' own pieces in the loop, then the partial sums (one set for each wave that shares a row's columns)
-  constexpr int wl = NW * Cfg::WAVE_LDS, per_col = Cfg::ROW_GROUPS * TILE * (int)sizeof(double), rl = per_col * (16 * NG + 1);
+  constexpr int wl = NW * Cfg::WAVE_LDS, per_col = Cfg::SHARES * TILE * (int)sizeof(double), rl = per_col * (16 * NG + 1);
   const size_t lds = std::max<size_t>(wl, (size_t)per_col * T);
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_strip<NG, ACC64, KIND>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, std::max(wl, rl));
@@ -458,12 +462,12 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
   return NUGPR_OK;
 }
 
-static bool mean_tiles_up_to(const std::vector<StripItem>& items, uint64_t most) {
+uint64_t strip_tiles(const std::vector<StripItem>& items) {
   uint64_t tiles = 0;
   for (const StripItem& it : items) tiles += it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0;
-  return tiles <= most * items.size();
+  return tiles;
 }
-bool short_strips(const std::vector<StripItem>& items) { return mean_tiles_up_to(items, 10); }
+bool short_strips(const std::vector<StripItem>& items) { return strip_tiles(items) <= 10 * items.size(); }
 
 // Tables with strips of symmetric blocks take the instantiation that pairs their tiles, strips of a basis the caller
 // supplied the row-major one, triangular strips the short or the long one by their mean number of tiles.
@@ -477,7 +481,7 @@ bool short_strips(const std::vector<StripItem>& items) { return mean_tiles_up_to
 // 60 / 66).  Row-major strips never gain: the basis is small beside the K_ii (96 x 2048 points, rank 256: 848 / 865 us).
 int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
   for (const StripItem& it : items)
-    if (it.blocked & 2u) return mean_tiles_up_to(items, 16) ? STRIP_SYM + STRIP_MANY : STRIP_SYM;
+    if (it.blocked & 2u) return strip_tiles(items) <= 16 * items.size() ? STRIP_SYM + STRIP_MANY : STRIP_SYM;
   if (!items.empty() && items[0].blocked == 0) return STRIP_ROWMAJOR;
   return (short_strips(items) ? STRIP_SHORT : STRIP_LONG) + (matrix_bytes >= (uint64_t)128 << 20 ? STRIP_STREAMED : 0);
 }
@@ -491,7 +495,18 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
 // stages a fourth workgroup fits, which pays while a strip has few tiles.  Product of 17 columns, three stages / two: 512 clusters
 // of 128 points 52.0 / 48.7 us, 256 x 256 86.7 / 82.9, 128 x 512 64.2 / 63.2, 256 x 512 137.7 / 134.8, 128 x 1024 140.7 / 139.6, but
 // 64 x 1536 126.2 / 130.5, 64 x 2048 198.0 / 208.6, and 2000 x 64, whose coupling strips are long, 212.9 / 219.7.
+// Few strips: a strip's four row groups in workgroups of their own (STRIP_QUARTERS).  A wave then issues a quarter of the matrix
+// instructions, of which it issued one after the other while most of the chip was idle; the vector rows are read four times.
+// Symmetric up to 128 strips of three tiles or more; triangular ones, which are uneven, up to 256 of four (128 of two).  One
+// column has no matrix instructions.  Whole strips / quarters, us, 17 columns fp64, 33 fp64, 17 fp32:
+//   product  4 x 512 points (32 strips) 18.0 / 14.5, 23.3 / 15.6, 16.7 / 15.1; 2 x 2048 (64) 38.6 / 27.0, 57.9 / 38.1, 32.5 / 22.5;
+//            8 x 1024 (128) 26.9 / 22.4, 36.4 / 28.6, 22.2 / 18.9; but 24 x 512 (192) 25.7 / 25.8, 32.9 / 36.4, 20.3 / 21.8, 2 x 128 13.5 / 14.8
+//   apply    4 x 512 23.0 / 17.0, 34.0 / 19.2, 16.3 / 12.0; 2 x 4096 (128) 89 / 47.5, 161 / 76, 72 / 35.5; 16 x 1024 (256) 35.4 / 29.7, 56.6 / 48.6,
+//            25.3 / 20.8; but 24 x 1024 (384) 37.1 / 40.2, 60.5 / 70.5, 26.4 / 29.2, 64 x 256 (256) 20.2 / 21.6, 28.7 / 31.5, 12.9 / 11.9
 static int kind_at(const StripTable& tab, int count, int T, bool acc64) {
+  const bool sym = (tab.kind & 3) == STRIP_SYM;
+  if (T > 1 && (tab.kind & 3) != STRIP_ROWMAJOR && count <= (sym ? 128 : 256) && tab.tiles >= tab.count * (sym ? 3 : count > 128 ? 4 : 2))
+    return (sym ? STRIP_SYM : STRIP_SHORT) + STRIP_QUARTERS;
   if (tab.kind & STRIP_MANY) return acc64 && T > 1 && T <= 17 && count > 768 ? tab.kind : tab.kind - STRIP_MANY;
   const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && count <= 512;
   return as_long ? tab.kind - STRIP_SHORT + STRIP_LONG : tab.kind;
@@ -513,6 +528,8 @@ static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, con
       break;
     case STRIP_LONG: return launch_width<ACC64, STRIP_LONG>(ng, count, T, s, a);
     case STRIP_SHORT: return launch_width<ACC64, STRIP_SHORT>(ng, count, T, s, a);
+    case STRIP_SYM + STRIP_QUARTERS: return launch_width<ACC64, STRIP_SYM + STRIP_QUARTERS>(ng, 4 * count, T, s, a);
+    case STRIP_SHORT + STRIP_QUARTERS: return launch_width<ACC64, STRIP_SHORT + STRIP_QUARTERS>(ng, 4 * count, T, s, a);
     case STRIP_ROWMAJOR: return launch_width<ACC64, STRIP_ROWMAJOR>(ng, count, T, s, a);
     case STRIP_LONG + STRIP_STREAMED: return launch_width<ACC64, STRIP_LONG + STRIP_STREAMED>(ng, count, T, s, a);
     case STRIP_SHORT + STRIP_STREAMED: return launch_width<ACC64, STRIP_SHORT + STRIP_STREAMED>(ng, count, T, s, a);
