@@ -96,11 +96,13 @@ constexpr int RING_STAGES = 3, RING_STAGE = 16 * 1024, RING = RING_STAGES * RING
 constexpr uint32_t waitcnt_vm(uint32_t n) {      // s_waitcnt immediate: vmcnt(n), the other counters unconstrained
   return (n & 15u) | ((n >> 4) << 14) | 0x0F70u;
 }
+// F = 2: 64 x 64 per workgroup and 32 x 32 per wave (one row tile of either operand, whose fragments the waves load in pairs, F
+// each), for launches that would not fill the chip otherwise: a step takes a quarter of the time.
 // Steps s0 .. s1 - 1 (whole tiles).  mine: first element of the strip (64 rows of a square block) that this wave loads:
-// row tile 0 / 1 of OpA, 0 / 1 of OpB for wave 0 .. 3.  TRI (of OpA): 0 none; 1 / 2: the tile of column tile diag is
+// row tile 0 / 1 of OpA, 0 / 1 of OpB for wave 0 .. 3 (F = 2: OpA, OpA, OpB, OpB).  TRI (of OpA): 0 none; 1 / 2: the tile of column tile diag is
 // triangular (column <= row / >= row is kept) and the tiles past it / before it count as zero whatever is stored there.
-template <int TRI, bool SWAP = false>
-__device__ __forceinline__ void block_gemm(v4f (&acc)[4][4], const float* mine, int s0, int s1, int diag, unsigned char* ring) {
+template <int TRI, bool SWAP = false, int F = 4>
+__device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, int s0, int s1, int diag, unsigned char* ring) {
 #if __HIP_DEVICE_COMPILE__
   typedef __attribute__((address_space(3))) const v4f* lds_v4f;
   typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
@@ -111,47 +113,49 @@ __device__ __forceinline__ void block_gemm(v4f (&acc)[4][4], const float* mine, 
   auto issue = [&](int q) {
     const int step = s0 + q;
     const float* at = mine + (uint64_t)(step >> 1) * (TILE * BLK_COLS) + (step & 1) * FRAG;
-    unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + 4 * w * 1024;
+    unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + F * w * 1024;
+    if (F == 2) at += (w & 1) * 4 * FRAG;
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < F; ++g)
       __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(at + g * 2 * FRAG) + piece, (lds_ptr)(st + g * 1024), 16, 0, 0);
   };
-  v4f a[2][4], b[2][4];
+  v4f a[2][F], b[2][F];
   // step q into the registers of its parity, once every wave's share of it has landed.  The barrier also says that every
   // wave has read step q - 1, whose stage then takes step q - 1 + RING_STAGES.
-  auto fetch_step = [&](int q, v4f (&fa)[4], v4f (&fb)[4]) {
-    if (q + RING_STAGES - 2 <= n - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(4 * (RING_STAGES - 2)));
+  auto fetch_step = [&](int q, v4f (&fa)[F], v4f (&fb)[F]) {
+    if (q + RING_STAGES - 2 <= n - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(F * (RING_STAGES - 2)));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     const unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + lane * 16;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) fa[g] = *(lds_v4f)(st + (4 * (w >> 1) + g) * 1024);
+    for (int g = 0; g < F; ++g) fa[g] = *(lds_v4f)(st + (F * (w >> 1) + g) * 1024);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) fb[g] = *(lds_v4f)(st + (8 + 4 * (w & 1) + g) * 1024);
+    for (int g = 0; g < F; ++g) fb[g] = *(lds_v4f)(st + (2 * F + F * (w & 1) + g) * 1024);
     if (q > 0 && q - 1 + RING_STAGES < n) issue(q - 1 + RING_STAGES);
   };
-  auto mult = [&](const v4f (&fa)[4], const v4f (&fb)[4], int i) {
+  auto mult = [&](const v4f (&fa)[F], const v4f (&fb)[F], int i) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < F; ++g)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < F; ++j)
         acc[g][j] = SWAP ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[g][i], fb[j][i], acc[g][j], 0, 0, 0)
                          : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][i], fa[g][i], acc[g][j], 0, 0, 0);
   };
-  auto step_of = [&](int q, v4f (&fa)[4], v4f (&fb)[4], v4f (&na)[4], v4f (&nb)[4]) {
+  auto step_of = [&](int q, v4f (&fa)[F], v4f (&fb)[F], v4f (&na)[F], v4f (&nb)[F]) {
+    const int row0 = F == 2 ? 32 * (w >> 1) : 0;
     const int step = s0 + q, tile = step >> 2;
     const bool counts = !((TRI == 1 && tile > diag) || (TRI == 2 && tile < diag));
     // (the step's reads are waited for here, where nothing younger is in flight, and not at a use behind a branch)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) asm volatile("" : "+v"(fa[g]), "+v"(fb[g]));
+    for (int g = 0; g < F; ++g) asm volatile("" : "+v"(fa[g]), "+v"(fb[g]));
     if (TRI != 0 && tile == diag) {
       const int k = 16 * (step & 3) + 4 * kg;
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int g = 0; g < F; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const bool keep = TRI == 1 ? k + i <= 16 * g + m : k + i >= 16 * g + m;
+          const bool keep = TRI == 1 ? k + i <= row0 + 16 * g + m : k + i >= row0 + 16 * g + m;
           fa[g][i] = keep ? fa[g][i] : 0.f;
         }
     }
@@ -173,11 +177,12 @@ __device__ __forceinline__ void block_gemm(v4f (&acc)[4][4], const float* mine, 
   }
 #endif
 }
-__device__ __forceinline__ void zero_block(v4f (&acc)[4][4]) {
+template <int F>
+__device__ __forceinline__ void zero_block(v4f (&acc)[F][F]) {
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < F; ++g)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[g][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < F; ++j) acc[g][j] = (v4f){0.f, 0.f, 0.f, 0.f};
 }
 // this lane's four values of fragment (g, j) of a 64 x 64 tile (a uniform pointer and a 32-bit lane offset)
 __device__ __forceinline__ v4f* fragment(float* tile, int g, int j) {
@@ -251,6 +256,26 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
   const int tid = threadIdx.x, lane = tid & 63, m = lane & 15, kg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   bool bad = false;
+  // inverse of diagonal block q by one wave, beside the next panel: lane m holds column m of it
+  auto invert = [&](int q) {
+    float l[16], y[16];
+    const float r = rdiag[16 * q + m];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      l[u] = sT[16 * q + m][16 * q + u];
+      y[u] = u == m ? 1.f : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      y[k] *= lane_value(r, k);
+#pragma unroll
+      for (int i = k + 1; i < 16; ++i) y[i] = fmaf(-lane_value(l[k], i), y[k], y[i]);
+    }
+    if (kg == 0) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) inv[(16 * q + u) * IP + m] = y[u];
+    }
+  };
 #pragma unroll 1
   for (int p = 0; p < 4; ++p) {
     if (p > 0) {                                // block (w, p) -= sum over the panels before of L(w, q) L(p, q)^T
@@ -276,7 +301,9 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
         float dj = lane_value(a[j], 16 * p + j);
         if (!(dj > 0.f) || !(dj < INFINITY)) { bad = true; dj = 1.f; }
         d = lane == 16 * p + j ? dj : d;
-        const float mi = lane > 16 * p + j ? a[j] * (1.f / dj) : 0.f;
+        float rd = __builtin_amdgcn_rcpf(dj);   // (one Newton step: 1 ulp, in place of a division's ten dependent instructions)
+        rd = fmaf(fmaf(-dj, rd, 1.f), rd, rd);
+        const float mi = lane > 16 * p + j ? a[j] * rd : 0.f;
 #pragma unroll
         for (int c = j + 1; c < 16; ++c) a[c] = fmaf(-mi, lane_value(a[j], 16 * p + c), a[c]);
       }
@@ -286,28 +313,12 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
         for (int u = 0; u < 16; ++u) sT[lane][16 * p + u] = lane == 16 * p + u ? sd : (lane > 16 * p + u ? a[u] * lane_value(rs, 16 * p + u) : 0.f);
         if (lane < 16 * p + 16) rdiag[lane] = rs;
       }
+    } else if (w == 1 && p > 0) {
+      invert(p - 1);
     }
     __syncthreads();
   }
-  {                                             // inverse of diagonal block w: lane m holds column m of it
-    float l[16], y[16];
-    const float r = rdiag[16 * w + m];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      l[u] = sT[16 * w + m][16 * w + u];
-      y[u] = u == m ? 1.f : 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      y[q] *= lane_value(r, q);
-#pragma unroll
-      for (int i = q + 1; i < 16; ++i) y[i] = fmaf(-lane_value(l[q], i), y[q], y[i]);
-    }
-    if (kg == 0) {
-#pragma unroll
-      for (int u = 0; u < 16; ++u) inv[(16 * w + u) * IP + m] = y[u];
-    }
-  }
+  if (w == 1) invert(3);
   __syncthreads();
   // acc += X Y for blocks: X row-major at x, Y row-major at y; a product's result enters the next one as its right factor
   // as it stands (component i of lane (m, kg) is element (4 kg + i, m), contraction index 4 kg + i)
@@ -568,29 +579,49 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
 }
 
 // blocks below the diagonal: L[m,k] <- L[m,k] inv(L[k,k])^T
+template <int F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, const float* G, int k, Pieces pieces,
                    const uint32_t* __restrict__ first, int n_rows) {
   __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
   int rank, item, part;
-  if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, (int)blockIdx.x, rank, item, 1u, part)) return;
+  if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, (int)blockIdx.x, rank, item, F == 2 ? 2u : 1u, part)) return;
   const ClusterInfo c = cl[cl[rank].by_size];
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ia = w >> 1, jb = w & 1;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ia = w >> 1, jb = w & 1, lane = threadIdx.x & 63;
   const int m = k + 1 + item, last = (int)c.nt - 1;
   float* L = Lf + c.koff;
   const float* from = k == 0 ? Kd + c.koff : L;
-  v4f acc[4][4];
-  zero_block(acc);
   // OpA = the inverse (columns of the result), OpB = the block's rows
-  block_gemm<1, true>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + w) * TILE * c.ld : from + (uint64_t)min(2 * m + w - 2, last) * TILE * c.ld,
-                      8 * k, 8 * (k + 1), 2 * k + ia, ring);
+  if (F == 2) {
+    // a workgroup per row tile (its two column tiles read the same rows, in place: one after the other, the second first)
+    const int row = 2 * m + part;
+    if (row > last) return;
+#pragma unroll 1
+    for (int q = 1; q >= 0; --q) {
+      v4f acc[F][F];
+      zero_block(acc);
+      block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + q) * TILE * c.ld : from + (uint64_t)row * TILE * c.ld, 8 * k, 8 * k + 4 * q + 4,
+                             2 * k + q, ring);
+      __syncthreads();                         // the ring starts over
+      float* lt = L + tile_base(c.ld, row, 2 * k + q);
+#pragma unroll
+      for (int g = 0; g < F; ++g)
+#pragma unroll
+        for (int j = 0; j < F; ++j)
+          *reinterpret_cast<v4f*>(lt + tile_offset(32 * jb + 16 * j + (lane & 15), 32 * ia + 16 * g + 4 * (lane >> 4))) = acc[g][j];
+    }
+    return;
+  }
+  v4f acc[F][F];
+  zero_block(acc);
+  block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + w) * TILE * c.ld : from + (uint64_t)min(2 * m + w - 2, last) * TILE * c.ld,
+                         8 * k, 8 * (k + 1), 2 * k + ia, ring);
   if (2 * m + jb > last) return;
   float* lt = L + tile_base(c.ld, 2 * m + jb, 2 * k + ia);
-  const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < F; ++g)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < F; ++j)
       *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = acc[g][j];
 }
 
@@ -602,38 +633,51 @@ void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* L
 // row-major strips.  Blocks of 128 x 128 (half is even, so a block's columns are whole; its second row tile may be missing).
 // STAGE 1: T^T[n][m] over the columns tn ..; longest products (small tn) first.  STAGE 2: Y21[m][n] over the columns up to
 // tm; longest (large tm) first.
-template <int STAGE>
+// F = 2: four workgroups an item, each one 64 x 64 tile of the block.
+template <int STAGE, int F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int half, Pieces pieces,
                    const uint32_t* __restrict__ first, int n) {
   __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
   int rank, item, part;
-  if (!list_item(pieces, first, 0u, n, (int)blockIdx.x, rank, item, 1u, part)) return;
+  if (!list_item(pieces, first, 0u, n, (int)blockIdx.x, rank, item, F == 2 ? 4u : 1u, part)) return;
   const ClusterInfo c = cl[cl[rank].by_size];
   const int hb = half / 2, node = item / (hb * hb), within = item % (hb * hb), last = (int)c.nt - 1;
   const int start = node * 2 * half, mid = start + half;
   const int rows = min(hb, (last - mid) / 2 + 1);                 // block rows of this node
-  const int tm = mid + 2 * (STAGE == 1 ? within % rows : rows - 1 - within / hb), tn = start + 2 * (STAGE == 1 ? within / rows : within % hb);
+  int tm = mid + 2 * (STAGE == 1 ? within % rows : rows - 1 - within / hb), tn = start + 2 * (STAGE == 1 ? within / rows : within % hb);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ia = w >> 1, jb = w & 1;
   float* L = Lf + c.koff;
   float* Y = G + c.koff;
   auto strip = [&](const float* base, int t) { return base + (uint64_t)min(t, last) * TILE * c.ld; };
-  v4f acc[4][4];
+  v4f acc[F][F];
   zero_block(acc);
+  if (F == 2) {
+    tm += part >> 1;
+    tn += part & 1;
+    if (tm > last) return;
+  }
+  // the wave's tiles, and (F = 2) its fragments in them
+  const int am = F == 2 ? 0 : STAGE == 1 ? jb : ia, an = F == 2 ? 0 : STAGE == 1 ? ia : jb, fa = F == 2 ? 2 * ia : 0, fb = F == 2 ? 2 * jb : 0;
   if (STAGE == 1) {
-    block_gemm<2>(acc, w < 2 ? strip(Y, tn + w) : strip(L, tm + w - 2), 4 * tn, 4 * mid, tn + ia, ring);
-    if (tm + jb > last) return;
-    put_tile(acc, L + tile_base(c.ld, tn + ia, tm + jb));
+    block_gemm<2, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tn : tn + w) : strip(L, F == 2 ? tm : tm + w - 2), 4 * tn, 4 * mid, tn + an, ring);
+    if (tm + am > last) return;
+    float* tt = here(L + tile_base(c.ld, tn + an, tm + am));
+#pragma unroll
+    for (int g = 0; g < F; ++g)
+#pragma unroll
+      for (int j = 0; j < F; ++j) *fragment(tt, fa + g, fb + j) = acc[g][j];
   } else {
-    block_gemm<1>(acc, w < 2 ? strip(Y, tm + w) : strip(L, tn + w - 2), 4 * mid, 4 * (min(tm + 1, last) + 1), tm + ia, ring);
-    if (tm + ia > last) return;
-    float *yl = Y + tile_base(c.ld, tm + ia, tn + jb), *yu = Y + tile_base(c.ld, tn + jb, tm + ia);
+    block_gemm<1, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tm : tm + w) : strip(L, F == 2 ? tn : tn + w - 2), 4 * mid,
+                            4 * (min(F == 2 ? tm : tm + 1, last) + 1), tm + am, ring);
+    if (tm + am > last) return;
+    float *yl = Y + tile_base(c.ld, tm + am, tn + an), *yu = Y + tile_base(c.ld, tn + an, tm + am);
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < F; ++g)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        *fragment(yl, g, j) = -acc[g][j];
-        float* to = yu + block_at_mirrored(g, j);
+      for (int j = 0; j < F; ++j) {
+        *fragment(yl, fa + g, fb + j) = -acc[g][j];
+        float* to = yu + block_at_mirrored(fa + g, fb + j);
 #pragma unroll
         for (int i = 0; i < 4; ++i) to[16 * i] = -acc[g][j][i];
       }
@@ -771,6 +815,9 @@ __global__ __launch_bounds__(256) void k_compensated_blocks(const ClusterInfo* _
   }
 }
 
+// Up to this many blocks of 128 x 128 in a launch leave half of the compute units idle: tiles of 64 x 64 then.
+constexpr uint64_t FEW_BLOCKS = 128;
+
 // How many workgroups share the bulk of a block (k_potrf_step's parts).  The chip holds 768 workgroups, three on a compute
 // unit, which then share its matrix cores; what counts is how full the last round is.  A workgroup alone on its unit leaves
 // the matrix cores idle for three eighths of the time, two for a fifth, three for a tenth; the block of column k and both ends
@@ -817,14 +864,25 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     for (int d = 0; d <= NUM_DIES; ++d) { pr.from[d] = (uint32_t)(items * parts * d / NUM_DIES); ps.from[d] = (uint32_t)(items * d / NUM_DIES); }
     hipLaunchKernelGGL(k_potrf_step, dim3((unsigned)grid_diag + (k > 0 ? pr.grid() : 0u)), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k,
                        n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, c->d_state);
-    if (items) hipLaunchKernelGGL(k_potrf_solve, dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+    if (items > FEW_BLOCKS) hipLaunchKernelGGL((k_potrf_solve<4>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+    else if (items) {
+      for (int d = 0; d <= NUM_DIES; ++d) ps.from[d] = (uint32_t)(2 * items * d / NUM_DIES);
+      hipLaunchKernelGGL((k_potrf_solve<2>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+    }
     parts_before = parts;
   }
   for (const TreeLevel& t : L.tree) {
+    const bool few = t.from1[NUM_DIES] <= FEW_BLOCKS;
     Pieces p1, p2;
-    for (int d = 0; d <= NUM_DIES; ++d) { p1.from[d] = t.from1[d]; p2.from[d] = t.from2[d]; }
-    hipLaunchKernelGGL((k_trtri_block<1>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, c->d_rows_before + t.at, t.ranks);
-    hipLaunchKernelGGL((k_trtri_block<2>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, c->d_rows_before + t.at, t.ranks);
+    for (int d = 0; d <= NUM_DIES; ++d) { p1.from[d] = t.from1[d] * (few ? 4 : 1); p2.from[d] = t.from2[d] * (few ? 4 : 1); }
+    const uint32_t* first = c->d_rows_before + t.at;
+    if (few) {
+      hipLaunchKernelGGL((k_trtri_block<1, 2>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks);
+      hipLaunchKernelGGL((k_trtri_block<2, 2>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks);
+    } else {
+      hipLaunchKernelGGL((k_trtri_block<1, 4>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks);
+      hipLaunchKernelGGL((k_trtri_block<2, 4>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks);
+    }
   }
   hipLaunchKernelGGL(k_logdet, dim3(L.nc), dim3(256), 0, s, c->d_cl, c->G, c->d_logdet);
   NUGPR_HIP(hipGetLastError());
