@@ -358,16 +358,16 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->Ppart = w + L.o_Ppart;
   c->dotpart = reinterpret_cast<double*>(w + L.o_dot);
   c->d_state = reinterpret_cast<PcgState*>(w + L.o_state);
-  c->alog = reinterpret_cast<double*>(w + L.o_alog);
-  c->blog = reinterpret_cast<double*>(w + L.o_blog);
+  // systems side by side, where a slot's logs hold a solve
+  const bool fits = c->params.max_iter <= L.slot_iter;
+  c->slots = fits ? L.slots : 1;
+  c->alog = reinterpret_cast<double*>(w + (fits ? L.o_alog : L.o_long_alog));
+  c->blog = reinterpret_cast<double*>(w + (fits ? L.o_blog : L.o_long_blog));
   c->d_logdet = reinterpret_cast<double*>(w + L.o_logdet);
   c->d_tiles = reinterpret_cast<uint64_t*>(w + L.o_tiles);
   hipStream_t s = as_stream(stream);
 
   auto fail = [&](int code) { nugpr_destroy(c); return code; };
-  // systems side by side, as far as their logs fit the pinned buffer
-  c->slots = L.slots;
-  while (c->slots > 1 && c->slots * c->params.max_iter > MAX_ITER_CAP) c->slots /= 2;
   // pinned host staging (host memory; the library allocates no device memory): the records of a solve; also the partial sums
   // of two dot products, or the log determinants of the clusters
   c->h_buf_doubles = std::max<size_t>(c->slots * host_record_doubles(c->params.max_iter), (size_t)2 * 1024 * MAX_COLS) + sizeof(PcgState) + L.nc;
@@ -851,7 +851,7 @@ int nugpr_train_step(nugpr_ctx* c, double* log_theta, double* adam_m, double* ad
     return launch_build_pair(c, theta.data(), i, h, std::exp(log_theta[i] + h), std::exp(log_theta[i] - h), s);
   };
   for (int k = 0; !forward && together && k < p;) {
-    const int width = k == 0 && c->slots >= 4 ? 2 : 1;        // parameters of this round: alpha and sigma^2, or one
+    const int width = k == 0 ? 2 : 1;        // parameters of this round: alpha and sigma^2, or one
     Operator ops[MAX_SLOTS];
     LossSolve solve[MAX_SLOTS];
     if (k == 2 && (rc = assemble_pair(0))) return rc;

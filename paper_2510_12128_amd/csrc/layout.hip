@@ -189,6 +189,13 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   // The blocks of a solve, once per system that can be taken side by side.  Up to 32768 points (256 partial sums a dot product):
   // there a launch of one system leaves most of the chip idle.
   L.slots = L.n_dot_blocks <= 256 ? MAX_SLOTS : 1;
+  // Their logs share the rows of one solve at the cap between them; a context that allows a solve more than its share takes one
+  // system at a time, with logs beside the slots.
+  L.slot_iter = L.max_iter / L.slots;
+  if (L.slots > 1) {
+    L.o_long_alog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
+    L.o_long_blog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
+  }
   cur = align_up(cur, 256);
   const size_t slot0 = cur;
   L.o_X = take(cur, vec);
@@ -202,8 +209,8 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_Ppart = take(cur, (size_t)L.nsP * L.ncr * L.T * sizeof(double));
   L.o_dot = take(cur, (size_t)4 * L.n_dot_blocks * MAX_COLS * sizeof(double));
   L.o_state = take(cur, sizeof(PcgState));
-  L.o_alog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
-  L.o_blog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
+  L.o_alog = take(cur, (size_t)L.slot_iter * MAX_COLS * sizeof(double));
+  L.o_blog = take(cur, (size_t)L.slot_iter * MAX_COLS * sizeof(double));
   cur = align_up(cur, 256);
   L.slot_bytes = cur - slot0;
   cur = slot0 + L.slots * L.slot_bytes;

@@ -189,6 +189,8 @@ struct Layout {
   size_t o_assign = 0, o_rep_ptr = 0, o_rep_pts = 0, o_rows_before = 0;
   size_t items_bytes = 0;
   int slots = 1;                     // MAX_SLOTS, or 1 on large problems
+  int slot_iter = 0;                 // iterations that the logs of a slot hold
+  size_t o_long_alog = 0, o_long_blog = 0;   // logs of a context that allows more (with slots > 1 only)
   size_t slot_bytes = 0;             // from a block of one slot (X .. blog) to that of the next
   int n_dot_blocks = 0;
   int max_iter = 0;

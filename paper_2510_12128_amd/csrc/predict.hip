@@ -143,7 +143,7 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
   int nsys = 1;
   for (int64_t j0 = 0; j0 < m; j0 += (int64_t)nsys * T) {
     const int64_t left = (m - j0 + T - 1) / T;                  // blocks
-    nsys = !together || left == 1 ? 1 : left == 2 || c->slots < 4 ? 2 : 4;        // (three: the last of four is empty)
+    nsys = !together || left == 1 ? 1 : left == 2 ? 2 : 4;        // (three: the last of four is empty)
     const unsigned ny = (unsigned)nsys;
     const int cnt = (int)std::min<int64_t>((int64_t)nsys * T, m - j0);
     hipLaunchKernelGGL((k_cross_block<VT>), dim3(grid, ny), dim3(256), 0, s, a, c->X, Xt, j0, cnt, n, T, U, sys);

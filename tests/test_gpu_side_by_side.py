@@ -6,7 +6,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-ALONE = 4096                       # iteration cap: one system at a time
+ALONE, SHARE = 4096, 1024            # iteration caps: one system at a time; the largest with four side by side
 STATS = ("loss_evals", "pcg_solves", "pcg_iterations", "pcg_iterations_max", "products", "products_reused", "precond_applies", "assembly_passes",
          "matrices_assembled", "factorisations")
 
@@ -31,11 +31,11 @@ def _contexts(lib, sizes, t, caps, acc_fp32, iso, spacing=4.0):
     ("largest", [1024] * 32, 4, False, 7.0),             # 32768 points
 ])
 def test_training_step_side_by_side(lib, name, sizes, t, iso, spacing, acc_fp32):
-    _, (alone, two, four) = _contexts(lib, sizes, t, (ALONE, 2048, 1024), acc_fp32, iso, spacing)
+    _, (alone, over, four) = _contexts(lib, sizes, t, (ALONE, SHARE + 1, SHARE), acc_fp32, iso, spacing)
     phi = np.log(np.array([0.9, 1.0, 0.3] if iso else [0.9, 1.1, 1.0, 0.3]))
     zero = np.zeros_like(phi)
     runs = []
-    for ctx in (alone, two, four):
+    for ctx in (alone, over, four):
         outs = []
         p, m, v = phi, zero, zero
         for k in range(3):                                # Adam moves on: from the second step the solver issues iterations ahead
@@ -49,18 +49,18 @@ def test_training_step_side_by_side(lib, name, sizes, t, iso, spacing, acc_fp32)
     assert runs[0][0][0] == 0
     assert runs[1] == runs[0]
     assert runs[2] == runs[0]
-    for ctx in (alone, two, four):
+    for ctx in (alone, over, four):
         ctx.close()
 
 
 @pytest.mark.parametrize("acc_fp32", [False, True])
 @pytest.mark.parametrize("sizes,t,spacing", [([64, 130, 97, 3, 200, 71], 4, 4.0), ([128, 129, 127], 16, 3.8)])
 def test_prediction_side_by_side(lib, sizes, t, spacing, acc_fp32):
-    X, (alone, two, four) = _contexts(lib, sizes, t, (ALONE, 2048, 1024), acc_fp32, False, spacing)
+    X, (alone, over, four) = _contexts(lib, sizes, t, (ALONE, SHARE + 1, SHARE), acc_fp32, False, spacing)
     theta = np.array([0.9, 1.1, 1.0, 0.3])
     T = t + 1
     rng = np.random.default_rng(7)
-    ctxs = (alone, two, four)
+    ctxs = (alone, over, four)
     for ctx in ctxs:
         ctx.nugpr_build_blocks(theta)
         assert ctx.nugpr_precond_factor()[0] == 0
