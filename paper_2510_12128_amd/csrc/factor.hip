@@ -243,8 +243,7 @@ __device__ __forceinline__ uint32_t block_at_mirrored(int g, int j) {
 // L^-1 = [Y11 0; -Y22 L21 Y11, Y22] over blocks, then pairs of blocks.
 // Panel, elimination without square roots (A = Lu D Lu^T): pivot j: m_i = a_ij / d_j (i > j), a_ic -= m_i a_cj (c > j);
 // then L = Lu D^1/2.  A pivot that is not positive and finite is replaced by 1 and reported.
-// Before: 64 pivots of one LDS round trip and one barrier each, the inverse carried along: a step of four clusters of 512
-// points (this and one short product) 34 us, now 17.
+// Before: 64 pivots of one LDS round trip and one barrier each, the inverse carried along: 37 us a tile on an idle chip, now 12.4.
 constexpr int LT = TILE + 1;                    // row stride of a tile in LDS
 constexpr int IP = 17;                          // and of an inverted diagonal block
 __device__ __forceinline__ float lane_value(float v, int lane) {
@@ -413,7 +412,6 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
   int rank = id, item = 0, part = 0;
   if (diag) {
     if (id >= n_diag) return;
-    __builtin_amdgcn_s_setprio(3);
   } else {
     if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, id - grid_diag, rank, item, (uint32_t)parts, part)) return;
   }
