@@ -237,7 +237,7 @@ def main():
     ncr = float(nc * r)
     vs = 8.0 if args.acc == "fp64" else 4.0
     kernel = ctx.nugpr_profile_kernel_name(T)
-    lower_only = kernel.endswith(", 1>")        # the instantiation that pairs the tiles of symmetric blocks
+    lower_only = int(kernel.rstrip(">").split(",")[-1]) & 3 == 1        # the kinds that pair the tiles of symmetric blocks
     # --- bytes of one launch of the dominant kernel, three accountings ---
     entries_full = float(np.sum(sizes ** 2) + ncr ** 2)                      # stored entries, whole squares
     tiles = np.ceil(sizes / 64.0)

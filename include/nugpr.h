@@ -331,7 +331,8 @@ int32_t nugpr_num_hyper(const nugpr_ctx* ctx);
  * nugpr_profile_enable(ctx, 1) each such launch is bracketed by HIP events on the stream
  * it runs on (at most 2048 launches are kept; later ones go untimed).
  * nugpr_profile_read synchronises `stream`, returns the summed kernel time in
- * milliseconds and the number of timed launches, and resets the counters.
+ * milliseconds and the number of timed launches, and resets the counters; a launch that
+ * serves several systems side by side counts once for each.
  * nugpr_profile_bytes returns the bytes one such launch moves at `ncols` columns:
  * the stored matrices it streams (4 * (sum b_i^2 + (n_c r)^2)) plus the vector blocks
  * it reads and writes in the context's arithmetic mode. */

@@ -457,7 +457,7 @@ int nugpr_profile_enable(nugpr_ctx* c, int32_t on) {
     }
   }
   c->prof_on = on != 0;
-  c->prof_used = 0;
+  c->prof_used = c->prof_systems = 0;
   return NUGPR_OK;
 }
 
@@ -471,8 +471,8 @@ int nugpr_profile_read(nugpr_ctx* c, double* total_ms, int32_t* launches, void* 
     acc += ms;
   }
   *total_ms = acc;
-  *launches = c->prof_used;
-  c->prof_used = 0;
+  *launches = c->prof_systems;
+  c->prof_used = c->prof_systems = 0;
   return NUGPR_OK;
 }
 

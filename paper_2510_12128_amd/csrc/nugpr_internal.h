@@ -252,6 +252,7 @@ struct nugpr_ctx {
   bool prof_on = false;
   std::vector<hipEvent_t> prof_ev;       // start/stop pairs
   int prof_used = 0;                     // pairs recorded since the last read
+  int prof_systems = 0;                  // systems that the launches between them served
   nugpr::HostFlags* h_flags = nullptr;   // pinned, one per slot
   uint64_t flag_seq = 0, tail_seq = 0;   // last numbers handed to the device
   int expect_iters[2] = {1, 1};          // iterations the last solve of each system took (when to report early)

@@ -624,6 +624,7 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, v
   if (timed) {
     NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used + 1], s));
     c->prof_used += 1;
+    c->prof_systems += nsys;
   }
   if (L.compensate) {                     // the fp32 residual of C - lambda_0 I, added slab by slab
     StripPort k2 = port[1];

@@ -53,6 +53,21 @@ def test_training_step_side_by_side(lib, name, sizes, t, iso, spacing, acc_fp32)
         ctx.close()
 
 
+def test_timed_launches_count_systems(lib):
+    """The timing of the product launch counts a launch once for every system it serves, so that time over launches is that of a
+    product.  With a cap of one iteration no product is issued in vain."""
+    _, (ctx,) = _contexts(lib, [64, 130, 97], 4, (1,), False, False, 30.0)
+    phi = np.log(np.array([0.9, 1.1, 1.0, 0.3]))
+    ctx.nugpr_profile_enable(True)
+    ctx.nugpr_stats_read(reset=True)
+    ctx.nugpr_train_step(phi, np.zeros(4), np.zeros(4), 0)
+    ms, launches = ctx.nugpr_profile_read()
+    stats = ctx.nugpr_stats_read()
+    assert stats["loss_evals"] == 9 and ms > 0
+    assert launches == stats["products"] == 5              # the base loss; two for each lengthscale (the others reuse its product)
+    ctx.close()
+
+
 @pytest.mark.parametrize("acc_fp32", [False, True])
 @pytest.mark.parametrize("sizes,t,spacing", [([64, 130, 97, 3, 200, 71], 4, 4.0), ([128, 129, 127], 16, 3.8)])
 def test_prediction_side_by_side(lib, sizes, t, spacing, acc_fp32):
