@@ -371,7 +371,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s);
 // one, Q holding the block-diagonal part only: a caller's fp32 blocks then cost no conversion passes)
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial = nullptr,
                bool* dq_done = nullptr, const float* D32 = nullptr, float* Q32 = nullptr);
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys = 1);
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s);
 // What a loss evaluation needs besides the solution, fetched with the solve's last synchronisation:
 // <b_c, x_c> per column and rho_0 = <r_0, M^-1 r_0>.
 // Which system a batched CG run solves.
@@ -400,10 +400,12 @@ struct PcgOutcome {
   int max_it, status;
   const double *alog, *blog;
 };
-// Several systems in lock step, to the bit what run_pcg gives for each: nsys = 1, or 2 or 4 up to the context's slots (one-hot
+// Several systems in lock step, to the bit what run_pcg gives for each: 1, or 2 to 4 up to the context's slots (one-hot
 // basis, no compensation, no Pade system).  B: the context's own right-hand sides, shared by all, or a block of slot 0; X a block
-// of slot 0.  A system that is done before the others keeps them company with zero steps.
-int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system = PCG_KPRIME);
+// of slot 0.  A system that is done before the others keeps them company with zero steps.  The launches take 1, 2 or 4: with
+// three, slot 3 takes part too, which the caller fills with zeros (and ops, of MAX_SLOTS then, with any operator); nothing of it
+// is counted or reported.
+int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int held, PcgOutcome* out, hipStream_t s, int system = PCG_KPRIME);
 // a system's part of the pinned buffer: logs of alpha and beta, final state, <b, x>
 inline size_t host_record_doubles(int max_iter) {
   return (size_t)2 * max_iter * MAX_COLS + (sizeof(PcgState) + sizeof(double) - 1) / sizeof(double) + MAX_COLS;

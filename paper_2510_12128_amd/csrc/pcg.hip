@@ -579,8 +579,9 @@ static int fold_parts(const nugpr_ctx* c, int T) {
 template <typename P> static P* slot_of(P* p, uint64_t stride, int e) { return (P*)((uintptr_t)p + (uint64_t)e * stride); }
 
 // The product of `nsys` systems side by side, each with its operator; D and Q those of system 0, the others a slot further
-// (the kept direction z_0 is shared).  More than one (2 or 4): one-hot basis, no compensation.
-static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, void* Q, int T, hipStream_t s, double* dq_partial,
+// (the kept direction z_0 is shared).  More than one (2 or 4): one-hot basis, no compensation.  The counters and the timing
+// take the first `held` of them.
+static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const void* D, void* Q, int T, hipStream_t s, double* dq_partial,
                    bool* dq_done, const float* D32, float* Q32) {
   const Layout& L = c->L;
   const uint64_t sys = L.slot_bytes;
@@ -603,10 +604,10 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, v
     else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(VB), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
     NUGPR_HIP(hipGetLastError());
     if (dq_done) *dq_done = dq_partial != nullptr;
-    c->stats.products_reused += nsys;
+    c->stats.products_reused += held;
     return NUGPR_OK;
   }
-  c->stats.products += nsys;
+  c->stats.products += held;
   const bool d_shared = D == c->Z0v;
   const uint64_t s_d = d_shared ? 0 : sys;
   if (!s_known && (rc = run_project(c, D, T, s, D32, nsys, s_d))) return rc;
@@ -624,7 +625,7 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, const void* D, v
   if (timed) {
     NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used + 1], s));
     c->prof_used += 1;
-    c->prof_systems += nsys;
+    c->prof_systems += held;
   }
   if (L.compensate) {                     // the fp32 residual of C - lambda_0 I, added slab by slab
     StripPort k2 = port[1];
@@ -652,7 +653,7 @@ static Operator operator_in_force(const nugpr_ctx* c) { return Operator{c->Kd, c
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial, bool* dq_done,
                const float* D32, float* Q32) {
   const Operator op = operator_in_force(c);
-  return product(c, &op, 1, D, Q, T, s, dq_partial, dq_done, D32, Q32);
+  return product(c, &op, 1, 1, D, Q, T, s, dq_partial, dq_done, D32, Q32);
 }
 
 // out = a * x  (elementwise over a vector block)
@@ -914,11 +915,11 @@ static int run_pade_q(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s
   return NUGPR_OK;
 }
 
-// (nsys > 1: R and Z of system 0, the others a slot further)
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys) {
+// (nsys > 1: R and Z of system 0, the others a slot further; the first `held` of them are counted)
+static int precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys, int held) {
   int rc;
   const uint64_t sys = c->L.slot_bytes;
-  c->stats.precond_applies += nsys;
+  c->stats.precond_applies += held;
   StripPort a[MAX_SLOTS] = {}, b[MAX_SLOTS] = {};
   for (int e = 0; e < nsys; ++e) {
     a[e].A = c->G; a[e].in = slot_of(R, sys, e); a[e].out = slot_of(c->Vv, sys, e);
@@ -927,6 +928,7 @@ int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int 
   if ((rc = launch_strip(c->tab_lowG, a, nsys, T, c->acc64, s, nsys))) return rc;
   return launch_strip(c->tab_upG, b, nsys, T, c->acc64, s, nsys);
 }
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s) { return precond(c, R, Z, T, s, 1, 1); }
 
 static int elementwise_grid(int64_t n, int T) {
   const int rpp = 256 / T;
@@ -963,9 +965,10 @@ int run_dot2(nugpr_ctx* c, const void* A0, const void* B0, const void* A1, const
 }
 
 template <typename VT>
-static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system) {
+static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, int held, PcgOutcome* out, hipStream_t s, int system) {
   const Layout& L = c->L;
   const uint64_t sys = L.slot_bytes;
+  const int nsys = held == 3 ? 4 : held;
   const unsigned ny = (unsigned)nsys;
   const bool extras = out[0].extras != nullptr;
   const int64_t n = L.n;
@@ -995,7 +998,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   } else {
     // x_0 = 0, r_0 = b, d_0 = z_0 = M^-1 r_0 written straight into D
     hipLaunchKernelGGL((k_pcg_init<VT>), dim3(1024, ny), dim3(256), 0, s, X, R, B, plain ? B : (const VT*)nullptr, D, n * T, sys, s_b);
-    if (!plain && (rc = run_precond(c, R, D, T, s, nsys))) return rc;
+    if (!plain && (rc = precond(c, R, D, T, s, nsys, held))) return rc;
     hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
     hipLaunchKernelGGL(k_pcg_begin, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, sys);
   }
@@ -1042,7 +1045,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   bool tail_current = false;
   while (it < max_iter) {
     bool dq_done = false;
-    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : product(c, ops, nsys, Dcur, Q, T, s, dq_sums, &dq_done, nullptr, nullptr))) return rc;
+    if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : product(c, ops, nsys, held, Dcur, Q, T, s, dq_sums, &dq_done, nullptr, nullptr))) return rc;
     if (!dq_done)
       hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
@@ -1070,7 +1073,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
       }
       if (n_active == 0 || it >= max_iter) break;
     }
-    if (!plain && (rc = run_precond(c, R, Z, T, s, nsys))) return rc;
+    if (!plain && (rc = precond(c, R, Z, T, s, nsys, held))) return rc;
     hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, rz_sums, nb, j, c->blog);
     hipLaunchKernelGGL((k_update_d<VT>), dim3(eg, ny), dim3(VB), 0, s, D, Dcur, Zr, c->d_state, n, T,
@@ -1085,7 +1088,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   // NaN / Inf among the coordinates of the last assembly (found by its scaling kernel, which marks system 0's state)
   const bool bad_points = c->assembly_mark != 0 && hs->nonfinite_mark == c->assembly_mark;
   int longest = 0, in_vain = 0;
-  for (int e = 0; e < nsys; ++e) {
+  for (int e = 0; e < held; ++e) {
     const PcgState* st = slot_of(hs, hsys, e);
     const double *dot = slot_of(hdot, hsys, e), *ha = slot_of(c->h_buf, hsys, e);
     PcgOutcome& o = out[e];
@@ -1158,9 +1161,9 @@ int store_known_starts(nugpr_ctx* c, hipStream_t s) {
   return c->acc64 ? store_known_t<double>(c, s) : store_known_t<float>(c, s);
 }
 
-int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int nsys, PcgOutcome* out, hipStream_t s, int system) {
-  if (c->acc64) return pcg_t<double>(c, (const double*)B, (double*)X, T, ops, nsys, out, s, system);
-  return pcg_t<float>(c, (const float*)B, (float*)X, T, ops, nsys, out, s, system);
+int run_pcg_systems(nugpr_ctx* c, const void* B, void* X, int T, const Operator* ops, int held, PcgOutcome* out, hipStream_t s, int system) {
+  if (c->acc64) return pcg_t<double>(c, (const double*)B, (double*)X, T, ops, held, out, s, system);
+  return pcg_t<float>(c, (const float*)B, (float*)X, T, ops, held, out, s, system);
 }
 
 int run_pcg(nugpr_ctx* c, const void* B, void* X, int T, int32_t* iters, double* alpha, double* beta,

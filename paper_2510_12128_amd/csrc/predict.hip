@@ -144,14 +144,15 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
   for (int64_t j0 = 0; j0 < m; j0 += (int64_t)nsys * T) {
     const int64_t left = (m - j0 + T - 1) / T;                  // blocks
     nsys = !together || left == 1 ? 1 : left == 2 ? 2 : 4;        // (three: the last of four is empty)
+    const int held = (int)std::min<int64_t>(nsys, left);
     const unsigned ny = (unsigned)nsys;
     const int cnt = (int)std::min<int64_t>((int64_t)nsys * T, m - j0);
     hipLaunchKernelGGL((k_cross_block<VT>), dim3(grid, ny), dim3(256), 0, s, a, c->X, Xt, j0, cnt, n, T, U, sys);
     NUGPR_HIP(hipGetLastError());
     if (var) {
       PcgOutcome out[MAX_SLOTS] = {};
-      if ((rc = run_pcg_systems(c, U, S, T, ops, nsys, out, s))) return rc;
-      for (int e = 0; e < nsys; ++e) {
+      if ((rc = run_pcg_systems(c, U, S, T, ops, held, out, s))) return rc;
+      for (int e = 0; e < held; ++e) {
         rc = out[e].status;
         if (rc == NUGPR_INDEFINITE || rc == NUGPR_NOT_FINITE) return rc;
         worst = std::max(worst, rc);

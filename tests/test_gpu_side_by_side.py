@@ -83,8 +83,13 @@ def test_prediction_side_by_side(lib, sizes, t, spacing, acc_fp32):
         pts = (X[rng.integers(0, len(X), m)] + 0.3 * rng.standard_normal((m, 2))).astype(np.float32)
         pts[::5] += 1e4                                   # out of reach of everything: zero right-hand sides
         for var in (True, False):
+            for ctx in ctxs:
+                ctx.nugpr_stats_read(reset=True)
             outs = [ctx.nugpr_predict(theta, pts, variance=var) for ctx in ctxs]
             assert outs[0]["code"] == 0
+            counts = [{k: x for k, x in ctx.nugpr_stats_read().items() if k in STATS} for ctx in ctxs]
+            assert counts[0]["pcg_solves"] == 1 + (-(-m // T) if var else 0)
+            assert counts[1] == counts[0] and counts[2] == counts[0], m
             for o in outs[1:]:
                 assert o["code"] == 0
                 assert np.array_equal(np.asarray(o["mean"]), np.asarray(outs[0]["mean"]))
