@@ -146,7 +146,8 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
     nsys = !together || left == 1 ? 1 : left == 2 ? 2 : 4;        // (three: the last of four is empty)
     const int held = (int)std::min<int64_t>(nsys, left);
     const unsigned ny = (unsigned)nsys;
-    const int cnt = (int)std::min<int64_t>((int64_t)nsys * T, m - j0);
+    int cnt = (int)std::min<int64_t>((int64_t)nsys * T, m - j0);
+    int failed = NUGPR_OK;
     hipLaunchKernelGGL((k_cross_block<VT>), dim3(grid, ny), dim3(256), 0, s, a, c->X, Xt, j0, cnt, n, T, U, sys);
     NUGPR_HIP(hipGetLastError());
     if (var) {
@@ -154,7 +155,12 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
       if ((rc = run_pcg_systems(c, U, S, T, ops, held, out, s))) return rc;
       for (int e = 0; e < held; ++e) {
         rc = out[e].status;
-        if (rc == NUGPR_INDEFINITE || rc == NUGPR_NOT_FINITE) return rc;
+        if (rc == NUGPR_INDEFINITE || rc == NUGPR_NOT_FINITE) {
+          if (e == 0) return rc;
+          failed = rc;                                          // the blocks ahead of it are good: as one after the other
+          cnt = e * T;
+          break;
+        }
         worst = std::max(worst, rc);
         mx_all = std::max(mx_all, out[e].max_it);
       }
@@ -172,6 +178,7 @@ static int predict_t(nugpr_ctx* c, const double* theta, const float* Xt, int64_t
       mean[j0 + q] = of[0];
       if (var) var[j0 + q] = a.alpha - of[MAX_COLS];
     }
+    if (failed) return failed;
   }
   if (max_iters_used) *max_iters_used = mx_all;
   return worst;

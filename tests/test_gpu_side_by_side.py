@@ -97,3 +97,32 @@ def test_prediction_side_by_side(lib, sizes, t, spacing, acc_fp32):
                     assert np.array_equal(np.asarray(o["var"]), np.asarray(outs[0]["var"]))
     for ctx in ctxs:
         ctx.close()
+
+
+@pytest.mark.parametrize("at", [0, 7, 10, 19, 29])
+def test_prediction_up_to_the_block_with_a_bad_point(lib, at):
+    """A test point that is not a number ends a prediction at its block: the blocks ahead of it have been written, in the same
+    set of launches or not."""
+    from paper_2510_12128_amd import binding as B
+    X, ctxs = _contexts(lib, [64, 130, 97, 3, 200, 71], 4, (ALONE, SHARE), False, False)
+    theta = np.array([0.9, 1.1, 1.0, 0.3])
+    T = 5
+    rng = np.random.default_rng(7)
+    pts = (X[rng.integers(0, len(X), 6 * T)] + 0.3 * rng.standard_normal((6 * T, 2))).astype(np.float32)
+    outs = []
+    for ctx in ctxs:
+        ctx.nugpr_build_blocks(theta)
+        assert ctx.nugpr_precond_factor()[0] == 0
+        good = ctx.nugpr_predict(theta, pts)
+        bad = pts.copy()
+        bad[at] = np.nan
+        o = ctx.nugpr_predict(theta, bad)
+        assert good["code"] == 0 and o["code"] == B.NUGPR_NOT_FINITE
+        ahead = at // T * T
+        for k in ("mean", "var"):
+            assert np.array_equal(o[k][:ahead], good[k][:ahead])
+            assert not o[k][ahead:].any()
+        outs.append(o)
+        ctx.close()
+    for k in ("mean", "var"):
+        assert np.array_equal(outs[0][k], outs[1][k])
