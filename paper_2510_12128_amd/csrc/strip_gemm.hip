@@ -503,12 +503,19 @@ int strip_kind(const std::vector<StripItem>& items, uint64_t matrix_bytes) {
 //            8 x 1024 (128) 26.9 / 22.4, 36.4 / 28.6, 22.2 / 18.9; but 24 x 512 (192) 25.7 / 25.8, 32.9 / 36.4, 20.3 / 21.8, 2 x 128 13.5 / 14.8
 //   apply    4 x 512 23.0 / 17.0, 34.0 / 19.2, 16.3 / 12.0; 2 x 4096 (128) 89 / 47.5, 161 / 76, 72 / 35.5; 16 x 1024 (256) 35.4 / 29.7, 56.6 / 48.6,
 //            25.3 / 20.8; but 24 x 1024 (384) 37.1 / 40.2, 60.5 / 70.5, 26.4 / 29.2, 64 x 256 (256) 20.2 / 21.6, 28.7 / 31.5, 12.9 / 11.9
+// Systems side by side (count = strips of all of them) take sums in the order of one alone.  All instantiations share a row's
+// columns among four waves but whole short strips of two column groups, which share them between two: those are for
+// several systems where they are for one, and where one takes quarters or long strips, several take quarters or long strips.
+// (33 columns fp64, by the strips of all systems / by those of one: training step 24 x 1000 points 4.26 / 4.41 ms, 16 x 1024 2.56 / 2.59;
+// prediction of 264 points 24 x 1000 2.60 / 2.71 ms, 40 x 300 1.12 / 1.18.)
 static int kind_at(const StripTable& tab, int count, int T, bool acc64) {
   const bool sym = (tab.kind & 3) == STRIP_SYM;
-  if (T > 1 && (tab.kind & 3) != STRIP_ROWMAJOR && count <= (sym ? 128 : 256) && tab.tiles >= tab.count * (sym ? 3 : count > 128 ? 4 : 2))
-    return (sym ? STRIP_SYM : STRIP_SHORT) + STRIP_QUARTERS;
+  auto quarters = [&](int strips) {
+    return T > 1 && (tab.kind & 3) != STRIP_ROWMAJOR && strips <= (sym ? 128 : 256) && tab.tiles >= tab.count * (sym ? 3 : strips > 128 ? 4 : 2);
+  };
+  if (quarters(count)) return (sym ? STRIP_SYM : STRIP_SHORT) + STRIP_QUARTERS;
   if (tab.kind & STRIP_MANY) return acc64 && T > 1 && T <= 17 && count > 768 ? tab.kind : tab.kind - STRIP_MANY;
-  const bool as_long = (tab.kind & 3) == STRIP_SHORT && acc64 && T > 17 && count <= 512;
+  const bool as_long = (tab.kind & 3) == STRIP_SHORT && T > 17 && (quarters(tab.count) || (acc64 && tab.count <= 512));
   return as_long ? tab.kind - STRIP_SHORT + STRIP_LONG : tab.kind;
 }
 

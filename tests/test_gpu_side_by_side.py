@@ -126,3 +126,22 @@ def test_prediction_up_to_the_block_with_a_bad_point(lib, at):
         ctx.close()
     for k in ("mean", "var"):
         assert np.array_equal(outs[0][k], outs[1][k])
+
+
+@pytest.mark.parametrize("acc_fp32", [False, True])
+@pytest.mark.parametrize("sizes,spacing", [([1000] * 24, 5.5), ([1024] * 16, 5.0), ([300] * 40, 5.0)], ids=["24x1000", "16x1024", "40x300"])
+def test_two_column_groups_side_by_side(lib, sizes, spacing, acc_fp32):
+    """33 columns, two column groups, and as many triangular strips as make one system alone and several side by side take
+    different instantiations of the strip kernel."""
+    X, ctxs = _contexts(lib, sizes, 32, (ALONE, SHARE), acc_fp32, False, spacing)
+    theta = np.array([0.9, 1.1, 1.0, 0.3])
+    rng = np.random.default_rng(9)
+    pts = (X[rng.integers(0, len(X), 6 * 33)] + 0.3 * rng.standard_normal((6 * 33, 2))).astype(np.float32)
+    outs = []
+    for ctx in ctxs:
+        step = ctx.nugpr_train_step(np.log(theta), np.zeros(4), np.zeros(4), 0)
+        post = ctx.nugpr_predict(theta, pts)
+        assert step["code"] == 0 and post["code"] == 0 and post["max_iters_used"] >= 3
+        outs.append((step["nll0"], step["grad"].tolist(), post["mean"].tolist(), post["var"].tolist()))
+        ctx.close()
+    assert outs[0] == outs[1]
