@@ -249,6 +249,12 @@ constexpr int IP = 17;                          // and of an inverted diagonal b
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
+// 2^-125 <= d < 2^125: the hardware's reciprocal neither takes nor gives subnormal numbers (a uniform test on the bits, which also
+// holds off what is not positive or not finite)
+__device__ __forceinline__ bool within_reciprocal(float d) {
+  const uint32_t bits = __builtin_bit_cast(uint32_t, d), least = (127u - 125u) << 23, past = (127u + 125u) << 23;
+  return bits - least < past - least;
+}
 // sT: the tile (lower triangle read), replaced by L; block (i, j), i > j, of L^-1 is left where block (j, i) of L would be.
 // inv: four 16 x IP inverted diagonal blocks; rdiag: 64 values.  Returns whether a pivot was bad (true for wave 0's threads).
 __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* rdiag) {
@@ -297,12 +303,17 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
       for (int u = 0; u < 16; ++u) a[u] = sT[lane][16 * p + u];
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        float dj = lane_value(a[j], 16 * p + j);
-        if (!(dj > 0.f) || !(dj < INFINITY)) { bad = true; dj = 1.f; }
+        float dj = lane_value(a[j], 16 * p + j), mi;
+        if (within_reciprocal(dj)) {            // (one Newton step: 1 ulp, in place of a division's ten dependent instructions)
+          float rd = __builtin_amdgcn_rcpf(dj);
+          rd = fmaf(fmaf(-dj, rd, 1.f), rd, rd);
+          mi = a[j] * rd;
+        } else {
+          if (!(dj > 0.f) || !(dj < INFINITY)) { bad = true; dj = 1.f; }
+          mi = a[j] / dj;
+        }
         d = lane == 16 * p + j ? dj : d;
-        float rd = __builtin_amdgcn_rcpf(dj);   // (one Newton step: 1 ulp, in place of a division's ten dependent instructions)
-        rd = fmaf(fmaf(-dj, rd, 1.f), rd, rd);
-        const float mi = lane > 16 * p + j ? a[j] * rd : 0.f;
+        mi = lane > 16 * p + j ? mi : 0.f;
 #pragma unroll
         for (int c = j + 1; c < 16; ++c) a[c] = fmaf(-mi, lane_value(a[j], 16 * p + c), a[c]);
       }

@@ -48,3 +48,28 @@ def test_factor_and_inverse_at_block_edges(lib, name):
             want -= 2.0 * float(torch.log(Y.diagonal()).sum())
         assert abs(logdet - want) <= 1e-12 * n + 1e-10 * abs(want)
     ctx.close()
+
+
+@pytest.mark.parametrize("alpha,noise", [(2e38, 0.5e38), (1.5e38, 0.3e38), (1e37, 2e36), (1e-36, 2e-37), (4e-38, 1e-38), (3e-38, 0.6e-38)])
+def test_factor_at_the_ends_of_the_number_range(lib, alpha, noise):
+    """Pivots whose reciprocal is subnormal (above 2^126) or that are subnormal themselves."""
+    import torch
+    from paper_2510_12128_amd import binding as B
+    sizes = [70, 200, 129]
+    n = sum(sizes)
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((n, 3)).astype(np.float32)
+    ctx = lib.Context(X, np.zeros(n, np.float32), np.concatenate([[0], np.cumsum(sizes)]), 2.0 * rng.integers(0, 2, (n, 2)) - 1.0, 1)
+    ctx.nugpr_build_blocks(np.array([2.0, 1.4, 0.8, alpha, noise]))
+    code, logdet, bad = ctx.nugpr_precond_factor()
+    assert code == 0 and bad == -1
+    u, unit = 2.0 ** -24, 2.0 ** -149
+    for i, b in enumerate(sizes):
+        K, L, Y = (ctx.nugpr_export(w, i).double() for w in (B.EXPORT_K, B.EXPORT_L, B.EXPORT_LINV))
+        # the bounds of the test above; subnormal entries are rounded to whole units in each of b steps, and the roundings go twice
+        # through a block's inverse and factor, whose condition number is at most sqrt(1 + 128 alpha / sigma^2) = 26 here
+        LL = L.abs() @ L.abs().T
+        assert float(((L @ L.T - K).abs() - 2 * 26 * b * unit).div(LL).max()) <= (b + 1 + 64) * u
+        res = (Y @ L - torch.eye(b, device=L.device, dtype=L.dtype)).abs() / (Y.abs() @ L.abs()).clamp_min(1.0)
+        assert float(res.max()) <= (b + 1 + 64) * u
+    ctx.close()
