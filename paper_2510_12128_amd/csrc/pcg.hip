@@ -184,7 +184,8 @@ __global__ __launch_bounds__(256) void k_pcg_alpha(PcgState* __restrict__ st, co
 
 // End-of-solve report, written by the device straight into pinned host memory: the per-column state, <b_c, x_c> summed from the
 // per-workgroup partials (fixed order), and the first `rows` rows of the alpha / beta logs.  It comes with the stop test of the
-// iteration that is expected to be the last (k_pcg_check; a kernel of its own, 5 - 7 us, otherwise: k_pcg_tail).
+// iteration that is expected to be the last, and of the one after it (k_pcg_check; a kernel of its own, 5 - 7 us, otherwise:
+// k_pcg_tail).
 struct Report {
   uint64_t seq;                    // 0: none
   int want_bx, rows;
@@ -194,19 +195,26 @@ struct Report {
   uint64_t hsys;                   // bytes from a system's part of the host buffer to the next one's
 };
 // what state and logs a report holds, by `threads` threads; state read past what this workgroup has cached
-__device__ __forceinline__ void copy_report(const PcgState* st, const Report& r, uint64_t sys, int at, int threads) {
+__device__ __forceinline__ void copy_state(const PcgState* st, const Report& r, int at, int threads) {
   const int words = (int)(sizeof(PcgState) / sizeof(int32_t));
   const volatile int32_t* src = reinterpret_cast<const volatile int32_t*>(st);
   int32_t* dst = reinterpret_cast<int32_t*>(of_system(r.h_state, r.hsys));
   for (int i = at; i < words; i += threads) dst[i] = src[i];
+}
+__device__ __forceinline__ void copy_logs(const Report& r, uint64_t sys, int T, int at, int threads) {
   const double *alog = of_system(r.alog, sys), *blog = of_system(r.blog, sys);
   double *h_alog = of_system(r.h_alog, r.hsys), *h_blog = of_system(r.h_blog, r.hsys);
-  for (int i = at; i < r.rows * MAX_COLS; i += threads) { h_alog[i] = alog[i]; h_blog[i] = blog[i]; }
+  for (int i = at; i < r.rows * T; i += threads) {
+    const int e = i / T * MAX_COLS + i % T;
+    h_alog[e] = alog[e];
+    h_blog[e] = blog[e];
+  }
 }
 
 // after the update: stop test on ||r_c|| (columns that meet it are frozen).  The workgroup that finishes
 // last gathers the cross-column bookkeeping (how many columns are still active, did any meet negative
 // curvature) and publishes it to the host: the flags, a system-scope fence, then the sequence number.
+// With a report the workgroups share the copy of the logs, which the host then waits for with the flags.
 __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, const double* __restrict__ partial,
                                                    int nblocks, int iter, double tol2, int T,
                                                    HostFlags* __restrict__ out, uint64_t seq, uint64_t sys, Report report) {
@@ -217,12 +225,14 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
   partial = of_system(partial, sys);
   out += blockIdx.y;
   const double rr = sum_partials(partial, nblocks, c, red, tid);
-  if (report.seq && report.want_bx) {
-    const double bx = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
-    if (tid == 0) {
-      of_system(report.h_bx, report.hsys)[c] = bx;
-      __threadfence_system();
+  if (report.seq) {
+    if (report.want_bx) {
+      const double bx = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
+      if (tid == 0) of_system(report.h_bx, report.hsys)[c] = bx;
     }
+    copy_logs(report, sys, T, c * 256 + tid, 256 * T);
+    __threadfence_system();
+    __syncthreads();
   }
   if (tid == 0) {
     if (st->active[c]) {
@@ -265,7 +275,7 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
   if (!report.seq) return;
   __threadfence();
   __syncthreads();                             // the state is what the other workgroups and thread 0 left
-  copy_report(st, report, sys, tid, 256);
+  copy_state(st, report, tid, 256);
   __threadfence_system();
   __syncthreads();
   if (tid == 0) {
@@ -462,7 +472,8 @@ __global__ __launch_bounds__(256) void k_pcg_tail(PcgState* __restrict__ st, con
     const double v = sum_partials(partial, nblocks, c, red, tid);
     if (tid == 0) of_system(report.h_bx, report.hsys)[c] = v;
   }
-  copy_report(st, report, sys, c * 256 + tid, 256 * T);
+  copy_state(st, report, c * 256 + tid, 256 * T);
+  copy_logs(report, sys, T, c * 256 + tid, 256 * T);
   __threadfence_system();
   __syncthreads();
   if (tid == 0) last = (atomicAdd(&st->tail_count, 1) == T - 1);
@@ -1027,8 +1038,9 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   const int sure = fuse ? std::min(rec.last[0], std::min(rec.last[1], rec.last[2])) : 1;
   nugpr_stats counted = c->stats, counted_before = c->stats;      // after the product of the present iteration, and the last
   // The end-of-solve report comes with the stop test of the iteration that is expected to be the last
-  // one, so that it is already on the host when the stop test says "done";
-  // a solve that ends earlier or later than the previous one of its kind gets the report after the loop.
+  // one, so that it is already on the host when the stop test says "done", and with that of the iteration after it;
+  // a solve that ends earlier or later than that gets the report after the loop (with one in every iteration from the expected
+  // one on, a solve of k more iterations than the last would copy k rows k times over).
   const int expect = c->expect_iters[plain ? 1 : 0];
   // (its <b, x> sums were left in the second partial set by the update kernel of the same iteration)
   auto next_report = [&](int rows) {
@@ -1050,7 +1062,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
       hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
     // the update, fused with ||r||^2 for the stop test and, in the iteration expected to be the last, <b, x>
-    const bool report = it + 1 >= expect || it + 1 >= max_iter;
+    const bool report = it + 1 == expect || it == expect || it + 1 >= max_iter;
     hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(VB), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
                        c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b, fuse && own && it == 0 ? (plain ? 1 : 0) : -1);
