@@ -16,9 +16,9 @@
  * Conventions
  *   - Pointers marked DEVICE are device pointers on the GPU current at
  *     nugpr_create; pointers marked HOST are ordinary host memory.
- *   - The caller owns every buffer, including ONE device workspace of at least
- *     nugpr_workspace_bytes() bytes (256-byte aligned).  The library allocates
- *     no device memory.  It never frees caller memory.
+ *   - The caller owns every buffer, including ONE device workspace of
+ *     nugpr_workspace_bytes() bytes (256-byte aligned; see there for less).  The
+ *     library allocates no device memory.  It never frees caller memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All
  *     GPU work is enqueued there.  Calls with host outputs return when those
  *     are complete: precond_factor, pcg_solve, predict, export and profile_read
@@ -173,7 +173,10 @@ typedef struct {
 
 /* Bytes of device workspace a problem of this shape needs.  Pure host arithmetic;
  * only n, d, n_clusters, rank, n_probes and cluster_offsets are read.  Returns 0 on
- * invalid input. */
+ * invalid input.  Up to 32768 points this holds the solver's blocks four times over, for the
+ * systems that nugpr_train_step and nugpr_predict solve side by side: a workspace smaller by up to
+ * 3 x 7 x 8 n (n_probes + 1) bytes is taken too, and the systems then one after the other, with the
+ * same results (as with a basis W, NUGPR_COMPENSATE or max_iter > 1024, which leave that part alone). */
 size_t nugpr_workspace_bytes(const nugpr_problem* problem);
 
 /* Validates the problem, lays out the workspace and builds the theta-independent

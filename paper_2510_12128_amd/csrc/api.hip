@@ -287,6 +287,10 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   Layout L;
   int rc = plan_layout(pb, prm->flags, L);
   if (rc) return rc;
+  // One system at a time where the context never takes more (run_pcg_systems) or the workspace has no room for them
+  if (L.slots > 1 && (pb->W || L.compensate || prm->max_iter > L.slot_iter || pb->workspace_bytes < L.total)) {
+    if ((rc = plan_layout(pb, prm->flags, L, prm->max_iter))) return rc;
+  }
   if (L.compensate && L.ncr > COMPENSATE_HOST_MAX && (prm->flags & NUGPR_ACC_FP32)) {
     set_error("NUGPR_COMPENSATE with n_clusters * rank > 512 needs the default (fp64) arithmetic mode");
     return NUGPR_ERR_INVALID;
@@ -358,11 +362,9 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->Ppart = w + L.o_Ppart;
   c->dotpart = reinterpret_cast<double*>(w + L.o_dot);
   c->d_state = reinterpret_cast<PcgState*>(w + L.o_state);
-  // systems side by side, where a slot's logs hold a solve
-  const bool fits = c->params.max_iter <= L.slot_iter;
-  c->slots = fits ? L.slots : 1;
-  c->alog = reinterpret_cast<double*>(w + (fits ? L.o_alog : L.o_long_alog));
-  c->blog = reinterpret_cast<double*>(w + (fits ? L.o_blog : L.o_long_blog));
+  c->slots = L.slots;
+  c->alog = reinterpret_cast<double*>(w + L.o_alog);
+  c->blog = reinterpret_cast<double*>(w + L.o_blog);
   c->d_logdet = reinterpret_cast<double*>(w + L.o_logdet);
   c->d_tiles = reinterpret_cast<uint64_t*>(w + L.o_tiles);
   hipStream_t s = as_stream(stream);

@@ -80,7 +80,7 @@ static void plan_factor(Layout& L) {
   }
 }
 
-int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
+int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_system_iter) {
   if (!pb || !pb->cluster_offsets) { set_error("null problem or cluster_offsets"); return NUGPR_ERR_INVALID; }
   if (pb->n <= 0 || pb->n > (int64_t)0x7fff0000) { set_error("n out of range"); return NUGPR_ERR_INVALID; }
   if (pb->d < 1 || pb->d > MAX_D) { set_error("d must be 1..64"); return NUGPR_ERR_INVALID; }
@@ -93,7 +93,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.n = pb->n; L.d = pb->d; L.nc = pb->n_clusters; L.r = pb->rank; L.t = pb->n_probes;
   L.T = L.t + 1;
   L.p = (flags & NUGPR_ISOTROPIC) ? 3 : L.d + 2;
-  L.max_iter = MAX_ITER_CAP;          // the coefficient logs are sized for the cap
+  L.max_iter = one_system_iter > 0 ? one_system_iter : MAX_ITER_CAP;          // rows of the coefficient logs
   L.compensate = (flags & NUGPR_COMPENSATE) != 0;
   if ((int64_t)L.nc * L.r > (int64_t)1 << 24) { set_error("n_clusters*rank too large"); return NUGPR_ERR_INVALID; }
   L.ncr = L.nc * L.r;
@@ -188,14 +188,10 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L) {
   L.o_S0 = take(cur, (size_t)L.ncr * L.T * sizeof(double));
   // The blocks of a solve, once per system that can be taken side by side.  Up to 32768 points (256 partial sums a dot product):
   // there a launch of one system leaves most of the chip idle.
-  L.slots = L.n_dot_blocks <= 256 ? MAX_SLOTS : 1;
-  // Their logs share the rows of one solve at the cap between them; a context that allows a solve more than its share takes one
-  // system at a time, with logs beside the slots.
+  L.slots = L.n_dot_blocks <= 256 && one_system_iter <= 0 ? MAX_SLOTS : 1;
+  // Their logs share the rows of one solve at the cap between them: a context that allows a solve more than its share takes one
+  // system at a time.
   L.slot_iter = L.max_iter / L.slots;
-  if (L.slots > 1) {
-    L.o_long_alog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
-    L.o_long_blog = take(cur, (size_t)L.max_iter * MAX_COLS * sizeof(double));
-  }
   cur = align_up(cur, 256);
   const size_t slot0 = cur;
   L.o_X = take(cur, vec);

@@ -190,9 +190,8 @@ struct Layout {
   size_t o_x0 = 0, o_Z0 = 0, o_P = 0, o_Clo = 0, o_S0 = 0, o_dav = 0;
   size_t o_assign = 0, o_rep_ptr = 0, o_rep_pts = 0, o_rows_before = 0;
   size_t items_bytes = 0;
-  int slots = 1;                     // MAX_SLOTS, or 1 on large problems
+  int slots = 1;                     // MAX_SLOTS, or 1 (large problems, contexts of one system at a time)
   int slot_iter = 0;                 // iterations that the logs of a slot hold
-  size_t o_long_alog = 0, o_long_blog = 0;   // logs of a context that allows more (with slots > 1 only)
   size_t slot_bytes = 0;             // from a block of one slot (X .. blog) to that of the next
   int n_dot_blocks = 0;
   int max_iter = 0;
@@ -247,7 +246,7 @@ struct nugpr_ctx {
   nugpr::BuildItem* d_pan_c = nullptr;       // work items of the coupling assembly
   int n_pan_diag = 0, n_pan_c = 0;
   nugpr::StripTable tab_WtD, tab_KC, tab_C, tab_WP, tab_lowG, tab_upG, tab_lowL;
-  int slots = 1;                         // systems the solver can take side by side (1, 2 or 4)
+  int slots = 1;                         // systems the solver can take side by side (1 or MAX_SLOTS)
   // optional event timing of the K_diag / C streaming launch
   bool prof_on = false;
   std::vector<hipEvent_t> prof_ev;       // start/stop pairs
@@ -313,7 +312,8 @@ int hip_fail(hipError_t e, const char* what);
   } while (0)
 
 // layout.cpp ----------------------------------------------------------------
-int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L);
+// (one_system_iter > 0: for one system at a time and solves of up to that many iterations)
+int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_system_iter = 0);
 
 // build_blocks.hip ----------------------------------------------------------
 int launch_setup(nugpr_ctx* c, const float* user_reps, const float* user_W, hipStream_t s);

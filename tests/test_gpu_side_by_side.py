@@ -145,3 +145,38 @@ def test_two_column_groups_side_by_side(lib, sizes, spacing, acc_fp32):
         outs.append((step["nll0"], step["grad"].tolist(), post["mean"].tolist(), post["var"].tolist()))
         ctx.close()
     assert outs[0] == outs[1]
+
+
+@pytest.mark.parametrize("t", [0, 4, 32])
+def test_workspace_for_one_system(lib, monkeypatch, t):
+    """Less workspace, by the three more sets of seven vector blocks: the same results, one system at a time; less than that is
+    refused."""
+    from paper_2510_12128_amd import binding as B
+    sizes = [64, 130, 97, 3, 200, 71]
+    n = sum(sizes)
+    whole = B.load_library()
+    less, whole_bytes = [0], 0
+
+    class Smaller:
+        def __getattr__(self, name):
+            return getattr(whole, name)
+
+        def nugpr_workspace_bytes(self, problem):
+            nonlocal whole_bytes
+            whole_bytes = whole.nugpr_workspace_bytes(problem)
+            return whole_bytes - less[0]
+
+    monkeypatch.setattr(B, "load_library", lambda: Smaller())
+    phi = np.log(np.array([0.9, 1.1, 1.0, 0.3]))
+    outs = []
+    for less[0] in (0, 3 * 7 * 8 * n * (t + 1)):
+        X, (ctx,) = _contexts(lib, sizes, t, (SHARE,), False, False)
+        o = ctx.nugpr_train_step(phi, np.zeros(4), np.zeros(4), 0)
+        p = ctx.nugpr_predict(np.exp(phi), X[:5 * (t + 1)])
+        assert o["code"] == 0 and p["code"] == 0
+        outs.append((o["nll0"], o["grad"].tolist(), p["mean"].tolist(), p["var"].tolist()))
+        ctx.close()
+    assert outs[0] == outs[1]
+    less[0] = whole_bytes - 4 * sum((64 * (-(-b // 64))) ** 2 for b in sizes)          # room for one of the matrices
+    with pytest.raises(B.NugprError):
+        _contexts(lib, sizes, t, (SHARE,), False, False)
