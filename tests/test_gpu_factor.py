@@ -13,6 +13,9 @@ SIZES = {
     "one-long": [2113],
     "long-and-short": [1665, 70, 1024, 3, 1471],
     "uneven-many": [64 * (1 + k % 7) + k for k in range(70)],          # more clusters than lanes look at in one go
+    # enough blocks for launches of whole blocks of 128 (test_factor_routes.py): odd and even numbers of tiles, ragged last ones
+    "whole-blocks": [513, 575, 641, 769, 833, 1025] * 10,
+    "whole-blocks-shared-sums": [1025] * 20 + [1087] * 20 + [1000] * 14 + [513, 70, 1],
 }
 
 
@@ -31,6 +34,8 @@ def test_factor_and_inverse_at_block_edges(lib, name):
         code, logdet, bad = ctx.nugpr_precond_factor()
         assert code == 0 and bad == -1
         want = 0.0
+        V = torch.randn(n, 3, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+        Z = ctx.nugpr_precond_apply(V)
         for i, b in enumerate(sizes):
             K = ctx.nugpr_export(B.EXPORT_K, i).double()
             L = ctx.nugpr_export(B.EXPORT_L, i).double()
@@ -44,7 +49,11 @@ def test_factor_and_inverse_at_block_edges(lib, name):
             # residual of an inverse by blocks, likewise relative to |Y| |L|
             res = (Y @ L - torch.eye(b, device=L.device, dtype=L.dtype)).abs() / (Y.abs() @ L.abs()).clamp_min(1.0)
             assert float(res.max()) <= (b + 1 + 64) * u, (name, i, float(res.max()) / u)
-            assert float(L.triu(1).abs().max()) == 0.0 and float(Y.triu(1).abs().max()) == 0.0
+            # the apply takes its second half from the mirror image of Y: fp64 sums over b terms, rounded to fp32
+            v = V[off[i]:off[i + 1]].double()
+            ref = Y.T @ (Y @ v)
+            bound = 2.0 ** -24 * ref.abs() + 2 * b * 2.0 ** -53 * (Y.abs().T @ (Y.abs() @ v.abs()))
+            assert float(((Z[off[i]:off[i + 1]].double() - ref).abs() / bound).max()) <= 1.0, (name, i)
             want -= 2.0 * float(torch.log(Y.diagonal()).sum())
         assert abs(logdet - want) <= 1e-12 * n + 1e-10 * abs(want)
     ctx.close()
