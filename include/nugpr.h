@@ -310,6 +310,11 @@ int nugpr_compensation_steps(const nugpr_ctx* ctx, int32_t* out /*HOST*/);
  * lambda_0, Householder tridiagonalisation + QL.  n = 1..4096.  Pure host arithmetic. */
 int nugpr_host_smallest_eigenvalue(const double* A /*HOST*/, int32_t n, double* out /*HOST*/);
 
+/* The two smallest eigenvalues e[0] <= e[1] (e[1] = infinity for n = 1) of a dense symmetric n x n matrix A
+ * (HOST, row-major fp64, not modified, both triangles read) and a unit eigenvector y (n entries) of e[0]: the
+ * host routine behind a step of the device iteration for lambda_0.  n = 1..24.  Pure host arithmetic. */
+int nugpr_host_lowest_eigenpair(const double* A /*HOST*/, int32_t n, double* e /*HOST, 2*/, double* y /*HOST, n*/);
+
 /* Halvings each hyperparameter's forward difference took in the last nugpr_train_step of a
  * NUGPR_FD_FORWARD context (Section 3.1): out is HOST, p entries; zeros before the first step. */
 int nugpr_fd_halvings(const nugpr_ctx* ctx, int32_t* out /*HOST*/);

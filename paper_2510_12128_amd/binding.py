@@ -119,6 +119,8 @@ def load_library():
     lib.nugpr_compensation_steps.argtypes = [vp, ip]
     lib.nugpr_host_smallest_eigenvalue.restype = C.c_int
     lib.nugpr_host_smallest_eigenvalue.argtypes = [dp, C.c_int32, dp]
+    lib.nugpr_host_lowest_eigenpair.restype = C.c_int
+    lib.nugpr_host_lowest_eigenpair.argtypes = [dp, C.c_int32, dp, dp]
     lib.nugpr_fd_halvings.restype = C.c_int
     lib.nugpr_fd_halvings.argtypes = [vp, ip]
     lib.nugpr_export.restype = C.c_int
@@ -177,6 +179,15 @@ def nugpr_host_smallest_eigenvalue(A):
     out = C.c_double()
     _check(load_library().nugpr_host_smallest_eigenvalue(_dptr(a), a.shape[0], C.byref(out)))
     return out.value
+
+
+def nugpr_host_lowest_eigenpair(A):
+    a = np.ascontiguousarray(np.asarray(A, dtype=np.float64))
+    if a.ndim != 2 or a.shape[0] != a.shape[1]:
+        raise NugprError(NUGPR_ERR_INVALID, "A must be square")
+    e, y = np.zeros(2), np.zeros(a.shape[0])
+    _check(load_library().nugpr_host_lowest_eigenpair(_dptr(a), a.shape[0], _dptr(e), _dptr(y)))
+    return e, y
 
 
 def nugpr_confidence_band(mean, var):

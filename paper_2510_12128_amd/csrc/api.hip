@@ -975,6 +975,18 @@ int nugpr_host_smallest_eigenvalue(const double* A, int32_t n, double* out) {
   return NUGPR_OK;
 }
 
+int nugpr_host_lowest_eigenpair(const double* A, int32_t n, double* e, double* y) {
+  if (!A || !e || !y || n < 1 || n > EIGMIN_MAX_BASIS) { set_error("lowest_eigenpair needs a matrix with n = 1..24"); return NUGPR_ERR_INVALID; }
+  std::vector<double> H((size_t)EIGMIN_MAX_BASIS * EIGMIN_MAX_BASIS, 0.0);
+  for (int i = 0; i < n; ++i)
+    for (int j = 0; j < n; ++j) {
+      H[(size_t)i * EIGMIN_MAX_BASIS + j] = A[(size_t)i * n + j];
+      if (!std::isfinite(A[(size_t)i * n + j])) { set_error("lowest_eigenpair: matrix not finite"); return NUGPR_ERR_INVALID; }
+    }
+  if (lowest_eigenpair(H, n, e[0], e[1], y)) { set_error("eigen-solve did not converge"); return NUGPR_ERR_INVALID; }
+  return NUGPR_OK;
+}
+
 int nugpr_fd_halvings(const nugpr_ctx* c, int32_t* out) {
   if (!c || !out) { set_error("null argument"); return NUGPR_ERR_INVALID; }
   for (int i = 0; i < c->L.p; ++i) out[i] = c->fd_halvings[i];

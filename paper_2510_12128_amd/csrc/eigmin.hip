@@ -37,7 +37,7 @@ namespace nugpr {
 typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int EB = 128;               // order of the preconditioner's diagonal blocks
 constexpr int EBP = EB + 1;           // row stride of a block in LDS (odd: column accesses spread over the banks)
-constexpr int DAV_MAX_BASIS = 24;     // basis vectors kept before a restart
+constexpr int DAV_MAX_BASIS = EIGMIN_MAX_BASIS;
 constexpr int DAV_KEEP = 3;           // Ritz vectors a restart keeps
 constexpr int DAV_MAX_STEPS = 150;
 
@@ -486,7 +486,7 @@ static void small_sym_eigen(std::vector<double>& A, int m, std::vector<double>& 
 // The two lowest eigenvalues and the eigenvector y of the lowest one, for the steps that need no more: Householder reduction
 // to tridiagonal form, eigenvalues by the QL iteration, the vector by inverse iteration there (Gaussian elimination with
 // row exchanges) and back.  H: m x m, row stride DAV_MAX_BASIS.  At 24 x 24 39 us; all eigenvectors by Jacobi rotations 220.
-static int lowest_eigenpair(const std::vector<double>& H, int m, double& e0, double& e1, double* y) {
+int lowest_eigenpair(const std::vector<double>& H, int m, double& e0, double& e1, double* y) {
   constexpr int S = DAV_MAX_BASIS;
   y[0] = 1.0;
   e0 = H[0];

@@ -19,6 +19,7 @@ constexpr int MAX_ITER_CAP = 4096;
 // idle): each has a slot of the workspace for its vector blocks, sums and scalars.
 constexpr int MAX_SLOTS = 4;
 constexpr int COMPENSATE_HOST_MAX = 512;     // lambda_0 of eq. (krep): dense host eigen-solve up to this n_c r, iteration on the device beyond
+constexpr int EIGMIN_MAX_BASIS = 24;         // basis vectors that iteration keeps before a restart
 constexpr double EIGMIN_REL_TOL = 2e-11;     // stopping tolerance of that iteration on lambda_0, relative to alpha
 constexpr double EIGMIN_PSD_TOL = 1e-5;      // at its step cap a Ritz value below this (times alpha) is accepted: lambda_min lies in [0, theta]
 // doubles of workspace the device iteration needs for a coupling matrix of leading dimension ldc with n rows:
@@ -336,6 +337,9 @@ int launch_nystrom_basis(nugpr_ctx* c, const double* theta, double jitter_rel, h
 // smallest eigenvalue of the kernel matrix of the representatives at theta: off-diagonal part from (c->C + c->Clo),
 // the scalar alpha on the diagonal, diagonal blocks for the preconditioner recomputed from the representatives
 int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double* lambda_out, int* steps_out);
+// The two lowest eigenvalues of the symmetric m x m matrix H (row stride EIGMIN_MAX_BASIS, m up to that) and a unit eigenvector y of
+// the lowest one; 0 on success
+int lowest_eigenpair(const std::vector<double>& H, int m, double& e0, double& e1, double* y);
 // Chi_ii = float(value), Clo_ii = what that drops
 int coupling_set_diag(nugpr_ctx* c, double value, hipStream_t s);
 

@@ -115,6 +115,64 @@ def test_host_smallest_eigenvalue_against_lapack(lib):
         B.nugpr_host_smallest_eigenvalue(np.zeros((0, 0)))
 
 
+def _symmetric(kind, m, rng):
+    A = rng.standard_normal((m, m))
+    A = A + A.T
+    h = m // 2
+    if kind in ("degenerate", "graded"):
+        w = rng.standard_normal(m)
+        w[:max(1, h)] = w.min()
+        if kind == "graded":
+            w = 10.0 ** rng.uniform(-14, 2, m)
+        Q = np.linalg.qr(A)[0]
+        A = (Q * w) @ Q.T
+    elif kind == "decoupled":                          # a tridiagonal form that falls apart
+        A[:h, h:] = A[h:, :h] = 0.0
+    elif kind == "twice":                              # every eigenvalue of the two halves twice
+        B = A[:h, :h].copy()
+        A = np.eye(m) * 20.0
+        A[:h, :h] = A[h:2 * h, h:2 * h] = B
+    elif kind == "diagonal":
+        A = np.diag(rng.standard_normal(m))
+    elif kind == "multiple of I":
+        A = 1.7 * np.eye(m)
+    elif kind == "zero":
+        A = np.zeros((m, m))
+    elif kind == "ones":
+        A = np.ones((m, m))
+    elif kind == "restart":                            # three Ritz values and new rows that hardly couple
+        k = min(3, m)
+        B = np.diag(np.sort(rng.uniform(0.0, 1.0, m)))
+        B[k:, :] += 10.0 ** rng.uniform(-18, 0) * A[k:, :]
+        A = B
+    elif kind == "wilkinson":                          # pairs of nearly equal eigenvalues
+        A = np.diag(np.abs(np.arange(m) - h).astype(float)) + np.eye(m, k=1) + np.eye(m, k=-1)
+    return 0.5 * (A + A.T)
+
+
+@pytest.mark.parametrize("kind", ["random", "degenerate", "graded", "decoupled", "twice", "diagonal", "multiple of I", "zero", "ones", "restart",
+                                  "wilkinson"])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 12, 23, 24])
+def test_host_lowest_eigenpair_against_lapack(lib, m, kind):
+    # one step of the device iteration for lambda_0: two eigenvalues and one vector, to rounding (m sums of m terms)
+    rng = np.random.default_rng(m)
+    for _ in range(20):
+        A = _symmetric(kind, m, rng)
+        (e0, e1), y = B.nugpr_host_lowest_eigenpair(A)
+        want = np.linalg.eigvalsh(A)
+        bound = 4.0 * m * 2.0 ** -52 * np.abs(A).sum(axis=1).max()
+        assert abs(e0 - want[0]) <= bound
+        assert e1 == np.inf if m == 1 else abs(e1 - want[1]) <= bound
+        assert np.linalg.norm(A @ y - e0 * y) <= bound
+        assert abs(np.linalg.norm(y) - 1.0) <= 4.0 * m * 2.0 ** -52
+
+
+def test_host_lowest_eigenpair_refuses(lib):
+    for A in (np.zeros((0, 0)), np.zeros((25, 25)), np.full((2, 2), np.nan), np.zeros((2, 3))):
+        with pytest.raises(B.NugprError):
+            B.nugpr_host_lowest_eigenpair(A)
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "_LIB", None)
     monkeypatch.setattr(B, "lib_path", lambda: str(tmp_path / "libnugpr.so"))
