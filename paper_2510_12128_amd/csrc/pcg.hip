@@ -31,17 +31,22 @@ __device__ __forceinline__ const P* of_system(const P* p, uint64_t stride) {
   return reinterpret_cast<const P*>(reinterpret_cast<const char*>(p) + (uint64_t)blockIdx.y * stride);
 }
 
-// The vector kernels with dot products: workgroups of 512 threads, a thread owns one column of every (512 / T)-th row, four
+// The vector kernels with dot products: workgroups of up to 512 threads, a thread owns one column of every (threads / T)-th row, four
 // rows at a time with all their loads ahead of the first use.  Up to 32768 points there is one workgroup a system on a compute
 // unit, so what bounds them is how many loads are in flight; beyond, HBM.  Update of two systems of 32768 x 17 values with 256
 // threads and a row at a time 22.0 us, now 13.9 (1024 threads: 18.9), of one of 131072 20.8 / 21.0 (28.6), of 262144 40 / 34; the
 // product's last pass 11.7 / 7.3, 14.9 / 13.2, 28 / 25.
 constexpr int VB = 512;
 constexpr int ROWS_AT_ONCE = 4;
-// sums[col] of the workgroup's VB values (thread = row of the pass times T + column), in a fixed order: eight groups of rows,
+// Narrow blocks: fewer threads, which the rows of a workgroup still fill, and shorter sums over them.  Eight iterations in fp64,
+// 128 / 256 / 512 threads in per cent of one row at a time with 256: one column 81 / 85 / 95 at 2048 points, 88 / 95 / 102 at
+// 32768, 92 / 94 / 104 at 131072; five columns 93 / 98 / 98 at 8192, 111 / 102 / 102, 98 / 96 / 100; eight 90 / 89 / 92 at 2048, 100 / 97 / 97,
+// 98 / 97 / 100; nine 90 / 87 / 89, 101 / 98 / 95, 98 / 98 / 99; seventeen 91 / 88 / 88, 98 / 93 / 90, 98 / 97 / 97.
+static int vector_threads(int T) { return T == 1 ? 128 : T <= 8 ? 256 : VB; }
+// sums[col] of the workgroup's values (thread = row of the pass times T + column), in a fixed order: eight groups of rows,
 // then the groups.  red holds the values; the result is valid for threads below T.
 __device__ __forceinline__ double column_sum(double* red, int T, int tid) {
-  const int rpp = VB / T, g = tid / T;
+  const int rpp = (int)blockDim.x / T, g = tid / T;
   __syncthreads();
   double s = 0.0;
   if (g < 8) {
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(VB) void k_dot(const VT* __restrict__ A0, const VT*
   A0 = of_system(A0, sa); B0 = of_system(B0, sb);
   A1 = of_system(A1, sa); B1 = of_system(B1, sb);
   partial = of_system(partial, sys);
-  const int rpp = VB / T;                       // rows per pass
+  const int rpp = (int)blockDim.x / T;          // rows per pass
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const int64_t rows_per_block = (n + gridDim.x - 1) / gridDim.x;
@@ -313,7 +318,7 @@ __global__ __launch_bounds__(256) void k_pcg_beta(PcgState* __restrict__ st, con
 // 271 / 273 at 32768 (256), 304 / 302 at 40960 (320), 372 / 351 at 65536 (512), 664 / 579 at 131072 (1024).
 constexpr int FUSE_BLOCKS = 256;
 __device__ __forceinline__ void sum_all_partials(const double* __restrict__ partial, int nblocks, int T, double* red, double* out) {
-  const int rpp = VB / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
+  const int rpp = (int)blockDim.x / T, tid = threadIdx.x, myrow = tid / T, col = tid - myrow * T;
   double s = 0.0;
   if (myrow < rpp) {
 #pragma unroll 4
@@ -345,7 +350,7 @@ __global__ __launch_bounds__(VB) void k_update_xr_dots(VT* __restrict__ X, VT* R
   if (B) B = of_system(B, s_b);
   st = of_system(st, sys); partial = of_system(partial, sys); alog = of_system(alog, sys);
   if (dqs) dqs = of_system(dqs, sys);
-  const int rpp = VB / T;
+  const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(VB) void k_update_d(VT* D, const VT* Din, const VT*
   __shared__ double red[VB];
   __shared__ double be[MAX_COLS];
   __shared__ int goes_on[MAX_COLS];
-  const int rpp = VB / T;
+  const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   if (rzs) {                                   // the step of k_pcg_beta (beta itself can be negative: rho_0 may be, by rounding)
@@ -548,7 +553,7 @@ __global__ __launch_bounds__(VB) void k_lincomb_dot(VT* __restrict__ Q, const VT
   const double a = of.a[blockIdx.y], b = of.b[blockIdx.y];
   Q = of_system(Q, sys);
   if (partial) partial = of_system(partial, sys);
-  const int rpp = VB / T;
+  const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -611,8 +616,8 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
       of.b[e] = ops[e].shift - of.a[e] * c->q0_shift;
     }
     const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
-    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), nb, dim3(VB), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, of, (int64_t)L.n, T, dq_partial, sys);
-    else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(VB), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
+    if (c->acc64) hipLaunchKernelGGL((k_lincomb_dot<double>), nb, dim3(vector_threads(T)), 0, s, (double*)Q, (const double*)c->Q0v, (const double*)D, of, (int64_t)L.n, T, dq_partial, sys);
+    else hipLaunchKernelGGL((k_lincomb_dot<float>), nb, dim3(vector_threads(T)), 0, s, (float*)Q, (const float*)c->Q0v, (const float*)D, of, (int64_t)L.n, T, dq_partial, sys);
     NUGPR_HIP(hipGetLastError());
     if (dq_done) *dq_done = dq_partial != nullptr;
     c->stats.products_reused += held;
@@ -774,7 +779,7 @@ __global__ __launch_bounds__(VB) void k_onehot_expand_dot(VT* __restrict__ Q, co
   __shared__ double red[VB];
   Q = of_system(Q, sys); P = of_system(P, sys); partial = of_system(partial, sys);
   D = of_system(D, s_d);
-  const int rpp = VB / T;
+  const int rpp = (int)blockDim.x / T;
   const int tid = threadIdx.x;
   const int myrow = tid / T, col = tid - myrow * T;
   const bool live = myrow < rpp;
@@ -849,8 +854,8 @@ static int run_expand(nugpr_ctx* c, void* Q, int T, hipStream_t s, const void* D
   if (c->onehot && dq_partial) {
     const dim3 nb((unsigned)L.n_dot_blocks, (unsigned)nsys);
     const uint64_t sys = L.slot_bytes;
-    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), nb, dim3(VB), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
-    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), nb, dim3(VB), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
+    if (c->acc64) hipLaunchKernelGGL((k_onehot_expand_dot<double>), nb, dim3(vector_threads(T)), 0, s, (double*)Q, (const double*)c->Ppart, c->assign, (const double*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
+    else hipLaunchKernelGGL((k_onehot_expand_dot<float>), nb, dim3(vector_threads(T)), 0, s, (float*)Q, (const float*)c->Ppart, c->assign, (const float*)D, (int64_t)L.n, T, dq_partial, parts, stride, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -952,7 +957,7 @@ static int dot2_t(nugpr_ctx* c, const VT* A0, const VT* B0, const VT* A1, const 
                   double* out1, hipStream_t s) {
   const Layout& L = c->L;
   const int nb = L.n_dot_blocks;
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart, (uint64_t)0, (uint64_t)0, (uint64_t)0);
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(vector_threads(T)), 0, s, A0, B0, A1, B1, (int64_t)L.n, T, c->dotpart, (uint64_t)0, (uint64_t)0, (uint64_t)0);
   NUGPR_HIP(hipGetLastError());
   NUGPR_HIP(hipMemcpyAsync(c->h_buf, c->dotpart, (size_t)2 * nb * MAX_COLS * sizeof(double), hipMemcpyDeviceToHost, s));
   NUGPR_HIP(hipStreamSynchronize(s));
@@ -984,6 +989,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   const bool extras = out[0].extras != nullptr;
   const int64_t n = L.n;
   const int nb = L.n_dot_blocks;
+  const int vt = vector_threads(T);
   // workgroups of the direction update: four rows a thread, and where each of them adds up the partial sums first, no more than two
   // on a compute unit
   const int eg = (int)std::min<int64_t>((n + ROWS_AT_ONCE * (VB / T) - 1) / (ROWS_AT_ONCE * (VB / T)), nb <= FUSE_BLOCKS ? 512 : 4096);
@@ -1010,7 +1016,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     // x_0 = 0, r_0 = b, d_0 = z_0 = M^-1 r_0 written straight into D
     hipLaunchKernelGGL((k_pcg_init<VT>), dim3(1024, ny), dim3(256), 0, s, X, R, B, plain ? B : (const VT*)nullptr, D, n * T, sys, s_b);
     if (!plain && (rc = precond(c, R, D, T, s, nsys, held))) return rc;
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(vt), 0, s, (const VT*)R, (const VT*)R, (const VT*)R, (const VT*)D, n, T, c->dotpart, sys, sys, sys);
     hipLaunchKernelGGL(k_pcg_begin, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart, nb, sys);
   }
   NUGPR_HIP(hipGetLastError());
@@ -1049,7 +1055,7 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
   };
   auto issue_tail = [&](int rows) -> int {
     if (extras)
-      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(VB), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
+      hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb, ny), dim3(vt), 0, s, B, (const VT*)X, B, (const VT*)X, n, T, c->dotpart, s_b, sys, sys);
     hipLaunchKernelGGL(k_pcg_tail, dim3(T, ny), dim3(256), 0, s, c->d_state, c->dotpart + (size_t)nb * MAX_COLS, nb, T, next_report(rows), c->h_flags, sys);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
@@ -1059,11 +1065,11 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
     bool dq_done = false;
     if ((rc = plain ? run_pade_q(c, Dcur, Q, T, s) : product(c, ops, nsys, held, Dcur, Q, T, s, dq_sums, &dq_done, nullptr, nullptr))) return rc;
     if (!dq_done)
-      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
+      hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(vt), 0, s, Dcur, (const VT*)Q, Dcur, (const VT*)Q, n, T, dq_sums, s_d, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_alpha, dim3(T), dim3(256), 0, s, c->d_state, dq_sums, nb, it, c->alog);
     // the update, fused with ||r||^2 for the stop test and, in the iteration expected to be the last, <b, x>
     const bool report = it + 1 == expect || it == expect || it + 1 >= max_iter;
-    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(VB), 0, s, X, R, first ? B : (const VT*)R, Dcur,
+    hipLaunchKernelGGL((k_update_xr_dots<VT>), dim3(nb, ny), dim3(vt), 0, s, X, R, first ? B : (const VT*)R, Dcur,
                        (const VT*)Q, (report && extras) ? B : (const VT*)nullptr, c->d_state, n, T, first ? 1 : 0,
                        c->dotpart, fuse ? dq_sums : (const double*)nullptr, it, c->alog, sys, first ? s_b : sys, s_d, s_b, fuse && own && it == 0 ? (plain ? 1 : 0) : -1);
     first = false;
@@ -1086,9 +1092,9 @@ static int pcg_t(nugpr_ctx* c, const VT* B, VT* X, int T, const Operator* ops, i
       if (n_active == 0 || it >= max_iter) break;
     }
     if (!plain && (rc = precond(c, R, Z, T, s, nsys, held))) return rc;
-    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(VB), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
+    hipLaunchKernelGGL((k_dot<1, VT>), dim3(nb, ny), dim3(vt), 0, s, (const VT*)R, Zr, (const VT*)R, Zr, n, T, rz_sums, sys, sys, sys);
     if (!fuse) hipLaunchKernelGGL(k_pcg_beta, dim3(T), dim3(256), 0, s, c->d_state, rz_sums, nb, j, c->blog);
-    hipLaunchKernelGGL((k_update_d<VT>), dim3(eg, ny), dim3(VB), 0, s, D, Dcur, Zr, c->d_state, n, T,
+    hipLaunchKernelGGL((k_update_d<VT>), dim3(eg, ny), dim3(vt), 0, s, D, Dcur, Zr, c->d_state, n, T,
                        fuse ? rz_sums : (const double*)nullptr, nb, j, c->blog, sys, s_d);
     NUGPR_HIP(hipGetLastError());
     Dcur = D;
@@ -1153,10 +1159,10 @@ static int store_known_t(nugpr_ctx* c, hipStream_t s) {
   const int nb = L.n_dot_blocks;
   const VT *B = (const VT*)c->Bv, *Z0 = (const VT*)c->Z0v, *P = (const VT*)c->Pv;
   const uint64_t one = 0;                // (one system)
-  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart, one, one, one);
+  hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(vector_threads(L.T)), 0, s, B, B, B, Z0, (int64_t)L.n, L.T, c->dotpart, one, one, one);
   hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 0);
   if (L.t > 0) {
-    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(VB), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart, one, one, one);
+    hipLaunchKernelGGL((k_dot<2, VT>), dim3(nb), dim3(vector_threads(L.T)), 0, s, P, P, P, P, (int64_t)L.n, L.T, c->dotpart, one, one, one);
     hipLaunchKernelGGL(k_store_known, dim3(L.T), dim3(256), 0, s, c->d_state, c->dotpart, nb, 1);
   }
   NUGPR_HIP(hipGetLastError());
