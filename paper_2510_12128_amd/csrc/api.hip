@@ -379,14 +379,15 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   if (e != hipSuccess) return fail(hip_fail(e, "hipHostMalloc(buf)"));
   std::memset(c->h_flags, 0, MAX_SLOTS * sizeof(HostFlags));
 
-  for (int i = 0; i < L.slots; ++i) {
-    e = hipMemsetAsync(reinterpret_cast<char*>(c->d_state) + i * L.slot_bytes, 0, sizeof(PcgState), s);      // counters in it start at zero
-    if (e != hipSuccess) return fail(hip_fail(e, "clear solver state"));
-  }
-  e = hipMemcpyAsync(c->d_cl, L.cl.data(), sizeof(ClusterInfo) * L.nc, hipMemcpyHostToDevice, s);
+  e = hipMemset2DAsync(c->d_state, L.slot_bytes, 0, sizeof(PcgState), (size_t)L.slots, s);      // counters in it start at zero
+  if (e != hipSuccess) return fail(hip_fail(e, "clear solver state"));
+  // the cluster table and the factorisation's work lists
+  const size_t lists = L.o_rows_before - L.o_cl;
+  std::vector<char> head(lists + L.rows_before.size() * sizeof(uint32_t));
+  std::memcpy(head.data(), L.cl.data(), sizeof(ClusterInfo) * L.nc);
+  std::memcpy(head.data() + lists, L.rows_before.data(), L.rows_before.size() * sizeof(uint32_t));
+  e = hipMemcpyAsync(c->d_cl, head.data(), head.size(), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return fail(hip_fail(e, "upload cluster table"));
-  e = hipMemcpyAsync(c->d_rows_before, L.rows_before.data(), L.rows_before.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return fail(hip_fail(e, "upload the factorisation's work lists"));
   Tables t;
   build_tables(L, t);
   const size_t total_items = t.WtD.size() + t.KC.size() + t.Conly.size() + t.WP.size() + t.lowG.size() + t.upG.size() + t.lowL.size();

@@ -155,6 +155,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   const size_t f = sizeof(float);
   const size_t vec = (size_t)L.n * L.T * sizeof(double);      // fp64 vector blocks (fp32 mode uses half)
   L.o_cl = take(cur, sizeof(ClusterInfo) * L.nc);
+  L.o_rows_before = take(cur, L.rows_before.size() * sizeof(uint32_t));        // (right behind: one upload)
   L.o_Kd = take(cur, L.kd_elems * f);
   L.o_G = take(cur, L.kd_elems * f);
   L.o_C = take(cur, (size_t)L.ldc * L.ldc * f);
@@ -179,7 +180,6 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.o_assign = take(cur, (size_t)L.n * sizeof(int32_t));
   L.o_rep_ptr = take(cur, ((size_t)L.ncr + 1) * sizeof(int32_t));
   L.o_rep_pts = take(cur, (size_t)L.n * sizeof(int32_t));
-  L.o_rows_before = take(cur, L.rows_before.size() * sizeof(uint32_t));
   L.o_B = take(cur, vec);
   L.o_x0 = take(cur, (size_t)L.n * sizeof(double));
   L.o_Z0 = take(cur, vec);
