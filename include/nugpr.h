@@ -285,8 +285,9 @@ int nugpr_train_step(nugpr_ctx* ctx, double* log_theta, double* adam_m, double* 
  * and never stored as a whole.  Xtest: DEVICE m x d row-major fp32, read only, caller
  * keeps ownership.  mean: HOST m doubles.  var: HOST m doubles or NULL (mean only).
  * max_iters_used: HOST, may be NULL.  Synchronises `stream`.  Returns NUGPR_OK,
- * NUGPR_NOT_CONVERGED (some solve hit max_iter; outputs written), NUGPR_INDEFINITE
- * (outputs not complete) or a negative error; m = 0 is a no-op. */
+ * NUGPR_NOT_CONVERGED (some solve hit max_iter; outputs written), NUGPR_INDEFINITE or
+ * NUGPR_NOT_FINITE (outputs written up to the block of n_probes+1 test points that met it) or
+ * a negative error; m = 0 is a no-op. */
 int nugpr_predict(nugpr_ctx* ctx, const double* theta /*HOST*/, const float* Xtest /*DEVICE*/,
                   int64_t m, double* mean /*HOST*/, double* var /*HOST*/, int32_t* max_iters_used,
                   void* stream);
@@ -348,7 +349,8 @@ int nugpr_profile_enable(nugpr_ctx* ctx, int32_t on);
 int nugpr_profile_read(nugpr_ctx* ctx, double* total_ms /*HOST*/, int32_t* launches /*HOST*/, void* stream);
 double nugpr_profile_bytes(const nugpr_ctx* ctx, int32_t ncols);
 
-/* Name of the kernel instantiation behind that launch for vector blocks of `ncols` columns, as profilers print it
+/* Name of the kernel instantiation behind that launch for one vector block of `ncols` columns (a launch that serves
+ * several systems side by side may take another one), as profilers print it
  * without the namespace (e.g. "k_strip<1, true, 1>"), copied into buf (HOST, at most len bytes
  * including the terminating zero).  Pure host logic; lets a caller match stored counter readings to the code
  * that is actually running. */

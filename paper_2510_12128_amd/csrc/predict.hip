@@ -51,7 +51,8 @@ __global__ __launch_bounds__(256) void k_cross_block(CrossArgs a, const float* _
 }
 
 // partial[0][block][col] = sum_i U[i,col] u[i],  partial[1][block][col] = sum_i U[i,col] S[i,col]
-// (S may be null: then only the first set is written).  Same fixed summation order as the CG dots.
+// (S may be null: then only the first set is written).  Fixed summation order: rows split among the workgroups as in the CG's
+// dots, 256 threads, one sum over the rows of a pass.
 template <typename VT>
 __global__ __launch_bounds__(256) void k_predict_dots(const VT* __restrict__ U, const VT* __restrict__ u,
                                                       const VT* __restrict__ S, int64_t n, int T,
