@@ -235,8 +235,9 @@ __global__ __launch_bounds__(256) void k_pcg_check(PcgState* __restrict__ st, co
       const double bx = sum_partials(partial + (int64_t)nblocks * MAX_COLS, nblocks, c, red, tid);
       if (tid == 0) of_system(report.h_bx, report.hsys)[c] = bx;
     }
-    copy_logs(report, sys, T, c * 256 + tid, 256 * T);
-    __threadfence_system();
+    const int at = c * 256 + tid;
+    copy_logs(report, sys, T, at, 256 * T);
+    if (at < report.rows * T || tid == 0) __threadfence_system();      // (whoever stored something)
     __syncthreads();
   }
   if (tid == 0) {
