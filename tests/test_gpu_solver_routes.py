@@ -197,3 +197,38 @@ def test_a_first_long_solve_takes_no_longer_than_the_next(lib):
             assert out["code"] == 0 and out["max_iters_used"] > 400
         ctx.close()
     assert min(first[1:]) <= 1.06 * min(later[1:]), (first, later)      # (the first repetition warms up)
+
+
+@pytest.mark.parametrize("acc_fp32", [False, True])
+@pytest.mark.parametrize("clusters", [5, 130])           # 562 points; 33130, where alpha and beta have kernels of their own
+def test_block_widths_around_the_workgroup_sizes(lib, clusters, acc_fp32):
+    """Blocks of 1, 8 and 9 columns and more change the workgroups of the vector kernels.  Every column meets its tolerance, and comes
+    out as it does in a block of another width: the sums are taken in another order, which moves a solution by no more than the
+    tolerance lets it stop."""
+    import torch
+    rng = np.random.default_rng(2)
+    sizes = (SIZES * (clusters // len(SIZES)) if clusters == len(SIZES) else [256] * clusters)[:clusters]
+    if clusters > len(SIZES):
+        sizes[-1] = 106                                   # rows that no number of workgroups divides
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    centres = 4.5 * np.stack([np.arange(clusters) % 12, np.arange(clusters) // 12], 1)
+    X = (np.repeat(centres, sizes, axis=0) + 0.4 * rng.standard_normal((off[-1], 2))).astype(np.float32)
+    tol = 1e-5
+    ctx = lib.Context(X, X[:, 0], off, 2.0 * rng.integers(0, 2, (off[-1], 16)) - 1.0, 4, tol=tol, max_iter=200, acc_fp32=acc_fp32)
+    ctx.nugpr_build_blocks(np.array([1.0, 1.0, 1.0, 1.0]))
+    assert ctx.nugpr_precond_factor()[0] == 0
+    b = torch.randn(int(off[-1]), 17, generator=torch.Generator("cuda").manual_seed(3), device="cuda")
+    ref = None
+    for ncols in (17, 1, 2, 3, 7, 8, 9, 16):
+        v = b[:, :ncols].contiguous()
+        code, x, iters, _, _ = ctx.nugpr_pcg_solve(v)
+        assert code == 0 and iters.max() >= 2
+        # the residual of the rounded solution: what the solver stopped at, and K' times its fp32 rounding (|K'| <= 260 here)
+        r = (v.double() - ctx.nugpr_matvec(x).double()).norm(dim=0) / v.double().norm(dim=0)
+        assert float(r.max()) <= tol + 2.0 ** -24 * 260.0 * 2.0, ncols
+        if ref is None:
+            ref = x.double()
+        else:                                             # (the smallest eigenvalue of K' is at least about 1, the noise)
+            d = (x.double() - ref[:, :ncols]).norm(dim=0) / v.double().norm(dim=0)
+            assert float(d.max()) <= 2.0 * (tol + 2.0 ** -24 * 260.0 * 2.0), ncols
+    ctx.close()
