@@ -6,7 +6,7 @@
 #include <limits>
 #include <mutex>
 #include <new>
-#include <unordered_map>
+#include <numeric>
 #include <vector>
 
 #include "nugpr_internal.h"
@@ -61,110 +61,122 @@ StripItem make_item(uint64_t a_off, uint32_t lda, uint32_t nrows, uint32_t c_beg
   return it;
 }
 
-void sort_longest_first(std::vector<StripItem>& v) {
-  std::stable_sort(v.begin(), v.end(), [](const StripItem& a, const StripItem& b) {
-    const uint32_t la = a.c_end > a.c_begin ? a.c_end - a.c_begin : 0;
-    const uint32_t lb = b.c_end > b.c_begin ? b.c_end - b.c_begin : 0;
-    return la > lb;
-  });
-}
+// Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by workgroup index, whatever is
+// still running on them, so a table is eight lists, one per die, and workgroup w takes item w / 8 of list w % 8.  Items that read
+// the same rows of the vector block or the same tiles (the strips of one cluster; the two sets of strips that share the tiles of a
+// pair of super-blocks of the coupling matrix) form a group and go to ONE die as far as they fit.
+struct Dealt {
+  std::vector<StripItem> items;
+  uint32_t from[NUM_XCD + 1] = {};
+};
+struct Groups {
+  std::vector<StripItem> items;
+  std::vector<size_t> first;            // of every group
+  void begin() { first.push_back(items.size()); }
+};
 
-// Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by
-// workgroup index.  Items that read the same rows of the vector block (the strips of one cluster,
-// the row strips of one column slab of C) are therefore placed 8 apart, so that they run on ONE die
-// and the slab is fetched from HBM once instead of once per die.  Inside a die's queue the order
-// (longest first) is kept.
-constexpr int NUM_XCD = 8;
-void arrange_for_dies(std::vector<StripItem>& v) {
-  if (v.size() < 2 * NUM_XCD) return;
-  std::vector<std::vector<StripItem>> q(NUM_XCD);
-  std::unordered_map<uint64_t, size_t> groups;       // number of a group in the order of appearance
-  groups.reserve(v.size());
-  for (const StripItem& it : v) {
-    const uint64_t key = ((uint64_t)it.port << 62) | ((uint64_t)it.in_row0 << 30) | (uint64_t)(it.c_begin & 0x3fffffffu);
-    const size_t g = groups.emplace(key, groups.size()).first->second;
-    q[g % NUM_XCD].push_back(it);
-  }
-  std::vector<size_t> pos(NUM_XCD, 0);
-  std::vector<StripItem> out;
-  out.reserve(v.size());
-  while (out.size() < v.size()) {
-    const int die = (int)(out.size() % NUM_XCD);
-    int src = die;
-    if (pos[src] >= q[src].size()) {          // this die's queue is empty: take from the fullest one
-      size_t best = 0;
-      for (int k = 0; k < NUM_XCD; ++k)
-        if (q[k].size() - pos[k] > best) { best = q[k].size() - pos[k]; src = k; }
-    }
-    out.push_back(q[src][pos[src]++]);
-  }
-  v.swap(out);
-}
-
-// The strips of a launch that is resident all at once, or nearly (four workgroups of short strips and two of long ones on
-// each of the 256 compute units), reach the units in rounds, longest first: one unit would get the longest strip of every
-// round, another one the shortest.  Every second round goes in reverse; an item keeps its die (its position modulo 8).
-// nugpr_precond_apply, fp64, 17 columns, as dealt / with this: 300 uneven clusters of 200 points on average (1200 strips)
-// 43 / 42 us, 33 columns 62 / 58 (57 under the loader wave); 128 uneven ones of 512 73 / 68; 32 x 1024 points 48 / 42;
-// 8 x 4096 (512 long strips) 136 / 114.  Launches of several rounds fill the gaps by themselves and are left as they are:
-// 64 x 2048 (2048 long strips) 249 / 253, 32 uneven clusters of 2048 (1024) 176 / 179, 1024 x 256 (4096 short) 118 / 118.
-void alternate_rounds(std::vector<StripItem>& v) {
-  constexpr size_t ROUND = 256;
-  if (v.size() > (short_strips(v) ? 5 : 2) * ROUND) return;
-  for (size_t from = ROUND; from < v.size(); from += 2 * ROUND) {
-    const size_t rows = std::min(ROUND, v.size() - from) / NUM_XCD;        // what is left of a last, partial row stays
-    for (size_t x = 0, y = rows; x + 1 < y; ++x) {
-      --y;
-      std::swap_ranges(v.begin() + from + x * NUM_XCD, v.begin() + from + (x + 1) * NUM_XCD, v.begin() + from + y * NUM_XCD);
+// What an item costs: its tiles, and the two ends of its workgroup (arguments, first loads, sums through LDS).
+uint64_t item_work(const StripItem& it) { return (it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0) + 2; }
+// Equal work for every die.  The groups, in the order given (the heaviest first), each go to the die with the least so far; a group
+// larger than what is missing there to an eighth of the whole is cut, and its rest dealt like a group of its own.  In the order of
+// the workgroups' numbers (groups to the dies in turn, a die without any left taking from the one with most) the busiest die had
+// up to half more than the mean.  Product of 33 columns, 64 uneven clusters of 4096 points on average, that way / now:
+// 2000 / 1436 us (busiest die 1.38 and 1.00 of the mean); a loss on 64 uneven clusters of 2048, 17 columns, 2810 / 2520.
+// With equal clusters the groups go in turn either way.
+Dealt deal_groups(const Groups& groups, bool longest_first = false) {
+  const std::vector<StripItem>& v = groups.items;
+  std::vector<uint32_t> work(v.size());
+  std::vector<uint8_t> die_of(v.size());
+  uint64_t total = 0, load[NUM_XCD] = {};
+  for (size_t i = 0; i < v.size(); ++i) total += work[i] = item_work(v[i]);
+  const uint64_t share = (total + NUM_XCD - 1) / NUM_XCD;
+  for (size_t g = 0; g < groups.first.size(); ++g) {
+    size_t at = groups.first[g];
+    const size_t end = g + 1 < groups.first.size() ? groups.first[g + 1] : v.size();
+    uint64_t rest = std::accumulate(work.begin() + at, work.begin() + end, (uint64_t)0);
+    while (at < end) {
+      const int die = (int)(std::min_element(load, load + NUM_XCD) - load);
+      // (whole if it exceeds the share by no more than an item, which the last piece of a cut could as well)
+      const uint64_t room = share > load[die] ? share - load[die] : 0;
+      const bool whole = rest <= room + work[at];
+      uint64_t taken = 0;
+      do {
+        taken += work[at];
+        die_of[at++] = (uint8_t)die;
+      } while (at < end && (whole || taken + work[at] <= room));
+      load[die] += taken;
+      rest -= taken;
     }
   }
-}
-
-// Dealing to the dies for whole groups of items that must run together (the strips of one cluster; the two sets of
-// strips that share the tiles of a pair of super-blocks of the coupling matrix): the groups go to the dies
-// in turn, in the order given, each die works through its groups in order, and a die whose queue has run
-// dry takes from the fullest one.
-uint64_t group_work(const std::vector<StripItem>& g) {
-  uint64_t w = 0;
-  for (const StripItem& it : g) w += it.c_end > it.c_begin ? it.c_end - it.c_begin : 0;
-  return w;
-}
-void heaviest_first(std::vector<std::vector<StripItem>>& groups, size_t from) {
-  std::stable_sort(groups.begin() + from, groups.end(),
-                   [](const std::vector<StripItem>& a, const std::vector<StripItem>& b) { return group_work(a) > group_work(b); });
-}
-std::vector<StripItem> deal_groups(std::vector<std::vector<StripItem>>& groups) {
-  std::vector<std::vector<StripItem>> q(NUM_XCD);
-  size_t total = 0;
-  for (size_t g = 0; g < groups.size(); ++g) {
-    q[g % NUM_XCD].insert(q[g % NUM_XCD].end(), groups[g].begin(), groups[g].end());
-    total += groups[g].size();
+  // in the order given, or the longest first: by counting
+  std::vector<uint32_t> order(v.size());
+  std::iota(order.begin(), order.end(), 0u);
+  if (longest_first && !v.empty()) {
+    std::vector<uint32_t> before(*std::max_element(work.begin(), work.end()) + 2, 0u);
+    for (uint32_t w : work) before[before.size() - 1 - w] += 1;
+    uint32_t sum = 0;
+    for (uint32_t& x : before) { const uint32_t count = x; x = sum; sum += count; }
+    for (uint32_t i = 0; i < v.size(); ++i) order[before[before.size() - 1 - work[i]]++] = i;
   }
-  std::vector<size_t> pos(NUM_XCD, 0);
-  std::vector<StripItem> out;
-  out.reserve(total);
-  while (out.size() < total) {
-    int src = (int)(out.size() % NUM_XCD);
-    if (pos[src] >= q[src].size()) {
-      size_t best = 0;
-      for (int k = 0; k < NUM_XCD; ++k)
-        if (q[k].size() - pos[k] > best) { best = q[k].size() - pos[k]; src = k; }
-    }
-    out.push_back(q[src][pos[src]++]);
+  Dealt out;
+  out.items.resize(v.size());
+  for (uint8_t d : die_of) out.from[d + 1] += 1;
+  for (int d = 0; d < NUM_XCD; ++d) out.from[d + 1] += out.from[d];
+  uint32_t next[NUM_XCD];
+  std::copy(out.from, out.from + NUM_XCD, next);
+  for (uint32_t i : order) out.items[next[die_of[i]]++] = v[i];
+  return out;
+}
+// Items without anything in common: to the dies in turn.
+Dealt deal_in_turn(const std::vector<StripItem>& v) {
+  Dealt out;
+  out.items.reserve(v.size());
+  for (size_t d = 0; d < NUM_XCD; ++d) {
+    for (size_t i = d; i < v.size(); i += NUM_XCD) out.items.push_back(v[i]);
+    out.from[d + 1] = (uint32_t)out.items.size();
   }
   return out;
 }
 
+// The strips of a launch that is resident all at once, or nearly (four workgroups of short strips and two of long ones on
+// each of the 256 compute units), reach the units in rounds, longest first: one unit would get the longest strip of every
+// round, another one the shortest.  Every second round goes in reverse.
+// nugpr_precond_apply, fp64, 17 columns, as dealt / with this: 300 uneven clusters of 200 points on average (1200 strips)
+// 43 / 42 us, 33 columns 62 / 58 (57 under the loader wave); 128 uneven ones of 512 73 / 68; 32 x 1024 points 48 / 42;
+// 8 x 4096 (512 long strips) 136 / 114.  Launches of several rounds fill the gaps by themselves and are left as they are:
+// 64 x 2048 (2048 long strips) 249 / 253, 32 uneven clusters of 2048 (1024) 176 / 179, 1024 x 256 (4096 short) 118 / 118.
+void alternate_rounds(Dealt& t) {
+  constexpr size_t ROUND = 256, OF_DIE = ROUND / NUM_XCD;
+  if (t.items.size() > (short_strips(t.items) ? 5 : 2) * ROUND) return;
+  for (int d = 0; d < NUM_XCD; ++d)
+    for (size_t from = t.from[d] + OF_DIE; from < t.from[d + 1]; from += 2 * OF_DIE)
+      std::reverse(t.items.begin() + from, t.items.begin() + std::min<size_t>(from + OF_DIE, t.from[d + 1]));
+}
+
+// The triangular strips of a matrix, a group per cluster.
+Dealt deal_triangles(const Groups& groups) {
+  Dealt t = deal_groups(groups, true);
+  alternate_rounds(t);
+  return t;
+}
+
 struct Tables {
-  std::vector<StripItem> WtD, KC, Conly, WP, lowG, upG, lowL;
+  Dealt WtD, KC, Conly, WP, lowG, upG, lowL;
 };
 
 void build_tables(const Layout& L, Tables& t) {
   const uint32_t r = (uint32_t)L.r;
-  std::vector<std::vector<StripItem>> kc_groups;      // work of the K_diag + C launch, by group (deal_groups)
-  for (int i = 0; i < L.nc; ++i) {
+  Groups k_groups, low_g, up_g, low_l;                // by cluster
+  std::vector<StripItem> wtd, wp;
+  const size_t strips = L.rows_pad / TILE;
+  for (Groups* g : {&k_groups, &low_g, &up_g, &low_l}) g->items.reserve(strips);
+  wp.reserve(strips);
+  // The largest clusters first.  (Equal ones in ascending order: the assembly writes cluster 0 last, so the product starts on
+  // blocks that are still in the memory-side cache.)
+  for (int place = 0; place < L.nc; ++place) {
+    const int i = (int)L.cl[place].by_size;
     const ClusterInfo& c = L.cl[i];
-    kc_groups.emplace_back();
+    for (Groups* g : {&k_groups, &low_g, &up_g, &low_l}) g->begin();
     // S_i = W_i^T D_i: strips over the r rows of W_i^T, columns split into nsS slabs
     const uint32_t chunks = c.nt, cpp = (chunks + L.nsS - 1) / L.nsS;
     for (uint32_t rs = 0; rs * TILE < r; ++rs) {
@@ -172,7 +184,7 @@ void build_tables(const Layout& L, Tables& t) {
       for (int k = 0; k < L.nsS; ++k) {
         const uint32_t cb = std::min<uint32_t>(k * cpp, chunks) * TILE;
         const uint32_t ce = std::min<uint32_t>(std::min<uint32_t>((k + 1) * cpp, chunks) * TILE, c.b);
-        t.WtD.push_back(make_item(c.wtoff + (uint64_t)rs * TILE * c.ld, c.ld, nrows, cb, std::max(cb, ce), c.row0,
+        wtd.push_back(make_item(c.wtoff + (uint64_t)rs * TILE * c.ld, c.ld, nrows, cb, std::max(cb, ce), c.row0,
                                   (uint32_t)i * r + rs * TILE, 0, k, 0, 0, 0.f));
       }
     }
@@ -180,20 +192,17 @@ void build_tables(const Layout& L, Tables& t) {
       const uint32_t nrows = std::min<uint32_t>(TILE, c.b - s * TILE);
       const uint64_t a_off = c.koff + (uint64_t)s * TILE * c.ld;
       const uint32_t row = c.row0 + s * TILE;
-      kc_groups.back().push_back(make_item(a_off, c.ld, nrows, 0, c.b, c.row0, row, s * TILE, 0, 0, 0, 1.f));
-      kc_groups.back().back().blocked = c.nt >= 2 ? 3 : 1;      // K_ii is symmetric: its strips pair up tile by tile
-      t.WP.push_back(make_item((uint64_t)row * L.ldw, (uint32_t)L.ldw, nrows, 0, r, (uint32_t)i * r, row, 0, 0, 0, 0, 0.f));
-      t.lowG.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
-      t.upG.push_back(make_item(a_off, c.ld, nrows, s * TILE, c.b, c.row0, row, s * TILE, 0, 0, 2, 0.f));
-      t.lowL.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
-      t.lowG.back().blocked = t.upG.back().blocked = t.lowL.back().blocked = 1;     // L and L^-1 are stored blocked too
+      k_groups.items.push_back(make_item(a_off, c.ld, nrows, 0, c.b, c.row0, row, s * TILE, 0, 0, 0, 1.f));
+      k_groups.items.back().blocked = c.nt >= 2 ? 3 : 1;      // K_ii is symmetric: its strips pair up tile by tile
+      wp.push_back(make_item((uint64_t)row * L.ldw, (uint32_t)L.ldw, nrows, 0, r, (uint32_t)i * r, row, 0, 0, 0, 0, 0.f));
+      low_g.items.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
+      up_g.items.push_back(make_item(a_off, c.ld, nrows, s * TILE, c.b, c.row0, row, s * TILE, 0, 0, 2, 0.f));
+      low_l.items.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
+      low_g.items.back().blocked = up_g.items.back().blocked = low_l.items.back().blocked = 1;     // L and L^-1 are stored blocked too
     }
   }
-  // the clusters first, heaviest first (the assembly writes cluster 0 last, so with equal clusters the product
-  // starts on blocks that are still in the memory-side cache), then the groups of the coupling matrix
-  heaviest_first(kc_groups, 0);
-  const size_t first_c_group = kc_groups.size();
-  // P = C S: strips over the n_c r rows of C, columns split into nsP slabs of cpp tiles.  C is symmetric:
+  std::vector<std::vector<StripItem>> c_groups;
+  // P = C S, behind the clusters: strips over the n_c r rows of C, columns split into nsP slabs of cpp tiles.  C is symmetric:
   // with the strips grouped like the slabs, the strips of row group I on slab k and the strips of row group
   // k on slab I share their tiles (one set reads them transposed) and form one group of work; see
   // k_strip for the order in which they visit them.
@@ -220,36 +229,40 @@ void build_tables(const Layout& L, Tables& t) {
     };
     for (uint32_t I = 0; I < ngroups; ++I)
       for (uint32_t k = I; k < ngroups; ++k) {
-        kc_groups.emplace_back();
+        c_groups.emplace_back();
         for (uint32_t rs = I * cpp; rs < std::min<uint32_t>((I + 1) * cpp, chunks) && rs * TILE < ncr; ++rs)
-          kc_groups.back().push_back(c_item(rs, (int)k));
+          c_groups.back().push_back(c_item(rs, (int)k));
         if (k != I)
           for (uint32_t rs = k * cpp; rs < std::min<uint32_t>((k + 1) * cpp, chunks) && rs * TILE < ncr; ++rs)
-            kc_groups.back().push_back(c_item(rs, (int)I));
+            c_groups.back().push_back(c_item(rs, (int)I));
       }
     // slabs past the last tile are empty; their items only clear their slab of the partial sums
-    kc_groups.emplace_back();
+    c_groups.emplace_back();
     for (int k = (int)ngroups; k < L.nsP; ++k)
-      for (uint32_t rs = 0; rs * TILE < ncr; ++rs) kc_groups.back().push_back(c_item(rs, k));
+      for (uint32_t rs = 0; rs * TILE < ncr; ++rs) c_groups.back().push_back(c_item(rs, k));
   }
-  heaviest_first(kc_groups, first_c_group);
-  t.KC = deal_groups(kc_groups);
-  sort_longest_first(t.WtD);
-  sort_longest_first(t.lowG);
-  sort_longest_first(t.upG);
-  sort_longest_first(t.lowL);
-  for (const StripItem& it : t.KC)
-    if (it.port == 1) t.Conly.push_back(it);       // the coupling product on its own (eq. (linear1) route)
-  arrange_for_dies(t.lowG);
-  arrange_for_dies(t.upG);
-  arrange_for_dies(t.lowL);
-  alternate_rounds(t.lowG);
-  alternate_rounds(t.upG);
-  alternate_rounds(t.lowL);
+  auto c_work = [](const std::vector<StripItem>& g) { uint64_t w = 0; for (const StripItem& it : g) w += item_work(it); return w; };
+  std::stable_sort(c_groups.begin(), c_groups.end(), [&](const auto& a, const auto& b) { return c_work(a) > c_work(b); });
+  Groups c_only;
+  for (const auto& g : c_groups)
+    for (Groups* to : {&c_only, &k_groups}) {
+      to->begin();
+      to->items.insert(to->items.end(), g.begin(), g.end());
+    }
+  t.Conly = deal_groups(c_only);                   // the coupling product on its own (eq. (linear1) route)
+  t.KC = deal_groups(k_groups);
+  std::stable_sort(wtd.begin(), wtd.end(), [](const StripItem& a, const StripItem& b) { return item_work(a) > item_work(b); });
+  t.WtD = deal_in_turn(wtd);
+  t.WP = deal_in_turn(wp);
+  t.lowG = deal_triangles(low_g);
+  t.upG = deal_triangles(up_g);
+  t.lowL = deal_triangles(low_l);
 }
 
-int upload_table(const std::vector<StripItem>& v, uint64_t matrix_elems, StripItem*& cursor, StripTable& tab, hipStream_t s) {
+int upload_table(const Dealt& t, uint64_t matrix_elems, StripItem*& cursor, StripTable& tab, hipStream_t s) {
+  const std::vector<StripItem>& v = t.items;
   tab.dev = cursor;
+  std::copy(t.from, t.from + NUM_XCD + 1, tab.from);
   tab.count = (int)v.size();
   tab.tiles = (int64_t)strip_tiles(v);
   tab.kind = strip_kind(v, matrix_elems * sizeof(float));
@@ -390,13 +403,13 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   if (e != hipSuccess) return fail(hip_fail(e, "upload cluster table"));
   Tables t;
   build_tables(L, t);
-  const size_t total_items = t.WtD.size() + t.KC.size() + t.Conly.size() + t.WP.size() + t.lowG.size() + t.upG.size() + t.lowL.size();
+  const size_t total_items = t.WtD.items.size() + t.KC.items.size() + t.Conly.items.size() + t.WP.items.size() + t.lowG.items.size() + t.upG.items.size() + t.lowL.items.size();
   if (total_items * sizeof(StripItem) > L.items_bytes) { set_error("internal: strip table overflow"); return fail(NUGPR_ERR_INVALID); }
   StripItem* cur = reinterpret_cast<StripItem*>(w + L.o_items);
   if ((rc = upload_table(t.WtD, L.wt_elems, cur, c->tab_WtD, s))) return fail(rc);
   if ((rc = upload_table(t.KC, L.kd_elems, cur, c->tab_KC, s))) return fail(rc);
   c->c_paired = false;
-  for (const StripItem& it : t.KC) c->c_paired = c->c_paired || (it.port == 1 && (it.blocked & 2u) != 0);
+  for (const StripItem& it : t.KC.items) c->c_paired = c->c_paired || (it.port == 1 && (it.blocked & 2u) != 0);
   if ((rc = upload_table(t.Conly, (uint64_t)L.ldc * L.ldc, cur, c->tab_C, s))) return fail(rc);
   if ((rc = upload_table(t.WP, (uint64_t)L.n * L.ldw, cur, c->tab_WP, s))) return fail(rc);
   if ((rc = upload_table(t.lowG, L.kd_elems, cur, c->tab_lowG, s))) return fail(rc);

@@ -90,6 +90,8 @@ struct StripItem {
 };
 static_assert(sizeof(StripItem) == 48, "StripItem layout");
 
+constexpr int NUM_XCD = 8;     // dies; workgroup w runs on die w % 8
+
 struct StripPort {
   const float* A;            // matrix base (always fp32)
   const void* in;            // input vector block, fp32 or fp64 by the arithmetic mode
@@ -107,13 +109,15 @@ struct StripArgs {
   int32_t T;                 // columns of the vector blocks (row stride)
   // 2^sys_log2 systems side by side: every row of eight items (one per die) once for each of them, with ports sys_ports
   // further a system, so that strips of two systems that read the same matrix meet in one die's L2
-  int32_t sys_log2, sys_ports, count;
+  int32_t sys_log2, sys_ports;
+  uint32_t from[NUM_XCD + 1];  // the dies' lists of items
   StripPort port[2 * MAX_SLOTS];
 };
 
 struct StripTable {
   StripItem* dev = nullptr;
   int count = 0;
+  uint32_t from[NUM_XCD + 1] = {};   // items from[d] .. from[d + 1] - 1 are die d's
   int64_t tiles = 0;     // of all items
   int kind = 0;          // which instantiation of the strip kernel serves it (strip_kind)
 };

@@ -317,14 +317,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
     if (turned(tile_of(u))) turn(sa[s % ST]);
     spread(sv[s % ST], cb[Cfg::AHEAD ? s & 1 : 0], cy[Cfg::AHEAD ? s & 1 : 0]);
   };
-  uint32_t id = Cfg::QUARTERS ? blockIdx.x >> 2 : blockIdx.x, first_port = 0;
-  if (a.sys_log2) {                                          // (the last row of items may be shorter than eight)
-    const uint32_t row = id >> (3 + a.sys_log2), len = min(8u, (uint32_t)a.count - 8 * row), at = id - (row << (3 + a.sys_log2));
-    const uint32_t e = at / len;
-    id = 8 * row + at - e * len;
-    first_port = e * (uint32_t)a.sys_ports;
-  }
-  const StripItem& it = a.items[id];
+  const uint32_t id = Cfg::QUARTERS ? blockIdx.x >> 2 : blockIdx.x, die = id % NUM_XCD, row = id / NUM_XCD;
+  const uint32_t at = a.from[die] + (row >> a.sys_log2), first_port = (row & ((1u << a.sys_log2) - 1)) * (uint32_t)a.sys_ports;
+  if (at >= a.from[die + 1]) return;                         // (the other dies' lists are longer)
+  const StripItem& it = a.items[at];
   const StripPort& pt = a.port[first_port + it.port];
   setup(it, pt);
   const int cnt = SP * S.cnt;                                // steps of a wave
@@ -527,8 +523,11 @@ const char* strip_kernel_name(const StripTable& tab, int T, bool acc64) {
 
 template <bool ACC64>
 static int launch_table(const StripTable& tab, int ng, int T, hipStream_t s, const StripArgs& a) {
-  const int count = tab.count << a.sys_log2;
-  switch (kind_at(tab, count, T, ACC64)) {
+  const int kind = kind_at(tab, tab.count << a.sys_log2, T, ACC64);
+  uint32_t longest = 0;
+  for (int d = 0; d < NUM_XCD; ++d) longest = std::max(longest, tab.from[d + 1] - tab.from[d]);
+  const int count = (int)(NUM_XCD * longest) << a.sys_log2;      // workgroups (quarters of them)
+  switch (kind) {
     case STRIP_SYM: return launch_width<ACC64, STRIP_SYM>(ng, count, T, s, a);
     case STRIP_SYM + STRIP_MANY:
       if constexpr (ACC64) return launch_kind<1, true, STRIP_SYM + STRIP_MANY>(count, T, s, a);
@@ -555,7 +554,7 @@ int launch_strip(const StripTable& tab, const StripPort* ports, int nports, int 
   a.T = T;
   a.sys_log2 = nsys / 2;
   a.sys_ports = nports / nsys;
-  a.count = tab.count;
+  std::copy(tab.from, tab.from + NUM_XCD + 1, a.from);
   const int ng = (T - 1 + 15) / 16;
   return acc64 ? launch_table<true>(tab, ng, T, s, a) : launch_table<false>(tab, ng, T, s, a);
 }
