@@ -76,7 +76,7 @@ struct Groups {
 };
 
 // What an item costs: its tiles, and the two ends of its workgroup (arguments, first loads, sums through LDS).
-uint64_t item_work(const StripItem& it) { return (it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0) + 2; }
+uint32_t item_work(const StripItem& it) { return (it.c_end > it.c_begin ? (it.c_end - it.c_begin + TILE - 1) / TILE : 0) + 2; }
 // Equal work for every die.  The groups, in the order given (the heaviest first), each go to the die with the least so far; a group
 // larger than what is missing there to an eighth of the whole is cut, and its rest dealt like a group of its own.  In the order of
 // the workgroups' numbers (groups to the dies in turn, a die without any left taking from the one with most) the busiest die had
@@ -87,8 +87,9 @@ Dealt deal_groups(const Groups& groups, bool longest_first = false) {
   const std::vector<StripItem>& v = groups.items;
   std::vector<uint32_t> work(v.size());
   std::vector<uint8_t> die_of(v.size());
-  uint64_t total = 0, load[NUM_XCD] = {};
-  for (size_t i = 0; i < v.size(); ++i) total += work[i] = item_work(v[i]);
+  for (size_t i = 0; i < v.size(); ++i) work[i] = item_work(v[i]);
+  uint64_t load[NUM_XCD] = {};
+  const uint64_t total = std::accumulate(work.begin(), work.end(), (uint64_t)0);
   const uint64_t share = (total + NUM_XCD - 1) / NUM_XCD;
   for (size_t g = 0; g < groups.first.size(); ++g) {
     size_t at = groups.first[g];
@@ -112,7 +113,7 @@ Dealt deal_groups(const Groups& groups, bool longest_first = false) {
   std::vector<uint32_t> order(v.size());
   std::iota(order.begin(), order.end(), 0u);
   if (longest_first && !v.empty()) {
-    std::vector<uint32_t> before(*std::max_element(work.begin(), work.end()) + 2, 0u);
+    std::vector<uint32_t> before(*std::max_element(work.begin(), work.end()) + 1, 0u);
     for (uint32_t w : work) before[before.size() - 1 - w] += 1;
     uint32_t sum = 0;
     for (uint32_t& x : before) { const uint32_t count = x; x = sum; sum += count; }
