@@ -3,7 +3,8 @@
 // paper applies the factor as an explicit inverse followed by batched products, Table 2),
 // log det of the preconditioner, and the right-hand sides B = [y | L Z].
 //
-// Everything runs on the fp32 matrix cores (v_mfma_f32_16x16x4_f32), products in blocks of 128 x 128, four waves of 64 x 64.
+// Products in blocks of 128 x 128, four waves of 64 x 64, on the bf16 matrix cores (an fp32 entry cut into three bf16 numbers without
+// loss, see block_gemm); the diagonal blocks on the fp32 ones.
 //   Cholesky: left-looking over block columns.  Step k: every block (m, k), m >= k, gets
 //     A[m,k] - sum_{j<k} L[m,j] L[k,j]^T in one batched launch over clusters (most of
 //     the sum one step ahead, see k_potrf_step); the workgroup that owns the diagonal
@@ -26,6 +27,10 @@
 namespace nugpr {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // Blocked storage seen tile by tile: element (r, q) of the 64 x 64 tile (tr, tc) of a square block lies at
 // tile_base(ld, tr, tc) + tile_offset(r, q) (= blocked_index(ld, 64 tr + r, 64 tc + q)).  The base is uniform over a
@@ -81,100 +86,163 @@ __device__ __forceinline__ bool list_item(const Pieces& pieces, const uint32_t* 
 // ---------------------------------------------------------------------------
 // Block products: a workgroup computes 128 x 128, each of its four waves one 64 x 64 tile
 // ---------------------------------------------------------------------------
-// acc += OpA[128 x K] OpB[128 x K]^T: wave w works on row tile w / 2 of OpA and w % 2 of OpB.  A step is 16 columns: sixteen
-// fragments of 1 KiB, four a wave, go from memory straight into a stage of an LDS ring (16-byte pieces, one instruction a
-// fragment), two steps ahead; for one workgroup barrier a wave reads its eight fragments, 16 bytes a lane, and issues 64
-// matrix instructions.  Lane (m, kg) holds (row m, columns 4 kg ..) of either operand, so component i of both feeds one
-// instruction whose contraction index is kg.  The roles are swapped (OpB is the row operand of the instruction): lane l ends
-// up with C[row l & 15][columns 4 (l >> 4) .. + 3] of each fragment, 16 bytes of a row.
-// The fragments of step q + 1 are read in the middle of step q's instructions, so neither the barrier nor the LDS is waited for
-// with idle matrix cores: without that 104 TFLOP/s at the last level of the inverse of 128 x 2048 points, with it 115.
-// What bounds it: the matrix cores, and the ends of a workgroup.  With 64 x 64 per workgroup (16 flop per byte through L2, two
-// barriers for 32 matrix instructions a wave) the two products of the tree took 4.27 + 0.5 ms there with the mirroring that
-// followed, now 3.85, and 31 + 1.2 ms on 64 uneven clusters of 4096 points, now 21.5 (the work lists below have their part in it).
-constexpr int RING_STAGES = 3, RING_STAGE = 16 * 1024, RING = RING_STAGES * RING_STAGE;
-constexpr uint32_t waitcnt_vm(uint32_t n) {      // s_waitcnt immediate: vmcnt(n), the other counters unconstrained
-  return (n & 15u) | ((n >> 4) << 14) | 0x0F70u;
+// acc += OpA[128 x K] OpB[128 x K]^T: wave w works on row tile w / 2 of OpA and w % 2 of OpB.
+// The fp32 entries are multiplied on the bf16 matrix cores, whose rate is 16 times that of the fp32 ones: an entry is cut, without
+// rounding, into three bf16 numbers h + m + l of 8 bits each (its 24 bits), and of the nine products of two entries the six that
+// reach 2^-24 are taken; those left out (m l, l m, l l) are below half an ulp of the product.  The products are exact, the sums
+// are kept in fp32.  These matrix cores do not round a sum but cut it, at the place of its largest term, so h h has
+// accumulators of its own, whose terms are all alike, and the five small products another set, which is added at the end: rms
+// error of a sum of K products in units of 2^-24 of its terms' magnitudes, fp32 instructions / this (probe on this card):
+// K = 128 0.46 / 0.20, terms of one sign 2.9 / 1.3; K = 2048 0.47 / 0.17, one sign 11.8 / 4.2 (54 in one set of accumulators).
+// A step is 32 columns: two fragments of 1 KiB of each of the sixteen row groups, eight a wave, are loaded a step ahead into
+// registers, cut, and put into LDS as three fragments of bf16 each, once for the two waves that read them.  Lane (m, kg) has (row m,
+// columns 4 kg .. + 3) of both fragments of a row group: its eight values are the operand of one contraction over 32 columns (of
+// which lane takes which columns makes no difference as long as both operands agree).  A wave reads its four row groups of OpA
+// and one of OpB after the other, 24 matrix instructions each.  The cutting (vector ALUs, which run beside the bf16 matrix cores,
+// unlike beside the fp32 ones) hides behind the matrix instructions of the other workgroup on the compute unit.  The roles are
+// swapped (OpB is the row operand of the instruction): lane l ends up with C[row l & 15][columns 4 (l >> 4) .. + 3] of each fragment,
+// 16 bytes of a row.
+// What bounds it: the bf16 matrix cores work 58 % of the last levels' cycles (clock 1.8 GHz under this load), the cutting takes another
+// 30 %, two fifths of it beside them.  The two products of the tree, fp32 instructions / this: 128 x 2048 points 3.9 / 2.4 ms, 64 uneven
+// clusters of 4096 points 23.7 / 14.4.  Not kept, whole factorisation of the latter (35.3 ms): every wave cuts what it reads, the fp32 fragments
+// loaded straight into LDS, 36.7; cutting placed between the matrix instructions of the same wave, for the second half of a step 39.7
+// (registers spill), for its last quarter 36.3; steps beyond a triangular tile multiplied as zeros and not passed over 35.8.
+constexpr int stage_bytes(int F) { return 12 * F * 1024; }
+struct Cut { v4u h, m, l; };                     // eight values each, two in a register
+__device__ __forceinline__ Cut cut(const v4f& first, const v4f& second) {
+  Cut c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v2f x = i < 2 ? (v2f){first[2 * i], first[2 * i + 1]} : (v2f){second[2 * i - 4], second[2 * i - 3]};
+    uint32_t part[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      part[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, v2bf));
+      if (k < 2) {
+        x[0] -= __builtin_bit_cast(float, part[k] << 16);
+        x[1] -= __builtin_bit_cast(float, part[k] & 0xffff0000u);
+      }
+    }
+    c.h[i] = part[0];
+    c.m[i] = part[1];
+    c.l[i] = part[2];
+  }
+  return c;
 }
+// up: a power of two that this wave's entries are multiplied by (see range_scale).
 // F = 2: 64 x 64 per workgroup and 32 x 32 per wave (one row tile of either operand, whose fragments the waves load in pairs, F
 // each), for launches that would not fill the chip otherwise: a step takes a quarter of the time.
-// Steps s0 .. s1 - 1 (whole tiles).  mine: first element of the strip (64 rows of a square block) that this wave loads:
+// Columns 16 s0 .. 16 s1 - 1 (whole tiles).  mine: first element of the strip (64 rows of a square block) that this wave loads:
 // row tile 0 / 1 of OpA, 0 / 1 of OpB for wave 0 .. 3 (F = 2: OpA, OpA, OpB, OpB).  TRI (of OpA): 0 none; 1 / 2: the tile of column tile diag is
-// triangular (column <= row / >= row is kept) and the tiles past it / before it count as zero whatever is stored there.
+// triangular for row tile 0 (column <= row / >= row is kept), the next one for row tile 1, and the tiles past it / before it count as zero
+// whatever is stored there.
 template <int TRI, bool SWAP = false, int F = 4>
-__device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, int s0, int s1, int diag, unsigned char* ring) {
+__device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, int s0, int s1, int diag, unsigned char* stage, float up = 1.f) {
 #if __HIP_DEVICE_COMPILE__
-  typedef __attribute__((address_space(3))) const v4f* lds_v4f;
-  typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
+  typedef __attribute__((address_space(3))) v4u* lds_v4u;
   const int lane = threadIdx.x & 63, m = lane & 15, kg = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t piece = (uint32_t)(m * 16 + 4 * kg) * 4u;      // (scalar base + 32-bit lane offset: one address register)
-  const int n = s1 - s0;
-  auto issue = [&](int q) {
-    const int step = s0 + q;
-    const float* at = mine + (uint64_t)(step >> 1) * (TILE * BLK_COLS) + (step & 1) * FRAG;
-    unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + F * w * 1024;
+  const int n = (s1 - s0) / 2;
+  if (n <= 0) return;
+  v4f raw[F][2];
+  auto load = [&](int q) {
+    const float* at = mine + (uint64_t)(s0 / 2 + q) * (TILE * BLK_COLS);
     if (F == 2) at += (w & 1) * 4 * FRAG;
 #pragma unroll
     for (int g = 0; g < F; ++g)
-      __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(at + g * 2 * FRAG) + piece, (lds_ptr)(st + g * 1024), 16, 0, 0);
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) raw[g][sub] = *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(at + g * 2 * FRAG + sub * FRAG) + piece);
   };
-  v4f a[2][F], b[2][F];
-  // step q into the registers of its parity, once every wave's share of it has landed.  The barrier also says that every
-  // wave has read step q - 1, whose stage then takes step q - 1 + RING_STAGES.
-  auto fetch_step = [&](int q, v4f (&fa)[F], v4f (&fb)[F]) {
-    if (q + RING_STAGES - 2 <= n - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(F * (RING_STAGES - 2)));
-    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const unsigned char* st = ring + (uint32_t)q % RING_STAGES * RING_STAGE + lane * 16;
+  // the tile of a step, and whether it counts for row tile t of OpA
+  auto tile_at = [&](int q) { return (s0 + 2 * q) >> 2; };
+  const int my_diag = diag + (F == 4 ? w : 0);   // (waves 0 and 1 load OpA)
+  v4f small[F][F];
 #pragma unroll
-    for (int g = 0; g < F; ++g) fa[g] = *(lds_v4f)(st + (F * (w >> 1) + g) * 1024);
+  for (int g = 0; g < F; ++g)
 #pragma unroll
-    for (int g = 0; g < F; ++g) fb[g] = *(lds_v4f)(st + (2 * F + F * (w & 1) + g) * 1024);
-    if (q > 0 && q - 1 + RING_STAGES < n) issue(q - 1 + RING_STAGES);
-  };
-  auto mult = [&](const v4f (&fa)[F], const v4f (&fb)[F], int i) {
+    for (int j = 0; j < F; ++j) small[g][j] = (v4f){0.f, 0.f, 0.f, 0.f};
+  lds_v4u mine_lds = (lds_v4u)(stage + F * w * 3 * 1024 + lane * 16);
+  const lds_v4u a_lds = (lds_v4u)(stage + F * (w >> 1) * 3 * 1024 + lane * 16), b_lds = (lds_v4u)(stage + (2 * F + F * (w & 1)) * 3 * 1024 + lane * 16);
+  auto meet = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  load(0);
+#pragma unroll 1
+  for (int q = 0; q < n; ++q) {
+    const int tile = tile_at(q);
+    if (TRI != 0 && w < 2 && tile == my_diag) {
+      const int row0 = F == 2 ? 32 * (w & 1) : 0;
 #pragma unroll
-    for (int g = 0; g < F; ++g)
+      for (int sub = 0; sub < 2; ++sub) {
+        const int k = 16 * ((s0 + 2 * q + sub) & 3) + 4 * kg;
 #pragma unroll
-      for (int j = 0; j < F; ++j)
-        acc[g][j] = SWAP ? __builtin_amdgcn_mfma_f32_16x16x4f32(fa[g][i], fb[j][i], acc[g][j], 0, 0, 0)
-                         : __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][i], fa[g][i], acc[g][j], 0, 0, 0);
-  };
-  auto step_of = [&](int q, v4f (&fa)[F], v4f (&fb)[F], v4f (&na)[F], v4f (&nb)[F]) {
-    const int row0 = F == 2 ? 32 * (w >> 1) : 0;
-    const int step = s0 + q, tile = step >> 2;
-    const bool counts = !((TRI == 1 && tile > diag) || (TRI == 2 && tile < diag));
-    // (the step's reads are waited for here, where nothing younger is in flight, and not at a use behind a branch)
+        for (int g = 0; g < F; ++g)
 #pragma unroll
-    for (int g = 0; g < F; ++g) asm volatile("" : "+v"(fa[g]), "+v"(fb[g]));
-    if (TRI != 0 && tile == diag) {
-      const int k = 16 * (step & 3) + 4 * kg;
+          for (int i = 0; i < 4; ++i) {
+            const bool keep = TRI == 1 ? k + i <= row0 + 16 * g + m : k + i >= row0 + 16 * g + m;
+            raw[g][sub][i] = keep ? raw[g][sub][i] : 0.f;
+          }
+      }
+    }
+    if (up != 1.f) {
 #pragma unroll
       for (int g = 0; g < F; ++g)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool keep = TRI == 1 ? k + i <= row0 + 16 * g + m : k + i >= row0 + 16 * g + m;
-          fa[g][i] = keep ? fa[g][i] : 0.f;
-        }
+        for (int sub = 0; sub < 2; ++sub) raw[g][sub] *= up;
     }
-    if (counts) { mult(fa, fb, 0); mult(fa, fb, 1); }
-    __builtin_amdgcn_sched_barrier(0);
-    if (q + 1 < n) fetch_step(q + 1, na, nb);
-    __builtin_amdgcn_sched_barrier(0);
-    if (counts) { mult(fa, fb, 2); mult(fa, fb, 3); }
-    __builtin_amdgcn_sched_barrier(0);
-  };
+    Cut mc[F];
 #pragma unroll
-  for (int q = 0; q < RING_STAGES; ++q)
-    if (q < n) issue(q);
-  fetch_step(0, a[0], b[0]);
-#pragma unroll 1
-  for (int q = 0; q < n; q += 2) {
-    step_of(q, a[0], b[0], a[1], b[1]);
-    step_of(q + 1, a[1], b[1], a[0], b[0]);
+    for (int g = 0; g < F; ++g) mc[g] = cut(raw[g][0], raw[g][1]);
+    if (q > 0) meet();                           // every wave has read step q - 1
+#pragma unroll
+    for (int g = 0; g < F; ++g) {
+      mine_lds[(3 * g) * 64] = mc[g].h;
+      mine_lds[(3 * g + 1) * 64] = mc[g].m;
+      mine_lds[(3 * g + 2) * 64] = mc[g].l;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (q + 1 < n) load(q + 1);
+    meet();
+    const int counted = diag + (F == 4 ? w >> 1 : 0);
+    if ((TRI == 1 && tile > counted) || (TRI == 2 && tile < counted)) continue;
+    Cut a[F], b[2];
+    auto get = [&](Cut& c, const lds_v4u from, int f) {
+      c.h = from[(3 * f) * 64];
+      c.m = from[(3 * f + 1) * 64];
+      c.l = from[(3 * f + 2) * 64];
+    };
+    get(b[0], b_lds, 0);
+#pragma unroll
+    for (int g = 0; g < F; ++g) get(a[g], a_lds, g);
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+      if (j + 1 < F) get(b[(j + 1) & 1], b_lds, j + 1);
+      const Cut& y = b[j & 1];
+      auto mult = [&](const v4u& x, const v4u& z, v4f& to) {
+        to = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x), __builtin_bit_cast(v8bf, z), to, 0, 0, 0)
+                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, z), __builtin_bit_cast(v8bf, x), to, 0, 0, 0);
+      };
+#pragma unroll
+      for (int g0 = 0; g0 < F; g0 += 2) {
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].h, y.h, acc[g][j]);
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].l, y.h, small[g][j]);
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].h, y.l, small[g][j]);
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].m, y.m, small[g][j]);
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].m, y.h, small[g][j]);
+#pragma unroll
+        for (int g = g0; g < g0 + 2; ++g) mult(a[g].h, y.m, small[g][j]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+#pragma unroll
+  for (int g = 0; g < F; ++g)
+#pragma unroll
+    for (int j = 0; j < F; ++j) acc[g][j] += small[g][j];
 #endif
 }
 template <int F>
@@ -209,13 +277,18 @@ __device__ __forceinline__ void add_tile(v4f (&acc)[4][4], const float* tile) {
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-__device__ __forceinline__ void put_difference(const float* from, const v4f (&acc)[4][4], float* tile) {
+__device__ __forceinline__ void put_difference(const float* from, const v4f (&acc)[4][4], float down, float* tile) {
   from = here(from);
   tile = here(tile);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *fragment(tile, g, j) = *fragment(from, g, j) - acc[g][j];
+    for (int j = 0; j < 4; ++j) {
+      v4f x = *fragment(from, g, j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = fmaf(-down, acc[g][j][i], x[i]);
+      *fragment(tile, g, j) = x;
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -388,10 +461,10 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
 // and bulk of a block row share a workgroup because, as workgroups of their own, the short finish ones either
 // delay the start of the long ones or wait behind them for a free slot.
 // A second launch multiplies the blocks below the diagonal by its inverse.
-// What bounds it: the matrix cores, half idle where a launch is one or two rounds of workgroups; 82 TFLOP/s on 64 uneven
-// clusters of 4096 points (23.7 + 2 ms; with tiles of 64 31.6 + 1.6 ms), 85 on 128 x 2048 (4.3 + 0.7 ms; 4.4 + 0.6 ms).  A block
-// column of 128 needs half as many steps as one of 64, reads the panel L[m, 0:k] half as often, and its diagonal workgroup
-// (47 us on an idle chip) is still done before the rows are.
+// What bounds it: the matrix cores and the cutting of their operands (block_gemm), and where a launch is one or two rounds of
+// workgroups their number.  Steps and multiplies of 64 uneven clusters of 4096 points: 15.6 ms (fp32 matrix instructions 23.1, tiles of 64
+// 33.2), of 128 x 2048 points 3.6 ms (5.1; 5.0).  A block column of 128 needs half as many steps as one of 64, reads the panel L[m, 0:k] half
+// as often, and its diagonal workgroup (47 us on an idle chip) is still done before the rows are.
 // (Rows past the end of a cluster: zero in the assembled blocks and therefore zero in L; identity in the diagonal tile.)
 // the tile in LDS and its inverse (factor_tile) to memory: L lower, the inverse with its mirror image
 __device__ __forceinline__ void store_factored(const float (*sT)[LT], const float* inv, float* l, float* y) {
@@ -412,12 +485,12 @@ __device__ __forceinline__ void store_factored(const float (*sT)[LT], const floa
   }
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, float* G, int k, int n_diag, int grid_diag,
-                  Pieces pieces, const uint32_t* __restrict__ first, int n_rows, int parts, int parts_before, PcgState* __restrict__ st) {
-  // the ring of the products and, once these are done, the tiles of the diagonal block share one piece of LDS
-  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
-  static_assert((2 * TILE * LT + 4 * 16 * IP + TILE) * sizeof(float) <= RING, "two tiles and the inverted blocks must fit");
+                  Pieces pieces, const uint32_t* __restrict__ first, int n_rows, int parts, int parts_before, float up, float down2, PcgState* __restrict__ st) {
+  // the stage of the products and, once these are done, the tiles of the diagonal block share one piece of LDS
+  __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(4)];
+  static_assert((2 * TILE * LT + 4 * 16 * IP + TILE) * sizeof(float) <= stage_bytes(4), "two tiles and the inverted blocks must fit");
   const int id = (int)blockIdx.x;
   const bool diag = id < grid_diag;
   int rank = id, item = 0, part = 0;
@@ -444,7 +517,7 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
     const int col = 2 * (k + ahead) + jb, row = 2 * m + ia;
     zero_block(acc);
     block_gemm<0>(acc, strip(w < 2 ? 2 * m + w : 2 * (k + ahead) + w - 2), ahead ? 8 * (k * part / parts) : 8 * (k - 1),
-                  ahead ? 8 * (k * (part + 1) / parts) : 8 * k, 0, ring);
+                  ahead ? 8 * (k * (part + 1) / parts) : 8 * k, 0, stage, up);
     if (!ahead && row <= last)
       for (int p = 1; p < parts_before; ++p) add_tile(acc, part_tile(k, p));
     if (diag) break;
@@ -452,20 +525,20 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
       const uint64_t tb = tile_base(c.ld, row, col);
       // what the products are subtracted from: the bulk result of the step before where there is one, or the assembled block
       if (part > 0) put_tile(acc, part_tile(k + 1, part));
-      else put_difference((!ahead && k > 1 ? L : A) + tb, acc, L + tb);
+      else put_difference((!ahead && k > 1 ? L : A) + tb, acc, down2, L + tb);
     }
     if (ahead) return;
-    __syncthreads();                           // the ring starts over
+    __syncthreads();                           // the stage is written again
   }
   if (!diag) return;                           // (k = 0: k_potrf_solve reads the assembled block)
   // ---- diagonal block [A00 .; A10 A11]: L00, L00^-1 = Y00;  L10 = A10 Y00^T;  A11 -= L10 L10^T;  L11, Y11;  Y10 = -Y11 L10 Y00 ----
-  float (*sT)[LT] = reinterpret_cast<float (*)[LT]>(ring);
+  float (*sT)[LT] = reinterpret_cast<float (*)[LT]>(stage);
   float (*sX)[LT] = sT + TILE;
   float *inv = &sX[TILE][0], *rdiag = inv + 4 * 16 * IP;
   const int lane = tid & 63, mm = lane & 15, kg = lane >> 4;
   const int b = (int)c.b;
   const bool two = 2 * k + 1 <= last;
-  __syncthreads();                             // every wave is done with the ring
+  __syncthreads();                             // every wave is done with the stage
   const float* base = k > 1 ? L : A;
   if (jb <= ia && 2 * k + ia <= last) {        // wave 0: A00, wave 2: A10, wave 3: A11, which waits in memory
     const uint64_t tb = tile_base(c.ld, 2 * k + ia, 2 * k + jb);
@@ -475,7 +548,9 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const v4f x = *fragment(base + tb, g, j) - acc[g][j];
+        v4f x = *fragment(base + tb, g, j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = fmaf(-down2, acc[g][j][e], x[e]);
         if (w == 3) *fragment(L + tb, g, j) = x;
         else {
           const int r = 16 * g + mm, q = 16 * j + 4 * kg;
@@ -589,10 +664,10 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
 
 // blocks below the diagonal: L[m,k] <- L[m,k] inv(L[k,k])^T
 template <int F>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : 4)))
 void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, const float* G, int k, Pieces pieces,
-                   const uint32_t* __restrict__ first, int n_rows) {
-  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
+                   const uint32_t* __restrict__ first, int n_rows, float up, float down) {
+  __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(F)];
   int rank, item, part;
   if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, (int)blockIdx.x, rank, item, F == 2 ? 2u : 1u, part)) return;
   const ClusterInfo c = cl[cl[rank].by_size];
@@ -610,28 +685,28 @@ void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* L
       v4f acc[F][F];
       zero_block(acc);
       block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + q) * TILE * c.ld : from + (uint64_t)row * TILE * c.ld, 8 * k, 8 * k + 4 * q + 4,
-                             2 * k + q, ring);
-      __syncthreads();                         // the ring starts over
+                             2 * k + q, stage, w < 2 ? 1.f : up);
+      __syncthreads();                         // the stage is written again
       float* lt = L + tile_base(c.ld, row, 2 * k + q);
 #pragma unroll
       for (int g = 0; g < F; ++g)
 #pragma unroll
         for (int j = 0; j < F; ++j)
-          *reinterpret_cast<v4f*>(lt + tile_offset(32 * jb + 16 * j + (lane & 15), 32 * ia + 16 * g + 4 * (lane >> 4))) = acc[g][j];
+          *reinterpret_cast<v4f*>(lt + tile_offset(32 * jb + 16 * j + (lane & 15), 32 * ia + 16 * g + 4 * (lane >> 4))) = acc[g][j] * down;
     }
     return;
   }
   v4f acc[F][F];
   zero_block(acc);
   block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + w) * TILE * c.ld : from + (uint64_t)min(2 * m + w - 2, last) * TILE * c.ld,
-                         8 * k, 8 * (k + 1), 2 * k + ia, ring);
+                         8 * k, 8 * (k + 1), 2 * k, stage, w < 2 ? 1.f : up);
   if (2 * m + jb > last) return;
   float* lt = L + tile_base(c.ld, 2 * m + jb, 2 * k + ia);
 #pragma unroll
   for (int g = 0; g < F; ++g)
 #pragma unroll
     for (int j = 0; j < F; ++j)
-      *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = acc[g][j];
+      *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = acc[g][j] * down;
 }
 
 // ---------------------------------------------------------------------------
@@ -644,10 +719,10 @@ void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* L
 // tm; longest (large tm) first.
 // F = 2: four workgroups an item, each one 64 x 64 tile of the block.
 template <int STAGE, int F>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : 4)))
 void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int half, Pieces pieces,
                    const uint32_t* __restrict__ first, int n) {
-  __shared__ __attribute__((aligned(1024))) unsigned char ring[RING];
+  __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(F)];
   int rank, item, part;
   if (!list_item(pieces, first, 0u, n, (int)blockIdx.x, rank, item, F == 2 ? 4u : 1u, part)) return;
   const ClusterInfo c = cl[cl[rank].by_size];
@@ -669,7 +744,7 @@ void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int 
   // the wave's tiles, and (F = 2) its fragments in them
   const int am = F == 2 ? 0 : STAGE == 1 ? jb : ia, an = F == 2 ? 0 : STAGE == 1 ? ia : jb, fa = F == 2 ? 2 * ia : 0, fb = F == 2 ? 2 * jb : 0;
   if (STAGE == 1) {
-    block_gemm<2, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tn : tn + w) : strip(L, F == 2 ? tm : tm + w - 2), 4 * tn, 4 * mid, tn + an, ring);
+    block_gemm<2, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tn : tn + w) : strip(L, F == 2 ? tm : tm + w - 2), 4 * tn, 4 * mid, tn, stage);
     if (tm + am > last) return;
     float* tt = here(L + tile_base(c.ld, tn + an, tm + am));
 #pragma unroll
@@ -678,7 +753,7 @@ void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int 
       for (int j = 0; j < F; ++j) *fragment(tt, fa + g, fb + j) = acc[g][j];
   } else {
     block_gemm<1, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tm : tm + w) : strip(L, F == 2 ? tn : tn + w - 2), 4 * mid,
-                            4 * (min(F == 2 ? tm : tm + 1, last) + 1), tm + am, ring);
+                            4 * (min(F == 2 ? tm : tm + 1, last) + 1), tm, stage);
     if (tm + am > last) return;
     float *yl = Y + tile_base(c.ld, tm + am, tn + an), *yu = Y + tile_base(c.ld, tn + an, tm + am);
 #pragma unroll
@@ -827,22 +902,29 @@ __global__ __launch_bounds__(256) void k_compensated_blocks(const ClusterInfo* _
 // Up to this many blocks of 128 x 128 in a launch leave half of the compute units idle: tiles of 64 x 64 then.
 constexpr uint64_t FEW_BLOCKS = 128;
 
-// How many workgroups share the bulk of a block (k_potrf_step's parts).  The chip holds 768 workgroups, three on a compute
-// unit, which then share its matrix cores; what counts is how full the last round is.  A workgroup alone on its unit leaves
-// the matrix cores idle for three eighths of the time, two for a fifth, three for a tenth; the block of column k and both ends
-// of a workgroup cost as much as 14 steps of 16 columns.  Steps of the factorisation of 128 x 2048 points (15 - k blocks of every
-// cluster below the diagonal), one workgroup a block / three or four: k = 8 423 / 393 us, 11 239 / 311, 13 160 / 219; of 64 uneven
-// clusters of 4096 points: k = 40 351 / 252, 53 447 / 84.
+// How many workgroups share the bulk of a block (k_potrf_step's parts).  The chip holds 512 workgroups, two on a compute unit, which
+// then share its matrix cores; what counts is how full the last round is.  A workgroup alone on its unit takes four fifths of the
+// time that two take; the block of column k and both ends of a workgroup cost as much as 45 half steps (16 columns).  64 uneven clusters
+// of 4096 points, whole factorisation: with sums never shared 40.6 ms, with the line of the fp32 instructions (768 workgroups, 14 half
+// steps) 35.8, with 20 / 45 / 70 half steps 35.4 / 35.3 / 35.5.
 static int bulk_parts(uint64_t items, int k) {
   int best = 1;
   double least = 0.0;
   for (int p = 1; p <= 8 && (p == 1 || 2 * p <= k); ++p) {
-    const uint64_t n = items * (uint64_t)p, left = (n % 768 + 255) / 256;
-    const double units = 3.3 * (double)(n / 768) + (left == 0 ? 0.0 : left == 1 ? 1.6 : left == 2 ? 2.5 : 3.3);
-    const double cost = units * (8.0 * k / p + 14.0);
+    const uint64_t n = items * (uint64_t)p, left = (n % 512 + 255) / 256;
+    const double units = 2.0 * (double)(n / 512) + (left == 0 ? 0.0 : left == 1 ? 1.6 : 2.0);
+    const double cost = units * (8.0 * k / p + 45.0);
     if (p == 1 || cost < least) { best = p; least = cost; }
   }
   return best;
+}
+
+// The smallest parts of a product are 2^-16 of it and the last parts of an entry 2^-16 of that, and the matrix cores take what is
+// below 2^-126 for zero: where the variances themselves are small, the entries of L, and those of the block that a multiply starts
+// from, are multiplied by the power of two that brings L to about 1.
+static float range_scale(const nugpr_ctx* c) {
+  const double a = c->theta_built[c->L.p - 2] + c->theta_built[c->L.p - 1];
+  return (a < 0x1p-40 && a > 0.0) || a > 0x1p100 ? (float)std::ldexp(1.0, -std::ilogb(a) / 2) : 1.f;
 }
 
 int launch_factor(nugpr_ctx* c, hipStream_t s) {
@@ -865,6 +947,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     return (int)(std::partition_point(L.blocks_by_rank.begin(), L.blocks_by_rank.end(), [&](uint32_t nb) { return (int)nb >= least; }) - L.blocks_by_rank.begin());
   };
   int parts_before = 1;
+  const float up = range_scale(c), down = 1.f / up;
   for (int k = 0; k < n_blocks; ++k) {
     const int n_diag = with_blocks(k + 1), grid_diag = (n_diag + NUM_DIES - 1) / NUM_DIES * NUM_DIES, n_rows = with_blocks(k + 2);
     const uint64_t items = L.rows_before[n_rows] - (uint64_t)n_rows * (uint64_t)(k + 1);
@@ -872,11 +955,11 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     Pieces pr, ps;
     for (int d = 0; d <= NUM_DIES; ++d) { pr.from[d] = (uint32_t)(items * parts * d / NUM_DIES); ps.from[d] = (uint32_t)(items * d / NUM_DIES); }
     hipLaunchKernelGGL(k_potrf_step, dim3((unsigned)grid_diag + (k > 0 ? pr.grid() : 0u)), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k,
-                       n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, c->d_state);
-    if (items > FEW_BLOCKS) hipLaunchKernelGGL((k_potrf_solve<4>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+                       n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, up, down * down, c->d_state);
+    if (items > FEW_BLOCKS) hipLaunchKernelGGL((k_potrf_solve<4>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, up, down);
     else if (items) {
       for (int d = 0; d <= NUM_DIES; ++d) ps.from[d] = (uint32_t)(2 * items * d / NUM_DIES);
-      hipLaunchKernelGGL((k_potrf_solve<2>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows);
+      hipLaunchKernelGGL((k_potrf_solve<2>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, up, down);
     }
     parts_before = parts;
   }

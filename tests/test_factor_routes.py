@@ -10,13 +10,13 @@ SOURCE = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))
 
 
 def shared_by(items, k):
-    """How many workgroups share a block's sum in step k: the number that fills the last round of three workgroups on each of 256
+    """How many workgroups share a block's sum in step k: the number that fills the last round of two workgroups on each of 256
     compute units best."""
     cost = {}
     for p in range(1, 9):
         if p == 1 or 2 * p <= k:
-            rounds, left = divmod(items * p, 768)
-            cost[p] = (3.3 * rounds + (0.0, 1.6, 2.5, 3.3)[-(-left // 256)]) * (8.0 * k / p + 14.0)
+            rounds, left = divmod(items * p, 512)
+            cost[p] = (2.0 * rounds + (0.0, 1.6, 2.0)[-(-left // 256)]) * (8.0 * k / p + 45.0)
     return min(cost, key=lambda p: (cost[p], p))
 
 
