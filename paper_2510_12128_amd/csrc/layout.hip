@@ -201,6 +201,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.o_Q = take(cur, vec);
   L.o_V = take(cur, vec);
   L.o_U = take(cur, vec);
+  L.o_digits = take(cur, L.T > 17 ? (size_t)(L.rows_pad + L.ldc) / TILE * DIGIT_BLOCK : 0);
   L.o_Spart = take(cur, (size_t)L.nsS * L.ncr * L.T * sizeof(double));
   L.o_Ppart = take(cur, (size_t)L.nsP * L.ncr * L.T * sizeof(double));
   L.o_dot = take(cur, (size_t)4 * L.n_dot_blocks * MAX_COLS * sizeof(double));
