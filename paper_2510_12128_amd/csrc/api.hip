@@ -350,6 +350,8 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->Kd2 = reinterpret_cast<float*>(w + L.o_Kd2);
   c->Q0v = w + L.o_Q0;
   c->C2 = reinterpret_cast<float*>(w + L.o_C2);
+  c->c_live = reinterpret_cast<uint32_t*>(w + L.o_c_live);
+  c->c2_live = c->c_live + L.n_c_tiles;
   c->Clo = !L.compensate ? nullptr : (L.ncr <= COMPENSATE_HOST_MAX ? reinterpret_cast<float*>(w + L.o_Clo) : c->C2);
   c->dav = L.ncr > COMPENSATE_HOST_MAX ? reinterpret_cast<double*>(w + L.o_dav) : nullptr;
   c->Wd = reinterpret_cast<float*>(w + L.o_Wd);

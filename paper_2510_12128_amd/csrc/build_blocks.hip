@@ -154,7 +154,8 @@ __device__ __forceinline__ void kernel_values(const double (&arg)[W], const doub
 template <bool COUPLING, int NKS, bool PAIR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PAIR ? 5 : 6, 7)))
 void k_build_tile(const PanelArgs a, const BuildItem* __restrict__ items, const double* __restrict__ S,
-                  const double* __restrict__ N, float* __restrict__ out_base, int r, float* __restrict__ out_base2) {
+                  const double* __restrict__ N, float* __restrict__ out_base, int r, float* __restrict__ out_base2,
+                  uint32_t* __restrict__ live, uint32_t* __restrict__ live2) {
   extern __shared__ __attribute__((aligned(16))) double sA[];      // 4 * kd * 16 doubles: row operands
   __shared__ __attribute__((aligned(32))) double sNr[TILE];
   __shared__ __attribute__((aligned(16))) float sT[4][16 * ST_LD];      // per wave: one 16-row group in transit
@@ -252,6 +253,9 @@ void k_build_tile(const PanelArgs a, const BuildItem* __restrict__ items, const 
 
   // second matrix of a pair: same offsets from the other base
   const int64_t side_off = PAIR ? (int64_t)(out_base2 - out_base) : 0;
+  // Clusters further apart than the kernel reaches: a group of coupling entries whose exponents are all below -300 is zero for every
+  // alpha that fp32 holds, without the polynomial.  some: whether the wave met another value (StripPort::live).
+  bool some[2] = {false, false};
   // the sixteen entries of this lane, one 16-row group at a time: masked (EDGE) or not
   auto entries = [&](auto edge_c) {
     constexpr bool EDGE = decltype(edge_c)::value;
@@ -277,7 +281,12 @@ void k_build_tile(const PanelArgs a, const BuildItem* __restrict__ items, const 
         double arg[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) arg[i] = PAIR ? fma(a.g[side], w[i], acc[ti][i]) : acc[ti][i];
-        kernel_values<4>(arg, a.coef, x);
+        if (COUPLING && !__any(fmax(fmax(arg[0], arg[1]), fmax(arg[2], arg[3])) > -300.0)) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = 0.f;
+        } else {
+          kernel_values<4>(arg, a.coef, x);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int row = 16 * ti + 4 * kk + i;
@@ -297,6 +306,7 @@ void k_build_tile(const PanelArgs a, const BuildItem* __restrict__ items, const 
           }
           st_w[i * ST_LD] = x[i];
         }
+        if (COUPLING) some[side] = some[side] || __any(x[0] != 0.f || x[1] != 0.f || x[2] != 0.f || x[3] != 0.f);
         if (a.mirror || tr == tc)
           *reinterpret_cast<float4*>(om + side * side_off + (ti >> 1) * (TILE * BLK_COLS) + (ti & 1) * FRAG + om_lane) =
               make_float4(x[0], x[1], x[2], x[3]);
@@ -318,6 +328,13 @@ void k_build_tile(const PanelArgs a, const BuildItem* __restrict__ items, const 
                     (COUPLING && (q0 + TILE - 1) / r >= p0 / r);
   if (edge) entries(std::true_type());
   else entries(std::false_type());
+  if (COUPLING) {                              // a byte a wave
+    const uint64_t word = (uint64_t)tr * (tr + 1) / 2 + tc;
+    if (lane == 0) {
+      reinterpret_cast<uint8_t*>(live + word)[wave] = some[0];
+      if (PAIR) reinterpret_cast<uint8_t*>(live2 + word)[wave] = some[1];
+    }
+  }
 }
 
 // What fp32 storage of the compensated coupling matrix drops (eq. (krep)): every entry of
@@ -586,11 +603,11 @@ static int build_impl(nugpr_ctx* c, const double* theta, hipStream_t s, int pair
 #define NUGPR_TILES(NKS)                                                                                         \
   do {                                                                                                           \
     if (pair) {                                                                                                  \
-      hipLaunchKernelGGL((k_build_tile<true, NKS, true>), gc, blk, lds, s, ac, c->d_pan_c, c->Rs, c->Rn, c->C, L.r, c->C2);      \
-      hipLaunchKernelGGL((k_build_tile<false, NKS, true>), gd, blk, lds, s, a, c->d_pan_diag, c->Xs, c->Xn, c->Kd, 1, c->Kd2);   \
+      hipLaunchKernelGGL((k_build_tile<true, NKS, true>), gc, blk, lds, s, ac, c->d_pan_c, c->Rs, c->Rn, c->C, L.r, c->C2, c->c_live, c->c2_live);      \
+      hipLaunchKernelGGL((k_build_tile<false, NKS, true>), gd, blk, lds, s, a, c->d_pan_diag, c->Xs, c->Xn, c->Kd, 1, c->Kd2, nullptr, nullptr);   \
     } else {                                                                                                     \
-      hipLaunchKernelGGL((k_build_tile<true, NKS, false>), gc, blk, lds, s, ac, c->d_pan_c, c->Rs, c->Rn, c->C, L.r, (float*)nullptr);    \
-      hipLaunchKernelGGL((k_build_tile<false, NKS, false>), gd, blk, lds, s, a, c->d_pan_diag, c->Xs, c->Xn, c->Kd, 1, (float*)nullptr); \
+      hipLaunchKernelGGL((k_build_tile<true, NKS, false>), gc, blk, lds, s, ac, c->d_pan_c, c->Rs, c->Rn, c->C, L.r, (float*)nullptr, c->c_live, nullptr);    \
+      hipLaunchKernelGGL((k_build_tile<false, NKS, false>), gd, blk, lds, s, a, c->d_pan_diag, c->Xs, c->Xn, c->Kd, 1, (float*)nullptr, nullptr, nullptr); \
     }                                                                                                            \
   } while (0)
   switch (a.kd / 4) {        // the dimensions of the usual workloads get their own instantiation
@@ -653,6 +670,7 @@ int swap_pair(nugpr_ctx* c) {
   if (c->theta_spare.empty()) { set_error("no spare blocks to switch to"); return NUGPR_ERR_STATE; }
   std::swap(c->Kd, c->Kd2);
   std::swap(c->C, c->C2);
+  std::swap(c->c_live, c->c2_live);
   c->theta_built.swap(c->theta_spare);
   c->theta_spare.clear();               // the blocks left behind are not used again
   c->kd_upper_valid = false;

@@ -161,6 +161,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.o_C = take(cur, (size_t)L.ldc * L.ldc * f);
   L.o_Kd2 = take(cur, L.kd_elems * f);
   L.o_C2 = take(cur, (size_t)L.ldc * L.ldc * f);
+  L.o_c_live = take(cur, 2 * L.n_c_tiles * sizeof(uint32_t));
   L.o_Wd = take(cur, (size_t)L.n * L.ldw * f);
   L.o_Wt = take(cur, L.wt_elems * f);
   L.o_reps = take(cur, (size_t)L.ncr * L.d * f);

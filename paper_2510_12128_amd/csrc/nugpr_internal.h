@@ -93,19 +93,40 @@ static_assert(sizeof(StripItem) == 56, "StripItem layout");
 
 constexpr int NUM_XCD = 8;     // dies; workgroup w runs on die w % 8
 
+// (64 bytes: what a workgroup reads of the arguments, which arrive cold, is one line for the head and one for its port)
 struct StripPort {
   const float* A;            // matrix base (always fp32)
   const void* in;            // input vector block, fp32 or fp64 by the arithmetic mode
   void* out;                 // output vector block(s), same type
-  uint64_t out_part_stride;  // elements between output slabs
+  uint32_t out_part_stride;  // elements between output slabs
   int32_t accumulate;        // out += result instead of out = result
   double scale = 1.0;        // the product is multiplied by this before anything is added
   double diag_add = 0.0;     // scalar added on the diagonal of items that ask for it
   const void* digits = nullptr;      // the input in digits (strip_digits.hip), or null
+  const uint32_t* live = nullptr;    // coupling matrix: a word for every lower tile (row tr, column tc at tr (tr + 1) / 2 + tc), zero where
+                                     // all of its entries are; or null
 };
+static_assert(sizeof(StripPort) == 64, "StripPort layout");
 
-// What every launch reads comes first, in the 136 bytes that one or two ports take up: the arguments arrive cold.  Preconditioner
-// apply (two launches), with the eight ports ahead of the rest / behind it: 51 clusters of 397 points, 25 columns 40.5 / 39.6 us.
+#ifdef __HIPCC__
+// Whether one of the tiles tb .. tb + nb - 1 of row j of the coupling matrix holds a value: those between clusters further apart than the
+// kernel reaches hold none, and an item of such tiles only clears its slab.  Product of 17 columns, 128 clusters of 2048 points in 20
+// dimensions with 128 representatives each, a third of whose tiles are the coupling's, none with a value at a lengthscale of 1: 532 / 395 us.
+// Items of up to three tiles are not looked at (the words arrive no sooner than a tile does: 4 x 512 points 14.8 / 14.95 us), nor
+// are those of more than 64.
+__device__ __forceinline__ bool any_live(const uint32_t* __restrict__ live, int j, int tb, int nb, int lane) {
+  if (nb < 4 || nb > 64) return true;
+  uint32_t word = 0;
+  if (lane < nb) {
+    const uint64_t hi = (uint64_t)max(j, tb + lane), lo = (uint64_t)min(j, tb + lane);
+    word = live[hi * (hi + 1) / 2 + lo];
+  }
+  return __ballot(word != 0u) != 0;
+}
+#endif
+
+// The head, which every workgroup reads, comes first.  Preconditioner apply (two launches), with eight ports ahead of it / behind it: 51
+// clusters of 397 points, 25 columns 40.5 / 39.6 us.
 struct StripArgs {
   const StripItem* items;
   int32_t T;                 // columns of the vector blocks (row stride)
@@ -113,6 +134,7 @@ struct StripArgs {
   // further a system, so that strips of two systems that read the same matrix meet in one die's L2
   int32_t sys_log2, sys_ports;
   uint32_t from[NUM_XCD + 1];  // the dies' lists of items
+  uint32_t pad_[2];
   StripPort port[2 * MAX_SLOTS];
 };
 
@@ -192,6 +214,7 @@ struct Layout {
   // byte offsets into the workspace
   size_t o_cl = 0, o_Kd = 0, o_G = 0, o_C = 0, o_Wd = 0, o_Wt = 0, o_reps = 0;
   size_t o_Q0 = 0;                   // K' z_0 kept from the base loss
+  size_t o_c_live = 0;               // which tiles of C hold a value; then the same of the spare C
   size_t o_Kd2 = 0, o_C2 = 0;        // spare K_diag and C: second matrix of a pair assembly
   size_t o_B = 0, o_X = 0, o_R = 0, o_Z = 0, o_D = 0, o_Q = 0, o_V = 0, o_U = 0;
   size_t o_digits = 0, o_Spart = 0, o_Ppart = 0, o_dot = 0, o_state = 0, o_alog = 0, o_blog = 0;
@@ -223,6 +246,7 @@ struct nugpr_ctx {
   nugpr::ClusterInfo* d_cl = nullptr;
   float *Kd = nullptr, *Lf = nullptr, *G = nullptr, *C = nullptr, *Wd = nullptr, *Wt = nullptr, *reps = nullptr;
   float *Kd2 = nullptr, *C2 = nullptr;     // spare blocks (launch_build_pair / swap_pair)
+  uint32_t *c_live = nullptr, *c2_live = nullptr;      // which tiles of C, of C2, hold a value (StripPort::live)
   // The Cholesky factor L has no storage of its own: the factorisation writes it into the spare K_diag blocks
   // (Lf = Kd2 at that time).  After the factorisation only the inverse factor G is applied; L itself is needed
   // for the right-hand sides B = [y | L Z], formed in the same call, and by nugpr_export.  The next lengthscale

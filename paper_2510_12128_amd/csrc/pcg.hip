@@ -595,6 +595,11 @@ static int fold_parts(const nugpr_ctx* c, int T) {
 
 template <typename P> static P* slot_of(P* p, uint64_t stride, int e) { return (P*)((uintptr_t)p + (uint64_t)e * stride); }
 
+// which tiles of a coupling matrix hold a value, as its assembly left it (under the compensation the diagonal is written later)
+static const uint32_t* live_tiles(const nugpr_ctx* c, const float* C) {
+  return c->L.compensate ? nullptr : C == c->C ? c->c_live : C == c->C2 ? c->c2_live : nullptr;
+}
+
 // The product of `nsys` systems side by side, each with its operator; D and Q those of system 0, the others a slot further
 // (the kept direction z_0 is shared).  More than one (2 or 4): one-hot basis, no compensation.  The counters and the timing
 // take the first `held` of them.
@@ -634,7 +639,7 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
     StripPort &k0 = port[2 * e], &k1 = port[2 * e + 1];
     k0.A = ops[e].Kd; k0.in = slot_of(D, s_d, e); k0.out = slot_of(Q, sys, e); k0.scale = ops[e].scale; k0.diag_add = ops[e].shift;
     k1.A = ops[e].C; k1.in = s_known ? c->S0v : slot_of(c->Spart, sys, e); k1.out = slot_of(c->Ppart, sys, e);
-    k1.out_part_stride = ppart; k1.scale = ops[e].scale;
+    k1.out_part_stride = ppart; k1.scale = ops[e].scale; k1.live = live_tiles(c, ops[e].C);
   }
   if (takes_digits(c, c->tab_KC, T)) {
     if ((rc = launch_digits(c, D, s_known ? c->S0v : c->Spart, T, s_d, s_known ? 0 : sys, nsys, s))) return rc;
@@ -650,7 +655,7 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
   }
   if (L.compensate) {                     // the fp32 residual of C - lambda_0 I, added slab by slab
     StripPort k2 = port[1];
-    k2.A = c->Clo; k2.accumulate = 1;
+    k2.A = c->Clo; k2.accumulate = 1; k2.live = nullptr;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
   const int parts = fold_parts(c, T);
@@ -884,11 +889,11 @@ static int run_lowrank_accumulate(nugpr_ctx* c, const void* D, void* Q, int T, h
   const uint64_t ppart = (uint64_t)L.ncr * T;
   if ((rc = run_project(c, D, T, s))) return rc;
   StripPort k1{};
-  k1.A = c->C; k1.in = c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
+  k1.A = c->C; k1.in = c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale; k1.live = live_tiles(c, c->C);
   if ((rc = launch_strip(c->tab_C, k1, k1, T, c->acc64, s))) return rc;
   if (L.compensate) {
     StripPort k2 = k1;
-    k2.A = c->Clo; k2.accumulate = 1;
+    k2.A = c->Clo; k2.accumulate = 1; k2.live = nullptr;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
   if (L.nsP > 1 && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s))) return rc;

@@ -154,10 +154,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const StripItem& it = a.items[at];
   const StripPort& pt = a.port[(row & ((1u << a.sys_log2) - 1)) * (uint32_t)a.sys_ports + it.port];
   const int c_begin = (int)it.c_begin, c_end = (int)it.c_end;
-  const int nb = c_end > c_begin ? (c_end - c_begin + TILE - 1) >> 6 : 0;
+  int nb = c_end > c_begin ? (c_end - c_begin + TILE - 1) >> 6 : 0;
   const uint32_t fl = it.blocked;
   const bool sym = (fl & 2u) != 0;
   const int kind = (int)((fl >> 2) & 3u), tb = c_begin >> 6, j_abs = (int)it.row_in_block >> 6;
+  if (pt.live && !any_live(pt.live, j_abs, tb, nb, lane)) nb = 0;
   const int jr = ((fl >> 4) & 0x7ffu) ? (int)((fl >> 15) & 0x7ffu) : j_abs - tb;
   const int jm = !sym || nb <= 0 ? 0 : (jr < nb ? jr : jr % nb);
   // the tile that holds the strip's own diagonal, and what becomes of it: multiplied apart (symmetric) or masked (triangular)
@@ -352,12 +353,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // The triangular strips (run_triangle): from 768 of 16 tiles or more on average.  Apply of 33 columns, fp64 instructions / this: 12 x 4096 285 / 259 us,
 // 32 x 4096 625 / 546, 64 x 2048 349 / 328; but 64 x 1024 (8.5 tiles) 105 / 116, 8 x 4096 (512 strips) 173 / 190, 128 x 512 71 / 77.
-// From 512 strips on (of one system, so that systems side by side take what one alone takes), of fp64 blocks of more than 17 columns.  Product of 33 columns, fp64 instructions / this: 8 clusters of
+// From 512 strips and 5000 tiles on (of one system, so that systems side by side take what one alone takes), of fp64 blocks of more than 17 columns.  Product of 33 columns, fp64 instructions / this: 8 clusters of
 // 2048 points (256 strips) 62.8 / 68.0 us, 16 (512) 96.1 / 87.4, 64 349 / 265, 32 x 1024 (512) 65.8 / 63.8, 128 x 512 106 / 85, 32 x 4096 605 / 466; of
 // 25 columns 59.5 / 64.3, 94.4 / 85.6, 336 / 251, 64.1 / 62.0, 99 / 78, 592 / 453.  Up to 17 columns there is nothing to gain: the matrix alone
-// takes that long to arrive (64 x 2048 200 / 203, 32 x 4096 377 / 366).
+// takes that long to arrive (64 x 2048 200 / 203, 32 x 4096 377 / 366).  With few tiles a strip the
+// digits' launch is what is felt: 64 x 512 (5120 tiles) 55.9 / 53.9, prediction on 65 uneven clusters of 163 (1026 tiles), 25 columns 344 / 359.
 bool takes_digits(const nugpr_ctx* c, const StripTable& tab, int T) {
-  return c->acc64 && c->digits && T > 17 && tab.count >= 512;
+  return c->acc64 && c->digits && T > 17 && tab.count >= 512 && tab.tiles >= 5000;
 }
 
 int launch_strip_digits(const StripArgs& a, int count, hipStream_t s) {

@@ -323,6 +323,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((WaveCf
   const StripItem& it = a.items[at];
   const StripPort& pt = a.port[first_port + it.port];
   setup(it, pt);
+  if (SYM && pt.live && !any_live(pt.live, S.j_abs, S.tbj + S.j_abs, S.cnt, lane)) S.cnt = 0;
   const int cnt = SP * S.cnt;                                // steps of a wave
   {
     if (cnt > 0) {
