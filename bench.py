@@ -248,7 +248,7 @@ def main():
     ncr = float(nc * r)
     vs = 8.0 if args.acc == "fp64" else 4.0
     kernel = ctx.nugpr_profile_kernel_name(T)
-    lower_only = kernel == "k_strip_digits" or int(kernel.rstrip(">").split(",")[-1]) & 3 == 1   # tiles of symmetric blocks pair up
+    lower_only = int(kernel.rstrip(">").split(",")[-1]) & 3 == 1   # tiles of symmetric blocks pair up
     # --- bytes of one launch of the dominant kernel, three accountings ---
     # Of the coupling matrix the tiles that hold a value count (the launch passes over the others; all of it under the compensation)
     ct = int(np.ceil(ncr / 64.0))

@@ -512,7 +512,7 @@ double nugpr_profile_bytes(const nugpr_ctx* c, int32_t ncols) {
 
 int nugpr_profile_kernel_name(const nugpr_ctx* c, int32_t ncols, char* buf, int32_t len) {
   if (!c || !buf || len < 1 || ncols < 1 || ncols > MAX_COLS) { set_error("bad argument"); return NUGPR_ERR_INVALID; }
-  const char* name = takes_digits(c, c->tab_KC, ncols) ? "k_strip_digits" : strip_kernel_name(c->tab_KC, ncols, c->acc64);
+  const char* name = strip_kernel_name(c->tab_KC, ncols, c->acc64);
   std::strncpy(buf, name, (size_t)len - 1);
   buf[len - 1] = 0;
   return NUGPR_OK;
@@ -649,7 +649,7 @@ int nugpr_precond_apply(nugpr_ctx* c, const float* R, float* Z, int32_t ncols, v
   if (!c->acc64) return run_precond(c, R, Z, ncols, s);
   const int64_t cnt = c->L.n * ncols;
   if ((rc = to_internal(c, R, c->Rv, cnt, s))) return rc;
-  if ((rc = run_precond(c, c->Rv, c->Zv, ncols, s))) return rc;
+  if ((rc = run_precond(c, c->Rv, c->Zv, ncols, s, true))) return rc;
   return from_internal(c, c->Zv, Z, cnt, s);
 }
 

@@ -986,7 +986,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
       hipLaunchKernelGGL((k_probes_to_block<float>), dim3(1024), dim3(256), 0, s, c->probes, (float*)c->Pv, (int64_t)L.n, L.t);
     StripPort p0{};
     p0.A = c->Lf; p0.in = c->Pv; p0.out = c->Bv;
-    int rc = run_triangle(c, c->tab_lowL, &p0, L.T, s);
+    int rc = launch_strip(c->tab_lowL, p0, p0, L.T, c->acc64, s);
     if (rc) return rc;
   }
   if (c->acc64) hipLaunchKernelGGL((k_set_col0<double>), dim3(1024), dim3(256), 0, s, (double*)c->Bv, c->y, (int64_t)L.n, L.T);

@@ -401,8 +401,7 @@ int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64
 // whether the strips of such a table take their input in digits
 bool takes_digits(const nugpr_ctx* c, const StripTable& tab, int T);
 // D (the points' rows) and S (the representatives', may be null) in digits into c->digits, one block per 64 rows of a cluster, then of S
-// (several systems: s_d, s_s bytes apart, the digits a slot)
-int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, uint64_t s_d, uint64_t s_s, int nsys, hipStream_t s);
+int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, hipStream_t s);
 // the strips of a table whose ports have their input in digits (called by launch_strip)
 int launch_strip_digits(const StripArgs& a, int count, hipStream_t s);
 
@@ -418,8 +417,8 @@ int launch_factor(nugpr_ctx* c, hipStream_t s);
 // one, Q holding the block-diagonal part only: a caller's fp32 blocks then cost no conversion passes)
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial = nullptr,
                bool* dq_done = nullptr, const float* D32 = nullptr, float* Q32 = nullptr);
-int run_triangle(nugpr_ctx* c, const StripTable& tab, StripPort* ports, int T, hipStream_t s, int nsys = 1);
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s);
+// (from_fp32: the block was widened from fp32, and the result becomes fp32)
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, bool from_fp32 = false);
 // What a loss evaluation needs besides the solution, fetched with the solve's last synchronisation:
 // <b_c, x_c> per column and rho_0 = <r_0, M^-1 r_0>.
 // Which system a batched CG run solves.

@@ -1,4 +1,6 @@
-// Strips on the integer matrix cores: products of k_strip's symmetric and triangular items with fp64 vector blocks of 18 to 33 columns.
+// Strips on the integer matrix cores: products of k_strip's symmetric and triangular items with vector blocks of 18 to 33 columns
+// which the caller holds in fp32 and wants in fp32 (nugpr_matvec, nugpr_precond_apply).  The solver keeps the fp64 instructions: with its
+// directions in digits too, a solve on 256 clusters of 4096 points took 157 iterations in place of 152.
 //
 // A 16 x 16 x 64 product of 8-bit integers takes a quarter of the cycles of a 16 x 16 x 4 one in fp64 for sixteen times the
 // terms, its sums are exact, and unlike the fp64 instructions it runs beside the vector ALUs.  So both factors are written
@@ -36,15 +38,12 @@ __device__ __forceinline__ long long whole_number(double x) {      // |x| <= 2^3
   return (long long)(int)hi * 65536 + (int)rint(fma(hi, -65536.0, x));
 }
 __global__ __launch_bounds__(256) void k_digits(const ClusterInfo* __restrict__ cl, int nc, uint32_t cluster_blocks, const double* __restrict__ D,
-                                                const double* __restrict__ S, int ncr, int T, unsigned char* __restrict__ out,
-                                                uint64_t s_d, uint64_t s_s, uint64_t s_out) {
+                                                const double* __restrict__ S, int ncr, int T, unsigned char* __restrict__ out) {
   constexpr int COLS = 16 * G + 1;
   __shared__ double rows[TILE * COLS], part[4][COLS], unit[COLS];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t block = blockIdx.x;
-  D = reinterpret_cast<const double*>(reinterpret_cast<const char*>(D) + blockIdx.y * s_d);
-  S = reinterpret_cast<const double*>(reinterpret_cast<const char*>(S) + blockIdx.y * s_s);
-  out += blockIdx.y * s_out + (uint64_t)block * DIGIT_BLOCK;
+  out += (uint64_t)block * DIGIT_BLOCK;
   const double* from;
   int valid;
   if (block < cluster_blocks) {
@@ -117,11 +116,11 @@ __global__ __launch_bounds__(256) void k_digits(const ClusterInfo* __restrict__ 
   }
 }
 
-int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, uint64_t s_d, uint64_t s_s, int nsys, hipStream_t s) {
+int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, hipStream_t s) {
   const Layout& L = c->L;
   const uint32_t cb = (uint32_t)(L.rows_pad / TILE), blocks = cb + (S ? (uint32_t)(L.ldc / TILE) : 0u);
-  hipLaunchKernelGGL(k_digits, dim3(blocks, (unsigned)nsys), dim3(256), 0, s, c->d_cl, L.nc, cb, static_cast<const double*>(D), static_cast<const double*>(S), L.ncr, T,
-                     static_cast<unsigned char*>(c->digits), s_d, s_s, L.slot_bytes);
+  hipLaunchKernelGGL(k_digits, dim3(blocks), dim3(256), 0, s, c->d_cl, L.nc, cb, static_cast<const double*>(D), static_cast<const double*>(S), L.ncr, T,
+                     static_cast<unsigned char*>(c->digits));
   NUGPR_HIP(hipGetLastError());
   return NUGPR_OK;
 }
@@ -132,7 +131,7 @@ int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, uint64_t s_
 // One workgroup = one item of k_strip's tables; the tiles of a symmetric one in the same order (its partner strip reads the same stored
 // tile at the same step).  Wave g takes the rows 16 g .. 16 g + 15 of the strip, so no sums have to meet.  A tile's digits of the
 // vector come into one of two stages of LDS (straight from memory, each wave a quarter) for all four waves, the wave's 16 x 64
-// entries into registers, both a tile ahead; one workgroup barrier a tile.  40 KiB of LDS and 128 registers a lane: four workgroups on a
+// entries into registers, both a tile ahead; one workgroup barrier a tile.  32 KiB of LDS and 128 registers a lane: four workgroups on a
 // compute unit.
 // What bounds it: what memory delivers.  64 uneven clusters of 4096 points, 33 columns: 1.07 ms (fp64 instructions 1.40), 5.5 GB at 5.2 TB/s, with
 // the matrix cores at 43 % and the vector ALUs at 75 % of the cycles; partner strips of clusters this large are not on the chip
@@ -351,13 +350,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 #endif
 }
 
-// The triangular strips (run_triangle): from 768 of 16 tiles or more on average.  Apply of 33 columns, fp64 instructions / this: 12 x 4096 285 / 259 us,
+// The triangular strips (run_precond): from 768 of 16 tiles or more on average.  Apply of 33 columns, fp64 instructions / this: 12 x 4096 285 / 259 us,
 // 32 x 4096 625 / 546, 64 x 2048 349 / 328; but 64 x 1024 (8.5 tiles) 105 / 116, 8 x 4096 (512 strips) 173 / 190, 128 x 512 71 / 77.
-// From 512 strips and 5000 tiles on (of one system, so that systems side by side take what one alone takes), of fp64 blocks of more than 17 columns.  Product of 33 columns, fp64 instructions / this: 8 clusters of
+// From 512 strips and 5000 tiles on, of more than 17 columns.  Product of 33 columns, fp64 instructions / this: 8 clusters of
 // 2048 points (256 strips) 62.8 / 68.0 us, 16 (512) 96.1 / 87.4, 64 349 / 265, 32 x 1024 (512) 65.8 / 63.8, 128 x 512 106 / 85, 32 x 4096 605 / 466; of
 // 25 columns 59.5 / 64.3, 94.4 / 85.6, 336 / 251, 64.1 / 62.0, 99 / 78, 592 / 453.  Up to 17 columns there is nothing to gain: the matrix alone
 // takes that long to arrive (64 x 2048 200 / 203, 32 x 4096 377 / 366).  With few tiles a strip the
-// digits' launch is what is felt: 64 x 512 (5120 tiles) 55.9 / 53.9, prediction on 65 uneven clusters of 163 (1026 tiles), 25 columns 344 / 359.
+// digits' launch is what is felt: 64 x 512 (5120 tiles) 55.9 / 53.9.
 bool takes_digits(const nugpr_ctx* c, const StripTable& tab, int T) {
   return c->acc64 && c->digits && T > 17 && tab.count >= 512 && tab.tiles >= 5000;
 }
