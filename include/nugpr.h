@@ -350,7 +350,7 @@ int nugpr_profile_read(nugpr_ctx* ctx, double* total_ms /*HOST*/, int32_t* launc
 double nugpr_profile_bytes(const nugpr_ctx* ctx, int32_t ncols);
 
 /* Name of the kernel instantiation behind that launch for one vector block of `ncols` columns (a launch that serves
- * several systems side by side, or nugpr_matvec, may take another one), as profilers print it
+ * several systems side by side may take another one), as profilers print it
  * without the namespace (e.g. "k_strip<1, true, 1>"), copied into buf (HOST, at most len bytes
  * including the terminating zero).  Pure host logic; lets a caller match stored counter readings to the code
  * that is actually running. */

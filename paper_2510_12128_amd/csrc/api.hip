@@ -194,13 +194,11 @@ void build_tables(const Layout& L, Tables& t) {
       const uint64_t a_off = c.koff + (uint64_t)s * TILE * c.ld;
       const uint32_t row = c.row0 + s * TILE;
       k_groups.items.push_back(make_item(a_off, c.ld, nrows, 0, c.b, c.row0, row, s * TILE, 0, 0, 0, 1.f));
-      k_groups.items.back().in_block = c.prow / TILE;
       k_groups.items.back().blocked = c.nt >= 2 ? 3 : 1;      // K_ii is symmetric: its strips pair up tile by tile
       wp.push_back(make_item((uint64_t)row * L.ldw, (uint32_t)L.ldw, nrows, 0, r, (uint32_t)i * r, row, 0, 0, 0, 0, 0.f));
       low_g.items.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
       up_g.items.push_back(make_item(a_off, c.ld, nrows, s * TILE, c.b, c.row0, row, s * TILE, 0, 0, 2, 0.f));
       low_l.items.push_back(make_item(a_off, c.ld, nrows, 0, s * TILE + nrows, c.row0, row, s * TILE, 0, 0, 1, 0.f));
-      low_g.items.back().in_block = up_g.items.back().in_block = low_l.items.back().in_block = c.prow / TILE;
       low_g.items.back().blocked = up_g.items.back().blocked = low_l.items.back().blocked = 1;     // L and L^-1 are stored blocked too
     }
   }
@@ -220,7 +218,6 @@ void build_tables(const Layout& L, Tables& t) {
       StripItem it = make_item((uint64_t)rs * TILE * L.ldc, (uint32_t)L.ldc, nrows, cb, std::max(cb, ce), 0, rs * TILE,
                                rs * TILE, k, 1, 0, 0.f);
       it.blocked = 1;
-      it.in_block = (uint32_t)(L.rows_pad / TILE);
       // the item whose columns hold the strip's own rows adds the port's scalar diagonal (used when the diagonal
       // of the matrix is carried as an exact scalar: the eigenvalue iteration for lambda_0)
       it.diag_add = (rs / cpp == (uint32_t)k) ? 1.f : 0.f;
@@ -378,7 +375,6 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->rep_pts = reinterpret_cast<int32_t*>(w + L.o_rep_pts);
   c->Pv = w + L.o_P;
   c->Spart = w + L.o_Spart;
-  c->digits = L.T > 17 ? w + L.o_digits : nullptr;
   c->Ppart = w + L.o_Ppart;
   c->dotpart = reinterpret_cast<double*>(w + L.o_dot);
   c->d_state = reinterpret_cast<PcgState*>(w + L.o_state);
@@ -614,8 +610,7 @@ int nugpr_matvec_static(nugpr_ctx* c, const float* D, float* Q, int32_t ncols, v
   char* base = static_cast<char*>(g_scratch_ptr[dev]);        // looked up at nugpr_create on this device
   if (!base) { set_error("static scratch address unknown on this device"); return NUGPR_ERR_STATE; }
   // the kernels take their buffers as arguments, as in nugpr_matvec: only the addresses differ.  Nothing in the
-  // scratch needs clearing: every slab and block that is read was written by an earlier kernel of this call.  (The input in digits, where
-  // a product of this size takes it, stays in the workspace.)
+  // scratch needs clearing: every slab and block that is read was written by an earlier kernel of this call.
   void *sDv = c->Dv, *sQv = c->Qv, *sS = c->Spart, *sP = c->Ppart;
   c->Dv = base; c->Qv = base + b_vec; c->Spart = base + 2 * b_vec; c->Ppart = base + 2 * b_vec + b_S;
   rc = nugpr_matvec(c, D, Q, ncols, stream);
@@ -649,7 +644,7 @@ int nugpr_precond_apply(nugpr_ctx* c, const float* R, float* Z, int32_t ncols, v
   if (!c->acc64) return run_precond(c, R, Z, ncols, s);
   const int64_t cnt = c->L.n * ncols;
   if ((rc = to_internal(c, R, c->Rv, cnt, s))) return rc;
-  if ((rc = run_precond(c, c->Rv, c->Zv, ncols, s, true))) return rc;
+  if ((rc = run_precond(c, c->Rv, c->Zv, ncols, s))) return rc;
   return from_internal(c, c->Zv, Z, cnt, s);
 }
 

@@ -212,7 +212,6 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.slot_bytes = cur - slot0;
   cur = slot0 + L.slots * L.slot_bytes;
   L.o_logdet = take(cur, (size_t)L.nc * sizeof(double));
-  L.o_digits = take(cur, L.T > 17 ? (size_t)(L.rows_pad + L.ldc) / TILE * DIGIT_BLOCK : 0);
   // tile list of the diagonal blocks (mirroring) + row-panel work items of the two assembly launches
   // tile list of the diagonal blocks + the assembly work items (32 bytes each, at most one per tile)
   L.o_tiles = take(cur, (5 * L.n_diag_tiles + 4 * L.n_c_tiles) * sizeof(uint64_t));

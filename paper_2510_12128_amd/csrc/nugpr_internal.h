@@ -85,11 +85,10 @@ struct StripItem {
   uint8_t port;          // which (matrix, in, out) triple of the launch
   uint8_t mode;          // 0 full, 1 lower triangle (col <= row), 2 upper triangle (col >= row)
   float diag_add;        // 1 for square diagonal blocks: out += port.diag_add * in[row]; else 0
-  uint32_t in_block;     // block of digits that holds the vector rows of column 0 (strip_digits.hip)
   uint32_t blocked;      // bit 0: the matrix is stored in blocks of operand fragments (blocked_index), else row-major;
                          // bit 1: full strip of a symmetric square block, upper tiles read as transposed lower ones
 };
-static_assert(sizeof(StripItem) == 56, "StripItem layout");
+static_assert(sizeof(StripItem) == 48, "StripItem layout");
 
 constexpr int NUM_XCD = 8;     // dies; workgroup w runs on die w % 8
 
@@ -98,11 +97,10 @@ struct StripPort {
   const float* A;            // matrix base (always fp32)
   const void* in;            // input vector block, fp32 or fp64 by the arithmetic mode
   void* out;                 // output vector block(s), same type
-  uint32_t out_part_stride;  // elements between output slabs
+  uint64_t out_part_stride;  // elements between output slabs
   int32_t accumulate;        // out += result instead of out = result
   double scale = 1.0;        // the product is multiplied by this before anything is added
   double diag_add = 0.0;     // scalar added on the diagonal of items that ask for it
-  const void* digits = nullptr;      // the input in digits (strip_digits.hip), or null
   const uint32_t* live = nullptr;    // coupling matrix: a word for every lower tile (row tr, column tc at tr (tr + 1) / 2 + tc), zero where
                                      // all of its entries are; or null
 };
@@ -145,9 +143,6 @@ struct StripTable {
   int64_t tiles = 0;     // of all items
   int kind = 0;          // which instantiation of the strip kernel serves it (strip_kind)
 };
-
-// bytes of a block of 64 rows of 33 columns in digits (strip_digits.hip): five KiB for each 16 columns, one for column 0, one for the scales
-constexpr int DIGIT_BLOCK = 12 * 1024;
 
 // ---------------------------------------------------------------------------
 // device-side PCG scalars (all double), one slot per column
@@ -217,7 +212,7 @@ struct Layout {
   size_t o_c_live = 0;               // which tiles of C hold a value; then the same of the spare C
   size_t o_Kd2 = 0, o_C2 = 0;        // spare K_diag and C: second matrix of a pair assembly
   size_t o_B = 0, o_X = 0, o_R = 0, o_Z = 0, o_D = 0, o_Q = 0, o_V = 0, o_U = 0;
-  size_t o_digits = 0, o_Spart = 0, o_Ppart = 0, o_dot = 0, o_state = 0, o_alog = 0, o_blog = 0;
+  size_t o_Spart = 0, o_Ppart = 0, o_dot = 0, o_state = 0, o_alog = 0, o_blog = 0;
   size_t o_theta = 0, o_logdet = 0, o_tiles = 0, o_items = 0;
   size_t o_Xs = 0, o_Xn = 0, o_Rs = 0, o_Rn = 0;
   size_t o_x0 = 0, o_Z0 = 0, o_P = 0, o_Clo = 0, o_S0 = 0, o_dav = 0;
@@ -259,7 +254,6 @@ struct nugpr_ctx {
   void *Bv = nullptr, *Xv = nullptr, *Rv = nullptr, *Zv = nullptr, *Dv = nullptr, *Qv = nullptr, *Vv = nullptr,
        *Uv = nullptr;
   void *Spart = nullptr, *Ppart = nullptr;
-  void* digits = nullptr;                // the product's input in digits (strip_digits.hip)
   // M^-1 [y | L Z]: the first preconditioned residual of every solve on the context's own right-hand
   // sides; it depends on the factor only, so the factorisation computes it once
   void* Z0v = nullptr;
@@ -397,14 +391,6 @@ const char* strip_kernel_name(const StripTable& tab, int T, bool acc64);
 int launch_sum_parts(const void* in, void* out, int64_t count, int parts, uint64_t stride, bool acc64,
                      hipStream_t s, int nsys = 1, uint64_t slot = 0);
 
-// strip_digits.hip -----------------------------------------------------------
-// whether the strips of such a table take their input in digits
-bool takes_digits(const nugpr_ctx* c, const StripTable& tab, int T);
-// D (the points' rows) and S (the representatives', may be null) in digits into c->digits, one block per 64 rows of a cluster, then of S
-int launch_digits(nugpr_ctx* c, const void* D, const void* S, int T, hipStream_t s);
-// the strips of a table whose ports have their input in digits (called by launch_strip)
-int launch_strip_digits(const StripArgs& a, int count, hipStream_t s);
-
 // factor.hip ----------------------------------------------------------------
 int launch_factor(nugpr_ctx* c, hipStream_t s);
 
@@ -417,8 +403,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s);
 // one, Q holding the block-diagonal part only: a caller's fp32 blocks then cost no conversion passes)
 int run_matvec(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s, double* dq_partial = nullptr,
                bool* dq_done = nullptr, const float* D32 = nullptr, float* Q32 = nullptr);
-// (from_fp32: the block was widened from fp32, and the result becomes fp32)
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, bool from_fp32 = false);
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s);
 // What a loss evaluation needs besides the solution, fetched with the solve's last synchronisation:
 // <b_c, x_c> per column and rho_0 = <r_0, M^-1 r_0>.
 // Which system a batched CG run solves.

@@ -641,10 +641,6 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
     k1.A = ops[e].C; k1.in = s_known ? c->S0v : slot_of(c->Spart, sys, e); k1.out = slot_of(c->Ppart, sys, e);
     k1.out_part_stride = ppart; k1.scale = ops[e].scale; k1.live = live_tiles(c, ops[e].C);
   }
-  if (D32 && takes_digits(c, c->tab_KC, T)) {      // (a caller's product from fp32 to fp32; the solver's keep fp64 throughout)
-    if ((rc = launch_digits(c, D, c->Spart, T, s))) return rc;
-    port[0].digits = port[1].digits = c->digits;
-  }
   const bool timed = c->prof_on && (size_t)(2 * c->prof_used + 1) < c->prof_ev.size();
   if (timed) NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used], s));
   if ((rc = launch_strip(c->tab_KC, port, 2 * nsys, T, c->acc64, s, nsys))) return rc;
@@ -909,7 +905,7 @@ int run_split_op(nugpr_ctx* c, const void* D, void* out, int T, hipStream_t s) {
   const int64_t cnt = c->L.n * T;
   StripPort up{};
   up.A = c->G; up.in = D; up.out = c->Vv;
-  if ((rc = launch_strip(c->tab_upG, up, up, T, c->acc64, s))) return rc;                           // U = Y^T D
+  if ((rc = launch_strip(c->tab_upG, up, up, T, c->acc64, s))) return rc;                 // U = Y^T D
   const bool identity = c->build_gen == c->factor_gen && !c->general_route &&
                         !(c->params.flags & (NUGPR_NO_SHORTCUTS | NUGPR_PRECOND_COMPENSATED));
   StripPort lo{};
@@ -942,7 +938,7 @@ static int run_pade_q(nugpr_ctx* c, const void* D, void* Q, int T, hipStream_t s
 }
 
 // (nsys > 1: R and Z of system 0, the others a slot further; the first `held` of them are counted)
-static int precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys, int held, bool digits = false) {
+static int precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, int nsys, int held) {
   int rc;
   const uint64_t sys = c->L.slot_bytes;
   c->stats.precond_applies += held;
@@ -951,18 +947,10 @@ static int precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, i
     a[e].A = c->G; a[e].in = slot_of(R, sys, e); a[e].out = slot_of(c->Vv, sys, e);
     b[e].A = c->G; b[e].in = a[e].out; b[e].out = slot_of(Z, sys, e);
   }
-  for (const bool lower : {true, false}) {
-    const StripTable& tab = lower ? c->tab_lowG : c->tab_upG;
-    StripPort* port = lower ? a : b;
-    if (digits && takes_digits(c, tab, T) && tab.count >= 768 && tab.tiles >= 16 * tab.count) {
-      if ((rc = launch_digits(c, port[0].in, nullptr, T, s))) return rc;
-      port[0].digits = c->digits;
-    }
-    if ((rc = launch_strip(tab, port, nsys, T, c->acc64, s, nsys))) return rc;
-  }
-  return NUGPR_OK;
+  if ((rc = launch_strip(c->tab_lowG, a, nsys, T, c->acc64, s, nsys))) return rc;
+  return launch_strip(c->tab_upG, b, nsys, T, c->acc64, s, nsys);
 }
-int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s, bool from_fp32) { return precond(c, R, Z, T, s, 1, 1, from_fp32); }
+int run_precond(nugpr_ctx* c, const void* R, void* Z, int T, hipStream_t s) { return precond(c, R, Z, T, s, 1, 1); }
 
 static int elementwise_grid(int64_t n, int T) {
   const int rpp = 256 / T;

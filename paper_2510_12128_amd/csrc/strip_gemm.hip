@@ -556,11 +556,6 @@ int launch_strip(const StripTable& tab, const StripPort* ports, int nports, int 
   a.sys_log2 = nsys / 2;
   a.sys_ports = nports / nsys;
   std::copy(tab.from, tab.from + NUM_XCD + 1, a.from);
-  if (acc64 && ports[0].digits) {
-    uint32_t longest = 0;
-    for (int d = 0; d < NUM_XCD; ++d) longest = std::max(longest, tab.from[d + 1] - tab.from[d]);
-    return launch_strip_digits(a, (int)(NUM_XCD * longest) << a.sys_log2, s);
-  }
   const int ng = (T - 1 + 15) / 16;
   return acc64 ? launch_table<true>(tab, ng, T, s, a) : launch_table<false>(tab, ng, T, s, a);
 }
