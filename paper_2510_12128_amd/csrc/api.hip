@@ -349,6 +349,10 @@ int nugpr_create(nugpr_ctx** out, const nugpr_problem* pb, const nugpr_params* p
   c->C2 = reinterpret_cast<float*>(w + L.o_C2);
   c->c_live = reinterpret_cast<uint32_t*>(w + L.o_c_live);
   c->c2_live = c->c_live + L.n_c_tiles;
+  {
+    const int tiles = (L.ldc / TILE + L.nsP - 1) / L.nsP;      // of an item of C (any_live)
+    c->c_skips = !L.compensate && tiles >= 4 && tiles <= 64;
+  }
   c->Clo = !L.compensate ? nullptr : (L.ncr <= COMPENSATE_HOST_MAX ? reinterpret_cast<float*>(w + L.o_Clo) : c->C2);
   c->dav = L.ncr > COMPENSATE_HOST_MAX ? reinterpret_cast<double*>(w + L.o_dav) : nullptr;
   c->Wd = reinterpret_cast<float*>(w + L.o_Wd);
@@ -597,8 +601,8 @@ int nugpr_matvec_static(nugpr_ctx* c, const float* D, float* Q, int32_t ncols, v
   const size_t vs = c->acc64 ? sizeof(double) : sizeof(float);
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   const size_t b_vec = c->acc64 ? up((size_t)L.n * ncols * vs) : 0;
-  const size_t b_S = up((size_t)L.nsS * L.ncr * ncols * vs), b_P = up((size_t)L.nsP * L.ncr * ncols * vs);
-  const size_t need = 2 * b_vec + b_S + b_P;
+  size_t b_S = up((size_t)L.nsS * L.ncr * ncols * vs);
+  const size_t b_P = up((size_t)L.nsP * L.ncr * ncols * vs), need = 2 * b_vec + b_S + b_P;
   if (need > STATIC_SCRATCH_BYTES) {
     set_error("nugpr_matvec_static: this product needs " + std::to_string(need) + " bytes of scratch, the static "
               "buffer holds " + std::to_string(STATIC_SCRATCH_BYTES) + "; use nugpr_matvec");
@@ -611,10 +615,17 @@ int nugpr_matvec_static(nugpr_ctx* c, const float* D, float* Q, int32_t ncols, v
   if (!base) { set_error("static scratch address unknown on this device"); return NUGPR_ERR_STATE; }
   // the kernels take their buffers as arguments, as in nugpr_matvec: only the addresses differ.  Nothing in the
   // scratch needs clearing: every slab and block that is read was written by an earlier kernel of this call.
+  // (Behind the projection lie the bytes that say which of its rows are not finite; a product whose slabs leave them no room
+  // multiplies every tile.)
+  const size_t b_odd = std::max(b_S, up(up((size_t)L.ncr * ncols * vs) + (size_t)L.ncr));
+  const bool skips = c->c_skips;
+  if (need - b_S + b_odd <= STATIC_SCRATCH_BYTES) b_S = b_odd;
+  else c->c_skips = false;
   void *sDv = c->Dv, *sQv = c->Qv, *sS = c->Spart, *sP = c->Ppart;
   c->Dv = base; c->Qv = base + b_vec; c->Spart = base + 2 * b_vec; c->Ppart = base + 2 * b_vec + b_S;
   rc = nugpr_matvec(c, D, Q, ncols, stream);
   c->Dv = sDv; c->Qv = sQv; c->Spart = sS; c->Ppart = sP;
+  c->c_skips = skips;
   return rc;
 }
 

@@ -186,7 +186,9 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.o_Z0 = take(cur, vec);
   L.o_P = take(cur, vec);
   L.o_Q0 = take(cur, vec);
-  L.o_S0 = take(cur, (size_t)L.ncr * L.T * sizeof(double));
+  // (a projection of T columns: the values, and behind them a byte for every few rows, see product)
+  const size_t projection = align_up((size_t)L.ncr * L.T * sizeof(double), 256) + (size_t)L.ncr;
+  L.o_S0 = take(cur, projection);
   // The blocks of a solve, once per system that can be taken side by side.  Up to 32768 points (256 partial sums a dot product):
   // there a launch of one system leaves most of the chip idle.
   L.slots = L.n_dot_blocks <= 256 && one_system_iter <= 0 ? MAX_SLOTS : 1;
@@ -202,7 +204,7 @@ int plan_layout(const nugpr_problem* pb, uint32_t flags, Layout& L, int one_syst
   L.o_Q = take(cur, vec);
   L.o_V = take(cur, vec);
   L.o_U = take(cur, vec);
-  L.o_Spart = take(cur, (size_t)L.nsS * L.ncr * L.T * sizeof(double));
+  L.o_Spart = take(cur, std::max((size_t)L.nsS * L.ncr * L.T * sizeof(double), projection));
   L.o_Ppart = take(cur, (size_t)L.nsP * L.ncr * L.T * sizeof(double));
   L.o_dot = take(cur, (size_t)4 * L.n_dot_blocks * MAX_COLS * sizeof(double));
   L.o_state = take(cur, sizeof(PcgState));

@@ -99,29 +99,14 @@ struct StripPort {
   void* out;                 // output vector block(s), same type
   uint64_t out_part_stride;  // elements between output slabs
   int32_t accumulate;        // out += result instead of out = result
+  uint32_t odd_at : 20;      // where live is given: a byte for every odd_rows rows of `in`, odd_at x 256 bytes behind its start,
+  uint32_t odd_rows : 12;    // that says whether one of their values is not finite
   double scale = 1.0;        // the product is multiplied by this before anything is added
   double diag_add = 0.0;     // scalar added on the diagonal of items that ask for it
   const uint32_t* live = nullptr;    // coupling matrix: a word for every lower tile (row tr, column tc at tr (tr + 1) / 2 + tc), zero where
                                      // all of its entries are; or null
 };
 static_assert(sizeof(StripPort) == 64, "StripPort layout");
-
-#ifdef __HIPCC__
-// Whether one of the tiles tb .. tb + nb - 1 of row j of the coupling matrix holds a value: those between clusters further apart than the
-// kernel reaches hold none, and an item of such tiles only clears its slab.  Product of 17 columns, 128 clusters of 2048 points in 20
-// dimensions with 128 representatives each, a third of whose tiles are the coupling's, none with a value at a lengthscale of 1: 532 / 395 us.
-// Items of up to three tiles are not looked at (the words arrive no sooner than a tile does: 4 x 512 points 14.8 / 14.95 us), nor
-// are those of more than 64.
-__device__ __forceinline__ bool any_live(const uint32_t* __restrict__ live, int j, int tb, int nb, int lane) {
-  if (nb < 4 || nb > 64) return true;
-  uint32_t word = 0;
-  if (lane < nb) {
-    const uint64_t hi = (uint64_t)max(j, tb + lane), lo = (uint64_t)min(j, tb + lane);
-    word = live[hi * (hi + 1) / 2 + lo];
-  }
-  return __ballot(word != 0u) != 0;
-}
-#endif
 
 // The head, which every workgroup reads, comes first.  Preconditioner apply (two launches), with eight ports ahead of it / behind it: 51
 // clusters of 397 points, 25 columns 40.5 / 39.6 us.
@@ -241,6 +226,7 @@ struct nugpr_ctx {
   nugpr::ClusterInfo* d_cl = nullptr;
   float *Kd = nullptr, *Lf = nullptr, *G = nullptr, *C = nullptr, *Wd = nullptr, *Wt = nullptr, *reps = nullptr;
   float *Kd2 = nullptr, *C2 = nullptr;     // spare blocks (launch_build_pair / swap_pair)
+  bool c_skips = false;                    // products pass over items of C without a value (StripPort::live)
   uint32_t *c_live = nullptr, *c2_live = nullptr;      // which tiles of C, of C2, hold a value (StripPort::live)
   // The Cholesky factor L has no storage of its own: the factorisation writes it into the spare K_diag blocks
   // (Lf = Kd2 at that time).  After the factorisation only the inverse factor G is applied; L itself is needed

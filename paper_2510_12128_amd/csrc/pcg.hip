@@ -595,9 +595,31 @@ static int fold_parts(const nugpr_ctx* c, int T) {
 
 template <typename P> static P* slot_of(P* p, uint64_t stride, int e) { return (P*)((uintptr_t)p + (uint64_t)e * stride); }
 
-// which tiles of a coupling matrix hold a value, as its assembly left it (under the compensation the diagonal is written later)
-static const uint32_t* live_tiles(const nugpr_ctx* c, const float* C) {
-  return c->L.compensate ? nullptr : C == c->C ? c->c_live : C == c->C2 ? c->c2_live : nullptr;
+// The one-hot projection (k_onehot_project): threads per representative and column, the power of two that leaves each at most eight
+// points on average (one round of gathers), as far as the workgroup has them; large workgroups once an ordinary one has not.
+struct ProjectShape { int block, parts, reps; };       // (reps: representatives of a workgroup)
+static ProjectShape project_shape(const Layout& L, int T) {
+  const int64_t want = (L.n + 8 * (int64_t)L.ncr - 1) / (8 * (int64_t)L.ncr);
+  ProjectShape p;
+  p.block = want > 256 / T ? 1024 : 256;
+  p.parts = 1;
+  while (2 * p.parts <= p.block / T && p.parts < want) p.parts *= 2;
+  p.reps = p.block / T / p.parts;
+  return p;
+}
+// Behind a projection of T columns: a byte for every odd_rows of its rows, whether a value there is not finite.
+constexpr int DENSE_ODD_ROWS = TILE;
+static size_t odd_offset(const nugpr_ctx* c, int T) {
+  return ((size_t)c->L.ncr * T * (c->acc64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
+}
+static int odd_rows(const nugpr_ctx* c, int T) { return c->onehot ? project_shape(c->L, T).reps : DENSE_ODD_ROWS; }
+// Products with C pass over items whose tiles hold no value, as the assembly of C left them (under the compensation its diagonal is
+// written later), and whose vector rows are finite.
+static void skip_dead_items(const nugpr_ctx* c, StripPort& port, int T) {
+  if (!c->c_skips) return;
+  port.live = port.A == c->C ? c->c_live : port.A == c->C2 ? c->c2_live : nullptr;
+  port.odd_at = (uint32_t)(odd_offset(c, T) / 256);
+  port.odd_rows = (uint32_t)odd_rows(c, T);
 }
 
 // The product of `nsys` systems side by side, each with its operator; D and Q those of system 0, the others a slot further
@@ -639,7 +661,8 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
     StripPort &k0 = port[2 * e], &k1 = port[2 * e + 1];
     k0.A = ops[e].Kd; k0.in = slot_of(D, s_d, e); k0.out = slot_of(Q, sys, e); k0.scale = ops[e].scale; k0.diag_add = ops[e].shift;
     k1.A = ops[e].C; k1.in = s_known ? c->S0v : slot_of(c->Spart, sys, e); k1.out = slot_of(c->Ppart, sys, e);
-    k1.out_part_stride = ppart; k1.scale = ops[e].scale; k1.live = live_tiles(c, ops[e].C);
+    k1.out_part_stride = ppart; k1.scale = ops[e].scale;
+    skip_dead_items(c, k1, T);
   }
   const bool timed = c->prof_on && (size_t)(2 * c->prof_used + 1) < c->prof_ev.size();
   if (timed) NUGPR_HIP(hipEventRecord(c->prof_ev[2 * c->prof_used], s));
@@ -651,7 +674,7 @@ static int product(nugpr_ctx* c, const Operator* ops, int nsys, int held, const 
   }
   if (L.compensate) {                     // the fp32 residual of C - lambda_0 I, added slab by slab
     StripPort k2 = port[1];
-    k2.A = c->Clo; k2.accumulate = 1; k2.live = nullptr;
+    k2.A = c->Clo; k2.accumulate = 1;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
   const int parts = fold_parts(c, T);
@@ -714,7 +737,8 @@ template <typename VT, typename ST>
 __global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ D, VT* __restrict__ Dwide,
                                                          const int32_t* __restrict__ rep_ptr,
                                                          const int32_t* __restrict__ rep_pts, VT* __restrict__ S,
-                                                         int ncr, int T, int parts, uint64_t s_d, uint64_t sys) {
+                                                         int ncr, int T, int parts, uint64_t s_d, uint64_t sys,
+                                                         uint8_t* __restrict__ odd) {
   __shared__ double red[1024];
   D = of_system(D, s_d);
   S = of_system(S, sys);
@@ -747,10 +771,26 @@ __global__ __launch_bounds__(1024) void k_onehot_project(const ST* __restrict__ 
   }
   red[tid] = s;
   __syncthreads();
+  bool bad = false;
   if (live && part == 0) {
     for (int k = 1; k < parts; ++k) s += red[tid + k * T];
-    S[(int64_t)a * T + col] = (VT)s;
+    const VT v = (VT)s;
+    S[(int64_t)a * T + col] = v;
+    bad = !(v - v == (VT)0);
   }
+  if (odd) {                                       // (uniform)
+    const int any = __syncthreads_or(bad);
+    if (tid == 0) of_system(odd, sys)[blockIdx.x] = any != 0;
+  }
+}
+// the same bytes for a projection that exists: DENSE_ODD_ROWS rows a workgroup
+template <typename VT>
+__global__ __launch_bounds__(256) void k_odd_rows(const VT* __restrict__ S, int ncr, int T, uint8_t* __restrict__ odd) {
+  const int64_t first = (int64_t)blockIdx.x * DENSE_ODD_ROWS * T, end = min((int64_t)ncr * T, first + (int64_t)DENSE_ODD_ROWS * T);
+  bool bad = false;
+  for (int64_t i = first + threadIdx.x; i < end; i += 256) bad |= !(S[i] - S[i] == (VT)0);
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) odd[blockIdx.x] = any != 0;
 }
 
 // out = Q + W P: out is Q itself, or the caller's fp32 block (the narrowing then costs no pass of its own)
@@ -826,20 +866,16 @@ static int elementwise_grid(int64_t n, int T);
 // fp64 mode only): the block is read from this fp32 array and its widened copy is written to D on the way.
 static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const float* D32, int nsys, uint64_t s_d) {
   const Layout& L = c->L;
+  uint8_t* odd = c->c_skips ? static_cast<uint8_t*>(c->Spart) + odd_offset(c, T) : nullptr;
   if (D32 && !(c->onehot && c->acc64)) { set_error("internal: fused widening needs the one-hot basis in fp64 mode"); return NUGPR_ERR_INVALID; }
   if (c->onehot) {
-    // threads per representative and column: the power of two that leaves each at most eight points on average (one round
-    // of gathers), as far as the workgroup has them; large workgroups once an ordinary one has not
-    const int64_t want = (L.n + 8 * (int64_t)L.ncr - 1) / (8 * (int64_t)L.ncr);
-    const int block = want > 256 / T ? 1024 : 256, rpp = block / T;
-    int parts = 1;
-    while (2 * parts <= rpp && parts < want) parts *= 2;
-    const int reps = rpp / parts;
-    const dim3 grid((unsigned)((L.ncr + reps - 1) / reps), (unsigned)nsys), blk((unsigned)block);
+    const ProjectShape shape = project_shape(L, T);
+    const int parts = shape.parts;
+    const dim3 grid((unsigned)((L.ncr + shape.reps - 1) / shape.reps), (unsigned)nsys), blk((unsigned)shape.block);
     const uint64_t sys = L.slot_bytes;
-    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), grid, blk, 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys);
-    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), grid, blk, 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys);
-    else hipLaunchKernelGGL((k_onehot_project<float, float>), grid, blk, 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T, parts, s_d, sys);
+    if (D32) hipLaunchKernelGGL((k_onehot_project<double, float>), grid, blk, 0, s, D32, (double*)const_cast<void*>(D), c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys, odd);
+    else if (c->acc64) hipLaunchKernelGGL((k_onehot_project<double, double>), grid, blk, 0, s, (const double*)D, (double*)nullptr, c->rep_ptr, c->rep_pts, (double*)c->Spart, L.ncr, T, parts, s_d, sys, odd);
+    else hipLaunchKernelGGL((k_onehot_project<float, float>), grid, blk, 0, s, (const float*)D, (float*)nullptr, c->rep_ptr, c->rep_pts, (float*)c->Spart, L.ncr, T, parts, s_d, sys, odd);
     NUGPR_HIP(hipGetLastError());
     return NUGPR_OK;
   }
@@ -849,6 +885,12 @@ static int run_project(nugpr_ctx* c, const void* D, int T, hipStream_t s, const 
   s0.A = c->Wt; s0.in = D; s0.out = c->Spart; s0.out_part_stride = spart;
   if ((rc = launch_strip(c->tab_WtD, s0, s0, T, c->acc64, s))) return rc;
   if (L.nsS > 1 && (rc = launch_sum_parts(c->Spart, c->Spart, (int64_t)spart, L.nsS, spart, c->acc64, s))) return rc;
+  if (odd) {                                       // (over slabs that are added up)
+    const dim3 grid((unsigned)((L.ncr + DENSE_ODD_ROWS - 1) / DENSE_ODD_ROWS));
+    if (c->acc64) hipLaunchKernelGGL((k_odd_rows<double>), grid, dim3(256), 0, s, (const double*)c->Spart, L.ncr, T, odd);
+    else hipLaunchKernelGGL((k_odd_rows<float>), grid, dim3(256), 0, s, (const float*)c->Spart, L.ncr, T, odd);
+    NUGPR_HIP(hipGetLastError());
+  }
   return NUGPR_OK;
 }
 
@@ -885,11 +927,12 @@ static int run_lowrank_accumulate(nugpr_ctx* c, const void* D, void* Q, int T, h
   const uint64_t ppart = (uint64_t)L.ncr * T;
   if ((rc = run_project(c, D, T, s))) return rc;
   StripPort k1{};
-  k1.A = c->C; k1.in = c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale; k1.live = live_tiles(c, c->C);
+  k1.A = c->C; k1.in = c->Spart; k1.out = c->Ppart; k1.out_part_stride = ppart; k1.scale = c->op_scale;
+  skip_dead_items(c, k1, T);
   if ((rc = launch_strip(c->tab_C, k1, k1, T, c->acc64, s))) return rc;
   if (L.compensate) {
     StripPort k2 = k1;
-    k2.A = c->Clo; k2.accumulate = 1; k2.live = nullptr;
+    k2.A = c->Clo; k2.accumulate = 1;
     if ((rc = launch_strip(c->tab_C, k2, k2, T, c->acc64, s))) return rc;
   }
   if (L.nsP > 1 && (rc = launch_sum_parts(c->Ppart, c->Ppart, (int64_t)ppart, L.nsP, ppart, c->acc64, s))) return rc;
@@ -1175,7 +1218,7 @@ static int store_known_t(nugpr_ctx* c, hipStream_t s) {
   // W^T z_0
   int rc = run_project(c, c->Z0v, L.T, s);
   if (rc) return rc;
-  NUGPR_HIP(hipMemcpyAsync(c->S0v, c->Spart, (size_t)L.ncr * L.T * sizeof(VT), hipMemcpyDeviceToDevice, s));
+  NUGPR_HIP(hipMemcpyAsync(c->S0v, c->Spart, odd_offset(c, L.T) + (size_t)L.ncr, hipMemcpyDeviceToDevice, s));
   return NUGPR_OK;
 }
 

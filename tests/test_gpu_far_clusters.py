@@ -35,6 +35,35 @@ def test_products_where_most_of_the_coupling_vanishes(lib, acc_fp32):
     ctx.close()
 
 
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("acc_fp32", [False, True])
+def test_values_that_are_not_finite_reach_every_row(lib, acc_fp32, dense):
+    """A NaN or infinity among the vector rows meets every row of the coupling matrix, zeros included: 0 times it is NaN."""
+    import torch
+    nc, b, rank = 40, 130, 128
+    n = nc * b
+    rng = np.random.default_rng(4)
+    centres = np.stack([6.0 * (np.arange(nc) % 4), 500.0 * (np.arange(nc) // 4)], 1)
+    X = (np.repeat(centres, b, axis=0) + 0.5 * rng.standard_normal((n, 2))).astype(np.float32)
+    ctx = lib.Context(X, np.zeros(n, np.float32), np.arange(nc + 1) * b, 2.0 * rng.integers(0, 2, (n, 32)) - 1.0, rank, acc_fp32=acc_fp32)
+    theta = np.array([1.5, 1.5, 1.3, 0.2])
+    ctx.nugpr_build_blocks(theta)
+    if dense:
+        ctx.nugpr_set_nystrom_basis(theta)
+    for T in (1, 2, 17, 33):
+        V = torch.as_tensor(rng.standard_normal((n, T)), dtype=torch.float32, device="cuda")
+        clean = ctx.nugpr_matvec(V)
+        assert bool(torch.isfinite(clean).all())
+        for at, col, bad in ((0, 0, float("nan")), (n - 1, T - 1, float("inf")), (7 * b + 129, T // 2, -float("inf")), (39 * b, T - 1, float("nan"))):
+            W = V.clone()
+            W[at, col] = bad
+            got = ctx.nugpr_matvec(W)
+            keep = [c for c in range(T) if c != col]
+            assert torch.equal(got[:, keep], clean[:, keep]), (T, at)
+            assert not bool(torch.isfinite(got[:, col]).any()), (T, at, int(torch.isfinite(got[:, col]).sum()))
+    ctx.close()
+
+
 def test_training_step_where_most_of_the_coupling_vanishes(lib):
     """Both matrices of a pair assembly against an assembly of their own each: entries differ by a rounding to fp32 (2^-25), whose
     difference over 2 h = 2e-3 is 1.5e-5 of a term of the loss at most."""
