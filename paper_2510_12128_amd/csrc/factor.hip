@@ -108,6 +108,19 @@ __device__ __forceinline__ bool list_item(const Pieces& pieces, const uint32_t* 
 // loaded straight into LDS, 36.7; cutting placed between the matrix instructions of the same wave, for the second half of a step 39.7
 // (registers spill), for its last quarter 36.3; steps beyond a triangular tile multiplied as zeros and not passed over 35.8.
 constexpr int stage_bytes(int F) { return 12 * F * 1024; }
+// Powers of two for the operands of the products.  The last part of an entry is 2^-16 of it, so a number at the lower end of fp32
+// (2^-149) is cut without loss once it is multiplied by 2^39.  With a = alpha + sigma^2 the entries of L are sqrt(a) at most, those of the
+// inverse factor Y 1 / sigma (sqrt(a) / sigma is below 2^12 where fp32 can factor at all), those of the intermediate of the tree T = L Y
+// sqrt(a) / sigma: brought to about 2^TO and 2^T, products of any two and their sums stay below 2^127.
+// Entries of L and Y between 2^-126 and 2^-100 (d = 20, lengthscale 0.45 of the spread, 142 .. 400 points): rms error of an entry
+// without the powers 1.6e-4 to 5.8e-4, with them 1e-7 to 7e-7 as on the fp32 matrix cores; factorisation of 64 uneven clusters of 4096 points
+// 35.0 / 35.7 ms.
+struct RangeScale {
+  static constexpr int TO = 40, T = 36;
+  static constexpr float UP_T = 0x1p36f;
+  int l, a, y;                                   // exponents for L, for the block that a multiply starts from, for Y
+  float up_l, up_a, up_y;
+};
 struct Cut { v4u h, m, l; };                     // eight values each, two in a register
 __device__ __forceinline__ Cut cut(const v4f& first, const v4f& second) {
   Cut c;
@@ -129,7 +142,8 @@ __device__ __forceinline__ Cut cut(const v4f& first, const v4f& second) {
   }
   return c;
 }
-// up: a power of two that this wave's entries are multiplied by (see range_scale).
+// up: a power of two that this wave's entries are multiplied by before they are cut, so that every fp32 entry is cut without loss (the
+// matrix cores take what is below 2^-126 for zero, see RangeScale); the sums carry both operands' powers.
 // F = 2: 64 x 64 per workgroup and 32 x 32 per wave (one row tile of either operand, whose fragments the waves load in pairs, F
 // each), for launches that would not fill the chip otherwise: a step takes a quarter of the time.
 // Columns 16 s0 .. 16 s1 - 1 (whole tiles).  mine: first element of the strip (64 rows of a square block) that this wave loads:
@@ -137,7 +151,7 @@ __device__ __forceinline__ Cut cut(const v4f& first, const v4f& second) {
 // triangular for row tile 0 (column <= row / >= row is kept), the next one for row tile 1, and the tiles past it / before it count as zero
 // whatever is stored there.
 template <int TRI, bool SWAP = false, int F = 4>
-__device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, int s0, int s1, int diag, unsigned char* stage, float up = 1.f) {
+__device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, int s0, int s1, int diag, unsigned char* stage, float up) {
 #if __HIP_DEVICE_COMPILE__
   typedef __attribute__((address_space(3))) v4u* lds_v4u;
   const int lane = threadIdx.x & 63, m = lane & 15, kg = lane >> 4;
@@ -183,12 +197,10 @@ __device__ __forceinline__ void block_gemm(v4f (&acc)[F][F], const float* mine, 
           }
       }
     }
-    if (up != 1.f) {
 #pragma unroll
-      for (int g = 0; g < F; ++g)
+    for (int g = 0; g < F; ++g)
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) raw[g][sub] *= up;
-    }
+      for (int sub = 0; sub < 2; ++sub) raw[g][sub] *= up;
     Cut mc[F];
 #pragma unroll
     for (int g = 0; g < F; ++g) mc[g] = cut(raw[g][0], raw[g][1]);
@@ -277,18 +289,16 @@ __device__ __forceinline__ void add_tile(v4f (&acc)[4][4], const float* tile) {
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-__device__ __forceinline__ void put_difference(const float* from, const v4f (&acc)[4][4], float down, float* tile) {
+__device__ __forceinline__ v4f times_power(const v4f& x, int e) {      // 2^e x
+  return (v4f){ldexpf(x[0], e), ldexpf(x[1], e), ldexpf(x[2], e), ldexpf(x[3], e)};
+}
+__device__ __forceinline__ void put_difference(const float* from, const v4f (&acc)[4][4], int down, float* tile) {
   from = here(from);
   tile = here(tile);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v4f x = *fragment(from, g, j);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = fmaf(-down, acc[g][j][i], x[i]);
-      *fragment(tile, g, j) = x;
-    }
+    for (int j = 0; j < 4; ++j) *fragment(tile, g, j) = *fragment(from, g, j) - times_power(acc[g][j], down);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -487,7 +497,7 @@ __device__ __forceinline__ void store_factored(const float (*sT)[LT], const floa
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, float* G, int k, int n_diag, int grid_diag,
-                  Pieces pieces, const uint32_t* __restrict__ first, int n_rows, int parts, int parts_before, float up, float down2, PcgState* __restrict__ st) {
+                  Pieces pieces, const uint32_t* __restrict__ first, int n_rows, int parts, int parts_before, RangeScale range, PcgState* __restrict__ st) {
   // the stage of the products and, once these are done, the tiles of the diagonal block share one piece of LDS
   __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(4)];
   static_assert((2 * TILE * LT + 4 * 16 * IP + TILE) * sizeof(float) <= stage_bytes(4), "two tiles and the inverted blocks must fit");
@@ -517,7 +527,7 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
     const int col = 2 * (k + ahead) + jb, row = 2 * m + ia;
     zero_block(acc);
     block_gemm<0>(acc, strip(w < 2 ? 2 * m + w : 2 * (k + ahead) + w - 2), ahead ? 8 * (k * part / parts) : 8 * (k - 1),
-                  ahead ? 8 * (k * (part + 1) / parts) : 8 * k, 0, stage, up);
+                  ahead ? 8 * (k * (part + 1) / parts) : 8 * k, 0, stage, range.up_l);
     if (!ahead && row <= last)
       for (int p = 1; p < parts_before; ++p) add_tile(acc, part_tile(k, p));
     if (diag) break;
@@ -525,7 +535,7 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
       const uint64_t tb = tile_base(c.ld, row, col);
       // what the products are subtracted from: the bulk result of the step before where there is one, or the assembled block
       if (part > 0) put_tile(acc, part_tile(k + 1, part));
-      else put_difference((!ahead && k > 1 ? L : A) + tb, acc, down2, L + tb);
+      else put_difference((!ahead && k > 1 ? L : A) + tb, acc, -2 * range.l, L + tb);
     }
     if (ahead) return;
     __syncthreads();                           // the stage is written again
@@ -548,9 +558,7 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        v4f x = *fragment(base + tb, g, j);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = fmaf(-down2, acc[g][j][e], x[e]);
+        const v4f x = *fragment(base + tb, g, j) - times_power(acc[g][j], -2 * range.l);
         if (w == 3) *fragment(L + tb, g, j) = x;
         else {
           const int r = 16 * g + mm, q = 16 * j + 4 * kg;
@@ -666,7 +674,7 @@ void k_potrf_step(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf
 template <int F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : 4)))
 void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* Lf, const float* G, int k, Pieces pieces,
-                   const uint32_t* __restrict__ first, int n_rows, float up, float down) {
+                   const uint32_t* __restrict__ first, int n_rows, RangeScale range) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(F)];
   int rank, item, part;
   if (!list_item(pieces, first, (uint32_t)k + 1, n_rows, (int)blockIdx.x, rank, item, F == 2 ? 2u : 1u, part)) return;
@@ -685,28 +693,28 @@ void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* L
       v4f acc[F][F];
       zero_block(acc);
       block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + q) * TILE * c.ld : from + (uint64_t)row * TILE * c.ld, 8 * k, 8 * k + 4 * q + 4,
-                             2 * k + q, stage, w < 2 ? 1.f : up);
+                             2 * k + q, stage, w < 2 ? range.up_y : range.up_a);
       __syncthreads();                         // the stage is written again
       float* lt = L + tile_base(c.ld, row, 2 * k + q);
 #pragma unroll
       for (int g = 0; g < F; ++g)
 #pragma unroll
         for (int j = 0; j < F; ++j)
-          *reinterpret_cast<v4f*>(lt + tile_offset(32 * jb + 16 * j + (lane & 15), 32 * ia + 16 * g + 4 * (lane >> 4))) = acc[g][j] * down;
+          *reinterpret_cast<v4f*>(lt + tile_offset(32 * jb + 16 * j + (lane & 15), 32 * ia + 16 * g + 4 * (lane >> 4))) = times_power(acc[g][j], -(range.a + range.y));
     }
     return;
   }
   v4f acc[F][F];
   zero_block(acc);
   block_gemm<1, true, F>(acc, w < 2 ? G + c.koff + (uint64_t)(2 * k + w) * TILE * c.ld : from + (uint64_t)min(2 * m + w - 2, last) * TILE * c.ld,
-                         8 * k, 8 * (k + 1), 2 * k, stage, w < 2 ? 1.f : up);
+                         8 * k, 8 * (k + 1), 2 * k, stage, w < 2 ? range.up_y : range.up_a);
   if (2 * m + jb > last) return;
   float* lt = L + tile_base(c.ld, 2 * m + jb, 2 * k + ia);
 #pragma unroll
   for (int g = 0; g < F; ++g)
 #pragma unroll
     for (int j = 0; j < F; ++j)
-      *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = acc[g][j] * down;
+      *reinterpret_cast<v4f*>(lt + tile_offset(16 * j + (lane & 15), 16 * g + 4 * (lane >> 4))) = times_power(acc[g][j], -(range.a + range.y));
 }
 
 // ---------------------------------------------------------------------------
@@ -721,7 +729,7 @@ void k_potrf_solve(const ClusterInfo* __restrict__ cl, const float* Kd, float* L
 template <int STAGE, int F>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(F == 4 ? 2 : 4)))
 void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int half, Pieces pieces,
-                   const uint32_t* __restrict__ first, int n) {
+                   const uint32_t* __restrict__ first, int n, RangeScale range) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage[stage_bytes(F)];
   int rank, item, part;
   if (!list_item(pieces, first, 0u, n, (int)blockIdx.x, rank, item, F == 2 ? 4u : 1u, part)) return;
@@ -744,26 +752,28 @@ void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int 
   // the wave's tiles, and (F = 2) its fragments in them
   const int am = F == 2 ? 0 : STAGE == 1 ? jb : ia, an = F == 2 ? 0 : STAGE == 1 ? ia : jb, fa = F == 2 ? 2 * ia : 0, fb = F == 2 ? 2 * jb : 0;
   if (STAGE == 1) {
-    block_gemm<2, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tn : tn + w) : strip(L, F == 2 ? tm : tm + w - 2), 4 * tn, 4 * mid, tn, stage);
+    block_gemm<2, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tn : tn + w) : strip(L, F == 2 ? tm : tm + w - 2), 4 * tn, 4 * mid, tn, stage,
+                            w < 2 ? range.up_y : range.up_l);
     if (tm + am > last) return;
     float* tt = here(L + tile_base(c.ld, tn + an, tm + am));
 #pragma unroll
     for (int g = 0; g < F; ++g)
 #pragma unroll
-      for (int j = 0; j < F; ++j) *fragment(tt, fa + g, fb + j) = acc[g][j];
+      for (int j = 0; j < F; ++j) *fragment(tt, fa + g, fb + j) = times_power(acc[g][j], -(range.y + range.l));
   } else {
     block_gemm<1, false, F>(acc, w < 2 ? strip(Y, F == 2 ? tm : tm + w) : strip(L, F == 2 ? tn : tn + w - 2), 4 * mid,
-                            4 * (min(F == 2 ? tm : tm + 1, last) + 1), tm, stage);
+                            4 * (min(F == 2 ? tm : tm + 1, last) + 1), tm, stage, w < 2 ? range.up_y : RangeScale::UP_T);
     if (tm + am > last) return;
     float *yl = Y + tile_base(c.ld, tm + am, tn + an), *yu = Y + tile_base(c.ld, tn + an, tm + am);
 #pragma unroll
     for (int g = 0; g < F; ++g)
 #pragma unroll
       for (int j = 0; j < F; ++j) {
-        *fragment(yl, fa + g, fb + j) = -acc[g][j];
+        const v4f y = times_power(-acc[g][j], -(range.y + RangeScale::T));
+        *fragment(yl, fa + g, fb + j) = y;
         float* to = yu + block_at_mirrored(fa + g, fb + j);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) to[16 * i] = -acc[g][j][i];
+        for (int i = 0; i < 4; ++i) to[16 * i] = y[i];
       }
   }
 }
@@ -919,12 +929,17 @@ static int bulk_parts(uint64_t items, int k) {
   return best;
 }
 
-// The smallest parts of a product are 2^-16 of it and the last parts of an entry 2^-16 of that, and the matrix cores take what is
-// below 2^-126 for zero: where the variances themselves are small, the entries of L, and those of the block that a multiply starts
-// from, are multiplied by the power of two that brings L to about 1.
-static float range_scale(const nugpr_ctx* c) {
+static RangeScale range_scale(const nugpr_ctx* c) {
   const double a = c->theta_built[c->L.p - 2] + c->theta_built[c->L.p - 1];
-  return (a < 0x1p-40 && a > 0.0) || a > 0x1p100 ? (float)std::ldexp(1.0, -std::ilogb(a) / 2) : 1.f;
+  const int e = a > 0.0 && std::isfinite(a) ? std::max(-126, std::min(128, std::ilogb(a))) : 0;
+  RangeScale r;
+  r.l = RangeScale::TO - e / 2;
+  r.a = std::min(RangeScale::TO - e, 120);
+  r.y = RangeScale::T + e / 2;
+  r.up_l = std::ldexp(1.f, r.l);
+  r.up_a = std::ldexp(1.f, r.a);
+  r.up_y = std::ldexp(1.f, r.y);
+  return r;
 }
 
 int launch_factor(nugpr_ctx* c, hipStream_t s) {
@@ -947,7 +962,7 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     return (int)(std::partition_point(L.blocks_by_rank.begin(), L.blocks_by_rank.end(), [&](uint32_t nb) { return (int)nb >= least; }) - L.blocks_by_rank.begin());
   };
   int parts_before = 1;
-  const float up = range_scale(c), down = 1.f / up;
+  const RangeScale range = range_scale(c);
   for (int k = 0; k < n_blocks; ++k) {
     const int n_diag = with_blocks(k + 1), grid_diag = (n_diag + NUM_DIES - 1) / NUM_DIES * NUM_DIES, n_rows = with_blocks(k + 2);
     const uint64_t items = L.rows_before[n_rows] - (uint64_t)n_rows * (uint64_t)(k + 1);
@@ -955,11 +970,11 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     Pieces pr, ps;
     for (int d = 0; d <= NUM_DIES; ++d) { pr.from[d] = (uint32_t)(items * parts * d / NUM_DIES); ps.from[d] = (uint32_t)(items * d / NUM_DIES); }
     hipLaunchKernelGGL(k_potrf_step, dim3((unsigned)grid_diag + (k > 0 ? pr.grid() : 0u)), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k,
-                       n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, up, down * down, c->d_state);
-    if (items > FEW_BLOCKS) hipLaunchKernelGGL((k_potrf_solve<4>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, up, down);
+                       n_diag, grid_diag, pr, c->d_rows_before, n_rows, parts, parts_before, range, c->d_state);
+    if (items > FEW_BLOCKS) hipLaunchKernelGGL((k_potrf_solve<4>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, range);
     else if (items) {
       for (int d = 0; d <= NUM_DIES; ++d) ps.from[d] = (uint32_t)(2 * items * d / NUM_DIES);
-      hipLaunchKernelGGL((k_potrf_solve<2>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, up, down);
+      hipLaunchKernelGGL((k_potrf_solve<2>), dim3(ps.grid()), dim3(256), 0, s, c->d_cl, Afac, c->Lf, c->G, k, ps, c->d_rows_before, n_rows, range);
     }
     parts_before = parts;
   }
@@ -969,11 +984,11 @@ int launch_factor(nugpr_ctx* c, hipStream_t s) {
     for (int d = 0; d <= NUM_DIES; ++d) { p1.from[d] = t.from1[d] * (few ? 4 : 1); p2.from[d] = t.from2[d] * (few ? 4 : 1); }
     const uint32_t* first = c->d_rows_before + t.at;
     if (few) {
-      hipLaunchKernelGGL((k_trtri_block<1, 2>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks);
-      hipLaunchKernelGGL((k_trtri_block<2, 2>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks);
+      hipLaunchKernelGGL((k_trtri_block<1, 2>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks, range);
+      hipLaunchKernelGGL((k_trtri_block<2, 2>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks, range);
     } else {
-      hipLaunchKernelGGL((k_trtri_block<1, 4>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks);
-      hipLaunchKernelGGL((k_trtri_block<2, 4>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks);
+      hipLaunchKernelGGL((k_trtri_block<1, 4>), dim3(p1.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p1, first, t.ranks, range);
+      hipLaunchKernelGGL((k_trtri_block<2, 4>), dim3(p2.grid()), dim3(256), 0, s, c->d_cl, c->Lf, c->G, t.half, p2, first, t.ranks, range);
     }
   }
   hipLaunchKernelGGL(k_logdet, dim3(L.nc), dim3(256), 0, s, c->d_cl, c->G, c->d_logdet);

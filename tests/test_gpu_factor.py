@@ -82,3 +82,35 @@ def test_factor_at_the_ends_of_the_number_range(lib, alpha, noise):
         res = (Y @ L - torch.eye(b, device=L.device, dtype=L.dtype)).abs() / (Y.abs() @ L.abs()).clamp_min(1.0)
         assert float(res.max()) <= (b + 1 + 64) * u
     ctx.close()
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e12, 1e-12])
+@pytest.mark.parametrize("name", ["around-a-block", "around-a-level", "long-and-short", "whole-blocks"])
+def test_factor_of_blocks_with_a_wide_spread(lib, name, scale):
+    """Entries from the scale of the variances down to the smallest that fp32 holds, every one held to its own size."""
+    import torch
+    from paper_2510_12128_amd import binding as B
+    sizes = SIZES[name]
+    n, d = sum(sizes), 20
+    rng = np.random.default_rng(6)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    ctx = lib.Context(X, np.zeros(n, np.float32), np.concatenate([[0], np.cumsum(sizes)]), 2.0 * rng.integers(0, 2, (n, 2)) - 1.0, 1)
+    ctx.nugpr_build_blocks(np.array([0.5] * d + [1.0 * scale, 0.1 * scale]))
+    assert ctx.nugpr_precond_factor()[0] == 0
+    u, unit = 2.0 ** -24, 2.0 ** -149
+    low = 0
+    for i, b in enumerate(sizes):
+        K, L, Y = (ctx.nugpr_export(w, i).double() for w in (B.EXPORT_K, B.EXPORT_L, B.EXPORT_LINV))
+        low += int(((K > 2.0 ** -126 * scale) & (K < 2.0 ** -100 * scale)).sum())
+        # element by element: (b + 1) u |L| |L|^T and what the explicit inverses of 128 x 128 blocks add (condition number below 4 at this
+        # spread: 64 u is more than enough); subnormal entries and intermediates are off by whole units in each of b steps, which
+        # meet entries of L or Y of up to max(1, s), s = sqrt(alpha + sigma^2) or 1 / sigma
+        LL = L.abs() @ L.abs().T
+        big = 4.0 * b * unit * max(1.0, float(L.abs().max()), float(Y.abs().max())) ** 2
+        assert float(((L @ L.T - K).abs() - big).div(LL + unit).max()) <= (b + 1 + 64) * u, (name, i)
+        # the inverse: Y21 = -Y22 (L21 Y11), each product off by b u of its terms' magnitudes, so Y L by that of |Y| |L| |Y| |L|
+        G = Y.abs() @ L.abs()
+        res = (Y @ L - torch.eye(b, device=L.device, dtype=L.dtype)).abs()
+        assert float((res - big).div(G @ G + unit).max()) <= (b + 1 + 64) * u, (name, i)
+    assert low > 1000
+    ctx.close()
