@@ -100,7 +100,7 @@ struct StripPort {
   uint64_t out_part_stride;  // elements between output slabs
   int32_t accumulate;        // out += result instead of out = result
   uint32_t odd_at : 20;      // where live is given: a byte for every odd_rows rows of `in`, odd_at x 256 bytes behind its start,
-  uint32_t odd_rows : 12;    // that says whether one of their values is not finite
+  uint32_t odd_rows : 12;    // that says whether one of their values is not finite; 0: all are finite
   double scale = 1.0;        // the product is multiplied by this before anything is added
   double diag_add = 0.0;     // scalar added on the diagonal of items that ask for it
   const uint32_t* live = nullptr;    // coupling matrix: a word for every lower tile (row tr, column tc at tr (tr + 1) / 2 + tc), zero where

@@ -614,10 +614,12 @@ static size_t odd_offset(const nugpr_ctx* c, int T) {
 }
 static int odd_rows(const nugpr_ctx* c, int T) { return c->onehot ? project_shape(c->L, T).reps : DENSE_ODD_ROWS; }
 // Products with C pass over items whose tiles hold no value, as the assembly of C left them (under the compensation its diagonal is
-// written later), and whose vector rows are finite.
+// written later), and whose vector rows are finite.  (Those of the kept projection of z_0 are: the first reduction of a solve refuses the
+// others.)
 static void skip_dead_items(const nugpr_ctx* c, StripPort& port, int T) {
   if (!c->c_skips) return;
   port.live = port.A == c->C ? c->c_live : port.A == c->C2 ? c->c2_live : nullptr;
+  if (port.in == c->S0v) return;
   port.odd_at = (uint32_t)(odd_offset(c, T) / 256);
   port.odd_rows = (uint32_t)odd_rows(c, T);
 }
@@ -1218,7 +1220,7 @@ static int store_known_t(nugpr_ctx* c, hipStream_t s) {
   // W^T z_0
   int rc = run_project(c, c->Z0v, L.T, s);
   if (rc) return rc;
-  NUGPR_HIP(hipMemcpyAsync(c->S0v, c->Spart, odd_offset(c, L.T) + (size_t)L.ncr, hipMemcpyDeviceToDevice, s));
+  NUGPR_HIP(hipMemcpyAsync(c->S0v, c->Spart, (size_t)L.ncr * L.T * sizeof(VT), hipMemcpyDeviceToDevice, s));
   return NUGPR_OK;
 }
 
