@@ -15,7 +15,7 @@ as a training run would; it is context, not `value`.
 `roofline` describes the dominant kernel, the launch that streams K_diag and the coupling matrix C once
 per product, timed live with HIP events inside the timed steps on the stream the library launches on.
 It is reported against BOTH ceilings it can meet: fp64 matrix arithmetic (2 T flops per stored entry; tiles of C
-without a value, which the launch passes over, do not count) and
+without a value do not count, whether the launch multiplies them or not) and
 HBM.  The HBM side is given three ways, each labelled: the bytes that physically cross HBM (hardware
 counters, read from the committed profile summary if and only if that summary names the kernel that is
 running), the bytes of the lower tiles the launch streams (what the code requests from memory), and the
@@ -30,6 +30,8 @@ import os
 import sys
 import time
 
+import numpy as np
+
 ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
@@ -39,12 +41,27 @@ FP64_MATRIX_PEAK_TFLOPS = 78.6
 
 
 def live_coupling_tiles(torch, C, ct):
-    """How many of the ct x ct tiles of 64 x 64 of the coupling matrix hold a value."""
-    n, count = C.shape[0], 0
+    """Which of the ct x ct tiles of 64 x 64 of the coupling matrix hold a value."""
+    n, live = C.shape[0], np.zeros((ct, ct), dtype=bool)
     for i in range(ct):
         rows = (C[64 * i:min(64 * i + 64, n)] != 0).any(0)
-        count += int(torch.nn.functional.pad(rows, (0, 64 * ct - n)).view(ct, 64).any(1).sum())
-    return count
+        live[i] = torch.nn.functional.pad(rows, (0, 64 * ct - n)).view(ct, 64).any(1).cpu().numpy()
+    return live
+
+
+def streamed_coupling_tiles(live):
+    """The tiles of the coupling matrix that the launch reads: all tiles of an item (a row of tiles of one column slab) that holds a
+    value or has fewer than 4 or more than 64 tiles.  Returns (tiles multiplied, stored lower tiles read)."""
+    ct = live.shape[0]
+    slabs = max(1, min(-(-2048 // ct), 16, ct))
+    per = -(-ct // slabs)
+    run = np.ones_like(live)
+    if 4 <= per <= 64:
+        for k in range(0, ct, per):
+            part = live[:, k:k + per]
+            if part.shape[1] >= 4:
+                run[:, k:k + per] = part.any(1)[:, None]
+    return int(run.sum()), int(np.tril(run | run.T).sum())
 
 
 def measured_traffic(config, acc, kernel):
@@ -73,7 +90,6 @@ def cpu_baseline(w, n_sample_clusters):
     """The fp64 oracle, as it stands, on the first clusters of the same workload:
     one loss evaluation (assembly + PCG + SLQ; the factor is built outside the timing,
     as on the GPU it is shared by the 1 + 2p evaluations of a step)."""
-    import numpy as np
     from oracle import nugpr_oracle as O
     k = min(n_sample_clusters, w.n_clusters)
     hi = int(w.offsets[k])
@@ -124,7 +140,6 @@ def main():
               "supported and no multi-GPU figure exists", file=sys.stderr)
         sys.exit(2)
 
-    import numpy as np
     import torch
     if not torch.cuda.is_available():
         print("bench.py needs a GPU", file=sys.stderr)
@@ -250,15 +265,19 @@ def main():
     kernel = ctx.nugpr_profile_kernel_name(T)
     lower_only = int(kernel.rstrip(">").split(",")[-1]) & 3 == 1   # tiles of symmetric blocks pair up
     # --- bytes of one launch of the dominant kernel, three accountings ---
-    # Of the coupling matrix the tiles that hold a value count (the launch passes over the others; all of it under the compensation)
+    # Of the coupling matrix the tiles that hold a value count as work (all of it under the compensation), and those that the launch reads
+    # as streamed.
     ct = int(np.ceil(ncr / 64.0))
-    live = ct * ct if args.compensate else live_coupling_tiles(torch, ctx.nugpr_export(EXPORT_C), ct)
+    mask = np.ones((ct, ct), dtype=bool) if args.compensate else live_coupling_tiles(torch, ctx.nugpr_export(EXPORT_C), ct)
+    live = int(mask.sum())
+    c_square, c_lower = streamed_coupling_tiles(mask)
     tiles = np.ceil(sizes / 64.0)
     entries_full = float(np.sum(sizes ** 2) + min(ncr ** 2, 4096.0 * live))  # whole squares
-    entries_lower = float(np.sum(tiles * (tiles + 1) / 2) + (live + min(live, ct)) / 2) * 4096.0   # lower 64 x 64 tiles
+    entries_lower = float(np.sum(tiles * (tiles + 1) / 2) + c_lower) * 4096.0   # lower 64 x 64 tiles
     vec_bytes = ctx.nugpr_profile_bytes(T) - 4.0 * float(np.sum(sizes ** 2) + ncr ** 2)     # D, S slabs in; Q, P slabs out
     bytes_full = 4.0 * entries_full + vec_bytes                               # dense-equivalent (every entry once)
     bytes_lower = 4.0 * entries_lower + vec_bytes                             # what the launch streams when it pairs tiles
+    bytes_square = 4.0 * float(np.sum(sizes ** 2) + min(ncr ** 2, 4096.0 * c_square)) + vec_bytes       # and when it does not
     flops = 2.0 * T * entries_full                                            # every entry meets every column
     dom_avg_ms = dom_ms / max(dom_launches, 1)
     sec = dom_avg_ms * 1e-3
@@ -266,15 +285,15 @@ def main():
     traffic = (rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"]) if rec else None
     tflops = flops / sec / 1e12 if dom_launches else 0.0
     frac_mfma = tflops / FP64_MATRIX_PEAK_TFLOPS if args.acc == "fp64" else None
-    requested = bytes_lower if lower_only else bytes_full
+    requested = bytes_lower if lower_only else bytes_square
     frac_hbm_physical = (traffic / sec / 1e9 / HBM_PEAK_GBPS) if (traffic and dom_launches) else None
     frac_hbm_requested = requested / sec / 1e9 / HBM_PEAK_GBPS if dom_launches else 0.0
     hbm_side = {"physical_bytes": traffic, "physical_gbps": traffic / sec / 1e9 if traffic else None,
                 "physical_frac": frac_hbm_physical, "physical_source": traffic_note,
                 "streamed_bytes": requested, "streamed_gbps": requested / sec / 1e9,
                 "streamed_frac": frac_hbm_requested,
-                "streamed_what": ("lower 64x64 tiles of K_diag and of what C holds + vector blocks" if lower_only else
-                                  "whole squares of K_diag and C + vector blocks"),
+                "streamed_what": ("lower 64x64 tiles of K_diag and of the items of C that are not passed over + vector blocks" if lower_only else
+                                  "whole squares of K_diag and the items of C that are not passed over + vector blocks"),
                 "dense_equivalent_bytes": bytes_full, "dense_equivalent_gbps": bytes_full / sec / 1e9,
                 "dense_equivalent_frac": bytes_full / sec / 1e9 / HBM_PEAK_GBPS,
                 "peak_gbps": HBM_PEAK_GBPS}
@@ -286,7 +305,8 @@ def main():
         gb = (traffic if traffic else requested) / sec / 1e9
         roof = {"bound": "hbm", "achieved": gb, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": hbm_best}
     roof.update({"traffic": traffic, "kernel": kernel + " (K_diag.D and C.S in one launch)",
-                 "flops_per_launch": flops, "coupling_tiles_with_a_value": live, "coupling_tiles": ct * ct, "avg_ms": dom_avg_ms, "launches_timed": dom_launches,
+                 "flops_per_launch": flops, "coupling_tiles_with_a_value": live, "coupling_tiles": ct * ct,
+                 "coupling_tiles_multiplied": c_square, "avg_ms": dom_avg_ms, "launches_timed": dom_launches,
                  "mfma_f64_frac": frac_mfma, "hbm": hbm_side})
 
     # one product K'.D through the C ABI (fp32 blocks in and out) with the default one-hot basis: the dominant
