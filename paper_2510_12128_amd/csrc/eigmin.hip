@@ -615,7 +615,8 @@ int coupling_lambda_min(nugpr_ctx* c, const double* theta, hipStream_t s, double
     StripPort q = p;
     q.A = c->Clo; q.diag_add = 0.0;
     // Both terms in one launch, like two systems side by side, where the partial sums of a product (of L.T columns) have room for the
-    // slabs of both; k_eig_newrow adds them up.  A loss on 32 uneven clusters of 1024 points, 24 steps: 1633 / 1568 us.
+    // slabs of both; k_eig_newrow adds them up.  A loss on 32 clusters of 1024 points with 64 representatives, 24 steps: 1211 / 1163 us, on uneven ones
+    // 1268 / 1230 (runs of one side differ by 0.5 %).
     if (together) {
       q.out = parts + (uint64_t)L.nsP * stride;
       const StripPort both[4] = {p, p, q, q};
