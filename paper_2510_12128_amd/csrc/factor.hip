@@ -102,9 +102,9 @@ __device__ __forceinline__ bool list_item(const Pieces& pieces, const uint32_t* 
 // unlike beside the fp32 ones) hides behind the matrix instructions of the other workgroup on the compute unit.  The roles are
 // swapped (OpB is the row operand of the instruction): lane l ends up with C[row l & 15][columns 4 (l >> 4) .. + 3] of each fragment,
 // 16 bytes of a row.
-// What bounds it: the bf16 matrix cores work 58 % of the last levels' cycles (clock 1.8 GHz under this load), the cutting takes another
-// 30 %, two fifths of it beside them.  The two products of the tree, fp32 instructions / this: 128 x 2048 points 3.9 / 2.4 ms, 64 uneven
-// clusters of 4096 points 23.7 / 14.4.  Not kept, whole factorisation of the latter (35.3 ms): every wave cuts what it reads, the fp32 fragments
+// What bounds it: the bf16 matrix cores work 55 % of the last levels' cycles (clock 1.8 GHz under this load), the vector
+// instructions (the cutting, mostly) take 46 % of the issue slots, partly beside them.  The two products of the tree, fp32 instructions / this: 128 x 2048 points 3.9 / 2.45 ms, 64 uneven
+// clusters of 4096 points 23.7 / 13.3.  Not kept, whole factorisation of the latter (35.3 ms before RangeScale): every wave cuts what it reads, the fp32 fragments
 // loaded straight into LDS, 36.7; cutting placed between the matrix instructions of the same wave, for the second half of a step 39.7
 // (registers spill), for its last quarter 36.3; steps beyond a triangular tile multiplied as zeros and not passed over 35.8.
 constexpr int stage_bytes(int F) { return 12 * F * 1024; }
@@ -472,8 +472,8 @@ __device__ __forceinline__ bool factor_tile(float (*sT)[LT], float* inv, float* 
 // delay the start of the long ones or wait behind them for a free slot.
 // A second launch multiplies the blocks below the diagonal by its inverse.
 // What bounds it: the matrix cores and the cutting of their operands (block_gemm), and where a launch is one or two rounds of
-// workgroups their number.  Steps and multiplies of 64 uneven clusters of 4096 points: 15.6 ms (fp32 matrix instructions 23.1, tiles of 64
-// 33.2), of 128 x 2048 points 3.6 ms (5.1; 5.0).  A block column of 128 needs half as many steps as one of 64, reads the panel L[m, 0:k] half
+// workgroups their number.  Steps and multiplies of 64 uneven clusters of 4096 points: 17.9 ms (fp32 matrix instructions 23.1, tiles of 64
+// 33.2), of 128 x 2048 points 3.7 ms (5.1; 5.0).  A block column of 128 needs half as many steps as one of 64, reads the panel L[m, 0:k] half
 // as often, and its diagonal workgroup (47 us on an idle chip) is still done before the rows are.
 // (Rows past the end of a cluster: zero in the assembled blocks and therefore zero in L; identity in the diagonal tile.)
 // the tile in LDS and its inverse (factor_tile) to memory: L lower, the inverse with its mirror image
