@@ -75,3 +75,29 @@ def test_static_scratch_matvec_refuses_products_beyond_its_buffer(lib):
     torch.cuda.synchronize(ctx.device)
     assert torch.equal(Q1, Q2)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [5119, 5000])
+def test_static_scratch_matvec_that_fills_its_buffer(lib, n):
+    """5119 points take the 16 MiB to the byte: nothing is left behind the projection for the bytes that say which of its rows are not
+    finite, and every tile of the coupling matrix is multiplied; 5000 points leave room, and items without a value are passed over."""
+    import torch
+    nc, rank, T = 49, 64, 33
+    sizes = [64] + [(n - 64) // 48 + (k < (n - 64) % 48) for k in range(48)]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    up = lambda v: (v + 255) // 256 * 256
+    slabs = up(nc * rank * T * 8) + up(16 * nc * rank * T * 8)          # one of W^T D (a cluster of one tile), sixteen of C S
+    need, cap = 2 * up(n * T * 8) + slabs, B.load_library().nugpr_matvec_static_max_bytes()
+    assert (need == cap) if n == 5119 else (need + up(nc * rank) + 256 <= cap)
+    rng = np.random.default_rng(8)
+    X = (np.repeat(np.arange(nc), sizes)[:, None] * 40.0 + rng.standard_normal((n, 2))).astype(np.float32)
+    ctx = lib.Context(X, np.zeros(n, np.float32), off, 2.0 * rng.integers(0, 2, (n, T - 1)) - 1.0, rank)
+    ctx.nugpr_build_blocks(np.array([1.5, 1.2, 1.1, 0.2]))
+    V = torch.as_tensor(rng.standard_normal((n, T)), dtype=torch.float32, device="cuda")
+    assert torch.equal(ctx.nugpr_matvec_static(V), ctx.nugpr_matvec(V))
+    V[17, 5] = float("nan")
+    got, ref = ctx.nugpr_matvec_static(V), ctx.nugpr_matvec(V)
+    assert bool(torch.isnan(got[:, 5]).all()) and bool(torch.isnan(ref[:, 5]).all())
+    keep = [c for c in range(T) if c != 5]
+    assert torch.equal(got[:, keep], ref[:, keep])
+    ctx.close()
