@@ -108,17 +108,17 @@ __device__ __forceinline__ bool list_item(const Pieces& pieces, const uint32_t* 
 // loaded straight into LDS, 36.7; cutting placed between the matrix instructions of the same wave, for the second half of a step 39.7
 // (registers spill), for its last quarter 36.3; steps beyond a triangular tile multiplied as zeros and not passed over 35.8.
 constexpr int stage_bytes(int F) { return 12 * F * 1024; }
-// Powers of two for the operands of the products.  The last part of an entry is 2^-16 of it, so a number at the lower end of fp32
-// (2^-149) is cut without loss once it is multiplied by 2^39.  With a = alpha + sigma^2 the entries of L are sqrt(a) at most, those of the
-// inverse factor Y 1 / sigma (sqrt(a) / sigma is below 2^12 where fp32 can factor at all), those of the intermediate of the tree T = L Y
-// sqrt(a) / sigma: brought to about 2^TO and 2^T, products of any two and their sums stay below 2^127.
+// Powers of two for the operands of the products.  The parts of an entry are multiples of its last bit, 2^-149 at least, so every fp32
+// number is cut without loss once it is multiplied by 2^23.  With a = alpha + sigma^2 the entries of L are sqrt(a) at most, those of the
+// inverse factor Y 1 / sigma, those of the intermediate of the tree T = L Y sqrt(a) / sigma (below 2^12 where fp32 can factor): with sqrt(a)
+// brought to 2^UP and 1 / sqrt(a) as well, products of any two and their sums stay below 2^127 for pivots down to 2^-70 a.
 // Entries of L and Y between 2^-126 and 2^-100 (d = 20, lengthscale 0.45 of the spread, 142 .. 400 points): rms error of an entry
 // without the powers 1.6e-4 to 5.8e-4, with them 1e-7 to 7e-7 as on the fp32 matrix cores; factorisation of 64 uneven clusters of 4096 points
 // 35.0 / 35.7 ms.
 struct RangeScale {
-  static constexpr int TO = 40, T = 36;
-  static constexpr float UP_T = 0x1p36f;
-  int l, a, y;                                   // exponents for L, for the block that a multiply starts from, for Y
+  static constexpr int UP = 24;
+  static constexpr float UP_T = 0x1p24f;
+  int l, a, y;                                   // exponents for L, for the block that a multiply starts from, for Y (for T: UP)
   float up_l, up_a, up_y;
 };
 struct Cut { v4u h, m, l; };                     // eight values each, two in a register
@@ -769,7 +769,7 @@ void k_trtri_block(const ClusterInfo* __restrict__ cl, float* Lf, float* G, int 
     for (int g = 0; g < F; ++g)
 #pragma unroll
       for (int j = 0; j < F; ++j) {
-        const v4f y = times_power(-acc[g][j], -(range.y + RangeScale::T));
+        const v4f y = times_power(-acc[g][j], -(range.y + RangeScale::UP));
         *fragment(yl, fa + g, fb + j) = y;
         float* to = yu + block_at_mirrored(fa + g, fb + j);
 #pragma unroll
@@ -933,9 +933,9 @@ static RangeScale range_scale(const nugpr_ctx* c) {
   const double a = c->theta_built[c->L.p - 2] + c->theta_built[c->L.p - 1];
   const int e = a > 0.0 && std::isfinite(a) ? std::max(-126, std::min(128, std::ilogb(a))) : 0;
   RangeScale r;
-  r.l = RangeScale::TO - e / 2;
-  r.a = std::min(RangeScale::TO - e, 120);
-  r.y = RangeScale::T + e / 2;
+  r.l = RangeScale::UP - e / 2;
+  r.a = std::min(RangeScale::UP - e, 120);
+  r.y = RangeScale::UP + e / 2;
   r.up_l = std::ldexp(1.f, r.l);
   r.up_a = std::ldexp(1.f, r.a);
   r.up_y = std::ldexp(1.f, r.y);
